@@ -27,7 +27,7 @@
 // are stored to a per-row scratch as they are formed; after the wavefront merge, with the final maximum
 // and normaliser known, a second pass turns them into attention weights and adds them to the open
 // planes of the row's feature state.
-#include "fk_common.h"
+#include "chunk.h"
 #include <mutex>
 
 namespace fk {
@@ -921,6 +921,70 @@ extern "C" fk_status fk_decode_step(const fk_cache_desc* desc, const void* q, vo
     return attn_entry(desc, P, max_len, softmax_scale, workspace, workspace_bytes, stream);
 }
 
+// ---------------------------------------------------------------------------------------------------------
+// fk_decode_window: the steps of a window at once (chunk.hip) where that is possible, else step by step
+// ---------------------------------------------------------------------------------------------------------
+namespace fk {
+static bool overlap(const void* a, size_t na, const void* b, size_t nb) {
+    const uintptr_t x = reinterpret_cast<uintptr_t>(a), y = reinterpret_cast<uintptr_t>(b);
+    return x < y + nb && y < x + na;
+}
+
+// At once: bf16, two steps or more, every pointer as fk_decode_step wants it (otherwise the step path reports the error), and
+// no buffer that the window writes shares memory with one that it reads for a later step, nor with another one that
+// it writes (one step's output used as a later step's input, new rows that lie in the cache): such calls have an order.
+static bool window_at_once(const fk_cache_desc* d, const void* q, const void* K, const void* V, const void* pos, const void* len,
+                           const void* k, const void* v, const void* pos_seq, int32_t T, const void* out, const void* ws) {
+    if (d->dtype != FK_BF16 || T < 2) return false;
+    if (!aligned16(q) || !aligned16(K) || !aligned16(V) || !aligned16(out) || !aligned16(k) || !aligned16(v) || !pos || !len) return false;
+    const size_t rows = (size_t)d->batch * d->n_kv_heads, row_bytes = (size_t)d->head_dim * 2;
+    if ((size_t)T * (d->n_q_heads / d->n_kv_heads) * rows >= (size_t)1 << 27) return false;   // 32-bit counts of queries
+    const size_t nq = (size_t)T * d->batch * d->n_q_heads * row_bytes, nn = (size_t)T * rows * row_bytes, nc = rows * d->capacity * row_bytes;
+    const size_t np = rows * d->capacity * 4, nl = rows * 4, ns = (size_t)T * d->batch * 4;
+    // the first six are written
+    const struct { const void* p; size_t n; } buf[] = {{out, nq}, {K, nc}, {V, nc}, {pos, np}, {len, nl}, {ws, nl},
+                                                       {q, nq},   {k, nn}, {v, nn}, {pos_seq, ns}};
+    for (int i = 0; i < 6; ++i)
+        for (int j = i + 1; j < 10; ++j)
+            if (overlap(buf[i].p, buf[i].n, buf[j].p, buf[j].n)) return false;
+    return true;
+}
+
+// Whether the steps at once are the faster way.  With at least one query tile per CU they are from two steps on (128 rows of
+// 2112 pairs, two steps: 46 against 49 us; eight: 48 against 183).  With fewer, a workgroup walks its row alone, about 1.9 us for
+// 128 pairs (8 rows of 8192 pairs: 124 us whatever the number of steps), while a single step spreads the row over the chip: 9 us
+// plus its bytes at 5.5 TB/s (8 rows of 8192: 12 - 15 us a step; 8 rows of 131000: 101 us a step against 1964 us at once).
+static bool window_pays(const fk_cache_desc* d, int32_t T, int32_t max_len) {
+    const double rows = (double)d->batch * d->n_kv_heads, tiles = rows * ((T * (d->n_q_heads / d->n_kv_heads) + 31) / 32);
+    if (tiles >= 256) return true;
+    const double step_us = 9.0 + rows * max_len * d->head_dim * 4 / 5.5e6;
+    return T * step_us >= 1.9 * ((max_len + 127) / 128);
+}
+
+static ChunkParams window_params(const fk_cache_desc* d, const void* q, void* K, void* V, int32_t* pos, int32_t* len, const void* k, const void* v,
+                                 const int32_t* pos_seq, int32_t T, float scale, void* out, void* ws) {
+    ChunkParams P = {};
+    P.q_seq = q;
+    P.k_seq = k;
+    P.v_seq = v;
+    P.K = K;
+    P.V = V;
+    P.pos = pos;
+    P.len = len;
+    P.pos_seq = pos_seq;
+    P.out_seq = out;
+    P.scale_log2e = scale * 1.4426950408889634f;
+    P.batch = d->batch;
+    P.n_kv = d->n_kv_heads;
+    P.g = d->n_q_heads / d->n_kv_heads;
+    P.cap = d->capacity;
+    P.T = T;
+    P.rows = d->batch * d->n_kv_heads;
+    P.row_cnt = reinterpret_cast<uint32_t*>(ws);
+    return P;
+}
+}  // namespace fk
+
 extern "C" fk_status fk_decode_window(const fk_cache_desc* desc, const void* q_seq, void* K, void* V, int32_t* pos,
                                       int32_t* len, const void* k_seq, const void* v_seq, const int32_t* pos_seq,
                                       int32_t n_steps, int32_t max_len_first, float softmax_scale, void* out_seq,
@@ -932,6 +996,13 @@ extern "C" fk_status fk_decode_window(const fk_cache_desc* desc, const void* q_s
     const size_t e = desc->dtype == FK_F32 ? 4 : 2;
     const size_t q_step = (size_t)desc->batch * desc->n_q_heads * desc->head_dim * e;   // bytes per step, multiples of 16
     const size_t kv_step = (size_t)desc->batch * desc->n_kv_heads * desc->head_dim * e;
+    if (window_at_once(desc, q_seq, K, V, pos, len, k_seq, v_seq, pos_seq, n_steps, out_seq, workspace) &&
+        window_pays(desc, n_steps, max_len_first)) {
+        const size_t need = fk_decode_attn_workspace(desc, max_len_first);
+        if (!workspace || workspace_bytes < need || !aligned16(workspace)) return FK_ERR_WORKSPACE;
+        return chunk_window(desc, window_params(desc, q_seq, K, V, pos, len, k_seq, v_seq, pos_seq, n_steps, softmax_scale, out_seq, workspace),
+                            (hipStream_t)stream);
+    }
     for (int32_t t = 0; t < n_steps; ++t) {
         const int64_t ml = (int64_t)max_len_first + t;
         s = fk_decode_step(desc, static_cast<const char*>(q_seq) + t * q_step, K, V, pos, len,
