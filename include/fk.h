@@ -267,7 +267,8 @@ fk_status fk_decode_step_feat(const fk_cache_desc *desc, const void *q, void *K,
  * call, step t at chunk position chunk_pos_first + t, on q_seq[t], k_seq[t], v_seq[t], pos_seq[t] with its
  * output in out_seq[t] and max_len = min(max_len_first + t, capacity).  Layouts as for fk_decode_window;
  * the window must end inside the chunk (chunk_pos_first + n_steps <= chunk_len).  Results are those of
- * the n_steps single calls.
+ * the n_steps single calls, bit for bit.  bf16 with head_dim 128: two launches for the whole window under the conditions of
+ * fk_decode_window (and 2 n_steps g <= capacity * GP, the space the workspace has for them); otherwise the steps one by one.
  */
 fk_status fk_decode_window_feat(const fk_cache_desc *desc, const void *q_seq, void *K, void *V, int32_t *pos,
                                 int32_t *len, const void *k_seq, const void *v_seq, const int32_t *pos_seq,

@@ -934,19 +934,20 @@ static bool overlap(const void* a, size_t na, const void* b, size_t nb) {
 // no buffer that the window writes shares memory with one that it reads for a later step, nor with another one that
 // it writes (one step's output used as a later step's input, new rows that lie in the cache): such calls have an order.
 static bool window_at_once(const fk_cache_desc* d, const void* q, const void* K, const void* V, const void* pos, const void* len,
-                           const void* k, const void* v, const void* pos_seq, int32_t T, const void* out, const void* ws) {
+                           const void* k, const void* v, const void* pos_seq, int32_t T, const void* out, const void* ws, const void* feat) {
     if (d->dtype != FK_BF16 || T < 2) return false;
     if (!aligned16(q) || !aligned16(K) || !aligned16(V) || !aligned16(out) || !aligned16(k) || !aligned16(v) || !pos || !len) return false;
     const size_t rows = (size_t)d->batch * d->n_kv_heads, row_bytes = (size_t)d->head_dim * 2;
     if ((size_t)T * (d->n_q_heads / d->n_kv_heads) * rows >= (size_t)1 << 27) return false;   // 32-bit counts of queries
     const size_t nq = (size_t)T * d->batch * d->n_q_heads * row_bytes, nn = (size_t)T * rows * row_bytes, nc = rows * d->capacity * row_bytes;
     const size_t np = rows * d->capacity * 4, nl = rows * 4, ns = (size_t)T * d->batch * 4;
-    // the first six are written
-    const struct { const void* p; size_t n; } buf[] = {{out, nq}, {K, nc}, {V, nc}, {pos, np}, {len, nl}, {ws, nl},
+    const size_t nf = feat ? np * kFeatPlanes * (d->n_q_heads / d->n_kv_heads <= 4 ? 4 : 8) : 0, nw = feat ? feat_workspace_bytes(d) : nl;
+    // the first seven are written
+    const struct { const void* p; size_t n; } buf[] = {{out, nq}, {K, nc}, {V, nc}, {pos, np}, {len, nl}, {ws, nw}, {feat, nf},
                                                        {q, nq},   {k, nn}, {v, nn}, {pos_seq, ns}};
-    for (int i = 0; i < 6; ++i)
-        for (int j = i + 1; j < 10; ++j)
-            if (overlap(buf[i].p, buf[i].n, buf[j].p, buf[j].n)) return false;
+    for (int i = 0; i < 7; ++i)
+        for (int j = i + 1; j < 11; ++j)
+            if (buf[i].n && buf[j].n && overlap(buf[i].p, buf[i].n, buf[j].p, buf[j].n)) return false;
     return true;
 }
 
@@ -996,7 +997,7 @@ extern "C" fk_status fk_decode_window(const fk_cache_desc* desc, const void* q_s
     const size_t e = desc->dtype == FK_F32 ? 4 : 2;
     const size_t q_step = (size_t)desc->batch * desc->n_q_heads * desc->head_dim * e;   // bytes per step, multiples of 16
     const size_t kv_step = (size_t)desc->batch * desc->n_kv_heads * desc->head_dim * e;
-    if (window_at_once(desc, q_seq, K, V, pos, len, k_seq, v_seq, pos_seq, n_steps, out_seq, workspace) &&
+    if (window_at_once(desc, q_seq, K, V, pos, len, k_seq, v_seq, pos_seq, n_steps, out_seq, workspace, nullptr) &&
         window_pays(desc, n_steps, max_len_first)) {
         const size_t need = fk_decode_attn_workspace(desc, max_len_first);
         if (!workspace || workspace_bytes < need || !aligned16(workspace)) return FK_ERR_WORKSPACE;
@@ -1105,6 +1106,19 @@ extern "C" fk_status fk_decode_window_feat(const fk_cache_desc* desc, const void
     if (n_steps < 0 || max_len_first <= 0 || max_len_first > desc->capacity) return FK_ERR_INVALID_ARG;
     if (!q_seq || !k_seq || !v_seq || !pos_seq || !out_seq) return FK_ERR_INVALID_ARG;
     if (chunk_len <= 0 || chunk_pos_first < 0 || (int64_t)chunk_pos_first + n_steps > chunk_len) return FK_ERR_INVALID_ARG;
+    // at once where the plain window is, and the two floats per query fit the logit scratch
+    const int g = desc->n_q_heads / desc->n_kv_heads;
+    if (desc->head_dim == 128 && feat && aligned16(feat) && (int64_t)n_steps * g * 2 <= (int64_t)desc->capacity * (g <= 4 ? 4 : 8) &&
+        window_at_once(desc, q_seq, K, V, pos, len, k_seq, v_seq, pos_seq, n_steps, out_seq, workspace, feat)) {
+        if (!workspace || workspace_bytes < feat_workspace_bytes(desc) || !aligned16(workspace)) return FK_ERR_WORKSPACE;
+        ChunkParams P = window_params(desc, q_seq, K, V, pos, len, k_seq, v_seq, pos_seq, n_steps, softmax_scale, out_seq, workspace);
+        P.stat = reinterpret_cast<float2*>(static_cast<char*>(workspace) + attn_counter_bytes(desc));
+        P.feat = feat;
+        P.chunk_pos = chunk_pos_first;
+        P.chunk_len = chunk_len;
+        const int64_t ml = (int64_t)max_len_first + n_steps - 1;
+        return chunk_window_feat(P, ml > desc->capacity ? desc->capacity : (int)ml, (hipStream_t)stream);
+    }
     const size_t e = desc->dtype == FK_F32 ? 4 : 2;
     const size_t q_step = (size_t)desc->batch * desc->n_q_heads * desc->head_dim * e;   // bytes per step, multiples of 16
     const size_t kv_step = (size_t)desc->batch * desc->n_kv_heads * desc->head_dim * e;

@@ -105,6 +105,20 @@ def device_args(desc, T, lens, seed):
     return mk(T, B, desc.n_q_heads, D), mk(B, H, cap, D), mk(B, H, cap, D), pos, ln, mk(T, B, H, D), mk(T, B, H, D), pn
 
 
+@pytest.mark.parametrize("g", [1, 2, 3, 4, 5, 6, 7, 8])
+@pytest.mark.parametrize("T,c0,L,lens,cap", [(37, 0, 37, [300, 0, 281, 31], 333), (9, 60, 128, [64, 255, 1], 300), (64, 0, 64, [700, 10], 800),
+                                             (5, 3, 200, [9, 12], 16)])
+def test_window_with_features_equals_the_single_steps_bit_for_bit(gpu, g, T, c0, L, lens, cap):
+    import paper_2602_03203_amd as fk
+    print(f"feature window g={g} T={T} chunk {c0}/{L} lens={lens} cap={cap}", flush=True)
+    desc = fk.CacheDesc(3, 2 * g, 2, 128, cap, "bf16")
+    args = device_args(desc, T, lens, 7 * g + T)
+    feat = torch.rand((3, 2, 6, cap, fk.feat_heads(desc)), device="cuda")
+    a, b = window_and_steps(gpu, fk, desc, args, T, min(max(lens) + 1, cap), 0.2, feat, c0, L)
+    for x, y in zip(a, b):
+        assert torch.equal(x.view(torch.uint8), y.view(torch.uint8))
+
+
 @pytest.mark.parametrize("features", [False, True])
 def test_window_keeps_a_later_steps_infinities_from_the_earlier_ones(gpu, features):
     """A value row of step 5 that holds an infinity and a NaN reaches the outputs from step 5 on, and no other."""
