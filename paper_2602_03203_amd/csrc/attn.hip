@@ -20,7 +20,10 @@
 // second contraction; its B operand is the V tile, transposed 8x8 inside each lane's registers
 // (byte permutes, no cross-lane traffic), so P.V is MFMA too and the accumulator lives in the
 // MFMA result layout.  The vector ALUs only do the softmax.
-// bf16, D = 64.  q.K^T on MFMA with the K operand loaded directly, P.V as fp32 FMA.
+// bf16, D = 64.  The same with shorter rows: the K operand is loaded directly (a row is four lanes x 16 bytes per k-step), V
+// 8 bytes a lane, and the probabilities go in as bf16 head plus bf16 remainder (16 significant bits), normalised by their
+// fp32 sum.  P.V as fp32 FMA, every key group its own accumulator and 64 of them to merge per workgroup, took 18.9 us at
+// 128 rows of 2048 pairs and 8.7 us at 8 rows of 300; this takes 14.6 and 6.2.
 // fp32.  q.K^T as fp32 FMA plus a DPP row reduction, P.V as fp32 FMA.
 //
 // fk_decode_step_feat (FEAT variant, Appendix B.1).  One workgroup per row.  The scaled base-2 logits
@@ -69,6 +72,16 @@ __device__ __forceinline__ uint4 ld_stream(const uint4* p) {
         return *p;
     }
 }
+template <bool NT>
+__device__ __forceinline__ uint2 ld_stream(const uint2* p) {
+    if constexpr (NT) {
+        typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
+        const u32x2 v = __builtin_nontemporal_load(reinterpret_cast<const u32x2*>(p));
+        return make_uint2(v.x, v.y);
+    } else {
+        return *p;
+    }
+}
 static constexpr size_t kStreamNtBytes = (size_t)352 << 20;  // K + V bytes of a launch from which NT loads are used
 
 // i-th dword of a 16-byte register quad; i is a compile-time constant after unrolling
@@ -87,10 +100,11 @@ __device__ __forceinline__ float row16_max(float v) {
 // ---- geometry ------------------------------------------------------------------------------
 template <typename T, int D, int G> struct AttnCfg {
     static constexpr bool MFMA = sizeof(T) == 2;
-    static constexpr bool PVM = MFMA && D == 128;           // P.V on MFMA as well
+    static constexpr bool PVM = MFMA;                       // P.V on MFMA as well
+    static constexpr bool SPLIT_P = PVM && D == 64;         // probabilities as bf16 head + remainder
     static constexpr int CH = D * (int)sizeof(T) / 16;      // 16-byte chunks per row = lanes per key (P.V layout)
     static constexpr int KG = kWave / CH;                   // key groups per wave in the P.V layout
-    static constexpr int WAVES = PVM ? 8 : (MFMA ? (G <= 4 ? 8 : 4) : 4);
+    static constexpr int WAVES = PVM ? 8 : 4;
     static constexpr int THREADS = WAVES * kWave;
     static constexpr int KT = MFMA ? 32 : KG * 4;           // keys per wave iteration
     static constexpr int VU = KT / KG;                      // V (and fp32 K) loads per lane per iteration
@@ -98,17 +112,17 @@ template <typename T, int D, int G> struct AttnCfg {
     static constexpr int GP = G <= 4 ? 4 : 8;               // heads padded to the MFMA result rows in use
     static constexpr int NG = PVM ? WAVES : WAVES * KG;     // partial accumulators per workgroup
     static constexpr int PS = KT + 8;                       // PVM: bf16 row stride of the P tile in LDS
-    static constexpr int KRS = 272;                         // PVM: padded byte stride of a K row in LDS
+    static constexpr int KRS = 272;                         // D = 128: padded byte stride of a K row in LDS
     // dynamic LDS (floats unless noted):
-    //   PVM:   m [NG][G] | l [NG][G] | w [NG][G] | M [8] | P tiles [WAVES][GP][PS] bf16 | K tiles [WAVES][KT][KRS] bytes
-    //          (a wavefront's partial accumulator [G][D] reuses its own K tile once its loop is over), 73 KB at G = 4:
-    //          two workgroups fit the 160 KB of a CU
+    //   PVM:   m [NG][G] | l [NG][G] | w [NG][G] | M [8] | P tiles [WAVES][GP][PS] bf16 (D = 64: head and remainder) | D = 128:
+    //          K tiles [WAVES][KT][KRS] bytes (a wavefront's partial accumulator [G][D] reuses its own K tile once its loop is
+    //          over), 73 KB at G = 4: two workgroups fit the 160 KB of a CU; D = 64: the partial accumulators
     //   other: acc [NG][G][D] | m [NG][G] | l [NG][G] | w [NG][G] | M [8] | p [WAVES][KT][GP] | corr [WAVES][GP]
-    static constexpr int ACC_STRIDE = PVM ? KT * KRS / 4 : G * D;  // floats between the partial accumulators
+    static constexpr int ACC_STRIDE = PVM && D == 128 ? KT * KRS / 4 : G * D;  // floats between the partial accumulators
     static constexpr size_t HEAD_FLOATS = 3 * (size_t)NG * G + 8;   // m, l, w, M
-    static constexpr size_t PB_BYTES = (size_t)WAVES * GP * PS * 2;  // PVM: the bf16 P tiles
+    static constexpr size_t PB_BYTES = (size_t)WAVES * GP * PS * 2 * (SPLIT_P ? 2 : 1);  // PVM: the bf16 P tiles
     static constexpr size_t LDS_BYTES =
-        PVM ? sizeof(float) * HEAD_FLOATS + PB_BYTES + (size_t)WAVES * KT * KRS
+        PVM ? sizeof(float) * (HEAD_FLOATS + (size_t)WAVES * ACC_STRIDE) + PB_BYTES
             : sizeof(float) * ((size_t)NG * G * D + HEAD_FLOATS + (size_t)WAVES * KT * GP + (size_t)WAVES * GP + 4);
     // attention-feature variant: lx [NG][G] exact normaliser partials | invL [8], behind everything else
     static constexpr size_t LDS_BYTES_FEAT = LDS_BYTES + sizeof(float) * ((size_t)NG * G + 8);
@@ -121,11 +135,11 @@ struct AttnPlan {
     bool rotate;    // workgroups start at different tiles of their splits
 };
 
-// Splits per row the plan aims at.  The bf16 D = 128 kernel saturates the memory system from 128 workgroups of
-// eight wavefronts when the cache sits in the Infinity Cache, so rows are split only when there are fewer rows
-// than that (no split = no cross-workgroup merge at the end of the launch); a cold cache comes from HBM, whose
-// latency takes every CU to cover: up to 256 workgroups; the other kernels want about two per CU.
-static int attn_want_splits(const fk_cache_desc* d) {
+// Splits per row that the workspace has records for, an upper bound on the plan's for any max_len.  The bf16 D = 128 kernel
+// saturates the memory system from 128 workgroups of eight wavefronts when the cache sits in the Infinity Cache, so rows are
+// split only when there are fewer rows than that (no split = no cross-workgroup merge at the end of the launch); a cold cache
+// comes from HBM, whose latency takes every CU to cover: up to 256 workgroups.
+static int attn_max_splits(const fk_cache_desc* d) {
     const int rows = d->batch * d->n_kv_heads;
     if (d->dtype == FK_BF16 && d->head_dim == 128 && (d->flags & FK_CACHE_COLD)) {
         const int want = 256 / rows;
@@ -136,15 +150,25 @@ static int attn_want_splits(const fk_cache_desc* d) {
     return want < 1 ? 1 : want;
 }
 
-// Upper bound on the splits any max_len can get (sizes the workspace).
-static int attn_max_splits(const fk_cache_desc* d) { return attn_want_splits(d); }
-
 static AttnPlan attn_plan(const fk_cache_desc* d, int max_len) {
-    const int tile = 32;
-    int want = attn_want_splits(d);
-    const int max_split = (max_len + tile - 1) / tile;
-    if (want > max_split) want = max_split;
-    if (want < 1) want = 1;
+    const int tile = 32, rows = d->batch * d->n_kv_heads;
+    int want = attn_max_splits(d);
+    // A split is worth its share of the merge (1 to 1.5 us, and 0.1 us for every record beyond sixteen) when it fills its wavefronts.
+    // bf16: eight wavefronts take 256 keys a round, about 1.1 us; fp32: four take 64 (D = 128: 32).  Measured per step, us:
+    //   8 rows, D = 64:  1500 keys  47 splits 12.8, 8: 6.9, 4: 7.5, 1: 12.7;  300 keys  10: 6.7, 1: 6.1;  8192 keys  64: 15.4, 32: 11.1, 16: 10.1
+    //   D = 128:  8 rows of 2048  16: 8.3, 8: 7.8;  8 rows of 300  10: 7.3, 1: 6.5;  1 row of 16000  125: 17.3, 32: 10.9, 16: 13.0
+    //   D = 64, 128 rows of 2048  4: 15.0, 2: 14.7, 1: 18.4;  32 rows of 2048  16: 10.2, 8: 8.2, 4: 9.0 (so 256 workgroups there)
+    //   fp32, 16 rows:  D = 128, 300 keys  10: 9.2, 5: 8.2;  D = 64, 500 keys  16: 9.1, 8: 7.0;  2 rows of 144  5: 5.7, 3: 5.8
+    int most;
+    if (d->dtype == FK_BF16) {
+        if (d->head_dim == 64 && want > (255 + rows) / rows) want = (255 + rows) / rows;
+        most = max_len <= 512 ? 1 : (max_len + 255) / 256;
+        if (most > 16) most = max_len / 512 > 16 ? max_len / 512 : 16;
+    } else {
+        most = max_len <= 1024 ? 8 : (max_len + 127) / 128;   // (the merge fetches eight records at a time)
+        if (most > (max_len + tile - 1) / tile) most = (max_len + tile - 1) / tile;
+    }
+    if (want > most) want = most;
     int split_len = (max_len + want - 1) / want;
     split_len = (split_len + tile - 1) / tile * tile;
     // (Rounding the splits down to whole rounds of the workgroup, with the rest of the row as a short split of its
@@ -216,7 +240,6 @@ __global__ __launch_bounds__((AttnCfg<T, D, G>::THREADS)) void attn_kernel(const
     float* s_w = s_l + NG * G;                 // [NG][G] merge weights 2^(m_g - M)
     float* s_M = s_w + NG * G;                 // [8] merged maximum per head
     float* s_p = s_M + 8;                      // other paths: [WAVES][KT][GP]; PVM: the bf16 P tiles
-    float* s_corr = s_p + WAVES * KT * GP;     // other paths: [WAVES][GP]
     unsigned char* s_kt = reinterpret_cast<unsigned char*>(s_p) + C::PB_BYTES;  // PVM: K tiles [WAVES][KT][KRS]
     float* s_acc = C::PVM ? reinterpret_cast<float*>(s_kt) : smem;  // partial g2 at s_acc + g2 * ACC_STRIDE, [G][D]
     __shared__ int s_last;
@@ -335,11 +358,13 @@ __global__ __launch_bounds__((AttnCfg<T, D, G>::THREADS)) void attn_kernel(const
     if constexpr (C::PVM) {
         constexpr int PS = C::PS, KRS = C::KRS;
         const int n16 = lane & 15, quad = lane >> 4;
-        uint16_t* my_pb = reinterpret_cast<uint16_t*>(s_p) + (size_t)wave * GP * PS;           // [GP][PS] bf16
-        unsigned char* my_k = s_kt + (size_t)wave * KT * KRS;
-        B128 qa[4];
+        constexpr int KS = D / 32;          // k-steps of q.K^T
+        constexpr int ET = D / 16;          // channel tiles of P.V
+        uint16_t* my_pb = reinterpret_cast<uint16_t*>(s_p) + (size_t)wave * GP * PS * (C::SPLIT_P ? 2 : 1);   // [GP][PS] bf16, D = 64: two
+        unsigned char* my_k = s_kt + (size_t)wave * KT * KRS;   // D = 128
+        B128 qa[KS];
 #pragma unroll
-        for (int ks = 0; ks < 4; ++ks) {
+        for (int ks = 0; ks < KS; ++ks) {
             if (n16 < G) qa[ks].u = *reinterpret_cast<const uint4*>(qrow + (size_t)n16 * D + ks * 32 + quad * 8);
             else qa[ks].u = make_uint4(0, 0, 0, 0);
         }
@@ -351,9 +376,9 @@ __global__ __launch_bounds__((AttnCfg<T, D, G>::THREADS)) void attn_kernel(const
             lx_run[i] = 0.f;
         }
         float* lg_row = FEAT ? P.logit + (size_t)row * P.cap * GP : nullptr;
-        f32x4_t o[8];  // o[e][i] = out[head quad*4 + i][channel n16*8 + e], un-normalised
+        f32x4_t o[ET];  // o[e][i] = out[head quad*4 + i][channel n16*ET + e], un-normalised
 #pragma unroll
-        for (int e = 0; e < 8; ++e) o[e] = (f32x4_t){0.f, 0.f, 0.f, 0.f};
+        for (int e = 0; e < ET; ++e) o[e] = (f32x4_t){0.f, 0.f, 0.f, 0.f};
 
         // Tiles are dealt round robin to the wavefronts; with P.rotate the deal starts from a tile that differs
         // from workgroup to workgroup (the online softmax does not care about the order).
@@ -362,8 +387,23 @@ __global__ __launch_bounds__((AttnCfg<T, D, G>::THREADS)) void attn_kernel(const
         for (int t = wave; t < ntiles; t += WAVES) {
             const int tt = t + rot < ntiles ? t + rot : t + rot - ntiles;
             const int base = start + tt * KT;
-            uint4 vr[8];
-            {
+            uint4 vr[8];  // D = 64: x, y only
+            B128 kd[2][2];  // D = 64: K operand
+            if constexpr (D == 64) {
+#pragma unroll
+                for (int nt = 0; nt < 2; ++nt) {
+                    const int kc = min(base + nt * 16 + n16, end - 1);
+#pragma unroll
+                    for (int ks = 0; ks < KS; ++ks) kd[nt][ks].u = ld_stream<NT>((kc == new_slot ? knew_row : Krow + (size_t)kc * CH) + ks * 4 + quad);
+                }
+#pragma unroll
+                for (int u = 0; u < 8; ++u) {  // lane (quad, n16): key base + quad*8 + u, channels n16*4 .. +4
+                    const int kc = min(base + quad * 8 + u, end - 1);
+                    const uint2 v2 = ld_stream<NT>(reinterpret_cast<const uint2*>(kc == new_slot ? vnew_row : Vrow + (size_t)kc * CH) + n16);
+                    vr[u].x = v2.x;
+                    vr[u].y = v2.y;
+                }
+            } else {
                 uint4 kr[8];  // lane (quad, n16): key base + quad*8 + u, 16-byte chunk n16
 #pragma unroll
                 for (int u = 0; u < 8; ++u) {
@@ -385,15 +425,16 @@ __global__ __launch_bounds__((AttnCfg<T, D, G>::THREADS)) void attn_kernel(const
             for (int nt = 0; nt < 2; ++nt) {
                 c[nt] = (f32x4_t){0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-                for (int ks = 0; ks < 4; ++ks) {
+                for (int ks = 0; ks < KS; ++ks) {
                     B128 kb;
-                    kb.u = *reinterpret_cast<const uint4*>(my_k + (nt * 16 + n16) * KRS + (ks * 4 + quad) * 16);
+                    if constexpr (D == 64) kb = kd[nt][ks];
+                    else kb.u = *reinterpret_cast<const uint4*>(my_k + (nt * 16 + n16) * KRS + (ks * 4 + quad) * 16);
                     c[nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(qa[ks].v, kb.v, c[nt], 0, 0, 0);
                 }
             }
             bool changed = false;
             float corr[4];
-            uint32_t pb[2][4];
+            uint32_t pb[2][4], pl[2][4];
             if constexpr (FEAT) {  // keep the step's logits: the second pass turns them into attention weights
                 if (quad * 4 < GP) {
                     if (base + n16 < end)
@@ -416,8 +457,14 @@ __global__ __launch_bounds__((AttnCfg<T, D, G>::THREADS)) void attn_kernel(const
                 const uint32_t u0 = __float_as_uint(e0) + 0x8000u, u1 = __float_as_uint(e1) + 0x8000u;
                 pb[0][i] = u0 >> 16;
                 pb[1][i] = u1 >> 16;
-                l_run[i] = l_run[i] * corr[i] + __uint_as_float(u0 & 0xffff0000u) + __uint_as_float(u1 & 0xffff0000u);
-                if constexpr (FEAT) lx_run[i] = lx_run[i] * corr[i] + e0 + e1;
+                if constexpr (C::SPLIT_P) {
+                    pl[0][i] = (__float_as_uint(e0 - __uint_as_float(u0 & 0xffff0000u)) + 0x8000u) >> 16;
+                    pl[1][i] = (__float_as_uint(e1 - __uint_as_float(u1 & 0xffff0000u)) + 0x8000u) >> 16;
+                    l_run[i] = l_run[i] * corr[i] + e0 + e1;
+                } else {
+                    l_run[i] = l_run[i] * corr[i] + __uint_as_float(u0 & 0xffff0000u) + __uint_as_float(u1 & 0xffff0000u);
+                    if constexpr (FEAT) lx_run[i] = lx_run[i] * corr[i] + e0 + e1;
+                }
                 m_run[i] = mn;
             }
             if (quad * 4 < GP) {
@@ -425,22 +472,29 @@ __global__ __launch_bounds__((AttnCfg<T, D, G>::THREADS)) void attn_kernel(const
                 for (int i = 0; i < 4; ++i) {
                     my_pb[(quad * 4 + i) * PS + n16] = (uint16_t)pb[0][i];
                     my_pb[(quad * 4 + i) * PS + 16 + n16] = (uint16_t)pb[1][i];
+                    if constexpr (C::SPLIT_P) {
+                        my_pb[(GP + quad * 4 + i) * PS + n16] = (uint16_t)pl[0][i];
+                        my_pb[(GP + quad * 4 + i) * PS + 16 + n16] = (uint16_t)pl[1][i];
+                    }
                 }
             }
             if (__any(changed)) {  // the running maximum moved: rescale what has been accumulated
 #pragma unroll
-                for (int e = 0; e < 8; ++e)
+                for (int e = 0; e < ET; ++e)
 #pragma unroll
                     for (int i = 0; i < 4; ++i) o[e][i] *= corr[i];
             }
             __builtin_amdgcn_wave_barrier();
             // A operand of P.V: P[head n16][k-slots quad*8 .. +8]; k-slot u of group quad is key base + quad*8 + u
-            B128 pa;
-            if (n16 < GP) pa.u = *reinterpret_cast<const uint4*>(my_pb + n16 * PS + quad * 8);
-            else pa.u = make_uint4(0, 0, 0, 0);
-            // B operand: tile e = channel n16*8 + e over this lane's 8 k-slots (8x8 transpose in registers)
+            B128 pa, pr;
+            pa.u = pr.u = make_uint4(0, 0, 0, 0);
+            if (n16 < GP) {
+                pa.u = *reinterpret_cast<const uint4*>(my_pb + n16 * PS + quad * 8);
+                if constexpr (C::SPLIT_P) pr.u = *reinterpret_cast<const uint4*>(my_pb + (GP + n16) * PS + quad * 8);
+            }
+            // B operand: tile e = channel n16*ET + e over this lane's 8 k-slots (8 x ET transpose in registers)
 #pragma unroll
-            for (int e = 0; e < 8; ++e) {
+            for (int e = 0; e < ET; ++e) {
                 const uint32_t sel = (e & 1) ? 0x07060302u : 0x05040100u;
                 B128 vb;
                 vb.u.x = __builtin_amdgcn_perm(dword_of(vr[1], e >> 1), dword_of(vr[0], e >> 1), sel);
@@ -448,6 +502,7 @@ __global__ __launch_bounds__((AttnCfg<T, D, G>::THREADS)) void attn_kernel(const
                 vb.u.z = __builtin_amdgcn_perm(dword_of(vr[5], e >> 1), dword_of(vr[4], e >> 1), sel);
                 vb.u.w = __builtin_amdgcn_perm(dword_of(vr[7], e >> 1), dword_of(vr[6], e >> 1), sel);
                 o[e] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(pa.v, vb.v, o[e], 0, 0, 0);
+                if constexpr (C::SPLIT_P) o[e] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(pr.v, vb.v, o[e], 0, 0, 0);
             }
             __builtin_amdgcn_wave_barrier();
         }
@@ -457,133 +512,17 @@ __global__ __launch_bounds__((AttnCfg<T, D, G>::THREADS)) void attn_kernel(const
             const int h = quad * 4 + i;
             const float ls = group_sum<16>(l_run[i]);
             if (h < G) {
-                float* dst = s_acc + (size_t)wave * C::ACC_STRIDE + (size_t)h * D + n16 * 8;  // own K tile: its loop is over
-                *reinterpret_cast<float4*>(dst) = make_float4(o[0][i], o[1][i], o[2][i], o[3][i]);
-                *reinterpret_cast<float4*>(dst + 4) = make_float4(o[4][i], o[5][i], o[6][i], o[7][i]);
+                float* dst = s_acc + (size_t)wave * C::ACC_STRIDE + (size_t)h * D + n16 * ET;  // D = 128: own K tile, its loop is over
+#pragma unroll
+                for (int e = 0; e < ET; e += 4) *reinterpret_cast<float4*>(dst + e) = make_float4(o[e][i], o[e + 1][i], o[e + 2][i], o[e + 3][i]);
                 if (n16 == 0) {
                     s_m[wave * G + h] = m_run[i];
                     s_l[wave * G + h] = ls;
                 }
             }
-            if constexpr (FEAT) {
+            if constexpr (FEAT && !C::SPLIT_P) {
                 const float lxs = group_sum<16>(lx_run[i]);
                 if (h < G && n16 == 0) smem[C::LX_OFFSET + wave * G + h] = lxs;
-            }
-        }
-    } else if constexpr (C::MFMA) {
-        constexpr int KS = D / 32;  // MFMA k-steps
-        const int n16 = lane & 15, quad = lane >> 4;
-        B128 qa[KS];
-#pragma unroll
-        for (int ks = 0; ks < KS; ++ks) {
-            if (n16 < G) qa[ks].u = *reinterpret_cast<const uint4*>(qrow + (size_t)n16 * D + ks * 32 + quad * 8);
-            else qa[ks].u = make_uint4(0, 0, 0, 0);
-        }
-        float m_run[4], l_run[4];
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            m_run[i] = kNegBig;
-            l_run[i] = 0.f;
-        }
-        float* my_p = s_p + (size_t)wave * KT * GP;
-        float* my_corr = s_corr + wave * GP;
-
-        for (int base = start + wave * KT; base < end; base += WAVES * KT) {
-            B128 kb[2][KS];
-            uint4 vr[VU];
-#pragma unroll
-            for (int nt = 0; nt < 2; ++nt) {
-                const int kc = min(base + nt * 16 + n16, end - 1);  // clamp: always a live slot
-#pragma unroll
-                for (int ks = 0; ks < KS; ++ks) kb[nt][ks].u = Krow[(size_t)kc * CH + ks * 4 + quad];
-            }
-#pragma unroll
-            for (int u = 0; u < VU; ++u) {
-                const int kc = min(base + u * KG + kgv, end - 1);
-                vr[u] = Vrow[(size_t)kc * CH + dl];
-            }
-            f32x4_t c[2];
-#pragma unroll
-            for (int nt = 0; nt < 2; ++nt) {
-                c[nt] = (f32x4_t){0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-                for (int ks = 0; ks < KS; ++ks)
-                    c[nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(qa[ks].v, kb[nt][ks].v, c[nt], 0, 0, 0);
-            }
-            // result layout: lane = key n16 of tile nt, element i = head quad*4 + i
-            if constexpr (FEAT) {
-                float* lg_row = P.logit + (size_t)row * P.cap * GP;
-                if (quad * 4 < GP) {
-                    if (base + n16 < end)
-                        *reinterpret_cast<float4*>(lg_row + (size_t)(base + n16) * GP + quad * 4) =
-                            make_float4(c[0][0] * P.scale_log2e, c[0][1] * P.scale_log2e, c[0][2] * P.scale_log2e, c[0][3] * P.scale_log2e);
-                    if (base + 16 + n16 < end)
-                        *reinterpret_cast<float4*>(lg_row + (size_t)(base + 16 + n16) * GP + quad * 4) =
-                            make_float4(c[1][0] * P.scale_log2e, c[1][1] * P.scale_log2e, c[1][2] * P.scale_log2e, c[1][3] * P.scale_log2e);
-                }
-            }
-            float p[2][4], corr[4];
-            bool changed = false;
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const float s0 = (base + n16 < end) ? c[0][i] * P.scale_log2e : kNegBig;
-                const float s1 = (base + 16 + n16 < end) ? c[1][i] * P.scale_log2e : kNegBig;
-                const float mn = fmaxf(m_run[i], row16_max(fmaxf(s0, s1)));
-                changed |= mn > m_run[i];
-                corr[i] = exp2f(m_run[i] - mn);
-                p[0][i] = exp2f(s0 - mn);
-                p[1][i] = exp2f(s1 - mn);
-                l_run[i] = l_run[i] * corr[i] + p[0][i] + p[1][i];
-                m_run[i] = mn;
-            }
-            const bool any_changed = __any(changed);
-            if (quad * 4 < GP) {
-                *reinterpret_cast<float4*>(my_p + (size_t)n16 * GP + quad * 4) = make_float4(p[0][0], p[0][1], p[0][2], p[0][3]);
-                *reinterpret_cast<float4*>(my_p + (size_t)(16 + n16) * GP + quad * 4) = make_float4(p[1][0], p[1][1], p[1][2], p[1][3]);
-                if (n16 == 0) *reinterpret_cast<float4*>(my_corr + quad * 4) = make_float4(corr[0], corr[1], corr[2], corr[3]);
-            }
-            __builtin_amdgcn_wave_barrier();
-            if (any_changed) {  // the running maximum moved: rescale what has been accumulated
-                float cr[GP];
-#pragma unroll
-                for (int h4 = 0; h4 < GP; h4 += 4) {
-                    const float4 t = *reinterpret_cast<const float4*>(my_corr + h4);
-                    cr[h4] = t.x; cr[h4 + 1] = t.y; cr[h4 + 2] = t.z; cr[h4 + 3] = t.w;
-                }
-#pragma unroll
-                for (int h = 0; h < G; ++h)
-#pragma unroll
-                    for (int e = 0; e < EPL; ++e) acc[h][e] *= cr[h];
-            }
-#pragma unroll
-            for (int u = 0; u < VU; ++u) {
-                float pp[GP];
-#pragma unroll
-                for (int h4 = 0; h4 < GP; h4 += 4) {
-                    const float4 t = *reinterpret_cast<const float4*>(my_p + (size_t)(u * KG + kgv) * GP + h4);
-                    pp[h4] = t.x; pp[h4 + 1] = t.y; pp[h4 + 2] = t.z; pp[h4 + 3] = t.w;
-                }
-                float vf[EPL];
-                Vec16<T>::unpack(vr[u], vf);
-#pragma unroll
-                for (int e = 0; e < EPL; ++e)
-#pragma unroll
-                    for (int h = 0; h < G; ++h) acc[h][e] = fmaf(pp[h], vf[e], acc[h][e]);
-            }
-            __builtin_amdgcn_wave_barrier();
-        }
-        // publish: every (wave, key group) its accumulator; m is uniform in the wave, l is the
-        // sum over the 16 key lanes and is credited to key group 0
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const float ls = group_sum<16>(l_run[i]);
-            const int h = quad * 4 + i;
-            if (n16 == 0 && h < G) {
-#pragma unroll
-                for (int g2 = 0; g2 < KG; ++g2) {
-                    s_m[(wave * KG + g2) * G + h] = m_run[i];
-                    s_l[(wave * KG + g2) * G + h] = g2 == 0 ? ls : 0.f;
-                }
             }
         }
     } else {
@@ -719,7 +658,7 @@ __global__ __launch_bounds__((AttnCfg<T, D, G>::THREADS)) void attn_kernel(const
         // in the chunk plane and in the windows that reach back to this step; the slot appended at this
         // step starts all six planes afresh.
         // exact normaliser partials: the bf16 D = 128 path keeps them apart from the rounded ones it uses for P.V
-        const float* s_lx = C::PVM ? smem + C::LX_OFFSET : s_l;
+        const float* s_lx = C::PVM && !C::SPLIT_P ? smem + C::LX_OFFSET : s_l;
         float* s_invL = smem + C::LX_OFFSET + NG * G;
         if (tid < G) {
             float ls = 0.f;
