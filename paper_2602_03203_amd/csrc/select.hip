@@ -14,10 +14,10 @@
 
 namespace fk {
 
-// LDS: hist [4][256] u32 (one histogram per pass, cleared once) | wavefront totals [16][2] | wavefront ORs [16] |
-// keys [lds_keys] u32
+// LDS (u32): histogram and list of range_select | histograms [4][256] of msd_select | wavefront totals [16][2] | wavefront minima
+// and maxima [16][2] | keys [lds_keys]
 static constexpr int kSelMaxLdsKeys = 36 * 1024;  // 144 KB of keys beside the histograms
-static constexpr int kSelLdsHead = 4 * 256 + 32 + 16;  // words before the keys: histograms, wavefront counts, wavefront ORs
+static constexpr int kSelLdsHead = kRangeWords + 4 * 256 + 32 + 32;  // words before the keys
 // (Four wavefronts per row instead of sixteen were measured and dropped: 11.3 against 8.1 us; a pass is a chain
 // key -> atomic -> barrier -> scan of LDS round trips, which more wavefronts shorten.)
 //
@@ -55,10 +55,11 @@ __global__ __launch_bounds__(THREADS) void select_keep_kernel(const float* __res
     int k = kmax;            // how many of them stay (0 <= k < ncand; a chunk: k <= ncand)
 
     extern __shared__ __attribute__((aligned(16))) uint32_t s_sel_mem[];
-    uint32_t* s_hist = s_sel_mem;                 // [4][256]
+    uint32_t* s_range = s_sel_mem;                // [kRangeWords]
+    uint32_t* s_hist = s_range + kRangeWords;     // [4][256]
     uint32_t* s_wtot = s_hist + 4 * 256;          // [16][2]: kept counts of every wavefront (greater, equal)
-    uint32_t* s_wor = s_wtot + 32;                // [16]: every wavefront's OR of key ^ first key
-    uint32_t* s_key = s_wor + 16;                 // [lds_keys]
+    uint32_t* s_wmm = s_wtot + 32;                // [16][2]: every wavefront's smallest and largest key
+    uint32_t* s_key = s_wmm + 32;                 // [lds_keys]
     uint32_t* s_slot = s_key + lds_keys;          // kSelMerge: [lds_keys] the candidates' slots
     constexpr int WAVES = THREADS / kWave;
     const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
@@ -89,25 +90,37 @@ __global__ __launch_bounds__(THREADS) void select_keep_kernel(const float* __res
     // The row's keys are read from global memory once and kept in LDS (rows beyond the LDS share of the launch are
     // re-read from global memory in every pass).  Eight loads in flight per thread.
     const bool in_lds = ncand <= lds_keys;  // kSelMerge: the host sized the launch so that it is
-    uint32_t base = 0, diff = ~0u;          // the keys' common bits, where known (msd_select)
-    for (int i = threadIdx.x; i < 4 * 256; i += THREADS) s_hist[i] = 0;
+    uint32_t key_lo = 0xffffffffu, key_hi = 0;  // smallest and largest key, gathered while the keys are written to LDS
+    for (int i = threadIdx.x; i < kRangeWords + 4 * 256; i += THREADS) s_range[i] = 0;
     if constexpr (MODE == kSelMerge) {
+        // Slot, then score: two dependent reads, eight of either in flight per thread (chunk by chunk, one survivor at a time, this
+        // gather took 15 of 37 us at 32 rows of 15360 survivors).
+        const int32_t* lists = sp.cand + (size_t)row * sp.nchunk * kmax;
+        for (int i0 = threadIdx.x; i0 < ncand; i0 += 8 * THREADS) {
+            int slot[8];
+            float v[8];
 #pragma unroll
-        for (int c = 0; c < kMaxChunks; ++c) {
-            if (c < sp.nchunk) {
-                const int32_t* list = sp.cand + ((size_t)row * sp.nchunk + c) * kmax;
-                const int cnt = base_of[c + 1] - base_of[c];
-                for (int o = threadIdx.x; o < cnt; o += THREADS) {
-                    const int slot = list[o];
-                    s_slot[base_of[c] + o] = (uint32_t)slot;
-                    s_key[base_of[c] + o] = score_key(sc[slot]);
+            for (int u = 0; u < 8; ++u) {
+                const int i = min(i0 + u * THREADS, ncand - 1);
+                int off = i;   // survivor i is number i - base_of[c] of its chunk c
+#pragma unroll
+                for (int c = 1; c < kMaxChunks; ++c) off = i >= base_of[c] ? c * kmax + i - base_of[c] : off;
+                slot[u] = lists[off];
+            }
+#pragma unroll
+            for (int u = 0; u < 8; ++u) v[u] = sc[slot[u]];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                if (i0 + u * THREADS < ncand) {
+                    const uint32_t key = score_key(v[u]);
+                    s_slot[i0 + u * THREADS] = (uint32_t)slot[u];
+                    s_key[i0 + u * THREADS] = key;
+                    key_lo = min(key_lo, key);
+                    key_hi = max(key_hi, key);
                 }
             }
         }
     } else if (in_lds) {
-        // on the way: which bits differ between any two keys of the row (the select starts at the highest of them)
-        base = score_key(sc[0]);
-        uint32_t spread = 0;
         for (int i0 = threadIdx.x; i0 < ncand; i0 += 8 * THREADS) {
             float v[8];
 #pragma unroll
@@ -117,18 +130,26 @@ __global__ __launch_bounds__(THREADS) void select_keep_kernel(const float* __res
                 if (i0 + u * THREADS < ncand) {
                     const uint32_t key = score_key(v[u]);
                     s_key[i0 + u * THREADS] = key;
-                    spread |= key ^ base;
+                    key_lo = min(key_lo, key);
+                    key_hi = max(key_hi, key);
                 }
             }
         }
-        spread = wave_or(spread);
-        if (lane == 0) s_wor[wave] = spread;
+    }
+    if (in_lds) {
+        wave_min_max(key_lo, key_hi);
+        if (lane == 0) {
+            s_wmm[2 * wave] = key_lo;
+            s_wmm[2 * wave + 1] = key_hi;
+        }
     }
     __syncthreads();
-    if (MODE != kSelMerge && in_lds) {
-        diff = 0;
+    if (in_lds) {
 #pragma unroll
-        for (int w = 0; w < WAVES; ++w) diff |= s_wor[w];
+        for (int w = 0; w < WAVES; ++w) {
+            key_lo = min(key_lo, s_wmm[2 * w]);
+            key_hi = max(key_hi, s_wmm[2 * w + 1]);
+        }
     }
     auto key_at = [&](int i) { return in_lds ? s_key[i] : score_key(sc[i]); };
 
@@ -137,8 +158,8 @@ __global__ __launch_bounds__(THREADS) void select_keep_kernel(const float* __res
     uint32_t want = (uint32_t)k;   // how many still to take among keys equal to the threshold
     if (k > 0) {
         auto key_of = [&](int i, bool& valid) { valid = true; return key_at(i); };
-        if (in_lds) msd_select<THREADS, 2>(key_of, ncand, (uint32_t)k, s_hist, base, diff, &prefix, &want);
-        else msd_select<THREADS, 16>(key_of, ncand, (uint32_t)k, s_hist, base, diff, &prefix, &want);
+        if (in_lds) range_select<THREADS, 2>(key_of, ncand, (uint32_t)k, s_range, s_hist, s_wtot, key_lo, key_hi, &prefix, &want);
+        else msd_select<THREADS, 16>(key_of, ncand, (uint32_t)k, s_hist, 0u, ~0u, &prefix, &want);
     }
     // now: keep key > prefix, and the first `want` keys == prefix (k == 0: keep no candidate).  Ordered pass: every
     // wavefront owns one contiguous stretch of the row and walks it 64 slots at a time (coalesced, no barrier inside):
@@ -299,9 +320,10 @@ __global__ __launch_bounds__(kSelThreads) void select_keep_sampled_kernel(const 
 // The same selection with the row in LDS (rows of up to kSampledLdsKeys candidates): both keys of every slot are formed
 // once, the radix passes and the ordered passes are those of select_keep_kernel (one barrier per pass, one ordered
 // walk per wavefront stretch), and the candidate marks take the place of the first key once the safe set is known.
-// LDS: hist [2][4][256] u32 | wavefront totals [16][4] | wavefront ORs [2][16] | key1 / candidate mark [lds_keys] |
-// key2 [lds_keys]
+// LDS (u32): histogram and list of range_select | histograms [4][256] of msd_select | wavefront totals [16][4] | wavefront minima
+// and maxima [16][4] | key1 / candidate mark [lds_keys] | key2 [lds_keys]
 static constexpr int kSampledLdsKeys = 18 * 1024;
+static constexpr int kSampledLdsHead = kRangeWords + 4 * 256 + 64 + 64;  // words before the keys
 template <int THREADS>
 __global__ __launch_bounds__(THREADS) void select_keep_sampled_lds_kernel(const float* __restrict__ scores,
                                                                           const float* __restrict__ noise,
@@ -324,18 +346,17 @@ __global__ __launch_bounds__(THREADS) void select_keep_sampled_lds_kernel(const 
     const int k2 = K - E;           // candidates that stay
 
     extern __shared__ __attribute__((aligned(16))) uint32_t s_sel_mem[];
-    uint32_t* s_hist = s_sel_mem;            // [2][4][256]
-    uint32_t* s_wtot = s_hist + 2 * 4 * 256; // [16][4]
-    uint32_t* s_wor = s_wtot + 64;           // [2][16] every wavefront's OR of key ^ first key, for either key
-    uint32_t* s_k1 = s_wor + 32;             // [lds_keys] key of the score; later 1 = candidate, 0 = safe
+    uint32_t* s_range = s_sel_mem;           // [kRangeWords]
+    uint32_t* s_hist = s_range + kRangeWords;// [4][256]
+    uint32_t* s_wtot = s_hist + 4 * 256;     // [16][4]
+    uint32_t* s_wmm = s_wtot + 64;           // [16][4] every wavefront's smallest and largest first and second key
+    uint32_t* s_k1 = s_wmm + 64;             // [lds_keys] key of the score; later 1 = candidate, 0 = safe
     uint32_t* s_k2 = s_k1 + lds_keys;        // [lds_keys] key of score - noise
     constexpr int WAVES = THREADS / kWave;
     const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
 
-    for (int i = threadIdx.x; i < 2 * 4 * 256; i += THREADS) s_hist[i] = 0;
-    // on the way: the bits in which any two keys of the row differ (either select starts at the highest of them)
-    const uint32_t base1 = score_key(sc[0]), base2 = score_key(sc[0] - nz[0]);
-    uint32_t spread1 = 0, spread2 = 0;
+    for (int i = threadIdx.x; i < kRangeWords; i += THREADS) s_range[i] = 0;
+    uint32_t min1 = 0xffffffffu, max1 = 0;   // of the first keys
     for (int i0 = threadIdx.x; i0 < others; i0 += 8 * THREADS) {
         float v[8], z[8];
 #pragma unroll
@@ -350,22 +371,20 @@ __global__ __launch_bounds__(THREADS) void select_keep_sampled_lds_kernel(const 
                 const uint32_t key1 = score_key(v[u]), key2 = score_key(v[u] - z[u]);
                 s_k1[i0 + u * THREADS] = key1;
                 s_k2[i0 + u * THREADS] = key2;
-                spread1 |= key1 ^ base1;
-                spread2 |= key2 ^ base2;
+                min1 = min(min1, key1);
+                max1 = max(max1, key1);
             }
     }
-    spread1 = wave_or(spread1);
-    spread2 = wave_or(spread2);
+    wave_min_max(min1, max1);
     if (lane == 0) {
-        s_wor[wave] = spread1;
-        s_wor[16 + wave] = spread2;
+        s_wmm[4 * wave] = min1;
+        s_wmm[4 * wave + 1] = max1;
     }
     __syncthreads();
-    uint32_t diff1 = 0, diff2 = 0;
 #pragma unroll
     for (int w = 0; w < WAVES; ++w) {
-        diff1 |= s_wor[w];
-        diff2 |= s_wor[16 + w];
+        min1 = min(min1, s_wmm[4 * w]);
+        max1 = max(max1, s_wmm[4 * w + 1]);
     }
 
     // every wavefront owns one contiguous stretch of the row (the ordered passes walk it 64 slots at a time)
@@ -375,8 +394,9 @@ __global__ __launch_bounds__(THREADS) void select_keep_sampled_lds_kernel(const 
     // (1) safe set: the k_safe best by score; everything else becomes a candidate
     uint32_t T1 = 0, want1 = 0;
     if (k_safe > 0)
-        msd_select<THREADS, 2>([&](int i, bool& valid) { valid = true; return s_k1[i]; }, others, (uint32_t)k_safe, s_hist, base1, diff1, &T1,
-                               &want1);
+        range_select<THREADS, 2>([&](int i, bool& valid) { valid = true; return s_k1[i]; }, others, (uint32_t)k_safe, s_range, s_hist, s_wtot,
+                                 min1, max1, &T1, &want1);
+    uint32_t min2 = 0xffffffffu, max2 = 0;   // of the candidates' second keys
     {
         uint32_t eq = 0;  // slots equal to T1 in this stretch
         if (k_safe > 0)
@@ -384,6 +404,8 @@ __global__ __launch_bounds__(THREADS) void select_keep_sampled_lds_kernel(const 
                 const int i = i0 + lane;
                 eq += (uint32_t)__popcll(__ballot(i < w1 && s_k1[min(i, others - 1)] == T1));
             }
+        __syncthreads();   // s_wtot and s_range have been read
+        for (int i = threadIdx.x; i < kRangeWords; i += THREADS) s_range[i] = 0;
         if (lane == 0) s_wtot[4 * wave] = eq;
         __syncthreads();
         uint32_t eq_run = 0;
@@ -397,16 +419,30 @@ __global__ __launch_bounds__(THREADS) void select_keep_sampled_lds_kernel(const 
             const uint32_t e_below = __builtin_amdgcn_mbcnt_hi((uint32_t)(me >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)me, 0));
             const bool safe = k_safe > 0 && (key > T1 || (is_eq && eq_run + e_below < want1));
             if (live) s_k1[i] = safe ? 0u : 1u;
+            if (live && !safe) {
+                min2 = min(min2, s_k2[i]);
+                max2 = max(max2, s_k2[i]);
+            }
             eq_run += (uint32_t)__popcll(me);
+        }
+        wave_min_max(min2, max2);
+        if (lane == 0) {
+            s_wmm[4 * wave + 2] = min2;
+            s_wmm[4 * wave + 3] = max2;
         }
     }
     __syncthreads();
+#pragma unroll
+    for (int w = 0; w < WAVES; ++w) {
+        min2 = min(min2, s_wmm[4 * w + 2]);
+        max2 = max(max2, s_wmm[4 * w + 3]);
+    }
 
     // (2) which candidates stay: the k2 largest t = score - noise among them
     uint32_t T2 = 0, want2 = 0;
     if (k2 > 0)
-        msd_select<THREADS, 2>([&](int i, bool& valid) { valid = s_k1[i] != 0u; return s_k2[i]; }, others, (uint32_t)k2,
-                               s_hist + 4 * 256, base2, diff2, &T2, &want2);
+        range_select<THREADS, 2>([&](int i, bool& valid) { valid = s_k1[i] != 0u; return s_k2[i]; }, others, (uint32_t)k2, s_range, s_hist, s_wtot,
+                                 min2, max2, &T2, &want2);
 
     // (3) ordered output: safe pairs, surviving candidates (ties to the lower slot), protected tail
     auto walk = [&](auto write_, uint32_t& keep_run, uint32_t& eq_run) {
@@ -564,7 +600,7 @@ extern "C" fk_status fk_select_keep_sampled(const fk_cache_desc* desc, const flo
     const int rows = desc->batch * desc->n_kv_heads;
     if (desc->capacity <= kSampledLdsKeys) {  // every row fits LDS with both of its keys
         const int lds_keys = (desc->capacity + 3) & ~3;
-        const size_t lds = sizeof(uint32_t) * (2 * 4 * 256 + 64 + 32 + 2 * (size_t)lds_keys);
+        const size_t lds = sizeof(uint32_t) * (kSampledLdsHead + 2 * (size_t)lds_keys);
         auto kern = select_keep_sampled_lds_kernel<kSelThreads>;
         static bool lds_ok[kMaxDevices] = {};
         if (!allow_dynamic_lds((const void*)kern, 160 * 1024, lds_ok)) return FK_ERR_LAUNCH;

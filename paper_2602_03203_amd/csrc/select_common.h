@@ -112,15 +112,24 @@ __device__ __forceinline__ void radix_threshold(int nslots, uint32_t k, KeyFn ke
     *want_out = want;
 }
 
-// OR over the wavefront (result in every lane).
-__device__ __forceinline__ uint32_t wave_or(uint32_t v) {
-    v |= dpp_u32<0x111, 0xF>(v);  // row_shr:1
-    v |= dpp_u32<0x112, 0xF>(v);  // row_shr:2
-    v |= dpp_u32<0x114, 0xF>(v);  // row_shr:4
-    v |= dpp_u32<0x118, 0xF>(v);  // row_shr:8
-    v |= dpp_u32<0x142, 0xA>(v);  // row_bcast:15 into rows 1 and 3
-    v |= dpp_u32<0x143, 0xC>(v);  // row_bcast:31 into rows 2 and 3
-    return (uint32_t)__builtin_amdgcn_readlane((int)v, kWave - 1);
+// minimum and maximum over the wavefront (results in every lane)
+template <int CTRL, int ROW_MASK>
+__device__ __forceinline__ uint32_t dpp_keep_u32(uint32_t v) {
+    return (uint32_t)__builtin_amdgcn_update_dpp((int)v, (int)v, CTRL, ROW_MASK, 0xF, false);  // lanes without a source keep theirs
+}
+__device__ __forceinline__ void wave_min_max(uint32_t& lo, uint32_t& hi) {
+#define FK_MIN_MAX_STEP(CTRL, MASK)                 \
+    lo = min(lo, dpp_keep_u32<CTRL, MASK>(lo));     \
+    hi = max(hi, dpp_keep_u32<CTRL, MASK>(hi));
+    FK_MIN_MAX_STEP(0x111, 0xF)  // row_shr:1
+    FK_MIN_MAX_STEP(0x112, 0xF)  // row_shr:2
+    FK_MIN_MAX_STEP(0x114, 0xF)  // row_shr:4
+    FK_MIN_MAX_STEP(0x118, 0xF)  // row_shr:8
+    FK_MIN_MAX_STEP(0x142, 0xA)  // row_bcast:15 into rows 1 and 3
+    FK_MIN_MAX_STEP(0x143, 0xC)  // row_bcast:31 into rows 2 and 3
+#undef FK_MIN_MAX_STEP
+    lo = (uint32_t)__builtin_amdgcn_readlane((int)lo, kWave - 1);
+    hi = (uint32_t)__builtin_amdgcn_readlane((int)hi, kWave - 1);
 }
 
 // Most-significant-digit-first passes (8-bit digits, at most four) over the slots [0, nslots) whose key_of(i, valid)
@@ -251,6 +260,175 @@ __device__ __forceinline__ void msd_select(KeyFn key_of, int nslots, uint32_t k,
     }
     *T_out = prefix;
     *want_out = want;
+}
+
+// ---- selection by range ------------------------------------------------------------------------------------------
+// The k-th best of the keys by ONE histogram over their range: kRangeBins equal bins from the smallest to the largest key
+// (keys of one sign: of the bit pattern, that is of the logarithm; of both signs: of the value, since most bit patterns between
+// them are numbers near 0 that no score takes), then the list of the keys in the cut's bin, ranked as in msd_select.  Digits of
+// the bit pattern put the scores of a row, whose exponents span a few octaves, into a handful of bins: every LDS atomic of a
+// wavefront then waits for the others on its word (15360 keys between 1.2 and 4.5: 12 us in the first pass, 2984 keys left),
+// and a second pass follows.  More than 64 keys in the bin (ties, outliers) or values the bins cannot divide (infinities of
+// both signs, NaN among negative and positive ones): msd_select on what is left.
+static constexpr int kRangeBins = 1024;
+// LDS words: histogram | list: count, threshold, how many of it, unused, 64 keys.  Zero on entry; dirty on return.
+static constexpr int kRangeWords = kRangeBins + 4 + kWave;
+
+__device__ __forceinline__ float key_score(uint32_t key) { return __uint_as_float((key & 0x80000000u) ? key ^ 0x80000000u : ~key); }
+
+// kmin, kmax: smallest and largest valid key.  hist4: [4][256] words for msd_select, contents undefined; part: 2 * THREADS / 64 words.
+// The other conditions are those of msd_select (every thread calls, 1 <= k <= number of valid slots).
+template <int THREADS, int U, typename KeyFn>
+__device__ __forceinline__ void range_select(KeyFn key_of, int nslots, uint32_t k, uint32_t* range, uint32_t* hist4, uint32_t* part,
+                                             uint32_t kmin, uint32_t kmax, uint32_t* T_out, uint32_t* want_out) {
+    const int lane = threadIdx.x & (kWave - 1);
+    if (kmin == kmax) {
+        *T_out = kmin;
+        *want_out = k;
+        return;
+    }
+    const bool by_value = (kmin ^ kmax) >> 31;
+    const float lo = key_score(kmin), scale = 1023.9f / (key_score(kmax) - lo);
+    const int shift = max(22 - __clz((int)(kmax - kmin)), 0);   // (kmax - kmin) >> shift < 1024
+    // a finite, positive scale: kmin and kmax are numbers and their difference is a normal one
+    const bool divides = !by_value || (scale > 0.f && scale < 3.4e38f);
+    auto bin_of = [&](uint32_t key) -> uint32_t {
+        if (by_value) return (uint32_t)min(max((int)((key_score(key) - lo) * scale), 0), kRangeBins - 1);   // monotone: so is every step
+        return (key - kmin) >> shift;
+    };
+    uint32_t bin = 0, want = k, inbin = 0xffffffffu;
+    if (divides) {
+        for (int i0 = 0; i0 < nslots; i0 += U * THREADS) {   // uniform trip count: the wavefront votes below
+            uint32_t kv[U];
+            bool ok[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) kv[u] = key_of(min(i0 + u * THREADS + (int)threadIdx.x, nslots - 1), ok[u]);
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const bool todo = ok[u] && i0 + u * THREADS + (int)threadIdx.x < nslots;
+                const uint32_t dg = bin_of(kv[u]);
+                const unsigned long long act = __ballot(todo);
+                if (act != 0) {   // one vote: a wavefront of equal bins adds its count once
+                    const int first = __ffsll((long long)act) - 1;
+                    const uint32_t lead = __builtin_amdgcn_readlane(dg, first);
+                    if (__ballot(todo && dg == lead) == act) {
+                        if (lane == first) atomicAdd(&range[lead], (uint32_t)__popcll(act));
+                    } else if (todo) {
+                        atomicAdd(&range[dg], 1u);
+                    }
+                }
+            }
+        }
+        __syncthreads();
+        // One wavefront finds the bin (sixteen doing it each for itself cost four turns on every SIMD): four blocks of 256 bins from the
+        // top, lane l owns the bins 255 - 4 l .. 252 - 4 l of each.
+        if (threadIdx.x < kWave) {
+            uint4 h[4];
+            uint32_t tot[4], incl[4];
+#pragma unroll
+            for (int b = 0; b < 4; ++b) h[b] = *reinterpret_cast<const uint4*>(range + 256 * (3 - b) + 252 - 4 * lane);
+#pragma unroll
+            for (int b = 0; b < 4; ++b) {
+                tot[b] = h[b].x + h[b].y + h[b].z + h[b].w;
+                incl[b] = wave_scan_incl(tot[b]);
+            }
+            uint32_t before = 0;   // keys in the blocks above
+#pragma unroll
+            for (int b = 0; b < 4; ++b) {
+                const uint32_t excl = before + incl[b] - tot[b];
+                if (excl < k && k <= excl + tot[b]) {   // one lane, one block
+                    const uint32_t c[4] = {h[b].w, h[b].z, h[b].y, h[b].x};
+                    uint32_t run = excl;
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) {
+                        if (run < k && k <= run + c[j]) {
+                            part[0] = 256 * (3 - b) + 255 - 4 * lane - j;
+                            part[1] = k - run;
+                            part[2] = c[j];
+                        }
+                        run += c[j];
+                    }
+                }
+                before += __builtin_amdgcn_readlane(incl[b], kWave - 1);
+            }
+        }
+        __syncthreads();
+        bin = part[0];
+        want = part[1];
+        inbin = part[2];   // 1 <= want <= inbin
+        if (inbin <= (uint32_t)kWave) {
+            uint32_t* list = range + kRangeBins;
+            for (int i0 = 0; i0 < nslots; i0 += U * THREADS) {
+                uint32_t kv[U];
+                bool ok[U];
+#pragma unroll
+                for (int u = 0; u < U; ++u) kv[u] = key_of(min(i0 + u * THREADS + (int)threadIdx.x, nslots - 1), ok[u]);
+#pragma unroll
+                for (int u = 0; u < U; ++u)
+                    if (ok[u] && i0 + u * THREADS + (int)threadIdx.x < nslots && bin_of(kv[u]) == bin) list[4 + atomicAdd(list, 1u)] = kv[u];
+            }
+            __syncthreads();
+            // One entry per lane of one wavefront; rank = entries before it under (key descending, place in the list), which depends on
+            // the list's order only among equal keys; an unused place holds 0 and is after every entry it is compared with.
+            if (threadIdx.x < kWave) {
+                const bool have = (uint32_t)lane < inbin;
+                const uint32_t key = list[4 + lane];
+                uint32_t rank = 0;
+                for (uint32_t q = 0; q < inbin; q += 4) {
+                    const uint4 e = *reinterpret_cast<const uint4*>(list + 4 + q);
+                    rank += (e.x > key || (e.x == key && q < (uint32_t)lane)) + (e.y > key || (e.y == key && q + 1 < (uint32_t)lane)) +
+                            (e.z > key || (e.z == key && q + 2 < (uint32_t)lane)) + (e.w > key || (e.w == key && q + 3 < (uint32_t)lane));
+                }
+                const int at = __ffsll((long long)__ballot(have && rank == want - 1)) - 1;   // exactly one lane
+                const uint32_t T = __builtin_amdgcn_readlane(key, at);
+                const uint32_t over = (uint32_t)__popcll(__ballot(have && key > T));
+                if (lane == 0) {
+                    list[1] = T;
+                    list[2] = want - over;
+                }
+            }
+            __syncthreads();
+            *T_out = list[1];
+            *want_out = list[2];
+            return;
+        }
+    }
+    // digit by digit among the keys of the bin (all keys, where there are no bins), from the highest bit in which any two differ
+    const bool all = !divides;
+    __syncthreads();   // part has been read
+    auto left = [&](int i, bool& valid) {
+        const uint32_t key = key_of(i, valid);
+        valid = valid && (all || bin_of(key) == bin);
+        return key;
+    };
+    uint32_t mn = kmin, mx = kmax;
+    if (!all) {
+        mn = 0xffffffffu;
+        mx = 0;
+        for (int i = threadIdx.x; i < nslots; i += THREADS) {
+            bool valid;
+            const uint32_t key = left(i, valid);
+            if (valid) {
+                mn = min(mn, key);
+                mx = max(mx, key);
+            }
+        }
+        wave_min_max(mn, mx);
+        if (lane == 0) {
+            part[2 * (threadIdx.x / kWave)] = mn;
+            part[2 * (threadIdx.x / kWave) + 1] = mx;
+        }
+    }
+    for (int i = threadIdx.x; i < 4 * 256; i += THREADS) hist4[i] = 0;
+    __syncthreads();
+    if (!all) {
+        for (int w = 0; w < THREADS / kWave; ++w) {
+            mn = min(mn, part[2 * w]);
+            mx = max(mx, part[2 * w + 1]);
+        }
+        __syncthreads();   // the caller's again
+    }
+    msd_select<THREADS, U>(left, nslots, want, hist4, mn, mn ^ mx, T_out, want_out);
 }
 
 }  // namespace fk

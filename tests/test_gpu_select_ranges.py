@@ -1,0 +1,85 @@
+"""Selection where the histogram over the keys' range can go wrong: value distributions that crowd one bin, both signs, infinities and NaN,
+ranges of a few bits, and row lengths around the workgroup's, against the oracle."""
+import numpy as np
+import pytest
+import torch
+
+import synth_inputs as si
+from util import random_cache
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def gpu():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import gpu_util
+    import paper_2602_03203_amd as fk
+    fk.lib()
+    return gpu_util
+
+
+def values(kind, n, seed):
+    z = si.normal(seed, si.T_SCORE, 0, np.arange(n)).astype(np.float32)
+    s = z.copy()
+    if kind == "positive":
+        s = np.exp(z)
+    elif kind == "negative":
+        s = -np.exp(3 * z)
+    elif kind == "outlier":           # all but two keys share one bin
+        s[n // 3], s[n // 2] = 1e30, -1e30
+    elif kind == "huge":              # the difference of the extremes overflows
+        s[n // 3], s[n // 2] = 3.4e38, -3.4e38
+    elif kind == "infinite":
+        s[::7], s[3::11] = np.inf, -np.inf
+    elif kind == "nan":
+        s[::5] = np.nan
+    elif kind == "denormal":          # both signs, a range below the smallest normal number
+        s = (z * 1e-40).astype(np.float32)
+    elif kind == "bits":              # neighbours of 1.0, many ties
+        s = (np.float32(1.0).view(np.uint32) + (si.hash_u64(seed, 1, 0, np.arange(n)) % np.uint64(37)).astype(np.uint32)).view(np.float32)
+    elif kind == "zeros":             # -0 and +0 are equal
+        s = np.where(z > 0.5, z, np.where(z > 0, np.float32(0.0), np.float32(-0.0))).astype(np.float32)
+    elif kind == "two":
+        s = np.where(z > 0, np.float32(2.5), np.float32(-1.0)).astype(np.float32)
+    elif kind == "equal":
+        s[:] = -3.0
+    return s
+
+
+KINDS = ["normal", "positive", "negative", "outlier", "huge", "infinite", "nan", "denormal", "bits", "zeros", "two", "equal"]
+
+
+@pytest.mark.parametrize("kind", KINDS)
+@pytest.mark.parametrize("n,budget,recent", [(2176, 2048, 128), (1025, 64, 0), (130, 100, 16), (5000, 1, 0), (9000, 2500, 100)])
+def test_selection_over_value_ranges(gpu, ora, kind, n, budget, recent):
+    import paper_2602_03203_amd as fk
+    print(f"select {kind} n={n} budget={budget} recent={recent}", flush=True)
+    c = random_cache(ora, 5, "bf16", 1, 2, n, 64, lens=[n])
+    desc = fk.CacheDesc(1, 2, 2, 64, n, "bf16")
+    sc = np.stack([values(kind, n, 40 + h) for h in range(2)])[None]
+    noise = si.gen_gumbel(77, (1, 2, n))
+    pos, ln = gpu.to_dev(c.pos), torch.full((1, 2), n, dtype=torch.int32, device="cuda")
+    keep = torch.full((1, 2, budget), -1, dtype=torch.int32, device="cuda")
+    fk.fk_select_keep(desc, gpu.to_dev(sc), pos, ln, n, budget, recent, keep)
+    gpu.assert_keep_equal(keep.cpu().numpy(), ora.select_keep(sc, c.pos, c.len, budget, recent, "sort"), c.len, budget, kind)
+    if kind not in ("nan", "infinite", "huge"):   # score - noise is a number
+        fk.fk_select_keep_sampled(desc, gpu.to_dev(sc), gpu.to_dev(noise), pos, ln, n, budget, recent, 2 * (n - budget), keep)
+        ref = ora.select_keep_sampled(sc, noise, c.pos, c.len, budget, recent, 2 * (n - budget))
+        gpu.assert_keep_equal(keep.cpu().numpy(), ref, c.len, budget, kind + " sampled")
+
+
+@pytest.mark.parametrize("kind", ["normal", "positive", "outlier", "bits", "infinite"])
+def test_split_selection_over_value_ranges(gpu, ora, kind):
+    import paper_2602_03203_amd as fk
+    n, budget, recent = 20011, 1500, 33
+    c = random_cache(ora, 6, "bf16", 1, 2, n, 64, lens=[n])
+    desc = fk.CacheDesc(1, 2, 2, 64, n, "bf16")
+    sc = np.stack([values(kind, n, 60 + h) for h in range(2)])[None]
+    need = fk.fk_select_keep_workspace(desc, n, budget, recent)
+    assert need > 0
+    keep = torch.full((1, 2, budget), -1, dtype=torch.int32, device="cuda")
+    fk.fk_select_keep_ws(desc, gpu.to_dev(sc), None, torch.full((1, 2), n, dtype=torch.int32, device="cuda"), n, budget, recent, keep,
+                         torch.empty(need, dtype=torch.uint8, device="cuda"))
+    gpu.assert_keep_equal(keep.cpu().numpy(), ora.select_keep(sc, c.pos, c.len, budget, recent, "sort"), c.len, budget, kind)
