@@ -202,7 +202,8 @@ struct AttnParams {
     const int32_t* pos_new;
     float scale_log2e;
     int n_kv, cap, split_len, nsplit;
-    int rotate;          // bf16 D = 128: workgroups start at different tiles of their splits
+    int rotate;          // bf16: workgroups start at different tiles of their splits
+    int by_length;       // bf16, streamed cache, unsplit rows: workgroup i takes the i-th longest row
     float* rec;          // [rows][nsplit][G][D + 2]
     uint32_t* row_cnt;   // [rows], zero between launches
     void* out;
@@ -225,15 +226,94 @@ __device__ __forceinline__ float4 keep_if(bool c, const float4 p) {
     return make_float4(c ? p.x : 0.f, c ? p.y : 0.f, c ? p.z : 0.f, c ? p.w : 0.f);
 }
 
+// The row at place `rank` of the rows from the longest to the shortest: lengths in 256 classes (equal within a 256th of the
+// longest), rows of a class in their order; lengths that differ by less than an eighth keep the order they have.  LDS words:
+// lengths [rows] | class counts [256] | maximum, minimum, result.  Every thread calls;
+// all workgroups of a launch see the same lengths (they change after the last one has finished).
+template <int THREADS>
+__device__ __forceinline__ int row_by_length(const int32_t* len, int rows, int cap, int rank, int* lds) {
+    int *s_len = lds, *s_cnt = lds + rows, *s_max = s_cnt + 256, *s_min = s_max + 1, *s_row = s_min + 1;
+    const int tid = threadIdx.x, lane = tid & (kWave - 1);
+    if (tid < 256) s_cnt[tid] = 0;
+    if (tid == 0) {
+        *s_max = 1;
+        *s_min = cap;
+    }
+    __syncthreads();
+    int lo = cap, hi = 1;
+    for (int r = tid; r < rows; r += THREADS) {
+        const int n = min(max(len[r], 0), cap);
+        s_len[r] = n;
+        lo = min(lo, n);
+        hi = max(hi, n);
+    }
+    if (lo < *s_min) atomicMin(s_min, lo);
+    if (hi > *s_max) atomicMax(s_max, hi);
+    __syncthreads();
+    lo = *s_min;
+    hi = *s_max;
+    if (hi - lo < hi / 8) {
+        __syncthreads();
+        return rank;
+    }
+    const float per_class = 255.9f / (float)*s_max;
+    auto cls = [&](int n) { return 255 - (int)((float)n * per_class); };   // the longest first
+    for (int r = tid; r < rows; r += THREADS) atomicAdd(&s_cnt[cls(s_len[r])], 1);
+    __syncthreads();
+    if (tid < kWave) {   // one wavefront, four classes a lane
+        int c[4], tot = 0;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) tot += c[j] = s_cnt[4 * lane + j];
+        int incl = tot;
+#pragma unroll
+        for (int off = 1; off < kWave; off <<= 1) {
+            const int o = __shfl_up(incl, off);
+            if (lane >= off) incl += o;
+        }
+        int run = incl - tot, mine = -1, left = 0;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            if (run <= rank && rank < run + c[j]) {   // one lane
+                mine = 4 * lane + j;
+                left = rank - run;
+            }
+            run += c[j];
+        }
+        const int src = __ffsll((long long)__ballot(mine >= 0)) - 1;
+        const int k = __builtin_amdgcn_readlane(mine, src);
+        left = __builtin_amdgcn_readlane(left, src);
+        for (int base = 0; base < rows; base += kWave) {   // the left-th row of class k
+            const int r = base + lane;
+            unsigned long long m = __ballot(r < rows && cls(s_len[min(r, rows - 1)]) == k);
+            const int n = __popcll(m);
+            if (left < n) {
+                for (; left > 0; --left) m &= m - 1;
+                if (lane == 0) *s_row = base + __ffsll((long long)m) - 1;
+                break;
+            }
+            left -= n;
+        }
+    }
+    __syncthreads();
+    const int row = *s_row;
+    __syncthreads();   // the LDS is the caller's again
+    return row;
+}
+
 template <typename T, int D, int G, bool FEAT, bool NT>
 __global__ __launch_bounds__((AttnCfg<T, D, G>::THREADS)) void attn_kernel(const AttnParams P) {
     using C = AttnCfg<T, D, G>;
     constexpr int CH = C::CH, KG = C::KG, WAVES = C::WAVES, KT = C::KT, VU = C::VU, EPL = C::EPL, GP = C::GP, NG = C::NG;
-    const int row = blockIdx.y, split = blockIdx.x;
+    extern __shared__ __attribute__((aligned(16))) float smem[];
+    constexpr bool CAN_ORDER = C::PVM && NT && !FEAT;
+    int row = blockIdx.y;
+    if constexpr (CAN_ORDER) {
+        if (P.by_length) row = row_by_length<C::THREADS>(P.len, gridDim.y, P.cap, row, reinterpret_cast<int*>(smem));
+    }
+    const int split = blockIdx.x;
     const int b = row / P.n_kv, hkv = row % P.n_kv;
     const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
 
-    extern __shared__ __attribute__((aligned(16))) float smem[];
     // PVM: head | P tiles | K tiles, the partial accumulators live in the K tiles; other paths: acc | head | p | corr
     float* s_m = C::PVM ? smem : smem + (size_t)NG * G * D;  // [NG][G]
     float* s_l = s_m + NG * G;                 // [NG][G]
@@ -258,6 +338,23 @@ __global__ __launch_bounds__((AttnCfg<T, D, G>::THREADS)) void attn_kernel(const
     // splits, out = sum_s acc_s 2^(m_s - m*) / sum_s l_s 2^(m_s - m*), and only then bumps len[row],
     // which every workgroup of the row has read by that time.
     auto finish = [&](bool wrote_record) {
+        if constexpr (CAN_ORDER) {
+            if (P.by_length) {   // other workgroups still look the lengths up: the last one to finish appends for all rows
+                if (!appending) return;
+                __syncthreads();
+                if (tid == 0) {
+                    s_last = __hip_atomic_fetch_add(&P.row_cnt[0], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == gridDim.y - 1;
+                    if (s_last) __hip_atomic_store(&P.row_cnt[0], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                }
+                __syncthreads();
+                if (s_last)
+                    for (int r = tid; r < (int)gridDim.y; r += C::THREADS) {
+                        const int len = min(max(P.len[r], 0), P.cap);
+                        if (len < P.cap) P.len[r] = len + 1;
+                    }
+                return;
+            }
+        }
         if (gridDim.x == 1) {
             if (do_append && tid == 0) P.len[row] = n;
             return;
@@ -758,10 +855,18 @@ static fk_status attn_launch(const fk_cache_desc* d, const AttnParams& base, int
     P.rec = reinterpret_cast<float*>(reinterpret_cast<char*>(ws) + attn_counter_bytes(d));
     if constexpr (C::PVM) {
         if ((d->flags & FK_CACHE_COLD) || (size_t)rows * max_len * D * sizeof(T) * 2 >= kStreamNtBytes) {  // not cache resident
+            // More rows than CUs: one workgroup per CU (LDS it does not use keeps the second one out) and the longest rows first, so
+            // that a ragged batch ends everywhere at about the same time.  With all rows on the chip at once every row gets the same
+            // share of the bandwidth, the longest are left alone at the end, and few workgroups cannot fill the memory system: 512
+            // rows of 1024 to 32768 pairs 806 -> 693 us.  One workgroup per CU and the look-up (about 1 us each) cost rows of one
+            // length a little, 512 rows of 8000 306 -> 313 us, of 4000 157 -> 156; hence the bound on the bytes.
+            P.by_length = p.nsplit == 1 && rows > 256 && rows <= 8192 && (size_t)rows * max_len * D * sizeof(T) * 2 >= ((size_t)1 << 30);
+            constexpr size_t kAlone = 84 * 1024;   // more than half of a CU's 160 KB
+            const size_t lds = P.by_length && C::LDS_BYTES < kAlone ? kAlone : C::LDS_BYTES;
             auto kern = attn_kernel<T, D, G, false, true>;
             static bool lds_ok[kMaxDevices] = {};
-            if (!allow_dynamic_lds((const void*)kern, C::LDS_BYTES, lds_ok)) return FK_ERR_LAUNCH;
-            hipLaunchKernelGGL(kern, dim3(p.nsplit, rows), dim3(C::THREADS), C::LDS_BYTES, st, P);
+            if (!allow_dynamic_lds((const void*)kern, kAlone > C::LDS_BYTES ? kAlone : C::LDS_BYTES, lds_ok)) return FK_ERR_LAUNCH;
+            hipLaunchKernelGGL(kern, dim3(p.nsplit, rows), dim3(C::THREADS), lds, st, P);
             return launch_status();
         }
     }

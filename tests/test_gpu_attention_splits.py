@@ -44,3 +44,31 @@ def test_step_at_split_and_tile_edges(gpu, ora, dtype, D, H, g, n, cold):
         gpu.assert_attn_close(gpu.out_to_f64(dev.out), ora.decode_attn(c, q, 0.2), dtype, f"step {t}")
     host = dev.host(ora)
     assert np.array_equal(host.K, c.K) and np.array_equal(host.V, c.V) and np.array_equal(host.pos, c.pos) and np.array_equal(host.len, c.len)
+
+
+@pytest.mark.parametrize("D,cap", [(128, 8000), (64, 16000)])
+def test_rows_taken_by_length_give_the_same_bits(gpu, D, cap):
+    """More rows than CUs and 1 GB of keys and values by the length hint: workgroups take the rows from the longest to the shortest.
+    A smaller hint keeps the plain order and must change nothing: outputs, appended rows, lengths (full, empty, equal ones)."""
+    import paper_2602_03203_amd as fk
+    B, H, g = 33, 8, 2
+    desc = fk.CacheDesc(B, H * g, H, D, cap, "bf16")
+    gen = torch.Generator(device="cuda").manual_seed(8)
+    mk = lambda *s: torch.randn(s, generator=gen, device="cuda", dtype=torch.bfloat16)   # noqa: E731
+    K0, V0, q, k, v = mk(B, H, cap, D), mk(B, H, cap, D), mk(2, B, H * g, D), mk(2, B, H, D), mk(2, B, H, D)
+    lens = torch.randint(0, cap + 1, (B, H), generator=gen, device="cuda", dtype=torch.int32)
+    lens[0, 0], lens[1, :4], lens[2] = 0, cap, 77
+    pn = torch.arange(2 * B, dtype=torch.int32, device="cuda").reshape(2, B)
+    res = []
+    for hint in (cap, 3000 * 128 // D):
+        K, V, ln, pos, ws = K0.clone(), V0.clone(), lens.clone(), torch.zeros((B, H, cap), dtype=torch.int32, device="cuda"), fk.new_attn_workspace(desc)
+        out = torch.zeros_like(q)
+        for t in range(2):
+            fk.fk_decode_step(desc, q[t], K, V, pos, ln, k[t], v[t], pn[t], hint, 0.1, out[t], ws)
+        only = torch.zeros_like(q[0])
+        fk.fk_decode_attn(desc, q[0], K, V, ln, hint, 0.1, only, ws)
+        assert int(ws[:4 * B * H].view(torch.int32).abs().max()) == 0
+        res.append((out, only, ln, pos, K, V))
+    assert torch.equal(res[0][2], torch.clamp(lens + 2, max=cap))
+    for a, b in zip(*res):
+        assert torch.equal(a.view(torch.uint8), b.view(torch.uint8))
