@@ -570,8 +570,8 @@ def main():
 
     def plan(n_steps, c0, lens_at, pos_dev, rec=None):
         """The library calls of n_steps decode steps from the step clock c0, marshalled NOW (fk.prepare) so that the
-        timed loop only makes the calls: a list of zero-argument callables.  Steps between two events go to the
-        library as ONE fk_decode_window call (the host comes back once per window, not once per step).  rec: dict
+        timed loop only makes the calls: a list of zero-argument callables, one per decode step, as a generation makes
+        them (fk_decode_window computes the steps of known tokens at once, which is not decoding).  rec: dict
         of lists that receives HIP-event pairs around every window's attention launches and around each of the
         three event kernels, and the number of moved pairs per event (the callables then also record the events)."""
         calls = []
@@ -582,12 +582,14 @@ def main():
             if rec is not None:
                 e = [torch.cuda.Event(enable_timing=True) for _ in range(2)]
                 calls.append(lambda ev=e[0]: ev.record(stream))
-            if feat is None:
-                calls.append(fk.prepare(fk.fk_decode_window, desc, dq[t:t + seg], Kc, Vc, posc, lenc, dk[t:t + seg], dv[t:t + seg],
-                                        pos_dev[t:t + seg], seg, ml, scale, dout[:seg], ws, stream))
-            else:
-                calls.append(fk.prepare(fk.fk_decode_window_feat, desc, dq[t:t + seg], Kc, Vc, posc, lenc, dk[t:t + seg], dv[t:t + seg],
-                                        pos_dev[t:t + seg], seg, ml, scale, feat, (c0 + t) % L, L, dout[:seg], fws, stream))
+            for i in range(seg):
+                mi = min(ml + i, w.capacity)
+                if feat is None:
+                    calls.append(fk.prepare(fk.fk_decode_step, desc, dq[t + i], Kc, Vc, posc, lenc, dk[t + i], dv[t + i], pos_dev[t + i], mi,
+                                            scale, dout[i], ws, stream))
+                else:
+                    calls.append(fk.prepare(fk.fk_decode_step_feat, desc, dq[t + i], Kc, Vc, posc, lenc, dk[t + i], dv[t + i], pos_dev[t + i],
+                                            mi, scale, feat, (c0 + t + i) % L, L, dout[i], fws, stream))
             if rec is not None:
                 calls.append(lambda ev=e[1]: ev.record(stream))
                 rec["attn"].append((t, seg, e))
@@ -704,7 +706,7 @@ def main():
                 ratio = profile_value(ratio_file, "traffic_over_algorithmic")
         result["roofline"] = {
             "kernel": "attn_kernel (fk_decode_step_feat: append + attention + attention-feature update, one launch)" if args.features
-            else "attn_kernel (fk_decode_step via fk_decode_window: append + attention, one launch per step)",
+            else "attn_kernel (fk_decode_step: append + attention, one launch per step)",
             "bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": achieved / HBM_PEAK_GBS,
             "traffic": None if ratio is None else ratio * avg_bytes,
             "traffic_source": None if ratio is None else f"profiles/{ratio_file}: counter bytes / algorithmic bytes of the same workload, times this run's algorithmic bytes",
