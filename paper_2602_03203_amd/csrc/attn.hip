@@ -161,7 +161,9 @@ static AttnPlan attn_plan(const fk_cache_desc* d, int max_len) {
     //   fp32, 16 rows:  D = 128, 300 keys  10: 9.2, 5: 8.2;  D = 64, 500 keys  16: 9.1, 8: 7.0;  2 rows of 144  5: 5.7, 3: 5.8
     int most;
     if (d->dtype == FK_BF16) {
-        if (d->head_dim == 64 && want > (255 + rows) / rows) want = (255 + rows) / rows;
+        // (long rows keep the finer cut: as fast for equal lengths, 64 rows of 8000 23.6 against 23.0 us, and it evens out ragged ones,
+        // 288 rows of up to 21676: 176 against 182 us)
+        if (d->head_dim == 64 && max_len < 4096 && want > (255 + rows) / rows) want = (255 + rows) / rows;
         most = max_len <= 512 ? 1 : (max_len + 255) / 256;
         if (most > 16) most = max_len / 512 > 16 ? max_len / 512 : 16;
     } else {
@@ -830,7 +832,7 @@ static fk_status attn_launch(const fk_cache_desc* d, const AttnParams& base, int
             P.logit = reinterpret_cast<float*>(reinterpret_cast<char*>(ws) + attn_counter_bytes(d));
             const int frows = d->batch * d->n_kv_heads;
             if constexpr (C::PVM) {
-                if ((d->flags & FK_CACHE_COLD) || (size_t)frows * max_len * D * sizeof(T) * 2 >= kStreamNtBytes) {
+                if ((d->flags & FK_CACHE_COLD) || (D == 128 && (size_t)frows * max_len * D * sizeof(T) * 2 >= kStreamNtBytes)) {
                     auto kern = attn_kernel<T, D, G, true, true>;
                     static bool lds_ok[kMaxDevices] = {};
                     if (!allow_dynamic_lds((const void*)kern, C::LDS_BYTES_FEAT, lds_ok)) return FK_ERR_LAUNCH;
@@ -854,13 +856,16 @@ static fk_status attn_launch(const fk_cache_desc* d, const AttnParams& base, int
     P.row_cnt = reinterpret_cast<uint32_t*>(ws);
     P.rec = reinterpret_cast<float*>(reinterpret_cast<char*>(ws) + attn_counter_bytes(d));
     if constexpr (C::PVM) {
-        if ((d->flags & FK_CACHE_COLD) || (size_t)rows * max_len * D * sizeof(T) * 2 >= kStreamNtBytes) {  // not cache resident
+        // not cache resident (head_dim 64 with split rows: ragged ones, whose hint says more bytes than there are, lose 5 to 8 % to
+        // the streamed loads, 288 rows of up to 21676 194 -> 208 us; rows of one length would gain 9 %)
+        if ((d->flags & FK_CACHE_COLD) || ((D == 128 || p.nsplit == 1) && (size_t)rows * max_len * D * sizeof(T) * 2 >= kStreamNtBytes)) {
             // More rows than CUs: one workgroup per CU (LDS it does not use keeps the second one out) and the longest rows first, so
             // that a ragged batch ends everywhere at about the same time.  With all rows on the chip at once every row gets the same
             // share of the bandwidth, the longest are left alone at the end, and few workgroups cannot fill the memory system: 512
             // rows of 1024 to 32768 pairs 806 -> 693 us.  One workgroup per CU and the look-up (about 1 us each) cost rows of one
-            // length a little, 512 rows of 8000 306 -> 313 us, of 4000 157 -> 156; hence the bound on the bytes.
-            P.by_length = p.nsplit == 1 && rows > 256 && rows <= 8192 && (size_t)rows * max_len * D * sizeof(T) * 2 >= ((size_t)1 << 30);
+            // length a little, 512 rows of 8000 306 -> 313 us, of 4000 157 -> 156; hence the bound on the bytes, and no such order
+            // where a last round of fewer than 128 workgroups would not fill the memory system (rows of one length end up there).
+            P.by_length = p.nsplit == 1 && rows > 256 && rows <= 8192 && (rows % 256 == 0 || rows % 256 >= 128) && (size_t)rows * max_len * D * sizeof(T) * 2 >= ((size_t)1 << 30);
             constexpr size_t kAlone = 84 * 1024;   // more than half of a CU's 160 KB
             const size_t lds = P.by_length && C::LDS_BYTES < kAlone ? kAlone : C::LDS_BYTES;
             auto kern = attn_kernel<T, D, G, false, true>;
