@@ -6,7 +6,10 @@
 // wavefronts, the same online softmax, the same merge - and what is shared between steps is the data: the sixteen rows of a
 // matrix product hold SPG = 16 / g steps of the group's g heads instead of one step and zeros, a workgroup runs
 // kGroups such groups on every tile it has loaded, and a launch has the workgroups of all steps.  New pairs are read from
-// k_seq / v_seq, so the steps need no order among themselves.
+// k_seq / v_seq, so the steps need no order among themselves.  128 rows, 2048 pairs, 128 steps: 271 + 106 us against 3.47 ms;
+// bound by the vector work of the softmax (one product of 16 rows with 32 keys takes 16 matrix and some 200 vector
+// instructions).  Two groups: with one the K and V tiles are read twice as often, with three the registers spill (524 us a window and
+// its scores against 380).
 //
 // The feature planes are sums over the steps IN ORDER, one fp32 addition per step: a second launch recomputes the logits (the
 // same products again: the same bits) with a pair per lane, its wavefronts walking the steps in order, so every plane is
