@@ -8,10 +8,10 @@
 //
 // pool is the only kernel that touches the O(T^2) input and is HBM bound: a workgroup owns one
 // (key tile, block, group) and streams g * L row segments of 256 bytes (16 lanes x 16 bytes, 16 rows per workgroup
-// instruction, eight loads in flight per thread); chunks wholly above the diagonal are never read (A is causal), so the traffic is the lower
-// triangle below query B + L.  future is a
+// instruction, eight loads in flight per thread); chunks wholly above the diagonal are never read (A is causal), so
+// the traffic is the lower triangle below query B + L.  future is a
 // running maximum down the block axis; trace is sequential by nature: one workgroup per group walks the
-// M steps with the radix select of fk_select_keep on keys in LDS (the next step's are loaded while a step selects).
+// M steps with the selection of fk_select_keep on keys in LDS (the next step's are loaded while a step selects).
 #include "select_common.h"
 
 namespace fk {
@@ -99,7 +99,7 @@ static constexpr int kTraceMaxCache = 12288;  // B + L positions and B keys in L
 // One workgroup per KV group.  LDS holds the cache's positions (ascending; B + L of them: the B of this step and the
 // L that are generated before the next one) and the keys of its first B entries under this step's future scores.
 // A step: (1) the loads of the NEXT step's future scores at every position that can still be a candidate then are
-// issued (they land while the step selects); (2) four radix passes find the key of the (B - L)-th best candidate;
+// issued (they land while the step selects); (2) range_select finds the key of the (B - L)-th best candidate;
 // (3) every wavefront walks its own contiguous stretch of the candidates, first to count its survivors, then, with
 // the counts of the stretches before it, to move them (position and next key) to the front in order.  Sources are
 // in registers before the barrier that precedes the moves, so the compaction is safe in place.

@@ -1,11 +1,11 @@
-// fk_select_keep: deterministic per-row top-k by radix select (Section 3.1: the most recent
+// fk_select_keep: deterministic per-row top-k by histogram (Section 3.1: the most recent
 // L pairs stay, the others are pruned to the B - L most important; Top-K form of the
 // sampling ablation).
 //
 // One workgroup per row.  Scores are read once, mapped to order-preserving 32-bit keys (larger key =
-// more important; -0 -> +0; NaN -> 0, below -inf) and kept in LDS.  Most-significant-digit-first passes over
-// 8-bit digits (LDS histograms, one barrier per pass; at most four, usually one and a short ranked list: see
-// msd_select) find the key T of the k-th best candidate and the number `take` of candidates equal to T that still
+// more important; -0 -> +0; NaN -> 0, below -inf) and kept in LDS.  One histogram over the range of the keys and a
+// short ranked list (range_select; rows beyond LDS and keys that it cannot tell apart: digit by digit, msd_select)
+// find the key T of the k-th best candidate and the number `take` of candidates equal to T that still
 // fit.  One ordered pass then writes the kept slots
 // ascending: every candidate above T, the first `take` candidates equal to T in slot order
 // (slot order is position order, so ties go to the lower position), and the protected tail.
@@ -318,7 +318,7 @@ __global__ __launch_bounds__(kSelThreads) void select_keep_sampled_kernel(const 
 
 
 // The same selection with the row in LDS (rows of up to kSampledLdsKeys candidates): both keys of every slot are formed
-// once, the radix passes and the ordered passes are those of select_keep_kernel (one barrier per pass, one ordered
+// once, the selections and the ordered passes are those of select_keep_kernel (range_select, one ordered
 // walk per wavefront stretch), and the candidate marks take the place of the first key once the safe set is known.
 // LDS (u32): histogram and list of range_select | histograms [4][256] of msd_select | wavefront totals [16][4] | wavefront minima
 // and maxima [16][4] | key1 / candidate mark [lds_keys] | key2 [lds_keys]

@@ -1,5 +1,5 @@
 // Device helpers of the selection kernels: order-preserving score keys, a workgroup scan and the
-// most-significant-digit-first radix select over a workgroup (used by fk_select_keep,
+// selections over a workgroup, by range and most significant digit first (used by fk_select_keep,
 // fk_select_keep_sampled and the Golden Eviction trace).
 #ifndef FK_SELECT_COMMON_H
 #define FK_SELECT_COMMON_H
