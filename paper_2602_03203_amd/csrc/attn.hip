@@ -166,6 +166,9 @@ static AttnPlan attn_plan(const fk_cache_desc* d, int max_len) {
         if (d->head_dim == 64 && max_len < 4096 && want > (255 + rows) / rows) want = (255 + rows) / rows;
         most = max_len <= 512 ? 1 : (max_len + 255) / 256;
         if (most > 16) most = max_len / 512 > 16 ? max_len / 512 : 16;
+        // a cold cache's latency takes more workgroups to cover, as long as the merge fetches the records in one go (32 rows of
+        // 565 pairs 8.7 -> 8.4 us, of 300 8.4 -> 8.0; 8 rows of 2000, up to 32 splits, stay at 256 keys: 15.4 against 18.2)
+        if (d->head_dim == 128 && (d->flags & FK_CACHE_COLD) && want <= 8) most = (max_len + 95) / 96;
     } else {
         most = max_len <= 1024 ? 8 : (max_len + 127) / 128;   // (the merge fetches eight records at a time)
         if (most > (max_len + tile - 1) / tile) most = (max_len + tile - 1) / tile;
