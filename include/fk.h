@@ -149,11 +149,11 @@ fk_status fk_decode_step_static(const fk_cache_desc *desc, const void *q, void *
  * max_len = min(max_len_first + t, capacity); max_len_first bounds len[r] + 1 at the first step.
  *   q_seq, out_seq [n_steps][batch][n_q_heads][head_dim], k_seq, v_seq [n_steps][batch][n_kv_heads][head_dim]
  *   dtype; pos_seq [n_steps][batch] int32.
- * Results are those of the n_steps single calls (out up to the rounding of the softmax weights); the host returns to its
- * caller once per window instead of once per step.  All inputs are taken as they are when the work runs: bf16 windows of
- * two steps or more are computed at once, one launch that reads K and V once for all steps, unless few long rows make single
- * steps the faster way or the buffers give the steps an order (out_seq overlaps q_seq, new rows lie in the cache, ...): then, and
- * for fp32, the steps run one launch each.  n_steps == 0 is a no-op.  On an error the steps before it stay enqueued.
+ * Results are those of the n_steps single calls, bit for bit; the host returns to its caller once per window instead of once
+ * per step.  All inputs are taken as they are when the work runs: bf16 windows are computed at once, one launch that reads K and V
+ * for many steps together, unless single steps are the faster way (few long rows, few steps) or the buffers give the steps an order
+ * (out_seq overlaps q_seq, new rows lie in the cache, ...): then, and for fp32, the steps run one launch each.  n_steps == 0 is a
+ * no-op.  On an error the steps before it stay enqueued.
  */
 fk_status fk_decode_window(const fk_cache_desc *desc, const void *q_seq, void *K, void *V, int32_t *pos,
                            int32_t *len, const void *k_seq, const void *v_seq, const int32_t *pos_seq,
@@ -267,8 +267,9 @@ fk_status fk_decode_step_feat(const fk_cache_desc *desc, const void *q, void *K,
  * call, step t at chunk position chunk_pos_first + t, on q_seq[t], k_seq[t], v_seq[t], pos_seq[t] with its
  * output in out_seq[t] and max_len = min(max_len_first + t, capacity).  Layouts as for fk_decode_window;
  * the window must end inside the chunk (chunk_pos_first + n_steps <= chunk_len).  Results are those of
- * the n_steps single calls, bit for bit.  bf16 with head_dim 128: two launches for the whole window under the conditions of
- * fk_decode_window (and 2 n_steps g <= capacity * GP, the space the workspace has for them); otherwise the steps one by one.
+ * the n_steps single calls, bit for bit.  bf16 with head_dim 128: two launches for the whole window, unless it is two steps of
+ * rows below 2048 pairs (max_len_first), its buffers give the steps an order, or 2 n_steps g > capacity * GP, the space the workspace
+ * has; otherwise the steps one by one.
  */
 fk_status fk_decode_window_feat(const fk_cache_desc *desc, const void *q_seq, void *K, void *V, int32_t *pos,
                                 int32_t *len, const void *k_seq, const void *v_seq, const int32_t *pos_seq,

@@ -10,7 +10,7 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 OBJDIR = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libfk.so")
-SOURCES = ["api.hip", "attn.hip", "cache_ops.hip", "chunk.hip", "chunk_feat.hip", "golden.hip", "score.hip", "select.hip"]
+SOURCES = ["api.hip", "attn.hip", "cache_ops.hip", "golden.hip", "score.hip", "select.hip", "window.hip"]
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-I" + os.path.join(ROOT, "include"), "-I" + CSRC,
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops", "-Wall", "-Wno-unused-function"]
 

@@ -30,7 +30,7 @@
 // are stored to a per-row scratch as they are formed; after the wavefront merge, with the final maximum
 // and normaliser known, a second pass turns them into attention weights and adds them to the open
 // planes of the row's feature state.
-#include "chunk.h"
+#include "window.h"
 #include <mutex>
 
 namespace fk {
@@ -129,65 +129,8 @@ template <typename T, int D, int G> struct AttnCfg {
     static constexpr size_t LX_OFFSET = LDS_BYTES / sizeof(float);  // float index of lx in the dynamic LDS
 };
 
-struct AttnPlan {
-    int split_len;  // keys per split (multiple of the wave tile)
-    int nsplit;     // splits per row
-    bool rotate;    // workgroups start at different tiles of their splits
-};
-
-// Splits per row that the workspace has records for, an upper bound on the plan's for any max_len.  The bf16 D = 128 kernel
-// saturates the memory system from 128 workgroups of eight wavefronts when the cache sits in the Infinity Cache, so rows are
-// split only when there are fewer rows than that (no split = no cross-workgroup merge at the end of the launch); a cold cache
-// comes from HBM, whose latency takes every CU to cover: up to 256 workgroups.
-static int attn_max_splits(const fk_cache_desc* d) {
-    const int rows = d->batch * d->n_kv_heads;
-    if (d->dtype == FK_BF16 && d->head_dim == 128 && (d->flags & FK_CACHE_COLD)) {
-        const int want = 256 / rows;
-        return want < 1 ? 1 : want;
-    }
-    const int target = (d->dtype == FK_BF16 && d->head_dim == 128) ? 128 : 512;
-    const int want = (target + rows - 1) / rows;
-    return want < 1 ? 1 : want;
-}
-
-static AttnPlan attn_plan(const fk_cache_desc* d, int max_len) {
-    const int tile = 32, rows = d->batch * d->n_kv_heads;
-    int want = attn_max_splits(d);
-    // A split is worth its share of the merge (1 to 1.5 us, and 0.1 us for every record beyond sixteen) when it fills its wavefronts.
-    // bf16: eight wavefronts take 256 keys a round, about 1.1 us; fp32: four take 64 (D = 128: 32).  Measured per step, us:
-    //   8 rows, D = 64:  1500 keys  47 splits 12.8, 8: 6.9, 4: 7.5, 1: 12.7;  300 keys  10: 6.7, 1: 6.1;  8192 keys  64: 15.4, 32: 11.1, 16: 10.1
-    //   D = 128:  8 rows of 2048  16: 8.3, 8: 7.8;  8 rows of 300  10: 7.3, 1: 6.5;  1 row of 16000  125: 17.3, 32: 10.9, 16: 13.0
-    //   D = 64, 128 rows of 2048  4: 15.0, 2: 14.7, 1: 18.4;  32 rows of 2048  16: 10.2, 8: 8.2, 4: 9.0 (so 256 workgroups there)
-    //   fp32, 16 rows:  D = 128, 300 keys  10: 9.2, 5: 8.2;  D = 64, 500 keys  16: 9.1, 8: 7.0;  2 rows of 144  5: 5.7, 3: 5.8
-    int most;
-    if (d->dtype == FK_BF16) {
-        // (long rows keep the finer cut: as fast for equal lengths, 64 rows of 8000 23.6 against 23.0 us, and it evens out ragged ones,
-        // 288 rows of up to 21676: 176 against 182 us)
-        if (d->head_dim == 64 && max_len < 4096 && want > (255 + rows) / rows) want = (255 + rows) / rows;
-        most = max_len <= 512 ? 1 : (max_len + 255) / 256;
-        if (most > 16) most = max_len / 512 > 16 ? max_len / 512 : 16;
-        // a cold cache's latency takes more workgroups to cover, as long as the merge fetches the records in one go (32 rows of
-        // 565 pairs 8.7 -> 8.4 us, of 300 8.4 -> 8.0; 8 rows of 2000, up to 32 splits, stay at 256 keys: 15.4 against 18.2)
-        if (d->head_dim == 128 && (d->flags & FK_CACHE_COLD) && want <= 8) most = (max_len + 95) / 96;
-    } else {
-        most = max_len <= 1024 ? 8 : (max_len + 127) / 128;   // (the merge fetches eight records at a time)
-        if (most > (max_len + tile - 1) / tile) most = (max_len + tile - 1) / tile;
-    }
-    if (want > most) want = most;
-    int split_len = (max_len + want - 1) / want;
-    split_len = (split_len + tile - 1) / tile * tile;
-    // (Rounding the splits down to whole rounds of the workgroup, with the rest of the row as a short split of its
-    // own, was measured and dropped: more workgroups than CUs end up two to a CU while other CUs idle, 85 -> 112 us
-    // at 64 rows of 16448 keys.)
-    AttnPlan p;
-    p.split_len = split_len;
-    p.nsplit = (max_len + split_len - 1) / split_len;
-    if (p.nsplit < 1) p.nsplit = 1;
-    // Start every workgroup at another tile of its split when the splits are long and the cache comes from HBM:
-    // workgroups that walk rows a near power of two apart in step crowd the same memory channels (measured on
-    // 512 MB per launch, 4128 keys per split: 5.2 TB/s in step, 6.3 TB/s rotated); short splits lose 2 % to it.
-    p.rotate = p.nsplit > 1 && split_len >= 2048;
-    return p;
+static AttnShape attn_shape(const fk_cache_desc* d) {
+    return {d->batch * d->n_kv_heads, d->head_dim, d->dtype == FK_BF16, (d->flags & FK_CACHE_COLD) != 0};
 }
 
 // workspace: [row arrival counters: rows u32] padded to 256 B | records
@@ -485,7 +428,7 @@ __global__ __launch_bounds__((AttnCfg<T, D, G>::THREADS)) void attn_kernel(const
         // Tiles are dealt round robin to the wavefronts; with P.rotate the deal starts from a tile that differs
         // from workgroup to workgroup (the online softmax does not care about the order).
         const int ntiles = (end - start + KT - 1) / KT;
-        const int rot = P.rotate ? (int)(((unsigned)row * 37u + (unsigned)split * 11u) % (unsigned)ntiles) : 0;
+        const int rot = P.rotate ? attn_rotation(row, split, ntiles) : 0;
         for (int t = wave; t < ntiles; t += WAVES) {
             const int tt = t + rot < ntiles ? t + rot : t + rot - ntiles;
             const int base = start + tt * KT;
@@ -850,7 +793,7 @@ static fk_status attn_launch(const fk_cache_desc* d, const AttnParams& base, int
             return launch_status();
         }
     }
-    const AttnPlan p = attn_plan(d, max_len);
+    const AttnPlan p = attn_plan(attn_shape(d), max_len);
     const int rows = d->batch * d->n_kv_heads;
     AttnParams P = base;
     P.split_len = p.split_len;
@@ -932,7 +875,7 @@ extern "C" size_t fk_decode_attn_workspace(const fk_cache_desc* desc, int32_t ma
     // sized for the largest split count any max_len can get, so one workspace serves every call
     const size_t g = desc->n_q_heads / desc->n_kv_heads;
     return attn_counter_bytes(desc) +
-           (size_t)desc->batch * desc->n_kv_heads * attn_max_splits(desc) * g * (desc->head_dim + 2) * sizeof(float);
+           (size_t)desc->batch * desc->n_kv_heads * attn_max_splits(attn_shape(desc)) * g * (desc->head_dim + 2) * sizeof(float);
 }
 
 extern "C" fk_status fk_decode_attn(const fk_cache_desc* desc, const void* q, const void* K, const void* V,
@@ -974,7 +917,7 @@ extern "C" fk_status fk_decode_step(const fk_cache_desc* desc, const void* q, vo
 }
 
 // ---------------------------------------------------------------------------------------------------------
-// fk_decode_window: the steps of a window at once (chunk.hip) where that is possible, else step by step
+// fk_decode_window: the steps of a window at once (window.hip) where that is possible, else step by step
 // ---------------------------------------------------------------------------------------------------------
 namespace fk {
 static bool overlap(const void* a, size_t na, const void* b, size_t nb) {
@@ -1003,20 +946,26 @@ static bool window_at_once(const fk_cache_desc* d, const void* q, const void* K,
     return true;
 }
 
-// Whether the steps at once are the faster way.  With at least one query tile per CU they are from two steps on (128 rows of
-// 2112 pairs, two steps: 46 against 49 us; eight: 48 against 183).  With fewer, a workgroup walks its row alone, about 1.9 us for
-// 128 pairs (8 rows of 8192 pairs: 124 us whatever the number of steps), while a single step spreads the row over the chip: 9 us
-// plus its bytes at 5.5 TB/s (8 rows of 8192: 12 - 15 us a step; 8 rows of 131000: 101 us a step against 1964 us at once).
+// Whether the steps at once are the faster way (the results are the same).  A workgroup, one per CU, walks its row alone whatever
+// the number of its steps: 3.6 us for 256 pairs (head_dim 64: 2.3) and 3.5 us (2.5) for every split of a split row, T = 2 to 128
+// steps of 1 row of 16000 pairs 333 us, of 64 rows of 8192 126 us, of 128 rows of 2048 31 us.  A single step spreads the row over the
+// chip: 8 us, its bytes at 7 TB/s, 0.15 us a split; those same three 15.5, 43 and 23 us.  The margin of a quarter is for the
+// workgroups' share of the bandwidth, which the first figure leaves out (128 rows of 2048, head_dim 64, two steps: 34 us at once, 32
+// one by one).
 static bool window_pays(const fk_cache_desc* d, int32_t T, int32_t max_len) {
-    const double rows = (double)d->batch * d->n_kv_heads, tiles = rows * ((T * (d->n_q_heads / d->n_kv_heads) + 31) / 32);
-    if (tiles >= 256) return true;
-    const double step_us = 9.0 + rows * max_len * d->head_dim * 4 / 5.5e6;
-    return T * step_us >= 1.9 * ((max_len + 127) / 128);
+    const int g = d->n_q_heads / d->n_kv_heads, spg = 16 / g;   // 16 / g steps, or twice as many, to a workgroup
+    const AttnShape shape = attn_shape(d);
+    const AttnPlan p = attn_plan(shape, max_len);
+    const double rows = shape.rows, groups = rows * ((T + spg - 1) / spg), rounds = groups <= 256 ? 1.0 : (groups / 2 + 255) / 256;
+    const bool narrow = d->head_dim == 64;
+    const double at_once = rounds * (6.0 + (p.nsplit > 1 ? p.nsplit * (narrow ? 2.5 : 3.5) : 0.0) + max_len / 256.0 * (narrow ? 2.3 : 3.6));
+    const double step = 8.0 + rows * max_len * d->head_dim * 4 / 7e6 + (p.nsplit > 1 ? 0.15 * p.nsplit : 0.0);
+    return T * step >= 1.25 * at_once;
 }
 
-static ChunkParams window_params(const fk_cache_desc* d, const void* q, void* K, void* V, int32_t* pos, int32_t* len, const void* k, const void* v,
+static WindowParams window_params(const fk_cache_desc* d, const void* q, void* K, void* V, int32_t* pos, int32_t* len, const void* k, const void* v,
                                  const int32_t* pos_seq, int32_t T, float scale, void* out, void* ws) {
-    ChunkParams P = {};
+    WindowParams P = {};
     P.q_seq = q;
     P.k_seq = k;
     P.v_seq = v;
@@ -1053,8 +1002,13 @@ extern "C" fk_status fk_decode_window(const fk_cache_desc* desc, const void* q_s
         window_pays(desc, n_steps, max_len_first)) {
         const size_t need = fk_decode_attn_workspace(desc, max_len_first);
         if (!workspace || workspace_bytes < need || !aligned16(workspace)) return FK_ERR_WORKSPACE;
-        return chunk_window(desc, window_params(desc, q_seq, K, V, pos, len, k_seq, v_seq, pos_seq, n_steps, softmax_scale, out_seq, workspace),
-                            (hipStream_t)stream);
+        WindowParams P = window_params(desc, q_seq, K, V, pos, len, k_seq, v_seq, pos_seq, n_steps, softmax_scale, out_seq, workspace);
+        P.shape = attn_shape(desc);
+        P.max_len_first = max_len_first;
+        // (the splits of a row never get fewer as its length grows)
+        const int64_t ml = (int64_t)max_len_first + n_steps - 1;
+        const bool split = attn_plan(P.shape, ml > desc->capacity ? desc->capacity : (int)ml).nsplit > 1;
+        return window_attn(P, split, (hipStream_t)stream);
     }
     for (int32_t t = 0; t < n_steps; ++t) {
         const int64_t ml = (int64_t)max_len_first + t;
@@ -1158,18 +1112,20 @@ extern "C" fk_status fk_decode_window_feat(const fk_cache_desc* desc, const void
     if (n_steps < 0 || max_len_first <= 0 || max_len_first > desc->capacity) return FK_ERR_INVALID_ARG;
     if (!q_seq || !k_seq || !v_seq || !pos_seq || !out_seq) return FK_ERR_INVALID_ARG;
     if (chunk_len <= 0 || chunk_pos_first < 0 || (int64_t)chunk_pos_first + n_steps > chunk_len) return FK_ERR_INVALID_ARG;
-    // at once where the plain window is, and the two floats per query fit the logit scratch
+    // At once where the buffers allow it and the two floats per query fit the logit scratch, but two steps of short rows (the second
+    // launch: 8 rows of 300 pairs 21 us against 18, 256 rows of 1024 60 against 58, 128 rows of 2048 58 against 64; three steps 22
+    // against 26, 65 against 87 and 58 against 95).
     const int g = desc->n_q_heads / desc->n_kv_heads;
-    if (desc->head_dim == 128 && feat && aligned16(feat) && (int64_t)n_steps * g * 2 <= (int64_t)desc->capacity * (g <= 4 ? 4 : 8) &&
+    if (desc->head_dim == 128 && feat && aligned16(feat) && (n_steps > 2 || max_len_first >= 2048) && (int64_t)n_steps * g * 2 <= (int64_t)desc->capacity * (g <= 4 ? 4 : 8) &&
         window_at_once(desc, q_seq, K, V, pos, len, k_seq, v_seq, pos_seq, n_steps, out_seq, workspace, feat)) {
         if (!workspace || workspace_bytes < feat_workspace_bytes(desc) || !aligned16(workspace)) return FK_ERR_WORKSPACE;
-        ChunkParams P = window_params(desc, q_seq, K, V, pos, len, k_seq, v_seq, pos_seq, n_steps, softmax_scale, out_seq, workspace);
+        WindowParams P = window_params(desc, q_seq, K, V, pos, len, k_seq, v_seq, pos_seq, n_steps, softmax_scale, out_seq, workspace);
         P.stat = reinterpret_cast<float2*>(static_cast<char*>(workspace) + attn_counter_bytes(desc));
         P.feat = feat;
         P.chunk_pos = chunk_pos_first;
         P.chunk_len = chunk_len;
         const int64_t ml = (int64_t)max_len_first + n_steps - 1;
-        return chunk_window_feat(P, ml > desc->capacity ? desc->capacity : (int)ml, (hipStream_t)stream);
+        return window_feat(P, ml > desc->capacity ? desc->capacity : (int)ml, (hipStream_t)stream);
     }
     const size_t e = desc->dtype == FK_F32 ? 4 : 2;
     const size_t q_step = (size_t)desc->batch * desc->n_q_heads * desc->head_dim * e;   // bytes per step, multiples of 16

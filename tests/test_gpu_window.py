@@ -1,5 +1,5 @@
-"""fk_decode_window and fk_decode_window_feat on a whole window at once: every workgroup shape of the launch rules, the edges of the
-tiles, rows that fill up inside the window, and calls whose buffers order the steps."""
+"""fk_decode_window and fk_decode_window_feat on a whole window at once: bit for bit the single steps over the splits, tile walks and
+workgroup shapes of the launch rules, the edges of the tiles, rows that fill up inside the window, and calls whose buffers order the steps."""
 import numpy as np
 import pytest
 import torch
@@ -33,17 +33,16 @@ def oracle_window(ora, c, q, k, v, pos, scale):
     return out
 
 
-# D, batch, KV heads, group, capacity, steps, row lengths (cycled over the rows), scale: the launch takes 8 x 1, 4 x 2, 2 x 4 or 1 x 4
-# wavefronts (queries x key splits) for many down to few query tiles
+# D, batch, KV heads, group, capacity, steps, row lengths (cycled over the rows), scale
 WINDOWS = [
-    (128, 16, 8, 4, 200, 66, [60, 0, 199, 131, 64, 63], 0.09),    # 8 x 1: 264 queries a row (a second, ragged tile); full rows
-    (64, 16, 16, 8, 140, 5, [64, 1, 0, 127, 139], 0.125),          # 8 x 1, head_dim 64
-    (128, 16, 8, 7, 300, 33, [128, 255, 40], 0.3),                 # 4 x 2, group of 7
-    (64, 16, 8, 5, 260, 40, [100, 259, 0], 0.2),                   # 4 x 2, head_dim 64
-    (128, 16, 8, 3, 300, 40, [128, 0, 290], 0.09),                 # 2 x 4
-    (64, 16, 8, 1, 600, 70, [500, 10], 0.4),                       # 2 x 4, one head per group
-    (128, 1, 2, 4, 700, 17, [530, 690], 0.09),                     # 1 x 4: few rows, longer than several tiles
-    (64, 2, 1, 8, 400, 2, [399, 128], 0.125),                      # 1 x 4, two steps, one row full after the first
+    (128, 16, 8, 4, 200, 66, [60, 0, 199, 131, 64, 63], 0.09),    # two groups of steps a workgroup, a ragged last one; full rows
+    (64, 16, 16, 8, 140, 5, [64, 1, 0, 127, 139], 0.125),          # head_dim 64, two steps to a group
+    (128, 16, 8, 7, 300, 33, [128, 255, 40], 0.3),                 # group of 7: two rows of a matrix product unused
+    (64, 16, 8, 5, 260, 40, [100, 259, 0], 0.2),                   # group of 5, head_dim 64
+    (128, 16, 8, 3, 300, 40, [128, 0, 290], 0.09),                 # one group of steps a workgroup
+    (64, 16, 8, 1, 600, 70, [500, 10], 0.4),                       # one head per group: sixteen steps in a product
+    (128, 1, 2, 4, 700, 17, [530, 690], 0.09),                     # few rows, split
+    (64, 2, 1, 8, 400, 2, [399, 128], 0.125),                      # two steps, one row full after the first
     (128, 2, 2, 4, 150, 9, [140, 3, 31, 32], -0.09),               # a negative scale
     (64, 1, 2, 2, 90, 12, [50, 0], 0.0),                           # scale 0: plain means
 ]
@@ -80,6 +79,9 @@ def window_and_steps(gpu, fk, desc, args, T, ml, scale, feat=None, c0=0, L=0):
         out = torch.zeros_like(q)
         f = None if feat is None else feat.clone()
         ws = fk.new_attn_workspace(desc) if feat is None else fk.new_feat_workspace(desc).fill_(0xA5)   # (needs no initialisation)
+        counters = (desc.batch * desc.n_kv_heads * 4 + 255) // 256 * 256
+        if feat is None:
+            ws[counters:] = 0xA5
         for t in range(0 if window else T):
             m = min(ml + t, desc.capacity)
             if feat is None:
@@ -88,6 +90,8 @@ def window_and_steps(gpu, fk, desc, args, T, ml, scale, feat=None, c0=0, L=0):
                 fk.fk_decode_step_feat(desc, q[t], K, V, pos, ln, k[t], v[t], pn[t], m, scale, f, c0 + t, L, out[t], ws)
         if window and feat is None:
             fk.fk_decode_window(desc, q, K, V, pos, ln, k, v, pn, T, ml, scale, out, ws)
+            assert bool((ws[counters:] == 0xA5).all())   # at once: single steps of split rows leave their records there
+            assert int(ws[:counters].max()) == 0
         elif window:
             fk.fk_decode_window_feat(desc, q, K, V, pos, ln, k, v, pn, T, ml, scale, f, c0, L, out, ws)
         torch.cuda.synchronize()
@@ -103,6 +107,37 @@ def device_args(desc, T, lens, seed):
     pos = torch.arange(cap, dtype=torch.int32, device="cuda").expand(B, H, cap).contiguous()
     pn = torch.arange(T * B, dtype=torch.int32, device="cuda").reshape(T, B) + 5000
     return mk(T, B, desc.n_q_heads, D), mk(B, H, cap, D), mk(B, H, cap, D), pos, ln, mk(T, B, H, D), mk(T, B, H, D), pn
+
+
+# D, batch, KV heads, group, capacity, steps, row lengths, length hint, cold, scale.  Splits: how many and how long follows from the hint
+# of every step, so it changes inside a window (1536 pairs: six to seven splits); long ones are walked from another tile in every
+# row (2 x 2112 pairs); more than 64 take the merge in batches.
+BITS = [
+    (128, 16, 8, 4, 200, 66, [60, 0, 199, 131, 64, 63], 200, False, 0.09),
+    (64, 32, 8, 8, 140, 5, [64, 1, 0, 127, 139], 140, False, 0.125),
+    (128, 16, 8, 7, 300, 33, [128, 255, 40], 256, False, -0.3),
+    (64, 1, 8, 5, 500, 40, [440, 259, 0], 441, False, 0.2),
+    (128, 2, 4, 4, 1700, 100, [1500, 1400, 3], 1501, False, 0.09),
+    (64, 2, 4, 4, 1700, 100, [1500, 1400, 3], 1501, False, 0.0),
+    (128, 3, 2, 3, 700, 50, [500, 3, 0], 501, False, 0.3),
+    (64, 8, 8, 1, 900, 40, [880, 31, 899], 881, True, 0.3),
+    (128, 4, 8, 3, 700, 30, [600, 699, 0], 601, True, 0.3),
+    (128, 1, 3, 8, 700, 50, [680, 3, 699], 600, False, 0.1),
+    (128, 8, 8, 2, 4300, 40, [4200, 100, 4095], 4201, False, 0.09),
+    (64, 2, 8, 6, 40000, 30, [39000, 100, 32767], 39001, True, 0.09),
+    (128, 1, 1, 4, 66000, 90, [65950], 65951, False, 0.09),
+    (64, 1, 1, 2, 66000, 90, [65930], 65951, False, 0.09),
+]
+
+
+@pytest.mark.parametrize("D,Bt,H,g,cap,T,lens,hint,cold,scale", BITS)
+def test_window_equals_the_single_steps_bit_for_bit(gpu, D, Bt, H, g, cap, T, lens, hint, cold, scale):
+    import paper_2602_03203_amd as fk
+    print(f"window bits D={D} batch={Bt} Hkv={H} g={g} cap={cap} T={T} lens={lens} cold={cold}", flush=True)
+    desc = fk.CacheDesc(Bt, H * g, H, D, cap, "bf16", cold=cold)
+    a, b = window_and_steps(gpu, fk, desc, device_args(desc, T, lens, D + T), T, hint, scale)
+    for x, y in zip(a, b):
+        assert torch.equal(x.view(torch.uint8), y.view(torch.uint8))
 
 
 @pytest.mark.parametrize("g", [1, 2, 3, 4, 5, 6, 7, 8])
