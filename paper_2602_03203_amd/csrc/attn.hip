@@ -422,8 +422,14 @@ __global__ __launch_bounds__((AttnCfg<T, D, G>::THREADS)) void attn_kernel(const
         }
         float* lg_row = FEAT ? P.logit + (size_t)row * P.cap * GP : nullptr;
         f32x4_t o[ET];  // o[e][i] = out[head quad*4 + i][channel n16*ET + e], un-normalised
+        // SPLIT_P: the remainders' part, apart from the heads': an infinite value times a remainder, which may be 0 or negative, must not
+        // turn the infinity that the head's product gives into a NaN
+        f32x4_t o_rest[C::SPLIT_P ? ET : 1];
 #pragma unroll
-        for (int e = 0; e < ET; ++e) o[e] = (f32x4_t){0.f, 0.f, 0.f, 0.f};
+        for (int e = 0; e < ET; ++e) {
+            o[e] = (f32x4_t){0.f, 0.f, 0.f, 0.f};
+            if constexpr (C::SPLIT_P) o_rest[e] = o[e];
+        }
 
         // Tiles are dealt round robin to the wavefronts; with P.rotate the deal starts from a tile that differs
         // from workgroup to workgroup (the online softmax does not care about the order).
@@ -527,7 +533,10 @@ __global__ __launch_bounds__((AttnCfg<T, D, G>::THREADS)) void attn_kernel(const
 #pragma unroll
                 for (int e = 0; e < ET; ++e)
 #pragma unroll
-                    for (int i = 0; i < 4; ++i) o[e][i] *= corr[i];
+                    for (int i = 0; i < 4; ++i) {
+                        o[e][i] *= corr[i];
+                        if constexpr (C::SPLIT_P) o_rest[e][i] *= corr[i];
+                    }
             }
             __builtin_amdgcn_wave_barrier();
             // A operand of P.V: P[head n16][k-slots quad*8 .. +8]; k-slot u of group quad is key base + quad*8 + u
@@ -547,9 +556,15 @@ __global__ __launch_bounds__((AttnCfg<T, D, G>::THREADS)) void attn_kernel(const
                 vb.u.z = __builtin_amdgcn_perm(dword_of(vr[5], e >> 1), dword_of(vr[4], e >> 1), sel);
                 vb.u.w = __builtin_amdgcn_perm(dword_of(vr[7], e >> 1), dword_of(vr[6], e >> 1), sel);
                 o[e] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(pa.v, vb.v, o[e], 0, 0, 0);
-                if constexpr (C::SPLIT_P) o[e] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(pr.v, vb.v, o[e], 0, 0, 0);
+                if constexpr (C::SPLIT_P) o_rest[e] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(pr.v, vb.v, o_rest[e], 0, 0, 0);
             }
             __builtin_amdgcn_wave_barrier();
+        }
+        if constexpr (C::SPLIT_P) {
+#pragma unroll
+            for (int e = 0; e < ET; ++e)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) o[e][i] = add_rest(o[e][i], o_rest[e][i]);
         }
         // publish one partial per wave
 #pragma unroll

@@ -246,13 +246,17 @@ __global__ __launch_bounds__(kXThreads, 2) void window_attn_kernel(const WindowP
             const int rot = rotate ? attn_rotation(row, sp, ntiles) : 0;
             float m_run[GROUPS], l_run[GROUPS][4], lx_run[GROUPS][4];   // l: one sum per key of a quarter of the tile, as in a single step
             xf32x4_t o[GROUPS][ET];                                       // o[k][e][i]: channel (quad * 4 + i) * ET + e, un-normalised
+            xf32x4_t o_rest[GROUPS][TERMS > 1 ? ET : 1];                  // the products of the terms after the first, apart (add_rest)
 #pragma unroll
             for (int k = 0; k < GROUPS; ++k) {
                 m_run[k] = kXNegBig;
 #pragma unroll
                 for (int i = 0; i < 4; ++i) l_run[k][i] = lx_run[k][i] = 0.f;
 #pragma unroll
-                for (int e = 0; e < ET; ++e) o[k][e] = (xf32x4_t){0.f, 0.f, 0.f, 0.f};
+                for (int e = 0; e < ET; ++e) {
+                    o[k][e] = (xf32x4_t){0.f, 0.f, 0.f, 0.f};
+                    if constexpr (TERMS > 1) o_rest[k][e] = o[k][e];
+                }
             }
             auto base_of = [&](int t) { return start + (t + rot < ntiles ? t + rot : t + rot - ntiles) * kXKT; };
             // The next tile's K is fetched a tile ahead, V while the tile's logits and weights are formed.
@@ -376,7 +380,10 @@ __global__ __launch_bounds__(kXThreads, 2) void window_attn_kernel(const WindowP
 #pragma unroll
                         for (int e = 0; e < ET; ++e)
 #pragma unroll
-                            for (int i = 0; i < 4; ++i) o[k][e][i] *= x[8];
+                            for (int i = 0; i < 4; ++i) {
+                                o[k][e][i] *= x[8];
+                                if constexpr (TERMS > 1) o_rest[k][e][i] *= x[8];
+                            }
                     }
                 }
                 __builtin_amdgcn_wave_barrier();
@@ -412,8 +419,9 @@ __global__ __launch_bounds__(kXThreads, 2) void window_attn_kernel(const WindowP
 #pragma unroll
                     for (int k = 0; k < GROUPS; ++k) {
                         if (k >= gpb) continue;
+                        o[k][e] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vb.v, pa[k][0].v, o[k][e], 0, 0, 0);
 #pragma unroll
-                        for (int s = 0; s < TERMS; ++s) o[k][e] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vb.v, pa[k][s].v, o[k][e], 0, 0, 0);
+                        for (int s = 1; s < TERMS; ++s) o_rest[k][e] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vb.v, pa[k][s].v, o_rest[k][e], 0, 0, 0);
                     }
                 }
                 __builtin_amdgcn_wave_barrier();
@@ -426,6 +434,12 @@ __global__ __launch_bounds__(kXThreads, 2) void window_attn_kernel(const WindowP
             for (int k = 0; k < GROUPS; ++k) {
                 if (k >= gpb) continue;
                 auto live = [&](int r) { return r < spg * G && step_of(k, r) >= ta && step_of(k, r) < tb; };
+                if constexpr (TERMS > 1) {
+#pragma unroll
+                    for (int e = 0; e < ET; ++e)
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) o[k][e][i] = add_rest(o[k][e][i], o_rest[k][e][i]);
+                }
                 float* dst = reinterpret_cast<float*>(my_k) + n16 * PART;   // the loop is over
 #pragma unroll
                 for (int i = 0; i < 4; ++i)
