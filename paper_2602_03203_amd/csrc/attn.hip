@@ -21,7 +21,7 @@
 // (byte permutes, no cross-lane traffic), so P.V is MFMA too and the accumulator lives in the
 // MFMA result layout.  The vector ALUs only do the softmax.
 // bf16, D = 64.  The same with shorter rows: the K operand is loaded directly (a row is four lanes x 16 bytes per k-step), V
-// 8 bytes a lane, and the probabilities go in as bf16 head plus bf16 remainder (16 significant bits), normalised by their
+// 8 bytes a lane, and the probabilities go in as three bf16 terms (all 24 bits of them), normalised by their
 // fp32 sum.  P.V as fp32 FMA, every key group its own accumulator and 64 of them to merge per workgroup, took 18.9 us at
 // 128 rows of 2048 pairs and 8.7 us at 8 rows of 300; this takes 14.6 and 6.2.
 // fp32.  q.K^T as fp32 FMA plus a DPP row reduction, P.V as fp32 FMA.
@@ -101,7 +101,7 @@ __device__ __forceinline__ float row16_max(float v) {
 template <typename T, int D, int G> struct AttnCfg {
     static constexpr bool MFMA = sizeof(T) == 2;
     static constexpr bool PVM = MFMA;                       // P.V on MFMA as well
-    static constexpr bool SPLIT_P = PVM && D == 64;         // probabilities as bf16 head + remainder
+    static constexpr bool SPLIT_P = PVM && D == 64;         // probabilities as three bf16 terms, together all 24 bits of them
     static constexpr int CH = D * (int)sizeof(T) / 16;      // 16-byte chunks per row = lanes per key (P.V layout)
     static constexpr int KG = kWave / CH;                   // key groups per wave in the P.V layout
     static constexpr int WAVES = PVM ? 8 : 4;
@@ -114,13 +114,14 @@ template <typename T, int D, int G> struct AttnCfg {
     static constexpr int PS = KT + 8;                       // PVM: bf16 row stride of the P tile in LDS
     static constexpr int KRS = 272;                         // D = 128: padded byte stride of a K row in LDS
     // dynamic LDS (floats unless noted):
-    //   PVM:   m [NG][G] | l [NG][G] | w [NG][G] | M [8] | P tiles [WAVES][GP][PS] bf16 (D = 64: head and remainder) | D = 128:
+    //   PVM:   m [NG][G] | l [NG][G] | w [NG][G] | M [8] | P tiles [WAVES][PROWS][PS] bf16 | D = 128:
     //          K tiles [WAVES][KT][KRS] bytes (a wavefront's partial accumulator [G][D] reuses its own K tile once its loop is
-    //          over), 73 KB at G = 4: two workgroups fit the 160 KB of a CU; D = 64: the partial accumulators
+    //          over), 73 KB at G = 4: two workgroups fit the 160 KB of a CU; D = 64: the partial accumulators, term by term
     //   other: acc [NG][G][D] | m [NG][G] | l [NG][G] | w [NG][G] | M [8] | p [WAVES][KT][GP] | corr [WAVES][GP]
-    static constexpr int ACC_STRIDE = PVM && D == 128 ? KT * KRS / 4 : G * D;  // floats between the partial accumulators
+    static constexpr int ACC_STRIDE = PVM && D == 128 ? KT * KRS / 4 : (SPLIT_P ? 3 : 1) * G * D;  // floats between the partial accumulators
     static constexpr size_t HEAD_FLOATS = 3 * (size_t)NG * G + 8;   // m, l, w, M
-    static constexpr size_t PB_BYTES = (size_t)WAVES * GP * PS * 2 * (SPLIT_P ? 2 : 1);  // PVM: the bf16 P tiles
+    static constexpr int PROWS = SPLIT_P ? 3 * GP : GP;               // PVM: rows of a P tile, term by term
+    static constexpr size_t PB_BYTES = (size_t)WAVES * PROWS * PS * 2;  // PVM: the bf16 P tiles
     static constexpr size_t LDS_BYTES =
         PVM ? sizeof(float) * (HEAD_FLOATS + (size_t)WAVES * ACC_STRIDE) + PB_BYTES
             : sizeof(float) * ((size_t)NG * G * D + HEAD_FLOATS + (size_t)WAVES * KT * GP + (size_t)WAVES * GP + 4);
@@ -405,12 +406,13 @@ __global__ __launch_bounds__((AttnCfg<T, D, G>::THREADS)) void attn_kernel(const
         const int n16 = lane & 15, quad = lane >> 4;
         constexpr int KS = D / 32;          // k-steps of q.K^T
         constexpr int ET = D / 16;          // channel tiles of P.V
-        uint16_t* my_pb = reinterpret_cast<uint16_t*>(s_p) + (size_t)wave * GP * PS * (C::SPLIT_P ? 2 : 1);   // [GP][PS] bf16, D = 64: two
+        uint16_t* my_pb = reinterpret_cast<uint16_t*>(s_p) + (size_t)wave * C::PROWS * PS;   // [PROWS][PS] bf16
         unsigned char* my_k = s_kt + (size_t)wave * KT * KRS;   // D = 128
         B128 qa[KS];
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks) {
-            if (n16 < G) qa[ks].u = *reinterpret_cast<const uint4*>(qrow + (size_t)n16 * D + ks * 32 + quad * 8);
+            const int h = C::SPLIT_P ? n16 % GP : n16;   // SPLIT_P: the heads once for every term (below)
+            if (h < G) qa[ks].u = *reinterpret_cast<const uint4*>(qrow + (size_t)h * D + ks * 32 + quad * 8);
             else qa[ks].u = make_uint4(0, 0, 0, 0);
         }
         float m_run[4], l_run[4], lx_run[4];  // lx: sum of the unrounded weights (feature variant)
@@ -422,13 +424,17 @@ __global__ __launch_bounds__((AttnCfg<T, D, G>::THREADS)) void attn_kernel(const
         }
         float* lg_row = FEAT ? P.logit + (size_t)row * P.cap * GP : nullptr;
         f32x4_t o[ET];  // o[e][i] = out[head quad*4 + i][channel n16*ET + e], un-normalised
-        // SPLIT_P: the remainders' part, apart from the heads': an infinite value times a remainder, which may be 0 or negative, must not
-        // turn the infinity that the head's product gives into a NaN
-        f32x4_t o_rest[C::SPLIT_P ? ET : 1];
+        // SPLIT_P: the three terms of a probability are rows of their own in the same product: heads 0 .. GP - 1 times (first, second, third
+        // term), GP = 4 twelve of the sixteen rows, GP = 8 two products.  The logits and the softmax are formed in every row (the query
+        // rows are repeated), so the sums of a term are rescaled like any others; they are added at the end, in the merge.  (A second product
+        // onto the rows of the second terms would leave 0 * inf in the others.)  Sums of their own also keep infinite values what they
+        // are: a later term may be 0 or negative.
+        constexpr bool THIRD = C::SPLIT_P && GP == 8;   // the third terms in a product of their own
+        f32x4_t o3[THIRD ? ET : 1];
 #pragma unroll
         for (int e = 0; e < ET; ++e) {
             o[e] = (f32x4_t){0.f, 0.f, 0.f, 0.f};
-            if constexpr (C::SPLIT_P) o_rest[e] = o[e];
+            if constexpr (THIRD) o3[e] = o[e];
         }
 
         // Tiles are dealt round robin to the wavefronts; with P.rotate the deal starts from a tile that differs
@@ -485,7 +491,7 @@ __global__ __launch_bounds__((AttnCfg<T, D, G>::THREADS)) void attn_kernel(const
             }
             bool changed = false;
             float corr[4];
-            uint32_t pb[2][4], pl[2][4];
+            uint32_t pb[2][4], p3[2][4];
             if constexpr (FEAT) {  // keep the step's logits: the second pass turns them into attention weights
                 if (quad * 4 < GP) {
                     if (base + n16 < end)
@@ -508,9 +514,18 @@ __global__ __launch_bounds__((AttnCfg<T, D, G>::THREADS)) void attn_kernel(const
                 const uint32_t u0 = __float_as_uint(e0) + 0x8000u, u1 = __float_as_uint(e1) + 0x8000u;
                 pb[0][i] = u0 >> 16;
                 pb[1][i] = u1 >> 16;
-                if constexpr (C::SPLIT_P) {
-                    pl[0][i] = (__float_as_uint(e0 - __uint_as_float(u0 & 0xffff0000u)) + 0x8000u) >> 16;
-                    pl[1][i] = (__float_as_uint(e1 - __uint_as_float(u1 & 0xffff0000u)) + 0x8000u) >> 16;
+                if constexpr (C::SPLIT_P) {   // each term of what the ones before leave; GP = 4: row quad q holds term q, GP = 8: q / 2
+                    const float r0 = e0 - __uint_as_float(u0 & 0xffff0000u), r1 = e1 - __uint_as_float(u1 & 0xffff0000u);
+                    const uint32_t v0 = __float_as_uint(r0) + 0x8000u, v1 = __float_as_uint(r1) + 0x8000u;
+                    p3[0][i] = __float_as_uint(r0 - __uint_as_float(v0 & 0xffff0000u)) >> 16;
+                    p3[1][i] = __float_as_uint(r1 - __uint_as_float(v1 & 0xffff0000u)) >> 16;
+                    const int term = quad * 4 / GP;
+                    pb[0][i] = term == 0 ? pb[0][i] : v0 >> 16;
+                    pb[1][i] = term == 0 ? pb[1][i] : v1 >> 16;
+                    if constexpr (!THIRD) {
+                        pb[0][i] = term < 2 ? pb[0][i] : p3[0][i];
+                        pb[1][i] = term < 2 ? pb[1][i] : p3[1][i];
+                    }
                     l_run[i] = l_run[i] * corr[i] + e0 + e1;
                 } else {
                     l_run[i] = l_run[i] * corr[i] + __uint_as_float(u0 & 0xffff0000u) + __uint_as_float(u1 & 0xffff0000u);
@@ -518,14 +533,16 @@ __global__ __launch_bounds__((AttnCfg<T, D, G>::THREADS)) void attn_kernel(const
                 }
                 m_run[i] = mn;
             }
-            if (quad * 4 < GP) {
+            if (quad * 4 < C::PROWS) {
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
                     my_pb[(quad * 4 + i) * PS + n16] = (uint16_t)pb[0][i];
                     my_pb[(quad * 4 + i) * PS + 16 + n16] = (uint16_t)pb[1][i];
-                    if constexpr (C::SPLIT_P) {
-                        my_pb[(GP + quad * 4 + i) * PS + n16] = (uint16_t)pl[0][i];
-                        my_pb[(GP + quad * 4 + i) * PS + 16 + n16] = (uint16_t)pl[1][i];
+                    if constexpr (THIRD) {
+                        if (quad < 2) {
+                            my_pb[(16 + quad * 4 + i) * PS + n16] = (uint16_t)p3[0][i];
+                            my_pb[(16 + quad * 4 + i) * PS + 16 + n16] = (uint16_t)p3[1][i];
+                        }
                     }
                 }
             }
@@ -535,16 +552,16 @@ __global__ __launch_bounds__((AttnCfg<T, D, G>::THREADS)) void attn_kernel(const
 #pragma unroll
                     for (int i = 0; i < 4; ++i) {
                         o[e][i] *= corr[i];
-                        if constexpr (C::SPLIT_P) o_rest[e][i] *= corr[i];
+                        if constexpr (THIRD) o3[e][i] *= corr[i];
                     }
             }
             __builtin_amdgcn_wave_barrier();
-            // A operand of P.V: P[head n16][k-slots quad*8 .. +8]; k-slot u of group quad is key base + quad*8 + u
+            // A operand of P.V: P[row n16][k-slots quad*8 .. +8]; k-slot u of group quad is key base + quad*8 + u
             B128 pa, pr;
             pa.u = pr.u = make_uint4(0, 0, 0, 0);
-            if (n16 < GP) {
-                pa.u = *reinterpret_cast<const uint4*>(my_pb + n16 * PS + quad * 8);
-                if constexpr (C::SPLIT_P) pr.u = *reinterpret_cast<const uint4*>(my_pb + (GP + n16) * PS + quad * 8);
+            if (n16 < C::PROWS) pa.u = *reinterpret_cast<const uint4*>(my_pb + n16 * PS + quad * 8);
+            if constexpr (THIRD) {
+                if (n16 < GP) pr.u = *reinterpret_cast<const uint4*>(my_pb + (16 + n16) * PS + quad * 8);
             }
             // B operand: tile e = channel n16*ET + e over this lane's 8 k-slots (8 x ET transpose in registers)
 #pragma unroll
@@ -556,29 +573,27 @@ __global__ __launch_bounds__((AttnCfg<T, D, G>::THREADS)) void attn_kernel(const
                 vb.u.z = __builtin_amdgcn_perm(dword_of(vr[5], e >> 1), dword_of(vr[4], e >> 1), sel);
                 vb.u.w = __builtin_amdgcn_perm(dword_of(vr[7], e >> 1), dword_of(vr[6], e >> 1), sel);
                 o[e] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(pa.v, vb.v, o[e], 0, 0, 0);
-                if constexpr (C::SPLIT_P) o_rest[e] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(pr.v, vb.v, o_rest[e], 0, 0, 0);
+                if constexpr (THIRD) o3[e] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(pr.v, vb.v, o3[e], 0, 0, 0);
             }
             __builtin_amdgcn_wave_barrier();
-        }
-        if constexpr (C::SPLIT_P) {
-#pragma unroll
-            for (int e = 0; e < ET; ++e)
-#pragma unroll
-                for (int i = 0; i < 4; ++i) o[e][i] = add_rest(o[e][i], o_rest[e][i]);
         }
         // publish one partial per wave
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
             const int h = quad * 4 + i;
             const float ls = group_sum<16>(l_run[i]);
-            if (h < G) {
-                float* dst = s_acc + (size_t)wave * C::ACC_STRIDE + (size_t)h * D + n16 * ET;  // D = 128: own K tile, its loop is over
+            const int ht = C::SPLIT_P ? h % GP : h, term = C::SPLIT_P ? h / GP : 0;   // SPLIT_P: row h holds term `term` of head ht
+            float* dst = s_acc + (size_t)wave * C::ACC_STRIDE + (size_t)(term * G + ht) * D + n16 * ET;  // D = 128: own K tile, its loop is over
+            if (ht < G && h < C::PROWS) {
 #pragma unroll
                 for (int e = 0; e < ET; e += 4) *reinterpret_cast<float4*>(dst + e) = make_float4(o[e][i], o[e + 1][i], o[e + 2][i], o[e + 3][i]);
-                if (n16 == 0) {
-                    s_m[wave * G + h] = m_run[i];
-                    s_l[wave * G + h] = ls;
-                }
+            }
+            if constexpr (THIRD) {
+                if (h < G) *reinterpret_cast<float4*>(dst + 2 * G * D) = make_float4(o3[0][i], o3[1][i], o3[2][i], o3[3][i]);
+            }
+            if (h < G && n16 == 0) {
+                s_m[wave * G + h] = m_run[i];
+                s_l[wave * G + h] = ls;
             }
             if constexpr (FEAT && !C::SPLIT_P) {
                 const float lxs = group_sum<16>(lx_run[i]);
@@ -696,8 +711,20 @@ __global__ __launch_bounds__((AttnCfg<T, D, G>::THREADS)) void attn_kernel(const
         const int h = idx / D, d = idx % D;
         const float mn = s_M[h];
         float a = 0.f, ls = 0.f;
+        if constexpr (C::SPLIT_P) {
+            float a2 = 0.f, a3 = 0.f;
 #pragma unroll 8
-        for (int g2 = 0; g2 < NG; ++g2) a = fmaf(s_acc[(size_t)g2 * C::ACC_STRIDE + (size_t)h * D + d], s_w[g2 * G + h], a);
+            for (int g2 = 0; g2 < NG; ++g2) {
+                const float *p = s_acc + (size_t)g2 * C::ACC_STRIDE + (size_t)h * D + d, w = s_w[g2 * G + h];
+                a = fmaf(p[0], w, a);
+                a2 = fmaf(p[G * D], w, a2);
+                a3 = fmaf(p[2 * G * D], w, a3);
+            }
+            a = add_terms(a, a2, a3);
+        } else {
+#pragma unroll 8
+            for (int g2 = 0; g2 < NG; ++g2) a = fmaf(s_acc[(size_t)g2 * C::ACC_STRIDE + (size_t)h * D + d], s_w[g2 * G + h], a);
+        }
         if (d == 0 || used == 1) {
 #pragma unroll 8
             for (int g2 = 0; g2 < NG; ++g2) ls = fmaf(s_l[g2 * G + h], s_w[g2 * G + h], ls);

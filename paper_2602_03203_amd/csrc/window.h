@@ -76,10 +76,9 @@ __host__ __device__ inline int attn_rotation(int row, int split, int ntiles) {
     return (int)(((unsigned)row * 37u + (unsigned)split * 11u) % (unsigned)ntiles);
 }
 
-// head_dim 64 (probabilities as several bf16 terms): the products of the first terms and those of the others as one sum; an infinity or a
-// NaN of the first stays what it is
-__device__ __forceinline__ float add_rest(float head, float rest) {
-    return (__float_as_uint(head) & 0x7f800000u) == 0x7f800000u ? head : head + rest;
+// head_dim 64, probabilities as three bf16 terms: the merged products of the terms; an infinity or a NaN of the first stays what it is
+__device__ __forceinline__ float add_terms(float first, float second, float third) {
+    return (__float_as_uint(first) & 0x7f800000u) == 0x7f800000u ? first : first + (second + third);
 }
 
 // ---- windows -----------------------------------------------------------------------------------------------------

@@ -48,17 +48,18 @@ static constexpr int kSplitBatch = 64;              // splits whose maxima are h
 template <int D, int GROUPS> struct WindowCfg {
     static constexpr int CH = D / 8, ET = D / 16, KS = D / 32;   // 16-byte chunks of a row, channel tiles, k-steps
     static constexpr int KRS = D * 2 + 16;                       // padded byte stride of a K (D = 128) or query row in LDS
-    static constexpr int TERMS = D == 64 ? 2 : 1;                // bf16 terms of a probability
+    static constexpr int TERMS = D == 64 ? 3 : 1;                // bf16 terms of a probability
     static constexpr int PART = D + 4;                           // float stride of a wavefront's partial accumulator [16][D]
-    // dynamic LDS: per wavefront K tile [32][KRS] bytes (D = 128) or partial accumulator | P tiles [8][GROUPS][TERMS][16][40] bf16 |
-    // queries [GROUPS][16][KRS] | m, l, exact l, weights [8][16] floats each | without features: split maxima [kSplitBatch][GROUPS * 16], merged splits [GROUPS * 16][D], their
-    // maxima and normalisers [GROUPS * 16], correction and weight of the split being merged [16]
-    static constexpr size_t WAVE_BYTES = D == 128 ? (size_t)kXKT * KRS : (size_t)16 * PART * 4;
-    static constexpr size_t P_BYTES = (size_t)kXWaves * GROUPS * TERMS * 16 * kXPS * 2;
+    // dynamic LDS: per wavefront K tile [32][KRS] bytes (D = 128) and P tiles [GROUPS][TERMS][16][40] bf16, later in their place its
+    // partial accumulators [TERMS][16][PART] | queries [GROUPS][16][KRS] | m, l, exact l, weights [8][16] floats each | with splits:
+    // maxima [kSplitBatch][GROUPS * 16], merged splits [GROUPS * 16][D], their maxima and normalisers [GROUPS * 16], correction and
+    // weight of the split being merged [16]
+    static constexpr size_t K_BYTES = D == 128 ? (size_t)kXKT * KRS : 0;
+    static constexpr size_t P_BYTES = (size_t)GROUPS * TERMS * 16 * kXPS * 2, PART_BYTES = (size_t)TERMS * 16 * PART * 4;
+    static constexpr size_t WAVE_BYTES = K_BYTES + P_BYTES > PART_BYTES ? K_BYTES + P_BYTES : PART_BYTES;
     static constexpr size_t Q_BYTES = (size_t)GROUPS * 16 * KRS;
-    static constexpr size_t LDS_BYTES = kXWaves * WAVE_BYTES + P_BYTES + Q_BYTES + 4 * sizeof(float) * kXWaves * 16;
+    static constexpr size_t LDS_BYTES = kXWaves * WAVE_BYTES + Q_BYTES + 4 * sizeof(float) * kXWaves * 16;
     static constexpr size_t MERGE_BYTES = sizeof(float) * (GROUPS * 16 * (kSplitBatch + D + 2) + 32);
-    static_assert((size_t)16 * PART * 4 <= WAVE_BYTES, "the partial accumulator reuses the K tile");
 };
 
 // maximum / sum over the four lanes that share a query (lane % 16)
@@ -102,8 +103,8 @@ __global__ __launch_bounds__(kXThreads, 2) void window_attn_kernel(const WindowP
 
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     unsigned char* my_k = smem + (size_t)wave * C::WAVE_BYTES;
-    uint16_t* my_pb = reinterpret_cast<uint16_t*>(smem + kXWaves * C::WAVE_BYTES) + (size_t)wave * GROUPS * TERMS * 16 * kXPS;
-    unsigned char* s_q = smem + kXWaves * C::WAVE_BYTES + C::P_BYTES;
+    uint16_t* my_pb = reinterpret_cast<uint16_t*>(my_k + C::K_BYTES);
+    unsigned char* s_q = smem + kXWaves * C::WAVE_BYTES;
     float* s_m = reinterpret_cast<float*>(s_q + C::Q_BYTES);   // [8][16]
     float *s_l = s_m + kXWaves * 16, *s_lx = s_l + kXWaves * 16, *s_w = s_lx + kXWaves * 16;
     uint32_t* s_top = reinterpret_cast<uint32_t*>(s_w + kXWaves * 16);   // [kSplitBatch][GROUPS * 16] maxima of the splits
@@ -246,7 +247,7 @@ __global__ __launch_bounds__(kXThreads, 2) void window_attn_kernel(const WindowP
             const int rot = rotate ? attn_rotation(row, sp, ntiles) : 0;
             float m_run[GROUPS], l_run[GROUPS][4], lx_run[GROUPS][4];   // l: one sum per key of a quarter of the tile, as in a single step
             xf32x4_t o[GROUPS][ET];                                       // o[k][e][i]: channel (quad * 4 + i) * ET + e, un-normalised
-            xf32x4_t o_rest[GROUPS][TERMS > 1 ? ET : 1];                  // the products of the terms after the first, apart (add_rest)
+            xf32x4_t o2[GROUPS][TERMS > 1 ? ET : 1], o3[GROUPS][TERMS > 1 ? ET : 1];   // those of the second and third terms
 #pragma unroll
             for (int k = 0; k < GROUPS; ++k) {
                 m_run[k] = kXNegBig;
@@ -255,7 +256,7 @@ __global__ __launch_bounds__(kXThreads, 2) void window_attn_kernel(const WindowP
 #pragma unroll
                 for (int e = 0; e < ET; ++e) {
                     o[k][e] = (xf32x4_t){0.f, 0.f, 0.f, 0.f};
-                    if constexpr (TERMS > 1) o_rest[k][e] = o[k][e];
+                    if constexpr (TERMS > 1) o2[k][e] = o3[k][e] = o[k][e];
                 }
             }
             auto base_of = [&](int t) { return start + (t + rot < ntiles ? t + rot : t + rot - ntiles) * kXKT; };
@@ -371,10 +372,16 @@ __global__ __launch_bounds__(kXThreads, 2) void window_attn_kernel(const WindowP
                         }
                     };
                     put(pb);
-                    if constexpr (TERMS > 1) {   // the remainder, rounded in its turn
+                    if constexpr (TERMS > 1) {   // each term of what the ones before leave
 #pragma unroll
-                        for (int j = 0; j < 8; ++j) u[j] = __float_as_uint(x[j] - __uint_as_float(u[j] & 0xffff0000u)) + 0x8000u;
-                        put(pb + 16 * kXPS);
+                        for (int s = 1; s < TERMS; ++s) {
+#pragma unroll
+                            for (int j = 0; j < 8; ++j) {
+                                x[j] -= __uint_as_float(u[j] & 0xffff0000u);
+                                u[j] = __float_as_uint(x[j]) + (s == 1 ? 0x8000u : 0u);   // (the third has no bits beyond bf16)
+                            }
+                            put(pb + s * 16 * kXPS);
+                        }
                     }
                     if (__any(changed)) {
 #pragma unroll
@@ -382,7 +389,10 @@ __global__ __launch_bounds__(kXThreads, 2) void window_attn_kernel(const WindowP
 #pragma unroll
                             for (int i = 0; i < 4; ++i) {
                                 o[k][e][i] *= x[8];
-                                if constexpr (TERMS > 1) o_rest[k][e][i] *= x[8];
+                                if constexpr (TERMS > 1) {
+                                    o2[k][e][i] *= x[8];
+                                    o3[k][e][i] *= x[8];
+                                }
                             }
                     }
                 }
@@ -420,8 +430,10 @@ __global__ __launch_bounds__(kXThreads, 2) void window_attn_kernel(const WindowP
                     for (int k = 0; k < GROUPS; ++k) {
                         if (k >= gpb) continue;
                         o[k][e] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vb.v, pa[k][0].v, o[k][e], 0, 0, 0);
-#pragma unroll
-                        for (int s = 1; s < TERMS; ++s) o_rest[k][e] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vb.v, pa[k][s].v, o_rest[k][e], 0, 0, 0);
+                        if constexpr (TERMS > 1) {
+                            o2[k][e] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vb.v, pa[k][1].v, o2[k][e], 0, 0, 0);
+                            o3[k][e] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vb.v, pa[k][2].v, o3[k][e], 0, 0, 0);
+                        }
                     }
                 }
                 __builtin_amdgcn_wave_barrier();
@@ -434,18 +446,18 @@ __global__ __launch_bounds__(kXThreads, 2) void window_attn_kernel(const WindowP
             for (int k = 0; k < GROUPS; ++k) {
                 if (k >= gpb) continue;
                 auto live = [&](int r) { return r < spg * G && step_of(k, r) >= ta && step_of(k, r) < tb; };
+                float* dst = reinterpret_cast<float*>(my_k) + n16 * PART + quad * 4 * ET;   // the loop is over
+                auto publish = [&](float* to, const xf32x4_t* x) {
+#pragma unroll
+                    for (int i = 0; i < 4; ++i)
+#pragma unroll
+                        for (int e = 0; e < ET; e += 4) *reinterpret_cast<float4*>(to + i * ET + e) = make_float4(x[e][i], x[e + 1][i], x[e + 2][i], x[e + 3][i]);
+                };
+                publish(dst, o[k]);
                 if constexpr (TERMS > 1) {
-#pragma unroll
-                    for (int e = 0; e < ET; ++e)
-#pragma unroll
-                        for (int i = 0; i < 4; ++i) o[k][e][i] = add_rest(o[k][e][i], o_rest[k][e][i]);
+                    publish(dst + 16 * PART, o2[k]);
+                    publish(dst + 32 * PART, o3[k]);
                 }
-                float* dst = reinterpret_cast<float*>(my_k) + n16 * PART;   // the loop is over
-#pragma unroll
-                for (int i = 0; i < 4; ++i)
-#pragma unroll
-                    for (int e = 0; e < ET; e += 4)
-                        *reinterpret_cast<float4*>(dst + (quad * 4 + i) * ET + e) = make_float4(o[k][e][i], o[k][e + 1][i], o[k][e + 2][i], o[k][e + 3][i]);
                 const float ls = quads_sum((l_run[k][0] + l_run[k][1]) + (l_run[k][2] + l_run[k][3]));
                 const float lxs = FEAT ? quads_sum((lx_run[k][0] + lx_run[k][1]) + (lx_run[k][2] + lx_run[k][3])) : 0.f;
                 if (quad == 0) {
@@ -490,8 +502,17 @@ __global__ __launch_bounds__(kXThreads, 2) void window_attn_kernel(const WindowP
                 for (int j = 0; j < 16 * D / kXThreads; ++j) {
                     const int r = (tid + j * kXThreads) / D, d = tid % D;
                     float a = 0.f, l = 0.f;
+                    float a2 = 0.f, a3 = 0.f;
 #pragma unroll
-                    for (int g2 = 0; g2 < kXWaves; ++g2) a = fmaf(reinterpret_cast<const float*>(smem + (size_t)g2 * C::WAVE_BYTES)[r * PART + d], s_w[g2 * 16 + r], a);
+                    for (int g2 = 0; g2 < kXWaves; ++g2) {
+                        const float *p = reinterpret_cast<const float*>(smem + (size_t)g2 * C::WAVE_BYTES) + r * PART + d, w = s_w[g2 * 16 + r];
+                        a = fmaf(p[0], w, a);
+                        if constexpr (TERMS > 1) {
+                            a2 = fmaf(p[16 * PART], w, a2);
+                            a3 = fmaf(p[32 * PART], w, a3);
+                        }
+                    }
+                    if constexpr (TERMS > 1) a = add_terms(a, a2, a3);
 #pragma unroll
                     for (int g2 = 0; g2 < kXWaves; ++g2) l = fmaf(s_l[g2 * 16 + r], s_w[g2 * 16 + r], l);
                     if (merging) {

@@ -1,4 +1,4 @@
-"""Decode steps at the edges of the split rule and of the head_dim 64 tiles, against the oracle."""
+"""Decode steps at the edges of the split rule and of the head_dim 64 tiles, against the oracle; the bits of head_dim 64 weights."""
 import numpy as np
 import pytest
 import torch
@@ -73,3 +73,37 @@ def test_rows_taken_by_length_give_the_same_bits(gpu, D, B, cap, small):
     assert torch.equal(res[0][2], torch.clamp(lens + 2, max=cap))
     for a, b in zip(*res):
         assert torch.equal(a.view(torch.uint8), b.view(torch.uint8))
+
+
+@pytest.mark.parametrize("g", [1, 4, 5, 8])
+@pytest.mark.parametrize("features", [False, True])
+def test_head_dim_64_weights_keep_their_24_bits(gpu, g, features):
+    """Four pairs a row: one of weight w and value M, three of weight 1 whose values (bf16 each) add up to -w M, the whole of it.  What is
+    left of the sum is M times the error of w.  Derived: a logit of at most 1 is rounded twice (2^-24 of 1.44 each), exp2f is good to
+    2^-23 and the sum to 2^-23 of M, below 2^-21 M together; a weight of 16 bits is off by up to 2^-17."""
+    import paper_2602_03203_amd as fk
+    B, D, M = 256, 64, 2.0 ** 20
+    gen = torch.Generator(device="cuda").manual_seed(2)
+    desc = fk.CacheDesc(B, g, 1, D, 8, "bf16")
+    K, V = torch.zeros((B, 1, 8, D), dtype=torch.bfloat16, device="cuda"), torch.zeros((B, 1, 8, D), dtype=torch.bfloat16, device="cuda")
+    q = torch.randn((B, 1, D), generator=gen, device="cuda").to(torch.bfloat16)
+    k = torch.randn((B, 1, D), generator=gen, device="cuda").to(torch.bfloat16)
+    z = (q.double() * k.double()).sum(2, keepdim=True)
+    k = torch.where(z > 0, -k, k)                                   # logits <= 0
+    scale = (1.0 / z.abs().amax()).item()                           # the largest is -1
+    scale = torch.tensor(scale, dtype=torch.float32).item()
+    w = torch.exp((q.double() * k.double()).sum(2) * scale)         # [B][1]
+    rest = w * M
+    for slot in range(3):
+        v = rest.to(torch.bfloat16)
+        V[:, :, slot, :] = -v[:, :, None]
+        rest = rest - v.double()
+    qg = q.expand(B, g, D).contiguous()
+    ln, pos = torch.full((B, 1), 3, dtype=torch.int32, device="cuda"), torch.zeros((B, 1, 8), dtype=torch.int32, device="cuda")
+    vn, pn, out = torch.full((B, 1, D), M, dtype=torch.bfloat16, device="cuda"), torch.zeros(B, dtype=torch.int32, device="cuda"), torch.zeros_like(qg)
+    if features:
+        fk.fk_decode_step_feat(desc, qg, K, V, pos, ln, k, vn, pn, 4, scale, fk.new_feat(desc), 0, 4, out, fk.new_feat_workspace(desc))
+    else:
+        fk.fk_decode_step(desc, qg, K, V, pos, ln, k, vn, pn, 4, scale, out, fk.new_attn_workspace(desc))
+    off = (out.double() * (3.0 + w[:, :, None]) - rest[:, :, None]).abs() / M
+    assert off.max() < 2.0 ** -21, f"weights off by 2^{torch.log2(off.max()).item():.1f}"
