@@ -555,6 +555,21 @@ __global__ __launch_bounds__((AttnCfg<T, D, G>::THREADS)) void attn_kernel(const
                         if constexpr (THIRD) o3[e][i] *= corr[i];
                     }
             }
+            if (base + KT > end) {
+                // The lanes past the end hold copies of the last pair, whose weight 0 there must not meet an infinity or a NaN.  Where it has
+                // one (the last quad's last register is a copy: all channels are looked at) the copies become zeros; zeroing them
+                // always takes 0.15 to 0.3 us of a step.
+                int tail = threadIdx.x;   // (opaque: addresses shared with the loads would stay in registers, 134 of them instead of 126)
+                asm volatile("" : "+v"(tail));
+                tail = (tail & (kWave - 1)) >> 4;   // quad
+                bool bad = pair_not_finite(vr[7].x) || pair_not_finite(vr[7].y);
+                if constexpr (D == 128) bad = bad || pair_not_finite(vr[7].z) || pair_not_finite(vr[7].w);
+                if (__any(bad && tail == 3)) {
+#pragma unroll
+                    for (int u = 0; u < 8; ++u)
+                        if (base + tail * 8 + u >= end) vr[u] = make_uint4(0, 0, 0, 0);
+                }
+            }
             __builtin_amdgcn_wave_barrier();
             // A operand of P.V: P[row n16][k-slots quad*8 .. +8]; k-slot u of group quad is key base + quad*8 + u
             B128 pa, pr;
@@ -666,6 +681,11 @@ __global__ __launch_bounds__((AttnCfg<T, D, G>::THREADS)) void attn_kernel(const
                 m[h] = mn;
 #pragma unroll
                 for (int e = 0; e < EPL; ++e) acc[h][e] *= corr;
+            }
+            if (base + KT > end) {   // past the end: zeros, as above
+#pragma unroll
+                for (int u = 0; u < VU; ++u)
+                    if (key[u] >= end) vr[u] = make_uint4(0, 0, 0, 0);
             }
 #pragma unroll
             for (int u = 0; u < VU; ++u) {

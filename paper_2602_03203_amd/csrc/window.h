@@ -76,6 +76,9 @@ __host__ __device__ inline int attn_rotation(int row, int split, int ntiles) {
     return (int)(((unsigned)row * 37u + (unsigned)split * 11u) % (unsigned)ntiles);
 }
 
+// bf16 pairs with an infinity or a NaN among them
+__device__ __forceinline__ bool pair_not_finite(uint32_t w) { return (w & 0x7f80u) == 0x7f80u || (w & 0x7f800000u) == 0x7f800000u; }
+
 // head_dim 64, probabilities as three bf16 terms: the merged products of the terms; an infinity or a NaN of the first stays what it is
 __device__ __forceinline__ float add_terms(float first, float second, float third) {
     return (__float_as_uint(first) & 0x7f800000u) == 0x7f800000u ? first : first + (second + third);

@@ -83,9 +83,6 @@ __device__ __forceinline__ uint32_t float_order(float f) {
 }
 __device__ __forceinline__ float order_float(uint32_t o) { return __uint_as_float((o & 0x80000000u) ? o ^ 0x80000000u : ~o); }
 
-// bf16 pairs with an infinity or a NaN among them
-__device__ __forceinline__ bool pair_not_finite(uint32_t w) { return (w & 0x7f80u) == 0x7f80u || (w & 0x7f800000u) == 0x7f800000u; }
-
 template <int D, bool FEAT, bool SPLIT, int GROUPS>
 __global__ __launch_bounds__(kXThreads, 2) void window_attn_kernel(const WindowParams P, int spg, int gpb, int blocks) {
     using C = WindowCfg<D, GROUPS>;
