@@ -23,7 +23,8 @@ static constexpr int kPoolU = 8;   // loads in flight per thread
 // 32 heads of 8192 tokens, bf16: 2.0 GB of causal entries in 341 us, 5.9 TB/s (354 us with a division per load to find the load's
 // head and query, four loads in flight).  Wider segments are no faster, 512 bytes 343 us, 1 KB 370 us: the fewer and longer
 // workgroups leave CUs idle at the end.
-template <typename T>
+// FEW: blocks of fewer than 64 queries.
+template <typename T, bool FEW>
 __global__ __launch_bounds__(kPoolThreads) void golden_pool_kernel(const T* __restrict__ A, int g, int Tn, size_t ld,
                                                                    int budget, int L, int M,
                                                                    float* __restrict__ a_tilde) {
@@ -38,26 +39,58 @@ __global__ __launch_bounds__(kPoolThreads) void golden_pool_kernel(const T* __re
     float acc[EPC];
 #pragma unroll
     for (int e = 0; e < EPC; ++e) acc[e] = 0.f;
+    const int qs = max(q0, i0), rows = q1 - qs;   // rows <= 0: above the diagonal for the whole block
     if (i_mine < q1 && (size_t)i_mine < ld) {
-        const T* base = A + (size_t)hp * g * Tn * ld + i_mine;
-        const int qs = max(q0, i0) + rg;   // (uniform over the lanes of a row group)
-        for (int h = 0; h < g; ++h) {
-            const T* head = base + (size_t)h * Tn * ld;
-            for (int q = qs; q < q1; q += RG * kPoolU) {
-                u32x4 v[kPoolU];
+        // read once, never again: non-temporal, so the lines do not push anything out of the caches
+        auto load = [](const T* p) { return __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(p)); };
+        if constexpr (!FEW) {   // head by head
+            for (int h = 0; h < g; ++h) {
+                const T* head = A + (size_t)(hp * g + h) * Tn * ld + i_mine;
+                for (int q = qs + rg; q < q1; q += RG * kPoolU) {
+                    u32x4 v[kPoolU];
 #pragma unroll
-                for (int u = 0; u < kPoolU; ++u) {
-                    const int qu = q + u * RG;
-                    // read once, never again: non-temporal, so the lines do not push anything out of the caches
-                    v[u] = (u32x4){0, 0, 0, 0};
-                    if (qu < q1 && qu >= i_mine) v[u] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(head + (size_t)qu * ld));
+                    for (int u = 0; u < kPoolU; ++u) {
+                        const int qu = q + u * RG;
+                        v[u] = (u32x4){0, 0, 0, 0};
+                        if (qu < q1 && qu >= i_mine) v[u] = load(head + (size_t)qu * ld);
+                    }
+                    float x[kPoolU][EPC];
+#pragma unroll
+                    for (int u = 0; u < kPoolU; ++u) Vec16<T>::unpack(make_uint4(v[u].x, v[u].y, v[u].z, v[u].w), x[u]);
+#pragma unroll
+                    for (int e = 0; e < EPC; ++e)
+                        acc[e] += ((x[0][e] + x[1][e]) + (x[2][e] + x[3][e])) + ((x[4][e] + x[5][e]) + (x[6][e] + x[7][e]));
                 }
-                float x[kPoolU][EPC];
+            }
+        } else {
+            // A head has less than the loads in flight take, so they go on into the next ones.  (Head by head, 32 heads of 4096 tokens, L = 16:
+            // 226 us, so 131; 32 heads of 2000 tokens in 4 groups, L = 8: 107 and 55.  From 64 queries on, head by head is 1 to 3 % the
+            // faster; a kernel of its own, because the other one's registers cost these short workgroups their number on a CU, 8 heads of 4096 tokens
+            // without pooling, L = 32: 52 us in one kernel, 42 so.)  This row group takes pairs (head, query) rg, rg + RG, ...: dh heads and dq queries on, one head
+            // more where that leaves the block.
+            constexpr int U = kPoolU / 2;
+            const int total = rows * g, dh = RG / rows, dq = RG % rows;
+            const size_t step = ((size_t)dh * Tn + dq) * ld, wrap = (size_t)(Tn - rows) * ld;
+            int q = rg % rows;
+            const T* p = A + ((size_t)(hp * g + rg / rows) * Tn + qs + q) * ld + i_mine;
+            for (int r = rg; r < total; r += RG * U) {
+                u32x4 v[U];
 #pragma unroll
-                for (int u = 0; u < kPoolU; ++u) Vec16<T>::unpack(make_uint4(v[u].x, v[u].y, v[u].z, v[u].w), x[u]);
+                for (int u = 0; u < U; ++u) {
+                    v[u] = (u32x4){0, 0, 0, 0};
+                    if (r + u * RG < total && qs + q >= i_mine) v[u] = load(p);
+                    p += step;
+                    q += dq;
+                    if (q >= rows) {
+                        q -= rows;
+                        p += wrap;
+                    }
+                }
+                float x[U][EPC];
 #pragma unroll
-                for (int e = 0; e < EPC; ++e)
-                    acc[e] += ((x[0][e] + x[1][e]) + (x[2][e] + x[3][e])) + ((x[4][e] + x[5][e]) + (x[6][e] + x[7][e]));
+                for (int u = 0; u < U; ++u) Vec16<T>::unpack(make_uint4(v[u].x, v[u].y, v[u].z, v[u].w), x[u]);
+#pragma unroll
+                for (int e = 0; e < EPC; ++e) acc[e] += (x[0][e] + x[1][e]) + (x[2][e] + x[3][e]);
             }
         }
     }
@@ -256,11 +289,11 @@ extern "C" fk_status fk_golden_scores(const void* A, int32_t dtype, int32_t n_q_
     hipStream_t st = (hipStream_t)stream;
     if (dtype == FK_F32) {
         const int KT = 64;
-        hipLaunchKernelGGL(golden_pool_kernel<float>, dim3((T + KT - 1) / KT, M, n_kv_heads), dim3(kPoolThreads), 0, st,
+        hipLaunchKernelGGL((interval < 64 ? golden_pool_kernel<float, true> : golden_pool_kernel<float, false>), dim3((T + KT - 1) / KT, M, n_kv_heads), dim3(kPoolThreads), 0, st,
                            (const float*)A, g, T, (size_t)ld, budget, interval, M, block_scores);
     } else {
         const int KT = 128;
-        hipLaunchKernelGGL(golden_pool_kernel<bf16_t>, dim3((T + KT - 1) / KT, M, n_kv_heads), dim3(kPoolThreads), 0, st,
+        hipLaunchKernelGGL((interval < 64 ? golden_pool_kernel<bf16_t, true> : golden_pool_kernel<bf16_t, false>), dim3((T + KT - 1) / KT, M, n_kv_heads), dim3(kPoolThreads), 0, st,
                            (const bf16_t*)A, g, T, (size_t)ld, budget, interval, M, block_scores);
     }
     hipLaunchKernelGGL(golden_future_kernel, dim3((T + 255) / 256, n_kv_heads), dim3(256), 0, st, block_scores, T, M, alpha);

@@ -81,6 +81,15 @@ def test_small_traces(gpu, dtype, Hq, g, T, B, L):
     assert run_case(gpu, dtype, Hq, g, T, B, L) > 0
 
 
+# pooling blocks around the number of queries from which they are taken head by head (64), fewer than a workgroup's row groups (16) and one;
+# the causal edge runs through the tiles
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("Hq,g,T,B,L", [(3, 3, 700, 130, 63), (4, 2, 700, 130, 64), (4, 4, 700, 130, 65), (5, 5, 400, 100, 15), (4, 2, 400, 100, 17),
+                                        (8, 8, 300, 60, 5), (3, 1, 200, 60, 1)])
+def test_pooling_of_short_blocks(gpu, dtype, Hq, g, T, B, L):
+    assert run_case(gpu, dtype, Hq, g, T, B, L) > 0
+
+
 @pytest.mark.parametrize("T", [48, 49])
 def test_traces_that_never_evict_or_evict_once(gpu, T):
     """T <= B + L: M = 0 and nothing is written; T = B + L + 1: one step whose block holds one query."""
