@@ -170,8 +170,11 @@ __global__ __launch_bounds__(kSelThreads) void golden_trace_kernel(const float* 
     for (int i = threadIdx.x; i < kRangeWords; i += kSelThreads) s_range[i] = 0;
     __syncthreads();
     const int stretch = ((budget + kSelWaves - 1) / kSelWaves + kWave - 1) / kWave * kWave;  // <= 64 * PER_LANE (host)
-    const int w0 = min(wave * stretch, budget), w1 = min(w0 + stretch, budget);
     for (int t = 1; t <= M; ++t) {
+        int tid = threadIdx.x;
+        // opaque: what is derived from it would be kept over the whole loop, 121 registers spilled
+        if constexpr (PER_LANE > 4) asm volatile("" : "+v"(tid));
+        const int lane = tid & (kWave - 1), wave = tid / kWave, w0 = min(wave * stretch, budget), w1 = min(w0 + stretch, budget);
         int32_t* out = kept + ((size_t)hp * M + (t - 1)) * budget;
         const bool more = t < M;
         const float* aln = al + (size_t)t * Tn;   // future scores of step t + 1
@@ -186,7 +189,7 @@ __global__ __launch_bounds__(kSelThreads) void golden_trace_kernel(const float* 
         float nxt[PER_LANE], nxt_new[PER_LANE];
 #pragma unroll
         for (int u = 0; u < PER_LANE; ++u) {
-            const int i = w0 + u * kWave + lane, j = (int)threadIdx.x + u * kSelThreads;
+            const int i = w0 + u * kWave + lane, j = tid + u * kSelThreads;
             nxt[u] = more && i < w1 ? aln[s_pos[i]] : 0.f;
             nxt_new[u] = more && j < L ? aln[new0 + j] : 0.f;
         }
@@ -194,8 +197,8 @@ __global__ __launch_bounds__(kSelThreads) void golden_trace_kernel(const float* 
         uint32_t kv[PER_LANE];
         int32_t pv[PER_LANE];
         if (k > 0) {
-            range_select<kSelThreads, 2>([&](int i, bool& valid) { valid = true; return s_key[i]; }, budget, (uint32_t)k, s_range, s_hist, s_wtot,
-                                         key_lo, key_hi, &Tk, &want);
+            range_select<kSelThreads, 2, true>([&](int i, bool& valid) { valid = true; return s_key[i]; }, budget, (uint32_t)k, s_range, s_hist, s_wtot,
+                                               range_plan(key_lo, key_hi), tid, &Tk, &want);
 #pragma unroll
             for (int u = 0; u < PER_LANE; ++u) {
                 const int i = w0 + u * kWave + lane;
@@ -211,7 +214,7 @@ __global__ __launch_bounds__(kSelThreads) void golden_trace_kernel(const float* 
             }
         }
         __syncthreads();  // every source is in registers, the counts are visible, the histogram has been read
-        for (int i = threadIdx.x; i < kRangeWords; i += kSelThreads) s_range[i] = 0;
+        for (int i = tid; i < kRangeWords; i += kSelThreads) s_range[i] = 0;
         key_lo = 0xffffffffu;
         key_hi = 0;
         if (k > 0) {
@@ -244,7 +247,7 @@ __global__ __launch_bounds__(kSelThreads) void golden_trace_kernel(const float* 
         // the L newest stay; then the L pairs generated before the next step join
 #pragma unroll
         for (int u = 0; u < PER_LANE; ++u) {
-            const int j = (int)threadIdx.x + u * kSelThreads;
+            const int j = tid + u * kSelThreads;
             if (j < L) {
                 out[k + j] = new0 + j;
                 s_pos[k + j] = new0 + j;

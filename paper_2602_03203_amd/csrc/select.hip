@@ -14,10 +14,10 @@
 
 namespace fk {
 
-// LDS (u32): histogram and list of range_select | histograms [4][256] of msd_select | wavefront totals [16][2] | wavefront minima
-// and maxima [16][2] | keys [lds_keys]
+// LDS (u32): histogram and list of range_select | histograms [4][256] of msd_select | wavefront totals [16][2] | key range
+// [kRangePart] | keys [lds_keys]
 static constexpr int kSelMaxLdsKeys = 36 * 1024;  // 144 KB of keys beside the histograms
-static constexpr int kSelLdsHead = kRangeWords + 4 * 256 + 32 + 32;  // words before the keys
+static constexpr int kSelLdsHead = kRangeWords + 4 * 256 + 32 + kRangePart;  // words before the keys
 // (Four wavefronts per row instead of sixteen were measured and dropped: 11.3 against 8.1 us; a pass is a chain
 // key -> atomic -> barrier -> scan of LDS round trips, which more wavefronts shorten.)
 //
@@ -58,8 +58,8 @@ __global__ __launch_bounds__(THREADS) void select_keep_kernel(const float* __res
     uint32_t* s_range = s_sel_mem;                // [kRangeWords]
     uint32_t* s_hist = s_range + kRangeWords;     // [4][256]
     uint32_t* s_wtot = s_hist + 4 * 256;          // [16][2]: kept counts of every wavefront (greater, equal)
-    uint32_t* s_wmm = s_wtot + 32;                // [16][2]: every wavefront's smallest and largest key
-    uint32_t* s_key = s_wmm + 32;                 // [lds_keys]
+    uint32_t* s_wmm = s_wtot + 32;                // [kRangePart]
+    uint32_t* s_key = s_wmm + kRangePart;         // [lds_keys]
     uint32_t* s_slot = s_key + lds_keys;          // kSelMerge: [lds_keys] the candidates' slots
     constexpr int WAVES = THREADS / kWave;
     const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
@@ -90,7 +90,7 @@ __global__ __launch_bounds__(THREADS) void select_keep_kernel(const float* __res
     // The row's keys are read from global memory once and kept in LDS (rows beyond the LDS share of the launch are
     // re-read from global memory in every pass).  Eight loads in flight per thread.
     const bool in_lds = ncand <= lds_keys;  // kSelMerge: the host sized the launch so that it is
-    uint32_t key_lo = 0xffffffffu, key_hi = 0;  // smallest and largest key, gathered while the keys are written to LDS
+    KeyRange kr;                            // gathered while the keys are written to LDS
     for (int i = threadIdx.x; i < kRangeWords + 4 * 256; i += THREADS) s_range[i] = 0;
     if constexpr (MODE == kSelMerge) {
         // Slot, then score: two dependent reads, eight of either in flight per thread (chunk by chunk, one survivor at a time, this
@@ -115,8 +115,7 @@ __global__ __launch_bounds__(THREADS) void select_keep_kernel(const float* __res
                     const uint32_t key = score_key(v[u]);
                     s_slot[i0 + u * THREADS] = (uint32_t)slot[u];
                     s_key[i0 + u * THREADS] = key;
-                    key_lo = min(key_lo, key);
-                    key_hi = max(key_hi, key);
+                    kr.add(key);
                 }
             }
         }
@@ -130,27 +129,14 @@ __global__ __launch_bounds__(THREADS) void select_keep_kernel(const float* __res
                 if (i0 + u * THREADS < ncand) {
                     const uint32_t key = score_key(v[u]);
                     s_key[i0 + u * THREADS] = key;
-                    key_lo = min(key_lo, key);
-                    key_hi = max(key_hi, key);
+                    kr.add(key);
                 }
             }
         }
     }
-    if (in_lds) {
-        wave_min_max(key_lo, key_hi);
-        if (lane == 0) {
-            s_wmm[2 * wave] = key_lo;
-            s_wmm[2 * wave + 1] = key_hi;
-        }
-    }
-    __syncthreads();
-    if (in_lds) {
-#pragma unroll
-        for (int w = 0; w < WAVES; ++w) {
-            key_lo = min(key_lo, s_wmm[2 * w]);
-            key_hi = max(key_hi, s_wmm[2 * w + 1]);
-        }
-    }
+    RangePlan rp = {};
+    if (in_lds) rp = kr.plan(ncand, s_wmm);
+    else __syncthreads();
     auto key_at = [&](int i) { return in_lds ? s_key[i] : score_key(sc[i]); };
 
     // (rows read from global memory: 16 loads in flight per thread)
@@ -158,7 +144,7 @@ __global__ __launch_bounds__(THREADS) void select_keep_kernel(const float* __res
     uint32_t want = (uint32_t)k;   // how many still to take among keys equal to the threshold
     if (k > 0) {
         auto key_of = [&](int i, bool& valid) { valid = true; return key_at(i); };
-        if (in_lds) range_select<THREADS, 2>(key_of, ncand, (uint32_t)k, s_range, s_hist, s_wtot, key_lo, key_hi, &prefix, &want);
+        if (in_lds) range_select<THREADS, 2>(key_of, ncand, (uint32_t)k, s_range, s_hist, s_wtot, rp, threadIdx.x, &prefix, &want);
         else msd_select<THREADS, 16>(key_of, ncand, (uint32_t)k, s_hist, 0u, ~0u, &prefix, &want);
     }
     // now: keep key > prefix, and the first `want` keys == prefix (k == 0: keep no candidate).  Ordered pass: every
@@ -320,10 +306,10 @@ __global__ __launch_bounds__(kSelThreads) void select_keep_sampled_kernel(const 
 // The same selection with the row in LDS (rows of up to kSampledLdsKeys candidates): both keys of every slot are formed
 // once, the selections and the ordered passes are those of select_keep_kernel (range_select, one ordered
 // walk per wavefront stretch), and the candidate marks take the place of the first key once the safe set is known.
-// LDS (u32): histogram and list of range_select | histograms [4][256] of msd_select | wavefront totals [16][4] | wavefront minima
-// and maxima [16][4] | key1 / candidate mark [lds_keys] | key2 [lds_keys]
+// LDS (u32): histogram and list of range_select | histograms [4][256] of msd_select | wavefront totals [16][4] | key ranges
+// [2][kRangePart] | key1 / candidate mark [lds_keys] | key2 [lds_keys]
 static constexpr int kSampledLdsKeys = 18 * 1024;
-static constexpr int kSampledLdsHead = kRangeWords + 4 * 256 + 64 + 64;  // words before the keys
+static constexpr int kSampledLdsHead = kRangeWords + 4 * 256 + 64 + 2 * kRangePart;  // words before the keys
 template <int THREADS>
 __global__ __launch_bounds__(THREADS) void select_keep_sampled_lds_kernel(const float* __restrict__ scores,
                                                                           const float* __restrict__ noise,
@@ -349,14 +335,14 @@ __global__ __launch_bounds__(THREADS) void select_keep_sampled_lds_kernel(const 
     uint32_t* s_range = s_sel_mem;           // [kRangeWords]
     uint32_t* s_hist = s_range + kRangeWords;// [4][256]
     uint32_t* s_wtot = s_hist + 4 * 256;     // [16][4]
-    uint32_t* s_wmm = s_wtot + 64;           // [16][4] every wavefront's smallest and largest first and second key
-    uint32_t* s_k1 = s_wmm + 64;             // [lds_keys] key of the score; later 1 = candidate, 0 = safe
+    uint32_t* s_wmm = s_wtot + 64;           // [2][kRangePart] range of the first keys, of the second keys
+    uint32_t* s_k1 = s_wmm + 2 * kRangePart; // [lds_keys] key of the score; later 1 = candidate, 0 = safe
     uint32_t* s_k2 = s_k1 + lds_keys;        // [lds_keys] key of score - noise
     constexpr int WAVES = THREADS / kWave;
     const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
 
     for (int i = threadIdx.x; i < kRangeWords; i += THREADS) s_range[i] = 0;
-    uint32_t min1 = 0xffffffffu, max1 = 0;   // of the first keys
+    KeyRange kr1;   // of the first keys
     for (int i0 = threadIdx.x; i0 < others; i0 += 8 * THREADS) {
         float v[8], z[8];
 #pragma unroll
@@ -371,21 +357,10 @@ __global__ __launch_bounds__(THREADS) void select_keep_sampled_lds_kernel(const 
                 const uint32_t key1 = score_key(v[u]), key2 = score_key(v[u] - z[u]);
                 s_k1[i0 + u * THREADS] = key1;
                 s_k2[i0 + u * THREADS] = key2;
-                min1 = min(min1, key1);
-                max1 = max(max1, key1);
+                kr1.add(key1);
             }
     }
-    wave_min_max(min1, max1);
-    if (lane == 0) {
-        s_wmm[4 * wave] = min1;
-        s_wmm[4 * wave + 1] = max1;
-    }
-    __syncthreads();
-#pragma unroll
-    for (int w = 0; w < WAVES; ++w) {
-        min1 = min(min1, s_wmm[4 * w]);
-        max1 = max(max1, s_wmm[4 * w + 1]);
-    }
+    const RangePlan rp1 = kr1.plan(others, s_wmm);
 
     // every wavefront owns one contiguous stretch of the row (the ordered passes walk it 64 slots at a time)
     const int stretch = (((others + WAVES - 1) / WAVES) + kWave - 1) / kWave * kWave;
@@ -395,8 +370,8 @@ __global__ __launch_bounds__(THREADS) void select_keep_sampled_lds_kernel(const 
     uint32_t T1 = 0, want1 = 0;
     if (k_safe > 0)
         range_select<THREADS, 2>([&](int i, bool& valid) { valid = true; return s_k1[i]; }, others, (uint32_t)k_safe, s_range, s_hist, s_wtot,
-                                 min1, max1, &T1, &want1);
-    uint32_t min2 = 0xffffffffu, max2 = 0;   // of the candidates' second keys
+                                 rp1, threadIdx.x, &T1, &want1);
+    KeyRange kr2;   // of the candidates' second keys
     {
         uint32_t eq = 0;  // slots equal to T1 in this stretch
         if (k_safe > 0)
@@ -419,30 +394,17 @@ __global__ __launch_bounds__(THREADS) void select_keep_sampled_lds_kernel(const 
             const uint32_t e_below = __builtin_amdgcn_mbcnt_hi((uint32_t)(me >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)me, 0));
             const bool safe = k_safe > 0 && (key > T1 || (is_eq && eq_run + e_below < want1));
             if (live) s_k1[i] = safe ? 0u : 1u;
-            if (live && !safe) {
-                min2 = min(min2, s_k2[i]);
-                max2 = max(max2, s_k2[i]);
-            }
+            if (live && !safe) kr2.add(s_k2[i]);
             eq_run += (uint32_t)__popcll(me);
         }
-        wave_min_max(min2, max2);
-        if (lane == 0) {
-            s_wmm[4 * wave + 2] = min2;
-            s_wmm[4 * wave + 3] = max2;
-        }
     }
-    __syncthreads();
-#pragma unroll
-    for (int w = 0; w < WAVES; ++w) {
-        min2 = min(min2, s_wmm[4 * w + 2]);
-        max2 = max(max2, s_wmm[4 * w + 3]);
-    }
+    const RangePlan rp2 = kr2.plan(others, s_wmm + kRangePart);
 
     // (2) which candidates stay: the k2 largest t = score - noise among them
     uint32_t T2 = 0, want2 = 0;
     if (k2 > 0)
         range_select<THREADS, 2>([&](int i, bool& valid) { valid = s_k1[i] != 0u; return s_k2[i]; }, others, (uint32_t)k2, s_range, s_hist, s_wtot,
-                                 min2, max2, &T2, &want2);
+                                 rp2, threadIdx.x, &T2, &want2);
 
     // (3) ordered output: safe pairs, surviving candidates (ties to the lower slot), protected tail
     auto walk = [&](auto write_, uint32_t& keep_run, uint32_t& eq_run) {

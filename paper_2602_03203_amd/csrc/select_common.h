@@ -268,44 +268,112 @@ __device__ __forceinline__ void msd_select(KeyFn key_of, int nslots, uint32_t k,
 // them are numbers near 0 that no score takes), then the list of the keys in the cut's bin, ranked as in msd_select.  Digits of
 // the bit pattern put the scores of a row, whose exponents span a few octaves, into a handful of bins: every LDS atomic of a
 // wavefront then waits for the others on its word (15360 keys between 1.2 and 4.5: 12 us in the first pass, 2984 keys left),
-// and a second pass follows.  More than 64 keys in the bin (ties, outliers) or values the bins cannot divide (infinities of
-// both signs, NaN among negative and positive ones): msd_select on what is left.
+// and a second pass follows.  More than 64 keys in the bin (256 of long rows): msd_select on them, which ends at once where
+// they are equal (ties).  Values that a few bins would hold (outliers, heavy tails: some wavefronts found a range far smaller
+// than that of all) or that bins cannot divide (infinities, NaN among negative and positive ones): msd_select from the start.
+// Measured, us, 128 rows of 2176 and 32 of 30000 keys: normal 6.3 and 28 (by digits 6.9 and 36), quotients of normal numbers 7.3
+// and 34 (by digits 6.8 and 33: the range is what they pay for; by range 10.6).
 static constexpr int kRangeBins = 1024;
-// LDS words: histogram | list: count, threshold, how many of it, unused, 64 keys.  Zero on entry; dirty on return.
-static constexpr int kRangeWords = kRangeBins + 4 + kWave;
+static constexpr int kRangeShort = 256;   // slots: by digits, which need no range (130 of them, sampled: 7.0 us, by range 7.5)
+static constexpr int kRangeList = 256, kRangeListRows = 8192;   // long rows list up to this many
+// LDS words: histogram | list: count, threshold, how many of it, unused, kRangeList keys.  Zero on entry; dirty on return.
+static constexpr int kRangeWords = kRangeBins + 4 + kRangeList;
 
 __device__ __forceinline__ float key_score(uint32_t key) { return __uint_as_float((key & 0x80000000u) ? key ^ 0x80000000u : ~key); }
 
-// kmin, kmax: smallest and largest valid key.  hist4: [4][256] words for msd_select, contents undefined; part: 2 * THREADS / 64 words.
+// Smallest and largest of the valid keys, gathered while they are formed: add() every key, then every thread calls plan().
+// One wavefront puts the sixteen wavefronts' ranges together and works out how to divide them, and the others wait: sixteen
+// doing it each for itself cost four turns on every SIMD.
+enum { kRangeDigits = -1, kRangeValue = -2, kRangeEqual = -3 };   // or, by bit pattern, the shift
+struct RangePlan {
+    uint32_t kmin, kmax;
+    float scale;
+    int how;
+};
+// crowded: some wavefronts found a far smaller range than all of them together
+__device__ __forceinline__ RangePlan range_plan(uint32_t kmin, uint32_t kmax, bool crowded = false) {
+    const float scale = 1023.9f / (key_score(kmax) - key_score(kmin));
+    int how = max(22 - __clz((int)(kmax - kmin)), 0);   // (kmax - kmin) >> how < 1024
+    // by value: a finite, positive scale: kmin and kmax are numbers and their difference is a normal one
+    if ((kmin ^ kmax) >> 31) how = !crowded && scale > 0.f && scale < 3.4e38f ? kRangeValue : kRangeDigits;
+    if (kmin == kmax) how = kRangeEqual;
+    return {kmin, kmax, scale, how};
+}
+static constexpr int kRangePart = 2 * kSelWaves + 4;   // LDS words, sixteen-byte aligned
+struct KeyRange {
+    uint32_t lo = 0xffffffffu, hi = 0;
+    __device__ __forceinline__ void add(uint32_t key) {
+        lo = min(lo, key);
+        hi = max(hi, key);
+    }
+    __device__ __forceinline__ RangePlan plan(int n, uint32_t* part) {   // n: slots; two barriers, one of short rows
+        if (n <= kRangeShort) {
+            __syncthreads();
+            return {0u, ~0u, 0.f, kRangeDigits};
+        }
+        static_assert(kSelWaves == 16, "one lane of a row per wavefront");
+        const int lane = threadIdx.x & (kWave - 1);
+        wave_min_max(lo, hi);
+        if (lane == 0) *reinterpret_cast<uint2*>(part + 2 * (threadIdx.x / kWave)) = make_uint2(lo, hi);
+        __syncthreads();
+        if (threadIdx.x < kWave) {
+            const uint2 r = *reinterpret_cast<const uint2*>(part + 2 * (lane & 15));
+            uint32_t mn = r.x, mx = r.y;
+#define FK_RANGE_STEP(CTRL)                          \
+    mn = min(mn, dpp_keep_u32<CTRL, 0xF>(mn));       \
+    mx = max(mx, dpp_keep_u32<CTRL, 0xF>(mx));
+            FK_RANGE_STEP(DPP_QUAD_XOR1)
+            FK_RANGE_STEP(DPP_QUAD_XOR2)
+            FK_RANGE_STEP(DPP_ROW_HALF_MIRROR)
+            FK_RANGE_STEP(DPP_ROW_MIRROR)
+#undef FK_RANGE_STEP
+            // Two of them, because one may have few keys; one where few have any.  (One without has NaN here.)
+            const bool narrow = lane < kSelWaves && 5.f * (key_score(r.y) - key_score(r.x)) < key_score(mx) - key_score(mn);
+            const int few = __popcll(__ballot(lane < kSelWaves && r.x <= r.y)) < 5;
+            const RangePlan rp = range_plan(mn, mx, __popcll(__ballot(narrow)) + few >= 2);
+            if (lane == 0) *reinterpret_cast<uint4*>(part + 2 * kSelWaves) = make_uint4(mn, mx, __float_as_uint(rp.scale), (uint32_t)rp.how);
+        }
+        __syncthreads();
+        const uint4 p = *reinterpret_cast<const uint4*>(part + 2 * kSelWaves);
+        return {p.x, p.y, __uint_as_float(p.z), (int)p.w};
+    }
+};
+
+// rp: of the valid keys; tid: threadIdx.x.  LOOP: for a caller with a loop round this, where code costs registers: no long
+// list, one msd_select.
+// hist4: [4][256] words for msd_select, contents undefined; part: 2 * THREADS / 64 words.
 // The other conditions are those of msd_select (every thread calls, 1 <= k <= number of valid slots).
-template <int THREADS, int U, typename KeyFn>
+template <int THREADS, int U, bool LOOP = false, typename KeyFn>
 __device__ __forceinline__ void range_select(KeyFn key_of, int nslots, uint32_t k, uint32_t* range, uint32_t* hist4, uint32_t* part,
-                                             uint32_t kmin, uint32_t kmax, uint32_t* T_out, uint32_t* want_out) {
-    const int lane = threadIdx.x & (kWave - 1);
-    if (kmin == kmax) {
-        *T_out = kmin;
+                                             const RangePlan rp, int tid, uint32_t* T_out, uint32_t* want_out) {
+    const int lane = tid & (kWave - 1);
+    const int how = __builtin_amdgcn_readfirstlane(rp.how);
+    if (how == kRangeEqual) {
+        *T_out = rp.kmin;
         *want_out = k;
         return;
     }
-    const bool by_value = (kmin ^ kmax) >> 31;
-    const float lo = key_score(kmin), scale = 1023.9f / (key_score(kmax) - lo);
-    const int shift = max(22 - __clz((int)(kmax - kmin)), 0);   // (kmax - kmin) >> shift < 1024
-    // a finite, positive scale: kmin and kmax are numbers and their difference is a normal one
-    const bool divides = !by_value || (scale > 0.f && scale < 3.4e38f);
+    if (!LOOP && how == kRangeDigits) {
+        for (int i = tid; i < 4 * 256; i += THREADS) hist4[i] = 0;
+        __syncthreads();
+        msd_select<THREADS, U>(key_of, nslots, k, hist4, rp.kmin, rp.kmin ^ rp.kmax, T_out, want_out);
+        return;
+    }
+    const float lo = key_score(rp.kmin);
     auto bin_of = [&](uint32_t key) -> uint32_t {
-        if (by_value) return (uint32_t)min(max((int)((key_score(key) - lo) * scale), 0), kRangeBins - 1);   // monotone: so is every step
-        return (key - kmin) >> shift;
+        if (how == kRangeValue) return (uint32_t)min(max((int)((key_score(key) - lo) * rp.scale), 0), kRangeBins - 1);   // monotone: so is every step
+        return (key - rp.kmin) >> how;
     };
     uint32_t bin = 0, want = k, inbin = 0xffffffffu;
-    if (divides) {
+    if (!LOOP || how != kRangeDigits) {
         for (int i0 = 0; i0 < nslots; i0 += U * THREADS) {   // uniform trip count: the wavefront votes below
             uint32_t kv[U];
             bool ok[U];
 #pragma unroll
-            for (int u = 0; u < U; ++u) kv[u] = key_of(min(i0 + u * THREADS + (int)threadIdx.x, nslots - 1), ok[u]);
+            for (int u = 0; u < U; ++u) kv[u] = key_of(min(i0 + u * THREADS + tid, nslots - 1), ok[u]);
 #pragma unroll
             for (int u = 0; u < U; ++u) {
-                const bool todo = ok[u] && i0 + u * THREADS + (int)threadIdx.x < nslots;
+                const bool todo = ok[u] && i0 + u * THREADS + tid < nslots;
                 const uint32_t dg = bin_of(kv[u]);
                 const unsigned long long act = __ballot(todo);
                 if (act != 0) {   // one vote: a wavefront of equal bins adds its count once
@@ -320,9 +388,9 @@ __device__ __forceinline__ void range_select(KeyFn key_of, int nslots, uint32_t 
             }
         }
         __syncthreads();
-        // One wavefront finds the bin (sixteen doing it each for itself cost four turns on every SIMD): four blocks of 256 bins from the
-        // top, lane l owns the bins 255 - 4 l .. 252 - 4 l of each.
-        if (threadIdx.x < kWave) {
+        // One wavefront finds the bin, as in KeyRange::plan: four blocks of 256 bins from the top, lane l owns the bins
+        // 255 - 4 l .. 252 - 4 l of each.
+        if (tid < kWave) {
             uint4 h[4];
             uint32_t tot[4], incl[4];
 #pragma unroll
@@ -362,15 +430,15 @@ __device__ __forceinline__ void range_select(KeyFn key_of, int nslots, uint32_t 
                 uint32_t kv[U];
                 bool ok[U];
 #pragma unroll
-                for (int u = 0; u < U; ++u) kv[u] = key_of(min(i0 + u * THREADS + (int)threadIdx.x, nslots - 1), ok[u]);
+                for (int u = 0; u < U; ++u) kv[u] = key_of(min(i0 + u * THREADS + tid, nslots - 1), ok[u]);
 #pragma unroll
                 for (int u = 0; u < U; ++u)
-                    if (ok[u] && i0 + u * THREADS + (int)threadIdx.x < nslots && bin_of(kv[u]) == bin) list[4 + atomicAdd(list, 1u)] = kv[u];
+                    if (ok[u] && i0 + u * THREADS + tid < nslots && bin_of(kv[u]) == bin) list[4 + atomicAdd(list, 1u)] = kv[u];
             }
             __syncthreads();
             // One entry per lane of one wavefront; rank = entries before it under (key descending, place in the list), which depends on
             // the list's order only among equal keys; an unused place holds 0 and is after every entry it is compared with.
-            if (threadIdx.x < kWave) {
+            if (tid < kWave) {
                 const bool have = (uint32_t)lane < inbin;
                 const uint32_t key = list[4 + lane];
                 uint32_t rank = 0;
@@ -392,36 +460,59 @@ __device__ __forceinline__ void range_select(KeyFn key_of, int nslots, uint32_t 
             *want_out = list[2];
             return;
         }
+        if (!LOOP && inbin <= (uint32_t)kRangeList && nslots >= kRangeListRows) {   // the same with one entry per lane of up to four wavefronts
+            uint32_t* list = range + kRangeBins;
+            for (int i = tid; i < nslots; i += THREADS) {
+                bool ok;
+                const uint32_t key = key_of(i, ok);
+                if (ok && bin_of(key) == bin) list[4 + atomicAdd(list, 1u)] = key;
+            }
+            __syncthreads();
+            if ((uint32_t)tid < inbin) {
+                const uint32_t key = list[4 + tid];
+                uint32_t above = 0, ties = 0;   // entries with a larger key; equal ones at earlier places
+#pragma unroll 4
+                for (uint32_t q = 0; q < inbin; q += 4) {
+                    const uint4 e = *reinterpret_cast<const uint4*>(list + 4 + q);
+                    above += (e.x > key) + (e.y > key) + (e.z > key) + (e.w > key);
+                    ties += (e.x == key && q < (uint32_t)tid) + (e.y == key && q + 1 < (uint32_t)tid) + (e.z == key && q + 2 < (uint32_t)tid) +
+                            (e.w == key && q + 3 < (uint32_t)tid);
+                }
+                if (above + ties == want - 1) {   // exactly one thread
+                    list[1] = key;
+                    list[2] = want - above;
+                }
+            }
+            __syncthreads();
+            *T_out = list[1];
+            *want_out = list[2];
+            return;
+        }
     }
-    // digit by digit among the keys of the bin (all keys, where there are no bins), from the highest bit in which any two differ
-    const bool all = !divides;
+    // digit by digit among the keys of the bin, from the highest bit in which any two differ
     __syncthreads();   // part has been read
     auto left = [&](int i, bool& valid) {
         const uint32_t key = key_of(i, valid);
-        valid = valid && (all || bin_of(key) == bin);
+        valid = valid && ((LOOP && how == kRangeDigits) || bin_of(key) == bin);
         return key;
     };
-    uint32_t mn = kmin, mx = kmax;
-    if (!all) {
-        mn = 0xffffffffu;
-        mx = 0;
-        for (int i = threadIdx.x; i < nslots; i += THREADS) {
-            bool valid;
-            const uint32_t key = left(i, valid);
-            if (valid) {
-                mn = min(mn, key);
-                mx = max(mx, key);
-            }
-        }
-        wave_min_max(mn, mx);
-        if (lane == 0) {
-            part[2 * (threadIdx.x / kWave)] = mn;
-            part[2 * (threadIdx.x / kWave) + 1] = mx;
+    uint32_t mn = 0xffffffffu, mx = 0;
+    for (int i = tid; i < nslots; i += THREADS) {
+        bool valid;
+        const uint32_t key = left(i, valid);
+        if (valid) {
+            mn = min(mn, key);
+            mx = max(mx, key);
         }
     }
-    for (int i = threadIdx.x; i < 4 * 256; i += THREADS) hist4[i] = 0;
+    wave_min_max(mn, mx);
+    if (lane == 0) {
+        part[2 * (tid / kWave)] = mn;
+        part[2 * (tid / kWave) + 1] = mx;
+    }
+    for (int i = tid; i < 4 * 256; i += THREADS) hist4[i] = 0;
     __syncthreads();
-    if (!all) {
+    {
         for (int w = 0; w < THREADS / kWave; ++w) {
             mn = min(mn, part[2 * w]);
             mx = max(mx, part[2 * w + 1]);

@@ -29,6 +29,10 @@ def values(kind, n, seed):
         s = -np.exp(3 * z)
     elif kind == "outlier":           # all but two keys share one bin
         s[n // 3], s[n // 2] = 1e30, -1e30
+    elif kind == "heavy tails":       # a range far wider than what most keys span
+        s = (z / (np.abs(np.roll(z, 1)) + np.float32(1e-4))).astype(np.float32)
+    elif kind == "one end":           # one wavefront's keys far from the others'
+        s[: n // 16] += np.float32(1e6)
     elif kind == "huge":              # the difference of the extremes overflows
         s[n // 3], s[n // 2] = 3.4e38, -3.4e38
     elif kind == "infinite":
@@ -48,11 +52,11 @@ def values(kind, n, seed):
     return s
 
 
-KINDS = ["normal", "positive", "negative", "outlier", "huge", "infinite", "nan", "denormal", "bits", "zeros", "two", "equal"]
+KINDS = ["normal", "positive", "negative", "outlier", "heavy tails", "one end", "huge", "infinite", "nan", "denormal", "bits", "zeros", "two", "equal"]
 
 
 @pytest.mark.parametrize("kind", KINDS)
-@pytest.mark.parametrize("n,budget,recent", [(2176, 2048, 128), (1025, 64, 0), (130, 100, 16), (5000, 1, 0), (9000, 2500, 100)])
+@pytest.mark.parametrize("n,budget,recent", [(2176, 2048, 128), (1025, 64, 0), (130, 100, 16), (273, 200, 16), (272, 200, 16), (5000, 1, 0), (9000, 2500, 100)])
 def test_selection_over_value_ranges(gpu, ora, kind, n, budget, recent):
     import paper_2602_03203_amd as fk
     print(f"select {kind} n={n} budget={budget} recent={recent}", flush=True)
@@ -64,10 +68,30 @@ def test_selection_over_value_ranges(gpu, ora, kind, n, budget, recent):
     keep = torch.full((1, 2, budget), -1, dtype=torch.int32, device="cuda")
     fk.fk_select_keep(desc, gpu.to_dev(sc), pos, ln, n, budget, recent, keep)
     gpu.assert_keep_equal(keep.cpu().numpy(), ora.select_keep(sc, c.pos, c.len, budget, recent, "sort"), c.len, budget, kind)
-    if kind not in ("nan", "infinite", "huge"):   # score - noise is a number
+    if kind != "nan":   # score - noise is a number or an infinity
         fk.fk_select_keep_sampled(desc, gpu.to_dev(sc), gpu.to_dev(noise), pos, ln, n, budget, recent, 2 * (n - budget), keep)
         ref = ora.select_keep_sampled(sc, noise, c.pos, c.len, budget, recent, 2 * (n - budget))
         gpu.assert_keep_equal(keep.cpu().numpy(), ref, c.len, budget, kind + " sampled")
+
+
+@pytest.mark.parametrize("n", [5000, 8192 + 16, 20000])
+@pytest.mark.parametrize("m,step", [(40, 1), (64, 3), (150, 0), (150, 2), (230, 1), (256, 1), (300, 1)])
+def test_cut_in_a_full_bin(gpu, ora, n, m, step):
+    """m keys a few bits apart (0: equal) around the cut, beside some of the others in its bin: below, at and beyond what is ranked as a list."""
+    import paper_2602_03203_amd as fk
+    print(f"select full bin n={n} m={m} step={step}", flush=True)
+    recent = 16
+    sc = np.stack([values("normal", n, 80 + h) for h in range(2)])
+    for h in range(2):
+        where = (np.arange(m) * 19 + 5 * h + 1) % (n - recent)
+        sc[h, where] = (np.float32(0.25).view(np.uint32) + np.uint32(step) * (np.arange(m, dtype=np.uint32) * 7 % m)).view(np.float32)
+    budget = int((sc[0, : n - recent] > 0.25 + 1e-4).sum()) + m // 2 + recent
+    c = random_cache(ora, 7, "bf16", 1, 2, n, 64, lens=[n])
+    desc = fk.CacheDesc(1, 2, 2, 64, n, "bf16")
+    pos, ln = gpu.to_dev(c.pos), torch.full((1, 2), n, dtype=torch.int32, device="cuda")
+    keep = torch.full((1, 2, budget), -1, dtype=torch.int32, device="cuda")
+    fk.fk_select_keep(desc, gpu.to_dev(sc[None]), pos, ln, n, budget, recent, keep)
+    gpu.assert_keep_equal(keep.cpu().numpy(), ora.select_keep(sc[None], c.pos, c.len, budget, recent, "sort"), c.len, budget, "full bin")
 
 
 @pytest.mark.parametrize("kind", ["normal", "positive", "outlier", "bits", "infinite"])
