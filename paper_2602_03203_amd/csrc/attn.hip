@@ -8,8 +8,8 @@
 // the split and keeps an online softmax (running maximum m, running sum l, un-normalised
 // accumulator acc); the wavefronts are merged through LDS and the splits of a row through a
 // small record in the workspace, the last workgroup of the row to arrive doing the final
-// log-sum-exp merge and the store of `out` (no second launch).  With at least 128 rows a row is
-// not split at all and the launch has no cross-workgroup traffic.
+// log-sum-exp merge and the store of `out` (no second launch).  Short rows, and rows of which there are
+// enough to fill the chip (attn_plan says where), are not split and the launch has no cross-workgroup traffic.
 //
 // bf16, D = 128.  K and V tiles of 32 keys are fetched with fully coalesced 128-bit loads (a row is
 // 16 lanes x 16 bytes, four rows per wavefront instruction).  The K tile is staged in LDS (padded
@@ -117,14 +117,14 @@ template <typename T, int D, int G> struct AttnCfg {
     //   PVM:   m [NG][G] | l [NG][G] | w [NG][G] | M [8] | P tiles [WAVES][PROWS][PS] bf16 | D = 128:
     //          K tiles [WAVES][KT][KRS] bytes (a wavefront's partial accumulator [G][D] reuses its own K tile once its loop is
     //          over), 73 KB at G = 4: two workgroups fit the 160 KB of a CU; D = 64: the partial accumulators, term by term
-    //   other: acc [NG][G][D] | m [NG][G] | l [NG][G] | w [NG][G] | M [8] | p [WAVES][KT][GP] | corr [WAVES][GP]
+    //   fp32:  acc [NG][G][D] | m [NG][G] | l [NG][G] | w [NG][G] | M [8]
     static constexpr int ACC_STRIDE = PVM && D == 128 ? KT * KRS / 4 : (SPLIT_P ? 3 : 1) * G * D;  // floats between the partial accumulators
     static constexpr size_t HEAD_FLOATS = 3 * (size_t)NG * G + 8;   // m, l, w, M
     static constexpr int PROWS = SPLIT_P ? 3 * GP : GP;               // PVM: rows of a P tile, term by term
     static constexpr size_t PB_BYTES = (size_t)WAVES * PROWS * PS * 2;  // PVM: the bf16 P tiles
     static constexpr size_t LDS_BYTES =
         PVM ? sizeof(float) * (HEAD_FLOATS + (size_t)WAVES * ACC_STRIDE) + PB_BYTES
-            : sizeof(float) * ((size_t)NG * G * D + HEAD_FLOATS + (size_t)WAVES * KT * GP + (size_t)WAVES * GP + 4);
+            : sizeof(float) * ((size_t)NG * G * D + HEAD_FLOATS);
     // attention-feature variant: lx [NG][G] exact normaliser partials | invL [8], behind everything else
     static constexpr size_t LDS_BYTES_FEAT = LDS_BYTES + sizeof(float) * ((size_t)NG * G + 8);
     static constexpr size_t LX_OFFSET = LDS_BYTES / sizeof(float);  // float index of lx in the dynamic LDS
@@ -263,12 +263,12 @@ __global__ __launch_bounds__((AttnCfg<T, D, G>::THREADS)) void attn_kernel(const
     const int b = row / P.n_kv, hkv = row % P.n_kv;
     const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
 
-    // PVM: head | P tiles | K tiles, the partial accumulators live in the K tiles; other paths: acc | head | p | corr
+    // PVM: head | P tiles | K tiles, the partial accumulators live in the K tiles; fp32: acc | head
     float* s_m = C::PVM ? smem : smem + (size_t)NG * G * D;  // [NG][G]
     float* s_l = s_m + NG * G;                 // [NG][G]
     float* s_w = s_l + NG * G;                 // [NG][G] merge weights 2^(m_g - M)
     float* s_M = s_w + NG * G;                 // [8] merged maximum per head
-    float* s_p = s_M + 8;                      // other paths: [WAVES][KT][GP]; PVM: the bf16 P tiles
+    float* s_p = s_M + 8;                      // PVM: the bf16 P tiles
     unsigned char* s_kt = reinterpret_cast<unsigned char*>(s_p) + C::PB_BYTES;  // PVM: K tiles [WAVES][KT][KRS]
     float* s_acc = C::PVM ? reinterpret_cast<float*>(s_kt) : smem;  // partial g2 at s_acc + g2 * ACC_STRIDE, [G][D]
     __shared__ int s_last;
@@ -386,7 +386,7 @@ __global__ __launch_bounds__((AttnCfg<T, D, G>::THREADS)) void attn_kernel(const
         } else if (tid == 2 * CH) {
             P.pos[(size_t)row * P.cap + n_old] = P.pos_new[b];
         }
-        if constexpr (!C::PVM) __syncthreads();  // the other paths read the row back from the cache
+        if constexpr (!C::PVM) __syncthreads();  // the fp32 path reads the row back from the cache
     }
     const int new_slot = owns_new ? n_old : -1;
     const uint4* Krow = reinterpret_cast<const uint4*>(Kr);

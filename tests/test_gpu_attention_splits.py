@@ -23,6 +23,8 @@ def gpu():
 CASES = [("bf16", 64, 2, g, n) for g, n in ((1, 30), (2, 31), (3, 32), (4, 511), (5, 512), (6, 513), (7, 767), (8, 1500))]
 CASES += [("bf16", 64, 1, 4, 8192), ("bf16", 64, 1, 4, 9000), ("bf16", 128, 1, 4, 8300), ("bf16", 128, 1, 8, 512), ("bf16", 128, 2, 5, 513),
           ("bf16", 64, 40, 2, 600), ("f32", 64, 2, 4, 63), ("f32", 64, 2, 7, 64), ("f32", 128, 1, 4, 300), ("f32", 64, 1, 3, 1024), ("f32", 64, 1, 4, 1060)]
+# 32 rows, head_dim 128: cold, one split up to 96 keys, two from 97, eight at most
+CASES += [("bf16", 128, 16, g, n) for g, n in ((4, 94), (4, 96), (7, 191), (2, 564), (1, 1500))]
 
 
 @pytest.mark.parametrize("dtype,D,H,g,n", CASES)
@@ -46,11 +48,11 @@ def test_step_at_split_and_tile_edges(gpu, ora, dtype, D, H, g, n, cold):
     assert np.array_equal(host.K, c.K) and np.array_equal(host.V, c.V) and np.array_equal(host.pos, c.pos) and np.array_equal(host.len, c.len)
 
 
-@pytest.mark.parametrize("D,B,cap,small", [(128, 50, 5400, 3000), (64, 64, 8300, 4000), (64, 64, 8300, 8299)])
+@pytest.mark.parametrize("D,B,cap,small", [(128, 50, 5400, 3000), (64, 64, 8300, 4000), (64, 64, 8300, 8100)])
 def test_rows_taken_by_length_give_the_same_bits(gpu, D, B, cap, small):
     """Many rows and 1 GB of keys and values by the length hint: workgroups take the rows from the longest to the shortest.  A
-    smaller hint keeps the plain order and must change nothing: outputs, appended rows, lengths (full, empty, equal ones).  (The
-    last case: the ordered launch twice.)"""
+    smaller hint keeps the plain order and must change nothing: outputs, appended rows, lengths (full, empty, equal ones).  Some
+    rows are held against plain sums."""
     import paper_2602_03203_amd as fk
     H, g = 8, 2
     desc = fk.CacheDesc(B, H * g, H, D, cap, "bf16")
@@ -73,6 +75,13 @@ def test_rows_taken_by_length_give_the_same_bits(gpu, D, B, cap, small):
     assert torch.equal(res[0][2], torch.clamp(lens + 2, max=cap))
     for a, b in zip(*res):
         assert torch.equal(a.view(torch.uint8), b.view(torch.uint8))
+    (_, only, ln, _, K, V), order = res[0], lens.flatten().argsort().tolist()
+    for r in [order[i] for i in (1, 2, 3, B * H // 4, B * H // 2, B * H - 7, B * H - 6, B * H - 1)] + [17, 18]:
+        b, h = divmod(r, H)
+        n = int(ln[b, h])
+        z = 0.1 * (q[0, b, h * g:(h + 1) * g].double() @ K[b, h, :n].double().T)
+        ref = torch.softmax(z, 1) @ V[b, h, :n].double()
+        gpu.assert_attn_close(gpu.out_to_f64(only)[b, h * g:(h + 1) * g], ref.cpu().numpy(), "bf16", f"row {r} of {n} pairs")
 
 
 @pytest.mark.parametrize("g", [1, 4, 5, 8])

@@ -172,7 +172,7 @@ def test_ragged_tail_lengths(gpu, ora):
 
 
 def test_qwen3_4b_layer_shape_sampled_rows(gpu, ora):
-    """configs[1] shapes (batch 16, 32/8 heads, D 128, bf16, B 2048, L 128, H 256) with a long prompt so that
+    """The Qwen3-4B layer shape (batch 16, 32/8 heads, D 128, bf16, B 2048, L 128, H 256) with a long prompt so that
     two events fall inside 300 steps; the oracle follows 3 sampled rows."""
     w = si.config(1).scaled(prompt=1920)
     assert lockstep_feat(gpu, ora, w, 300, sample_rows=[(0, 0), (7, 3), (15, 7)], check_every=16) >= 2
@@ -186,14 +186,14 @@ def test_other_storage_types_and_head_sizes(gpu, ora, g, dtype, D):
 
 
 def test_tiny_workload_full_run_with_features(gpu, ora):
-    """configs[0] end to end (fp32, head_dim 64, 512 steps, 16 event clocks) with the feature path."""
+    """The tiny workload end to end (fp32, head_dim 64, 512 steps, 16 event clocks) with the feature path."""
     w = si.config(0)
     assert lockstep_feat(gpu, ora, w, w.steps) == 16
 
 
 def test_window_call_equals_the_single_steps(gpu):
-    """fk_decode_window_feat enqueues the same launches as the per-step calls: every buffer ends bit-identical (the
-    per-step path is the one the other tests of this file hold against the oracle)."""
+    """fk_decode_window_feat computes the steps of a window at once: every buffer ends bit-identical to the per-step calls
+    (the path that the other tests of this file hold against the oracle)."""
     import paper_2602_03203_amd as fk
     Bt, Hq, Hkv, D, cap, L, n0, steps, c0 = 3, 8, 2, 128, 300, 32, 200, 20, 7
     d = fk.CacheDesc(Bt, Hq, Hkv, D, cap, "bf16")

@@ -82,26 +82,33 @@ def test_decode_attn_closed_forms_on_device(gpu, ora):
     np.testing.assert_allclose(got2[0, 2], c2.V[0, 0, 217].astype(np.float64), atol=1e-5)
 
 
-def test_split_merge_many_splits_back_to_back(gpu, ora):
-    """One row cut into as many splits as the plan ever uses (128 workgroups whose records are merged by the last one to
-    arrive), 64 launches in a row on one workspace with no host synchronisation in between: every launch must find the
-    arrival counter at zero and every merge must see all records of its own launch.  Cold-cache variant too."""
+@pytest.mark.parametrize("n,splits,splits_cold", [(19777, 37, 37), (131072, 128, 256)])
+def test_split_merge_many_splits_back_to_back(gpu, ora, n, splits, splits_cold):
+    """One row cut into many splits, at 131072 pairs as many as the plan ever uses (128 workgroups, cold 256, whose records are
+    merged by the last one to arrive), 64 launches in a row on one workspace with no host synchronisation in between: every
+    launch must find the arrival counter at zero and every merge must see all records of its own launch.  The records say how
+    many splits there were."""
     import paper_2602_03203_amd as fk
-    D, cap, n, g, nq = 128, 20000, 19777, 4, 64
+    D, cap, g, nq, different = 128, n + 223, 4, 64, 64 if n < 100000 else 8
     c = random_cache(ora, 4711, "bf16", 1, 1, cap, D, lens=[n], scale=0.5)
+    qs = [random_q(9000 + i, "bf16", 1, g, D, scale=1.0 + 0.05 * i) for i in range(different)]
+    refs = [ora.decode_attn(c, q, 0.2) for q in qs]
+    dq = gpu.to_dev(np.stack(qs))
+    dev = gpu.DevCache(c, g)
     for cold in (False, True):
+        print(f"split merge n={n} cold={cold}", flush=True)
         desc = fk.CacheDesc(1, g, 1, D, cap, "bf16", cold=cold)
-        dev = gpu.DevCache(c, g)
         ws = fk.new_attn_workspace(desc)
-        qs = [random_q(9000 + i, "bf16", 1, g, D, scale=1.0 + 0.05 * i) for i in range(nq)]
-        dq = gpu.to_dev(np.stack(qs))
+        records = ws[256:].view(torch.int32)[:(ws.numel() - 256) // (g * (D + 2) * 4) * g * (D + 2)].view(-1, g * (D + 2))
+        records.fill_(-1)
         outs = torch.empty((nq, 1, g, D), dtype=torch.bfloat16, device="cuda")
         for i in range(nq):
-            fk.fk_decode_attn(desc, dq[i], dev.K, dev.V, dev.len, n, 0.2, outs[i], ws)
+            fk.fk_decode_attn(desc, dq[i % different], dev.K, dev.V, dev.len, n, 0.2, outs[i], ws)
         torch.cuda.synchronize()
         assert int(ws[:4].view(torch.int32)[0]) == 0          # the row's arrival counter is back at zero
+        assert int((records != -1).any(1).sum()) == (splits_cold if cold else splits)
         for i in range(nq):
-            gpu.assert_attn_close(gpu.out_to_f64(outs[i]), ora.decode_attn(c, qs[i], 0.2), "bf16", f"launch {i} (cold={cold})")
+            gpu.assert_attn_close(gpu.out_to_f64(outs[i]), refs[i % different], "bf16", f"launch {i} (cold={cold})")
 
 
 def test_rows_of_a_sequence_may_hold_different_counts(gpu, ora):

@@ -116,7 +116,7 @@ def lockstep(gpu, ora, w, n_steps, sample_rows=None, scale=None, check_every=1, 
 
 @pytest.mark.parametrize("fused", [True, False])
 def test_tiny_workload_full_run(gpu, ora, fused):
-    """configs[0] end to end: 512 steps, 16 event clocks (14 with rows over budget), every row."""
+    """The tiny fp32 workload end to end: 512 steps, 16 event clocks (14 with rows over budget), every row."""
     w = si.config(0)
     assert lockstep(gpu, ora, w, w.steps, fused=fused) == 16
 
@@ -127,7 +127,7 @@ def test_tiny_workload_peaked_softmax(gpu, ora):
 
 
 def test_qwen3_4b_layer_shape_sampled_rows(gpu, ora):
-    """configs[1] shapes and launch configuration (batch 16, 32/8 heads, D 128, bf16, B 2048, L 128,
+    """The Qwen3-4B layer shape and launch configuration (batch 16, 32/8 heads, D 128, bf16, B 2048, L 128,
     capacity 2176); the prompt is lengthened so that two events fall inside 400 steps.  The device
     runs all 128 rows; the oracle follows 4 sampled rows."""
     w = si.config(1).scaled(prompt=1920)
@@ -138,11 +138,11 @@ def test_qwen3_4b_layer_shape_sampled_rows(gpu, ora):
 
 
 def test_qwen3_4b_layer_all_rows_around_an_event(gpu, ora):
-    """configs[1] at the steady state bench.py times (batch 16, 32/8 heads, D 128, bf16, B 2048, L 128, rows at
-    B + L - 2 pairs): EVERY one of the 128 rows is compared with the oracle for the two decode steps before an
-    eviction event (enqueued by one fk_decode_window call, as bench.py does), the event itself (scores; keep-sets on
-    the oracle's scores and on the device's own; K, V, positions and lengths after the compaction, bit for bit)
-    and the two steps after it."""
+    """The Qwen3-4B layer shape at the steady state bench.py times (batch 16, 32/8 heads, D 128, bf16, B 2048, L 128, rows
+    at B + L - 2 pairs): EVERY one of the 128 rows is compared with the oracle for the two decode steps before an eviction
+    event (two fk_decode_step calls, as bench.py does; the same steps as one fk_decode_window call, which computes them at
+    once, on a copy), the event itself (scores; keep-sets on the oracle's scores and on the device's own; K, V, positions
+    and lengths after the compaction, bit for bit) and the two steps after it."""
     import paper_2602_03203_amd as fk
     w = si.config(1)
     B, L, g, Bt, Hkv = w.budget, w.interval, w.group, w.batch, w.n_kv_heads
@@ -155,14 +155,26 @@ def test_qwen3_4b_layer_all_rows_around_an_event(gpu, ora):
     dW = [gpu.to_dev(x) for x in W]
     q, k, v, p = bulk_step_inputs(w, 0, 0, 4, lens0)
     dq, dk, dv, dp = (gpu.to_dev(x) for x in (q, k, v, p))
-    outs = torch.empty((4, Bt, w.n_q_heads, w.head_dim), dtype=torch.bfloat16, device="cuda")
+    outs, at_once = (torch.empty((4, Bt, w.n_q_heads, w.head_dim), dtype=torch.bfloat16, device="cuda") for _ in range(2))
     for scale in (w.softmax_scale, 128.0 ** 0.5):   # near-uniform and unit-variance logits, each on a fresh copy
         cc = c.copy()
         d2 = gpu.DevCache(cc, w.n_q_heads)
-        fk.fk_decode_window(d2.desc, dq[:2], d2.K, d2.V, d2.pos, d2.len, dk[:2], dv[:2], dp[:2], 2, start + 1, scale, outs[:2], d2.ws)
-        for t in range(2):
-            ora.append(cc, k[t], v[t], p[t])
-            gpu.assert_attn_close(gpu.out_to_f64(outs[t]), ora.decode_attn(cc, q[t], scale), "bf16", f"scale {scale:.3f} step {t}")
+
+        def steps(first, max_len):
+            """Two steps one by one on d2, and as a window on a copy of it."""
+            d3 = [t.clone() for t in (d2.K, d2.V, d2.pos, d2.len)]
+            pair = slice(first, first + 2)
+            for t in range(first, first + 2):
+                fk.fk_decode_step(d2.desc, dq[t], d2.K, d2.V, d2.pos, d2.len, dk[t], dv[t], dp[t], max_len + t - first, scale, outs[t], d2.ws)
+            fk.fk_decode_window(d2.desc, dq[pair], *d3, dk[pair], dv[pair], dp[pair], 2, max_len, scale, at_once[pair], d2.ws)
+            assert torch.equal(outs[pair].view(torch.int16), at_once[pair].view(torch.int16))
+            for a, b in zip(d3, (d2.K, d2.V, d2.pos, d2.len)):
+                assert torch.equal(a, b)
+            for t in range(first, first + 2):
+                ora.append(cc, k[t], v[t], p[t])
+                gpu.assert_attn_close(gpu.out_to_f64(outs[t]), ora.decode_attn(cc, q[t], scale), "bf16", f"scale {scale:.3f} step {t}")
+
+        steps(0, start + 1)
         assert int(d2.len.min()) == B + L == int(d2.len.max())
         print("all rows: event", flush=True)
         fk.fk_score_kv(d2.desc, d2.K, d2.V, d2.len, B + L, *dW, d2.scores, skip_len=B)
@@ -183,23 +195,20 @@ def test_qwen3_4b_layer_all_rows_around_an_event(gpu, ora):
         assert np.array_equal(h.len, cc.len) and (h.len == B).all()
         assert np.array_equal(h.pos[:, :, :B], cc.pos[:, :, :B])
         assert np.array_equal(h.K[:, :, :B], cc.K[:, :, :B]) and np.array_equal(h.V[:, :, :B], cc.V[:, :, :B])
-        fk.fk_decode_window(d2.desc, dq[2:], d2.K, d2.V, d2.pos, d2.len, dk[2:], dv[2:], dp[2:], 2, B + 1, scale, outs[2:], d2.ws)
-        for t in range(2, 4):
-            ora.append(cc, k[t], v[t], p[t])
-            gpu.assert_attn_close(gpu.out_to_f64(outs[t]), ora.decode_attn(cc, q[t], scale), "bf16", f"scale {scale:.3f} step {t}")
+        steps(2, B + 1)
         assert int(d2.len.min()) == B + 2 == int(d2.len.max())
     del dev
 
 
 def test_gqa7_mixture_sampled_rows(gpu, ora):
-    """configs[3] shapes (28/4 heads, D 128, B 4096, L 64) with duplicate-heavy keys: exact score ties."""
+    """The GQA-7 shapes (28/4 heads, D 128, B 4096, L 64) with duplicate-heavy keys: exact score ties."""
     w = si.config(3).scaled(layers=1, batch=4, prompt=4096 - 64)
     rows = [(0, 0), (3, 2)]
     assert lockstep(gpu, ora, w, 200, sample_rows=rows, scale=128.0 ** 0.5, check_every=16) >= 2
 
 
 def test_long_budget_shape_sampled_rows(gpu, ora):
-    """configs[2] row shape (32/8 heads, D 128, B 16384, L 128, capacity 16512), two sequences of one
+    """The long-budget row shape (32/8 heads, D 128, B 16384, L 128, capacity 16512), two sequences of one
     layer: rows are split across workgroups (few rows) and compaction / selection run several tiles."""
     w = si.config(2).scaled(layers=1, batch=2, prompt=16384 - 128)
     rows = [(0, 1), (1, 6)]
@@ -207,7 +216,7 @@ def test_long_budget_shape_sampled_rows(gpu, ora):
 
 
 def test_ragged_batch_shape_sampled_rows(gpu, ora):
-    """configs[4] shape (ragged lengths up to 32768, B 8192, L 128, capacity 32896), four sequences: the
+    """The ragged-batch shape ( lengths up to 32768, B 8192, L 128, capacity 32896), four sequences: the
     first event prunes rows far over budget in one go, rows under budget are left alone."""
     w = si.config(4).scaled(batch=4)
     lens0 = si.initial_lengths(w)
@@ -219,7 +228,7 @@ def test_ragged_batch_shape_sampled_rows(gpu, ora):
 
 
 def test_stack_layer_shapes_at_full_batch_sampled_rows(gpu, ora):
-    """One layer of configs[2] (batch 8, B 16384: 64 rows, two splits per row) and of configs[3] (batch 16,
+    """One layer of the long-budget shape (batch 8, B 16384: 64 rows, two splits per row) and of the GQA-7 shape (batch 16,
     GQA 7, B 4096: 64 rows) in the launch configuration bench.py uses, caches just under the first event;
     the oracle follows two rows of each, the other rows hold copies of their data."""
     w = si.config(2).scaled(layers=1, prompt=16384 - 64)
@@ -229,7 +238,7 @@ def test_stack_layer_shapes_at_full_batch_sampled_rows(gpu, ora):
 
 
 def test_ragged_batch_at_full_size_sampled_rows(gpu, ora):
-    """configs[4] as bench.py runs it: 64 sequences (512 rows, 8.6 GB of cache), lengths 1024 .. 32768, B 8192;
+    """The ragged batch as bench.py runs it: 64 sequences (512 rows, 8.6 GB of cache), lengths 1024 .. 32768, B 8192;
     the oracle follows one row far over budget, one under it and the longest one."""
     w = si.config(4)
     lens = si.initial_lengths(w)
@@ -274,7 +283,7 @@ def test_one_shot_prefill_compression(gpu, ora):
 
 
 def test_sampled_policy_tiny_workload_full_run(gpu, ora):
-    """configs[0] end to end under the Top-K multinomial eviction policy (Section 3.1 Eq. 2): every event
+    """The tiny fp32 workload end to end under the Top-K multinomial eviction policy (Section 3.1 Eq. 2): every event
     draws the evicted pairs among the 2L lowest-scored ones; keep-sets and caches stay bit exact."""
     w = si.config(0)
     assert lockstep(gpu, ora, w, w.steps, sampled=True) == 16
