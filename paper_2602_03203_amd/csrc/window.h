@@ -47,9 +47,14 @@ __host__ __device__ inline AttnPlan attn_plan(const AttnShape& a, int max_len) {
         if (a.head_dim == 64 && max_len < 4096 && want > (255 + rows) / rows) want = (255 + rows) / rows;
         most = max_len <= 512 ? 1 : (max_len + 255) / 256;
         if (most > 16) most = max_len / 512 > 16 ? max_len / 512 : 16;
-        // a cold cache's latency takes more workgroups to cover, as long as the merge fetches the records in one go (32 rows of
-        // 565 pairs 8.7 -> 8.4 us, of 300 8.4 -> 8.0; 8 rows of 2000, up to 32 splits, stay at 256 keys: 15.4 against 18.2)
-        if (a.head_dim == 128 && a.cold && want <= 8) most = (max_len + 95) / 96;
+        // A cold cache's latency takes more workgroups to cover, as long as the merge fetches the records in one go, eight at a time: 8 rows
+        // of 500 pairs 8.1 -> 6.7 us, of 1000 7.8 -> 7.1, of 1500 8.0 -> 7.7; 32 rows of 565 8.7 -> 8.4; beyond eight 8 rows of 2000 take
+        // 18.2 (15.4).  Not below one round of the wavefronts: 8 rows of 256 6.5 -> 5.6 us unsplit, 64 rows 7.6 -> 6.2.
+        if (a.head_dim == 128 && a.cold && max_len > 256) {
+            const int fine = (max_len + 95) / 96;
+            if (want <= 8) most = fine;
+            else if (most < 8) most = fine < 8 ? fine : 8;
+        }
     } else {
         most = max_len <= 1024 ? 8 : (max_len + 127) / 128;   // (the merge fetches eight records at a time)
         if (most > (max_len + tile - 1) / tile) most = (max_len + tile - 1) / tile;

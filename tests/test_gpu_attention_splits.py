@@ -23,8 +23,8 @@ def gpu():
 CASES = [("bf16", 64, 2, g, n) for g, n in ((1, 30), (2, 31), (3, 32), (4, 511), (5, 512), (6, 513), (7, 767), (8, 1500))]
 CASES += [("bf16", 64, 1, 4, 8192), ("bf16", 64, 1, 4, 9000), ("bf16", 128, 1, 4, 8300), ("bf16", 128, 1, 8, 512), ("bf16", 128, 2, 5, 513),
           ("bf16", 64, 40, 2, 600), ("f32", 64, 2, 4, 63), ("f32", 64, 2, 7, 64), ("f32", 128, 1, 4, 300), ("f32", 64, 1, 3, 1024), ("f32", 64, 1, 4, 1060)]
-# 32 rows, head_dim 128: cold, one split up to 96 keys, two from 97, eight at most
-CASES += [("bf16", 128, 16, g, n) for g, n in ((4, 94), (4, 96), (7, 191), (2, 564), (1, 1500))]
+# head_dim 128, cold: one split up to 256 keys, then splits of 96, at most eight
+CASES += [("bf16", 128, 16, g, n) for g, n in ((4, 254), (4, 256), (7, 287), (2, 564), (1, 1500))] + [("bf16", 128, 2, 4, 256), ("bf16", 128, 1, 8, 766)]
 
 
 @pytest.mark.parametrize("dtype,D,H,g,n", CASES)
