@@ -406,6 +406,7 @@ __global__ __launch_bounds__((AttnCfg<T, D, G>::THREADS)) void attn_kernel(const
         const int n16 = lane & 15, quad = lane >> 4;
         constexpr int KS = D / 32;          // k-steps of q.K^T
         constexpr int ET = D / 16;          // channel tiles of P.V
+        constexpr int HR = G < 4 ? G : 4;   // of a lane's four result rows, those that can belong to a head
         uint16_t* my_pb = reinterpret_cast<uint16_t*>(s_p) + (size_t)wave * C::PROWS * PS;   // [PROWS][PS] bf16
         unsigned char* my_k = s_kt + (size_t)wave * KT * KRS;   // D = 128
         B128 qa[KS];
@@ -503,7 +504,7 @@ __global__ __launch_bounds__((AttnCfg<T, D, G>::THREADS)) void attn_kernel(const
                 }
             }
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
+            for (int i = 0; i < HR; ++i) {
                 const float s0 = (base + n16 < end) ? c[0][i] * P.scale_log2e : kNegBig;
                 const float s1 = (base + 16 + n16 < end) ? c[1][i] * P.scale_log2e : kNegBig;
                 const float mn = fmaxf(m_run[i], row16_max(fmaxf(s0, s1)));
@@ -535,7 +536,7 @@ __global__ __launch_bounds__((AttnCfg<T, D, G>::THREADS)) void attn_kernel(const
             }
             if (quad * 4 < C::PROWS) {
 #pragma unroll
-                for (int i = 0; i < 4; ++i) {
+                for (int i = 0; i < HR; ++i) {
                     my_pb[(quad * 4 + i) * PS + n16] = (uint16_t)pb[0][i];
                     my_pb[(quad * 4 + i) * PS + 16 + n16] = (uint16_t)pb[1][i];
                     if constexpr (THIRD) {
@@ -550,7 +551,7 @@ __global__ __launch_bounds__((AttnCfg<T, D, G>::THREADS)) void attn_kernel(const
 #pragma unroll
                 for (int e = 0; e < ET; ++e)
 #pragma unroll
-                    for (int i = 0; i < 4; ++i) {
+                    for (int i = 0; i < HR; ++i) {
                         o[e][i] *= corr[i];
                         if constexpr (THIRD) o3[e][i] *= corr[i];
                     }
@@ -574,7 +575,7 @@ __global__ __launch_bounds__((AttnCfg<T, D, G>::THREADS)) void attn_kernel(const
             // A operand of P.V: P[row n16][k-slots quad*8 .. +8]; k-slot u of group quad is key base + quad*8 + u
             B128 pa, pr;
             pa.u = pr.u = make_uint4(0, 0, 0, 0);
-            if (n16 < C::PROWS) pa.u = *reinterpret_cast<const uint4*>(my_pb + n16 * PS + quad * 8);
+            if (n16 < C::PROWS && n16 % 4 < HR) pa.u = *reinterpret_cast<const uint4*>(my_pb + n16 * PS + quad * 8);
             if constexpr (THIRD) {
                 if (n16 < GP) pr.u = *reinterpret_cast<const uint4*>(my_pb + (16 + n16) * PS + quad * 8);
             }
@@ -594,7 +595,7 @@ __global__ __launch_bounds__((AttnCfg<T, D, G>::THREADS)) void attn_kernel(const
         }
         // publish one partial per wave
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
+        for (int i = 0; i < HR; ++i) {
             const int h = quad * 4 + i;
             const float ls = group_sum<16>(l_run[i]);
             const int ht = C::SPLIT_P ? h % GP : h, term = C::SPLIT_P ? h / GP : 0;   // SPLIT_P: row h holds term `term` of head ht
