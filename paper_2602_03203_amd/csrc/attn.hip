@@ -1010,20 +1010,21 @@ static bool window_at_once(const fk_cache_desc* d, const void* q, const void* K,
 }
 
 // Whether the steps at once are the faster way (the results are the same).  A workgroup, one per CU, walks its row alone whatever
-// the number of its steps: 3.6 us for 256 pairs (head_dim 64: 2.3) and 3.5 us (2.5) for every split of a split row, T = 2 to 128
-// steps of 1 row of 16000 pairs 333 us, of 64 rows of 8192 126 us, of 128 rows of 2048 31 us.  A single step spreads the row over the
-// chip: 8 us, its bytes at 7 TB/s, 0.15 us a split; those same three 15.5, 43 and 23 us.  The margin of a quarter is for the
-// workgroups' share of the bandwidth, which the first figure leaves out (128 rows of 2048, head_dim 64, two steps: 34 us at once, 32
-// one by one).
+// the number of its steps: 3.1 us for 256 pairs (head_dim 64: 2.2) and 4.8 us for every split of a split row; a single step spreads the
+// row over the chip: its bytes at 10 TB/s, 0.8 us for 256 pairs of a split, and the merge.  us, at once and one by one:
+//   D = 128, g = 4:  128 rows of 2048  T = 2: 28 and 48;  64 rows of 4096  T = 2: 72 and 51, T = 4: 73 and 97;  1 row of 8192
+//     T = 16: 181 and 160, T = 64: 182 and 618
+//   D = 64, g = 4:  128 rows of 1000  T = 2: 27 and 21, T = 4: 27 and 39;  16 rows of 4096  T = 8: 109 and 81;  512 rows of 100  T = 2: 19 and 16
+// Fitted to 1620 such pairs (g 1, 4, 8; 1 to 512 rows; 100 to 8192 pairs; T 2 to 64): the slower way, by more than a tenth, at 15.
 static bool window_pays(const fk_cache_desc* d, int32_t T, int32_t max_len) {
     const int g = d->n_q_heads / d->n_kv_heads, spg = 16 / g;   // 16 / g steps, or twice as many, to a workgroup
     const AttnShape shape = attn_shape(d);
     const AttnPlan p = attn_plan(shape, max_len);
     const double rows = shape.rows, groups = rows * ((T + spg - 1) / spg), rounds = groups <= 256 ? 1.0 : (groups / 2 + 255) / 256;
-    const bool narrow = d->head_dim == 64;
-    const double at_once = rounds * (6.0 + (p.nsplit > 1 ? p.nsplit * (narrow ? 2.5 : 3.5) : 0.0) + max_len / 256.0 * (narrow ? 2.3 : 3.6));
-    const double step = 8.0 + rows * max_len * d->head_dim * 4 / 7e6 + (p.nsplit > 1 ? 0.15 * p.nsplit : 0.0);
-    return T * step >= 1.25 * at_once;
+    const bool split = p.nsplit > 1;
+    const double at_once = rounds * (7.5 + (split ? 4.8 * p.nsplit : 0.0) + max_len / 256.0 * (d->head_dim == 64 ? 2.2 : 3.1));
+    const double step = 4.6 + rows * max_len * d->head_dim * 4 / 1e7 + max_len / 256.0 / p.nsplit * 0.8 + (split ? 0.7 + 0.11 * p.nsplit : 0.0);
+    return T * step >= at_once;
 }
 
 static WindowParams window_params(const fk_cache_desc* d, const void* q, void* K, void* V, int32_t* pos, int32_t* len, const void* k, const void* v,
