@@ -135,7 +135,7 @@ __global__ __launch_bounds__(THREADS) void select_keep_kernel(const float* __res
         }
     }
     RangePlan rp = {};
-    if (in_lds) rp = kr.plan(ncand, s_wmm);
+    if (in_lds) rp = kr.plan(s_wmm);
     else __syncthreads();
     auto key_at = [&](int i) { return in_lds ? s_key[i] : score_key(sc[i]); };
 
@@ -360,7 +360,9 @@ __global__ __launch_bounds__(THREADS) void select_keep_sampled_lds_kernel(const 
                 kr1.add(key1);
             }
     }
-    const RangePlan rp1 = kr1.plan(others, s_wmm);
+    RangePlan rp1 = {};
+    if (k_safe > 0) rp1 = kr1.plan(s_wmm);
+    else __syncthreads();
 
     // every wavefront owns one contiguous stretch of the row (the ordered passes walk it 64 slots at a time)
     const int stretch = (((others + WAVES - 1) / WAVES) + kWave - 1) / kWave * kWave;
@@ -398,7 +400,7 @@ __global__ __launch_bounds__(THREADS) void select_keep_sampled_lds_kernel(const 
             eq_run += (uint32_t)__popcll(me);
         }
     }
-    const RangePlan rp2 = kr2.plan(others, s_wmm + kRangePart);
+    const RangePlan rp2 = kr2.plan(s_wmm + kRangePart, 4 * K >= others || K >= 512);
 
     // (2) which candidates stay: the k2 largest t = score - noise among them
     uint32_t T2 = 0, want2 = 0;

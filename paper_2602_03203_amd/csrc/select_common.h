@@ -274,7 +274,6 @@ __device__ __forceinline__ void msd_select(KeyFn key_of, int nslots, uint32_t k,
 // Measured, us, 128 rows of 2176 and 32 of 30000 keys: normal 6.3 and 28 (by digits 6.9 and 36), quotients of normal numbers 7.3
 // and 34 (by digits 6.8 and 33: the range is what they pay for; by range 10.6).
 static constexpr int kRangeBins = 1024;
-static constexpr int kRangeShort = 256;   // slots: by digits, which need no range (130 of them, sampled: 7.0 us, by range 7.5)
 static constexpr int kRangeList = 256, kRangeListRows = 8192;   // long rows list up to this many
 // LDS words: histogram | list: count, threshold, how many of it, unused, kRangeList keys.  Zero on entry; dirty on return.
 static constexpr int kRangeWords = kRangeBins + 4 + kRangeList;
@@ -306,11 +305,8 @@ struct KeyRange {
         lo = min(lo, key);
         hi = max(hi, key);
     }
-    __device__ __forceinline__ RangePlan plan(int n, uint32_t* part) {   // n: slots; two barriers, one of short rows
-        if (n <= kRangeShort) {
-            __syncthreads();
-            return {0u, ~0u, 0.f, kRangeDigits};
-        }
+    // two barriers; dense: some sixteen keys or more to a wavefront that has any (fewer have a narrow range by chance)
+    __device__ __forceinline__ RangePlan plan(uint32_t* part, bool dense = true) {
         static_assert(kSelWaves == 16, "one lane of a row per wavefront");
         const int lane = threadIdx.x & (kWave - 1);
         wave_min_max(lo, hi);
@@ -330,7 +326,7 @@ struct KeyRange {
             // Two of them, because one may have few keys; one where few have any.  (One without has NaN here.)
             const bool narrow = lane < kSelWaves && 5.f * (key_score(r.y) - key_score(r.x)) < key_score(mx) - key_score(mn);
             const int few = __popcll(__ballot(lane < kSelWaves && r.x <= r.y)) < 5;
-            const RangePlan rp = range_plan(mn, mx, __popcll(__ballot(narrow)) + few >= 2);
+            const RangePlan rp = range_plan(mn, mx, dense && __popcll(__ballot(narrow)) + few >= 2);
             if (lane == 0) *reinterpret_cast<uint4*>(part + 2 * kSelWaves) = make_uint4(mn, mx, __float_as_uint(rp.scale), (uint32_t)rp.how);
         }
         __syncthreads();
@@ -339,8 +335,7 @@ struct KeyRange {
     }
 };
 
-// rp: of the valid keys; tid: threadIdx.x.  LOOP: for a caller with a loop round this, where code costs registers: no long
-// list, one msd_select.
+// rp: of the valid keys; tid: threadIdx.x.  LOOP: for a caller with a loop round this, where code costs registers: no long list.
 // hist4: [4][256] words for msd_select, contents undefined; part: 2 * THREADS / 64 words.
 // The other conditions are those of msd_select (every thread calls, 1 <= k <= number of valid slots).
 template <int THREADS, int U, bool LOOP = false, typename KeyFn>
@@ -353,19 +348,13 @@ __device__ __forceinline__ void range_select(KeyFn key_of, int nslots, uint32_t 
         *want_out = k;
         return;
     }
-    if (!LOOP && how == kRangeDigits) {
-        for (int i = tid; i < 4 * 256; i += THREADS) hist4[i] = 0;
-        __syncthreads();
-        msd_select<THREADS, U>(key_of, nslots, k, hist4, rp.kmin, rp.kmin ^ rp.kmax, T_out, want_out);
-        return;
-    }
     const float lo = key_score(rp.kmin);
     auto bin_of = [&](uint32_t key) -> uint32_t {
         if (how == kRangeValue) return (uint32_t)min(max((int)((key_score(key) - lo) * rp.scale), 0), kRangeBins - 1);   // monotone: so is every step
         return (key - rp.kmin) >> how;
     };
     uint32_t bin = 0, want = k, inbin = 0xffffffffu;
-    if (!LOOP || how != kRangeDigits) {
+    if (how != kRangeDigits) {
         for (int i0 = 0; i0 < nslots; i0 += U * THREADS) {   // uniform trip count: the wavefront votes below
             uint32_t kv[U];
             bool ok[U];
@@ -468,6 +457,14 @@ __device__ __forceinline__ void range_select(KeyFn key_of, int nslots, uint32_t 
                 if (ok && bin_of(key) == bin) list[4 + atomicAdd(list, 1u)] = key;
             }
             __syncthreads();
+            const uint4 quad = *reinterpret_cast<const uint4*>(list + 4 + 4 * lane);   // four entries a lane
+            const uint32_t one = list[4], at = 4 * (uint32_t)lane;
+            if (__all((at >= inbin || quad.x == one) && (at + 1 >= inbin || quad.y == one) && (at + 2 >= inbin || quad.z == one) &&
+                      (at + 3 >= inbin || quad.w == one))) {   // equal scores: nothing to rank (8320 keys, 200 of them 16.0 -> 11.6 us)
+                *T_out = one;
+                *want_out = want;
+                return;
+            }
             if ((uint32_t)tid < inbin) {
                 const uint32_t key = list[4 + tid];
                 uint32_t above = 0, ties = 0;   // entries with a larger key; equal ones at earlier places
@@ -489,36 +486,39 @@ __device__ __forceinline__ void range_select(KeyFn key_of, int nslots, uint32_t 
             return;
         }
     }
-    // digit by digit among the keys of the bin, from the highest bit in which any two differ
-    __syncthreads();   // part has been read
+    // digit by digit: all keys, or those of the bin, from the highest bit in which any two differ (one msd_select for both: a copy is 6 KB
+    // of instructions)
+    uint32_t mn = rp.kmin, mx = rp.kmax;
     auto left = [&](int i, bool& valid) {
         const uint32_t key = key_of(i, valid);
-        valid = valid && ((LOOP && how == kRangeDigits) || bin_of(key) == bin);
+        valid = valid && (how == kRangeDigits || bin_of(key) == bin);
         return key;
     };
-    uint32_t mn = 0xffffffffu, mx = 0;
-    for (int i = tid; i < nslots; i += THREADS) {
-        bool valid;
-        const uint32_t key = left(i, valid);
-        if (valid) {
-            mn = min(mn, key);
-            mx = max(mx, key);
-        }
-    }
-    wave_min_max(mn, mx);
-    if (lane == 0) {
-        part[2 * (tid / kWave)] = mn;
-        part[2 * (tid / kWave) + 1] = mx;
-    }
+    __syncthreads();   // part has been read
     for (int i = tid; i < 4 * 256; i += THREADS) hist4[i] = 0;
-    __syncthreads();
-    {
+    if (how != kRangeDigits) {
+        mn = 0xffffffffu;
+        mx = 0;
+        for (int i = tid; i < nslots; i += THREADS) {
+            bool valid;
+            const uint32_t key = left(i, valid);
+            if (valid) {
+                mn = min(mn, key);
+                mx = max(mx, key);
+            }
+        }
+        wave_min_max(mn, mx);
+        if (lane == 0) {
+            part[2 * (tid / kWave)] = mn;
+            part[2 * (tid / kWave) + 1] = mx;
+        }
+        __syncthreads();
         for (int w = 0; w < THREADS / kWave; ++w) {
             mn = min(mn, part[2 * w]);
             mx = max(mx, part[2 * w + 1]);
         }
-        __syncthreads();   // the caller's again
     }
+    __syncthreads();   // the histograms are clear; part is the caller's again
     msd_select<THREADS, U>(left, nslots, want, hist4, mn, mn ^ mx, T_out, want_out);
 }
 
