@@ -18,6 +18,10 @@ namespace fk {
 // [kRangePart] | keys [lds_keys]
 static constexpr int kSelMaxLdsKeys = 36 * 1024;  // 144 KB of keys beside the histograms
 static constexpr int kSelLdsHead = kRangeWords + 4 * 256 + 32 + kRangePart;  // words before the keys
+// Two workgroups of sixteen wavefronts share a CU if a wavefront takes no more than 80 scalar registers (800 of them a SIMD, and
+// sixteen more for every wavefront): 512 rows of 2176 keys 12.8 -> 10.2 us with 78 instead of 93, sampled 22.3 -> 16.9 with 78 instead of 90 (20.1 before
+// its range selection, with 58); 40 to 50 of them spilled to vector lanes do not show at 128 rows.
+#define FK_TWO_PER_CU __attribute__((amdgpu_num_sgpr(80)))
 // (Four wavefronts per row instead of sixteen were measured and dropped: 11.3 against 8.1 us; a pass is a chain
 // key -> atomic -> barrier -> scan of LDS round trips, which more wavefronts shorten.)
 //
@@ -35,7 +39,7 @@ struct SelSplit {
 };
 
 template <int THREADS, int MODE>
-__global__ __launch_bounds__(THREADS) void select_keep_kernel(const float* __restrict__ scores,
+__global__ __launch_bounds__(THREADS) FK_TWO_PER_CU void select_keep_kernel(const float* __restrict__ scores,
                                                               const int32_t* __restrict__ len,
                                                               int cap, int budget, int recent, int lds_keys,
                                                               int32_t* __restrict__ keep, SelSplit sp) {
@@ -311,7 +315,7 @@ __global__ __launch_bounds__(kSelThreads) void select_keep_sampled_kernel(const 
 static constexpr int kSampledLdsKeys = 18 * 1024;
 static constexpr int kSampledLdsHead = kRangeWords + 4 * 256 + 64 + 2 * kRangePart;  // words before the keys
 template <int THREADS>
-__global__ __launch_bounds__(THREADS) void select_keep_sampled_lds_kernel(const float* __restrict__ scores,
+__global__ __launch_bounds__(THREADS) FK_TWO_PER_CU void select_keep_sampled_lds_kernel(const float* __restrict__ scores,
                                                                           const float* __restrict__ noise,
                                                                           const int32_t* __restrict__ len, int cap,
                                                                           int budget, int recent, int n_cand, int lds_keys,
