@@ -122,6 +122,7 @@ BITS = [
     (128, 3, 2, 3, 700, 50, [500, 3, 0], 501, False, 0.3),
     (64, 8, 8, 1, 900, 40, [880, 31, 899], 881, True, 0.3),
     (128, 4, 8, 3, 700, 30, [600, 699, 0], 601, True, 0.3),
+    (128, 1, 4, 4, 700, 40, [480, 699, 250], 481, True, 0.1),     # few cold rows: six to seven splits of 96
     (128, 1, 3, 8, 700, 50, [680, 3, 699], 600, False, 0.1),
     (128, 8, 8, 2, 4300, 40, [4200, 100, 4095], 4201, False, 0.09),
     (64, 2, 8, 6, 40000, 30, [39000, 100, 32767], 39001, True, 0.09),
