@@ -10,8 +10,7 @@
 // (key tile, block, group) and streams g * L row segments of 256 bytes (16 lanes x 16 bytes, 16 rows per workgroup
 // instruction, eight loads in flight per thread); chunks wholly above the diagonal are never read (A is causal), so
 // the traffic is the lower triangle below query B + L.  future is a
-// running maximum down the block axis; trace is sequential by nature: one workgroup per group walks the
-// M steps with the selection of fk_select_keep on keys in LDS (the next step's are loaded while a step selects).
+// running maximum down the block axis; trace is sequential by nature: one workgroup per group walks the M steps.
 #include "select_common.h"
 
 namespace fk {
@@ -127,9 +126,430 @@ __global__ void golden_future_kernel(const float* __restrict__ a_tilde, int Tn, 
     }
 }
 
-static constexpr int kTraceMaxCache = 12288;  // B + L positions and B keys in LDS (96 KB)
+static constexpr int kTraceMaxCache = 12288;               // B + L
+static constexpr int kTraceMaxLds = 152 * 1024;            // dynamic
+static constexpr int kTrThreads = 1024, kTrHold = 512;     // threads of the workgroup; those that hold the candidates
+static constexpr int kTrWrite = kTrThreads - kTrHold - kWave, kTrWriteWaves = kTrWrite / kWave;   // those that write; one wavefront finds the cut
+static constexpr int kTrBins = 512, kTrCap = 8, kTrCut = 320;   // bins, places of a bin, bin of the last step's cut
+static constexpr int kTraceSlots = 4096, kTrFresh = 5;      // golden_trace_kernel: budget; newest pairs of a writing thread, at most
+static constexpr uint32_t kStays = 0x80000000u, kTrDown = 0xfffffffeu;   // a position p is compared as kTrDown - p, the lower one above
 
-// One workgroup per KV group.  LDS holds the cache's positions (ascending; B + L of them: the B of this step and the
+// The eviction trace.  One workgroup per KV group walks the M steps; what bounds it is the chain of one step after the other, so
+// a step has two barriers, and what the next step does not wait for runs beside it.
+//   Half of the workgroup holds the B candidates, each in a register slot of some thread, in no order.  Candidates are ranked
+// by (future score, then position, the lower one above), all different, so "the E = L lowest go" is one threshold.  A slot
+// whose pair goes takes one of the L newest pairs, candidates from the next step on: nothing is moved.
+//   The threshold: the cut moves little from step to step, so the keys around the last one are counted in 512 bins of the bit pattern,
+// its bin the 320th, and a bin has places for the first eight pairs themselves.  Keys above the bins are not counted, keys below
+// them by vote.  One wavefront finds the bin in which the count from the bottom reaches E and ranks its pairs; bins get finer or
+// coarser as they fill.  Where the bin has more pairs (ties) or the cut has left the bins, and at the first step, the pairs
+// that are left (or all) are counted again over their own range, of the keys or, if those are equal, of the positions.
+//   The other wavefronts write the results two steps later: they keep the candidates in position order, each with the slot that holds it,
+// look up which slots were given away, close the gaps and append the newest.
+//   Step t, first part: cut found | slots given away at t - 1 filled | step t - 2 written.  Second part: who goes, the others counted for
+// t + 1 | the newest counted, the gaps of t - 1 looked up.
+//   us a step, and with all candidates moved in order at every step, four barriers beside those of a range_select: 8 groups of 2048 pairs,
+// L = 128: 2.4 (4.9); 4 of 512, L = 32: 1.4 (3.4); 8 of 4096, L = 128: 3.6 (6.7); the cut always among hundreds of equal keys: 4.8 (4.7),
+// 2.8 (3.7) and 7.6 (6.9).  What is left is the issue of some 4000 instructions on one CU.  Measured and not kept: the writing wavefronts load
+// the next scores in position order for all (3.1: their instructions cost more than the scattered loads); 256 bins (the cut leaves them).
+// PER: slots of a holding thread.
+struct TraceLds {   // byte offsets in the dynamic LDS
+    int sorted, fresh, fresh_slot, gone, bytes;
+};
+__host__ __device__ inline TraceLds trace_lds(int budget, int L) {
+    TraceLds s;
+    s.sorted = kTrBins * kTrCap * 8;          // [kTrBins][kTrCap] (position, key)
+    s.fresh = s.sorted + 8 * budget;          // [budget] (position, slot) of the candidates in position order
+    s.fresh_slot = s.fresh + 16 * L;          // [2][L] keys of the newest pairs at the next two steps
+    s.gone = s.fresh_slot + 4 * L;            // [2][L] uint16_t slots that the newest pairs took
+    s.bytes = s.gone + budget;                // [budget] uint8_t the slot was given away
+    return s;
+}
+
+// Where the count over the bins from the bottom reaches E; one wavefront.  bin < 0: it does not.
+struct TraceCut {
+    int bin;
+    uint32_t want, inbin, near;   // number of the cut in its bin, pairs of the bin, pairs of the eight bins around it
+};
+__device__ __forceinline__ TraceCut trace_cut(const uint32_t* hist, uint32_t E, int lane) {
+    const uint4 a = *reinterpret_cast<const uint4*>(hist + 8 * lane), b = *reinterpret_cast<const uint4*>(hist + 8 * lane + 4);
+    const uint32_t c[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
+    const uint32_t tot = ((c[0] + c[1]) + (c[2] + c[3])) + ((c[4] + c[5]) + (c[6] + c[7]));
+    const uint32_t incl = wave_scan_incl(tot);
+    uint32_t left = E - (incl - tot);   // number of the cut from this lane's first pair on
+    const unsigned long long who = __ballot(left - 1u < tot);   // 1 <= left <= tot: one lane, or none
+    if (who == 0) return {-1, 0, 0, 0};
+    uint32_t sub = 0, in = c[0];
+#pragma unroll
+    for (int j = 1; j < 8; ++j) {   // past the bins below it
+        const bool on = left > in && sub == (uint32_t)j - 1;
+        left = on ? left - in : left;
+        sub = on ? j : sub;
+        in = on ? c[j] : in;
+    }
+    const int src = __ffsll((long long)who) - 1;
+    return {8 * src + (int)__builtin_amdgcn_readlane(sub, src), (uint32_t)__builtin_amdgcn_readlane(left, src),
+            (uint32_t)__builtin_amdgcn_readlane(in, src), (uint32_t)__builtin_amdgcn_readlane(tot, src)};
+}
+// the want-th lowest of a bin's pairs (inbin <= kTrCap of them): key and position
+__device__ __forceinline__ uint2 trace_rank(const uint2* bin, uint32_t inbin, uint32_t want, int lane) {
+    const uint2 e = bin[lane & (kTrCap - 1)];
+    const unsigned long long me = (unsigned long long)e.y << 32 | e.x;
+    uint32_t rank = 0;
+#pragma unroll
+    for (int q = 0; q < kTrCap; q += 2) {
+        const uint4 o = *reinterpret_cast<const uint4*>(bin + q);
+        rank += ((unsigned long long)o.y << 32 | o.x) < me && (uint32_t)q < inbin;
+        rank += ((unsigned long long)o.w << 32 | o.z) < me && (uint32_t)q + 1 < inbin;
+    }
+    const int at = __ffsll((long long)__ballot((uint32_t)lane < inbin && rank == want - 1)) - 1;   // one lane: all differ
+    return make_uint2(__builtin_amdgcn_readlane(e.y, at), __builtin_amdgcn_readlane(e.x, at));
+}
+
+template <int PER>
+__global__ __launch_bounds__(kTrThreads) void golden_trace_kernel(const float* __restrict__ alpha, int Tn, int M, int budget, int L,
+                                                                  int32_t* __restrict__ kept) {
+    constexpr int ORD = PER + (PER + 6) / 7;   // ordered entries of a writing thread: seven wavefronts' for eight's slots
+    static_assert(ORD * kTrWrite >= PER * kTrHold, "a place for every candidate");
+    extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+    const TraceLds off = trace_lds(budget, L);
+    uint2* s_bin = reinterpret_cast<uint2*>(smem);
+    uint2* s_sorted = reinterpret_cast<uint2*>(smem + off.sorted);
+    uint2* s_fresh = reinterpret_cast<uint2*>(smem + off.fresh);
+    uint16_t* s_fresh_slot = reinterpret_cast<uint16_t*>(smem + off.fresh_slot);
+    uint8_t* s_gone = smem + off.gone;
+    __shared__ __attribute__((aligned(16))) uint32_t s_hist[3][kTrBins];   // this step's, the next one's; of a recount, zero in between
+    // [0] key and [1] position of the highest pair that goes | [2] found: 2 by position | [3] shift of the bins, [4] first key of the bins | not found: the
+    // cut is number [5] of the pairs with keys [6] .. [7]
+    __shared__ __attribute__((aligned(16))) uint32_t s_cut[8];
+    __shared__ uint32_t s_taken[2], s_lo, s_hi, s_count[kTrWriteWaves];
+    const int hp = blockIdx.x, k = budget - L, wave = threadIdx.x / kWave;
+    constexpr int HOLD = kTrHold / kWave;   // wavefronts 0 .. HOLD - 1 hold the candidates, HOLD finds the cut, the others write
+    const bool holds = wave < HOLD, cuts = wave == HOLD;
+    const float* al = alpha + (size_t)hp * M * Tn;
+    int32_t* out = kept + (size_t)hp * M * budget;
+    if (k == 0) {   // only the newest stay
+        for (int t = 1; t <= M; ++t)
+            for (int j = threadIdx.x; j < L; j += kTrThreads) out[(size_t)(t - 1) * budget + j] = budget + (t - 1) * L + j;
+        return;
+    }
+    // Holding threads: position (descending) and key of a candidate (slots without one: all ones, above every candidate), its next key and
+    // the score it comes from.  Writing threads: position and slot of the ordered entries, the next two scores of the newest pairs.
+    constexpr int FR = ORD < kTrFresh ? ORD : kTrFresh, NX = PER > FR ? PER : FR;   // FR: newest pairs of a writing thread
+    uint32_t np[ORD], key[ORD], key_next[PER], gone = 0;   // gone: a bit for every slot given away
+    float next[NX], next2[FR];
+    {
+        const int tid = threadIdx.x;
+        for (int j = tid; j < budget; j += kTrThreads) {
+            s_sorted[j] = make_uint2(j, j);
+            s_gone[j] = 0;
+        }
+        static_assert(3 * kTrBins <= 2 * kTrThreads, "");
+        for (int i = tid; i < 3 * kTrBins; i += kTrThreads) s_hist[i / kTrBins][i % kTrBins] = 0;
+        if (tid < 2) s_taken[tid] = 0;
+        if (tid == 0) {
+            s_lo = 0xffffffffu;
+            s_hi = 0;
+            s_cut[2] = 0;   // the first step has no bins
+            s_cut[3] = 0;
+            s_cut[5] = (uint32_t)L;
+            s_cut[6] = 0;
+            s_cut[7] = kTrDown;
+        }
+#pragma unroll
+        for (int u = 0; u < ORD; ++u) {
+            const int i = u * kTrHold + tid, j = u * kTrWrite + tid - kTrHold - kWave;
+            const bool candidate = holds && u < PER && i < budget;
+            np[u] = candidate ? kTrDown - (uint32_t)i : 0xffffffffu;
+            key[u] = candidate ? score_key(al[i]) : 0xffffffffu;
+            if (u < PER) key_next[u] = 0xffffffffu;
+            if (u < NX) {
+                next[u] = 0.f;
+                if (candidate && M > 1) next[u] = al[Tn + i];
+                if (wave > HOLD && u < FR && j < L && M > 1) next[u] = al[Tn + budget + j];
+            }
+            if (u < FR) {
+                next2[u] = 0.f;
+                if (wave > HOLD && j < L && M > 2) next2[u] = al[2 * (size_t)Tn + budget + j];
+            }
+        }
+    }
+    const int stretch = ((budget + kTrWriteWaves - 1) / kTrWriteWaves + kWave - 1) / kWave * kWave;   // ordered entries of a writing wavefront
+    __syncthreads();
+    for (int t = 1; t <= M + 2; ++t) {   // step t is decided, step t - 2 written
+        int tid = threadIdx.x;
+        asm volatile("" : "+v"(tid));   // opaque: what is derived from it would be kept over the whole loop, in registers that spill
+        const int lane = tid & (kWave - 1), write_tid = tid - kTrHold - kWave;
+        if (holds) {
+            uint32_t n = 0, first = 0;
+#pragma unroll
+            for (int u = 0; u < PER; ++u) n += (uint32_t)__popcll(__ballot((gone >> u) & 1));
+            if (lane == 0) first = atomicAdd(&s_taken[t & 1], n);
+            if (tid < kTrBins) s_hist[(t + 1) & 1][tid] = 0;
+            if (tid == 0) s_taken[(t + 1) & 1] = 0;
+            first = __builtin_amdgcn_readfirstlane(first);
+#pragma unroll
+            for (int u = 0; u < PER; ++u) key_next[u] = np[u] == 0xffffffffu ? 0xffffffffu : score_key(next[u]);
+            // the j-th of the slots given away at t - 1 takes the j-th of the then newest pairs (a few at a time, so that the reads overlap)
+            constexpr int STEP = PER < 4 ? PER : 4;
+#pragma unroll
+            for (int u0 = 0; u0 < PER; u0 += STEP) {
+                int j[STEP];
+                uint2 f[STEP];
+#pragma unroll
+                for (int v = 0; v < STEP; ++v) {
+                    const unsigned long long all = __ballot((gone >> (u0 + v)) & 1);
+                    j[v] = min((int)(first + __builtin_amdgcn_mbcnt_hi((uint32_t)(all >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)all, 0))), L - 1);
+                    first += (uint32_t)__popcll(all);
+                    f[v] = s_fresh[((t - 1) & 1) * L + j[v]];
+                }
+#pragma unroll
+                for (int v = 0; v < STEP; ++v) {
+                    const int u = u0 + v;
+                    const bool g = (gone >> u) & 1;
+                    np[u] = g ? kTrDown - (uint32_t)(budget + (t - 2) * L + j[v]) : np[u];
+                    key[u] = g ? f[v].x : key[u];
+                    key_next[u] = g ? f[v].y : key_next[u];
+                    if (g) {
+                        s_gone[u * kTrHold + tid] = 1;
+                        s_fresh_slot[((t - 1) & 1) * L + j[v]] = (uint16_t)(u * kTrHold + tid);
+                    }
+                }
+            }
+        } else if (cuts) {
+            if (t > 1 && t <= M) {
+                __builtin_amdgcn_s_setprio(3);   // everything waits for this
+                int shift = (int)s_cut[3];
+                const TraceCut c = trace_cut(s_hist[t & 1], (uint32_t)L, lane);
+                if (c.bin > 0 && c.inbin <= (uint32_t)kTrCap && !(c.bin == kTrCut && s_cut[2] == 2)) {   // (pairs counted by vote are not listed)
+                    const uint2 T = trace_rank(s_bin + c.bin * kTrCap, c.inbin, c.want, lane);
+                    if (c.near > 24 && shift > 0) --shift;
+                    else if (c.near < 6 && shift < 22) ++shift;
+                    if (lane == 0) {
+                        *reinterpret_cast<uint4*>(s_cut) = make_uint4(T.x, T.y, 1u, (uint32_t)shift);
+                        s_cut[4] = __builtin_elementwise_sub_sat(T.x, (uint32_t)kTrCut << shift);
+                    }
+                } else if (lane == 0) {
+                    const bool in = c.bin > 0;
+                    const uint32_t lo = s_cut[4] + ((uint32_t)max(c.bin, 0) << shift);
+                    s_cut[2] = 0;
+                    s_cut[5] = in ? c.want : (uint32_t)L;
+                    s_cut[6] = in ? lo : 0u;
+                    s_cut[7] = in ? lo + min((1u << shift) - 1u, kTrDown - lo) : kTrDown;
+                }
+                __builtin_amdgcn_s_setprio(0);
+            }
+        } else {
+            if (t > 2) {   // step t - 2: those that stayed, in order, then the newest
+                int32_t* row = out + (size_t)(t - 3) * budget;
+                const int new0 = budget + (t - 3) * L;
+                uint32_t before = 0;
+#pragma unroll
+                for (int w = 0; w < kTrWriteWaves; ++w) before += w < wave - HOLD - 1 ? s_count[w] : 0u;
+#pragma unroll
+                for (int u = 0; u < ORD; ++u) {
+                    const bool stays = (key[u] & kStays) != 0;
+                    const unsigned long long all = __ballot(stays);
+                    if (stays) {
+                        const uint32_t dst = before + __builtin_amdgcn_mbcnt_hi((uint32_t)(all >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)all, 0));
+                        s_sorted[dst] = make_uint2(np[u], key[u] & ~kStays);
+                        row[dst] = (int32_t)np[u];
+                    }
+                    before += (uint32_t)__popcll(all);
+                }
+#pragma unroll
+                for (int u = 0; u < FR; ++u) {
+                    if (u * kTrWrite >= L) break;
+                    const int j = u * kTrWrite + write_tid;
+                    if (j < L) {
+                        s_sorted[k + j] = make_uint2((uint32_t)(new0 + j), s_fresh_slot[(t & 1) * L + j]);
+                        row[k + j] = new0 + j;
+                    }
+                }
+            }
+            if (t < M) {
+#pragma unroll
+                for (int u = 0; u < FR; ++u) {
+                    if (u * kTrWrite >= L) break;
+                    const int j = u * kTrWrite + write_tid;
+                    if (j < L) s_fresh[(t & 1) * L + j] = make_uint2(score_key(next[u]), score_key(next2[u]));
+                }
+            }
+        }
+        __syncthreads();
+        if (__builtin_expect(t <= M && s_cut[2] == 0, 0)) {
+            // count the pairs that are left over their own range, until the cut's bin can be ranked
+            uint32_t want = s_cut[5], klo = s_cut[6], khi = s_cut[7];
+            uint32_t plo = kTrDown - (uint32_t)(budget + (t - 1) * L - 1), phi = kTrDown;
+            uint32_t* hist = s_hist[2];
+            int shift = (int)s_cut[3];
+            bool whole = klo == 0 && khi == kTrDown;
+            for (;;) {
+                auto member = [&](int u) { return (key[u] >= klo) & (key[u] <= khi) & (np[u] >= plo) & (np[u] <= phi); };
+                if (klo != khi) {
+                    uint32_t lo = 0xffffffffu, hi = 0;
+                    if (holds) {
+#pragma unroll
+                        for (int u = 0; u < PER; ++u) {
+                            lo = member(u) ? min(lo, key[u]) : lo;
+                            hi = member(u) ? max(hi, key[u]) : hi;
+                        }
+                        wave_min_max(lo, hi);
+                        if (lane == 0 && lo <= hi) {
+                            atomicMin(&s_lo, lo);
+                            atomicMax(&s_hi, hi);
+                        }
+                    }
+                    __syncthreads();
+                    klo = s_lo;
+                    khi = s_hi;
+                }
+                const bool by_key = klo != khi;
+                const uint32_t first = by_key ? klo : plo, span = by_key ? khi - klo : phi - plo;
+                const int sh = span == 0 ? 0 : max(23 - __clz((int)span), 0);   // span >> sh < 512
+                if (holds) {
+#pragma unroll
+                    for (int u = 0; u < PER; ++u) {
+                        const bool in = member(u);
+                        const uint32_t bin = ((by_key ? key[u] : np[u]) - first) >> sh;
+                        const unsigned long long act = __ballot(in);
+                        if (act == 0) continue;
+                        const uint32_t lead = __builtin_amdgcn_readlane(bin, __ffsll((long long)act) - 1);
+                        if (__popcll(act) > kTrCap && __ballot(in && bin == lead) == act) {   // one bin, and more than it has places for
+                            if (lane == 0) atomicAdd(&hist[lead], (uint32_t)__popcll(act));
+                        } else if (in) {
+                            const uint32_t place = atomicAdd(&hist[bin], 1u);
+                            if (place < (uint32_t)kTrCap) s_bin[bin * kTrCap + place] = make_uint2(np[u], key[u]);
+                        }
+                    }
+                }
+                __syncthreads();
+                if (cuts) {
+                    const TraceCut c = trace_cut(hist, want, lane);   // it is there
+                    const bool found = c.inbin <= (uint32_t)kTrCap;
+                    uint2 T = make_uint2(0u, 0u);
+                    if (found) T = trace_rank(s_bin + c.bin * kTrCap, c.inbin, c.want, lane);
+                    // the next step's bins: two or three pairs to one
+                    if (by_key && !found) shift = min(max(sh - (30 - __clz((int)c.inbin)), 0), 22);
+                    else if (by_key && whole) shift = min(sh, 22);
+                    if (lane == 0) {
+                        const uint32_t lo = first + ((uint32_t)c.bin << sh);
+                        *reinterpret_cast<uint4*>(s_cut) = make_uint4(T.x, T.y, found ? by_key ? 1 : 2 : 0, (uint32_t)shift);
+                        *reinterpret_cast<uint4*>(s_cut + 4) = make_uint4(__builtin_elementwise_sub_sat(T.x, (uint32_t)kTrCut << shift), c.want, lo, lo + min((1u << sh) - 1u, first + span - lo));
+                        s_lo = 0xffffffffu;
+                        s_hi = 0;
+                    }
+#pragma unroll
+                    for (int i = 0; i < kTrBins; i += 4 * kWave) *reinterpret_cast<uint4*>(hist + i + 4 * lane) = make_uint4(0, 0, 0, 0);
+                }
+                __syncthreads();
+                if (s_cut[2] != 0) break;
+                whole = false;
+                want = s_cut[5];
+                if (by_key) {
+                    klo = s_cut[6];
+                    khi = s_cut[7];
+                } else {
+                    plo = s_cut[6];
+                    phi = s_cut[7];
+                }
+                __syncthreads();   // s_cut has been read
+            }
+        }
+        if (cuts) {
+            if (t < M) {   // the newest pairs are candidates of step t + 1
+                const uint32_t base = s_cut[4], shift = s_cut[3];
+                uint32_t* hist = s_hist[(t + 1) & 1];
+                uint32_t low = 0;
+                for (int j0 = 0; j0 < L; j0 += kWave) {
+                    const int j = min(j0 + lane, L - 1);
+                    const uint32_t x = s_fresh[(t & 1) * L + j].x, bin = j0 + lane < L ? __builtin_elementwise_sub_sat(x, base) >> shift : (uint32_t)kTrBins;
+                    low += (uint32_t)__popcll(__ballot(bin == 0));
+                    if (bin - 1u < (uint32_t)(kTrBins - 1)) {
+                        const uint32_t place = atomicAdd(&hist[bin], 1u);
+                        if (place < (uint32_t)kTrCap) s_bin[bin * kTrCap + place] = make_uint2(kTrDown - (uint32_t)(budget + (t - 1) * L + j), x);
+                    }
+                }
+                if (lane == 0 && low) atomicAdd(&hist[0], low);
+            }
+        } else if (holds) {
+            gone = 0;
+            if (t <= M) {
+                const uint4 c4 = *reinterpret_cast<const uint4*>(s_cut);
+                const uint32_t base = s_cut[4];
+                const unsigned long long cut = (unsigned long long)(uint32_t)__builtin_amdgcn_readfirstlane(c4.x) << 32 | (uint32_t)__builtin_amdgcn_readfirstlane(c4.y);
+                const int shift = __builtin_amdgcn_readfirstlane(c4.w);
+                const float* after = al + (size_t)(t + 1) * Tn;   // scores of step t + 2
+                uint32_t* hist = s_hist[(t + 1) & 1];
+                uint32_t low = 0, equal = 0;
+                const bool crowd = c4.z == 2;   // the cut went through equal keys: atomics on one word take turns, so they are counted by vote
+                constexpr int STEP = PER < 4 ? PER : 4;
+#pragma unroll
+                for (int u0 = 0; u0 < PER; u0 += STEP) {
+                    uint32_t bin[STEP], place[STEP];
+#pragma unroll
+                    for (int v = 0; v < STEP; ++v) {
+                        const int u = u0 + v;
+                        const bool g = ((unsigned long long)key[u] << 32 | np[u]) <= cut;
+                        gone |= g ? 1u << u : 0u;
+                        key[u] = key_next[u];
+                        bin[v] = __builtin_elementwise_sub_sat(key[u], base) >> shift;
+                        bin[v] = g ? (uint32_t)kTrBins : bin[v];
+                        low += (uint32_t)__popcll(__ballot(bin[v] == 0));
+                        if (crowd) {
+                            equal += (uint32_t)__popcll(__ballot(bin[v] == (uint32_t)kTrCut));
+                            bin[v] = bin[v] == (uint32_t)kTrCut ? (uint32_t)kTrBins : bin[v];
+                        }
+                        place[v] = kTrCap;
+                        if (bin[v] - 1u < (uint32_t)(kTrBins - 1)) place[v] = atomicAdd(&hist[bin[v]], 1u);
+                    }
+#pragma unroll
+                    for (int v = 0; v < STEP; ++v)
+                        if (place[v] < (uint32_t)kTrCap) s_bin[bin[v] * kTrCap + place[v]] = make_uint2(np[u0 + v], key[u0 + v]);
+                    if (t + 2 <= M) {
+#pragma unroll
+                        for (int v = 0; v < STEP; ++v)
+                            if (np[u0 + v] != 0xffffffffu) next[u0 + v] = after[kTrDown - np[u0 + v]];
+                    }
+                }
+                if (lane == 0 && low) atomicAdd(&hist[0], low);
+                if (lane == 0 && equal) atomicAdd(&hist[kTrCut], equal);
+            }
+        } else {
+            if (t > 1 && t <= M + 1) {   // which of the ordered candidates of step t - 1 stayed
+                const int w = wave - HOLD - 1, w0 = min(w * stretch, budget), w1 = min(w0 + stretch, budget);
+                uint8_t g[ORD];
+                uint32_t n = 0;
+#pragma unroll
+                for (int u = 0; u < ORD; ++u) {
+                    const uint2 e = s_sorted[min(w0 + u * kWave + lane, budget - 1)];
+                    np[u] = e.x;
+                    key[u] = e.y;
+                }
+#pragma unroll
+                for (int u = 0; u < ORD; ++u) g[u] = s_gone[key[u]];
+#pragma unroll
+                for (int u = 0; u < ORD; ++u) {
+                    const bool live = w0 + u * kWave + lane < w1;
+                    if (live && g[u]) s_gone[key[u]] = 0;
+                    n += (uint32_t)__popcll(__ballot(live && !g[u]));
+                    if (live && !g[u]) key[u] |= kStays;
+                }
+                if (lane == 0) s_count[w] = n;
+            }
+#pragma unroll
+            for (int u = 0; u < FR; ++u) {   // scores at steps t + 2 and t + 3 of the pairs that are the newest at step t + 1
+                if (u * kTrWrite >= L) break;
+                const int j = u * kTrWrite + write_tid;
+                if (j < L && t + 2 <= M) next[u] = al[(size_t)(t + 1) * Tn + budget + t * L + j];
+                if (j < L && t + 3 <= M) next2[u] = al[(size_t)(t + 2) * Tn + budget + t * L + j];
+            }
+        }
+        __syncthreads();
+    }
+}
+
+// Budgets beyond kTraceSlots, whose slots do not fit the registers (4 groups of 8000, L = 256: 12.3 us a step, with sixteen slots a thread, 180 registers of them spilled, 10 to 30).  One workgroup per KV group.  LDS holds the cache's positions (ascending; B + L of them: the B of this step and the
 // L that are generated before the next one) and the keys of its first B entries under this step's future scores.
 // A step: (1) the loads of the NEXT step's future scores at every position that can still be a candidate then are
 // issued (they land while the step selects); (2) range_select finds the key of the (B - L)-th best candidate;
@@ -138,7 +558,7 @@ static constexpr int kTraceMaxCache = 12288;  // B + L positions and B keys in L
 // in registers before the barrier that precedes the moves, so the compaction is safe in place.
 // PER_LANE: candidates one lane holds (stretch of a wavefront / 64) and newest pairs one thread holds (L / 1024), at most.
 template <int PER_LANE>
-__global__ __launch_bounds__(kSelThreads) void golden_trace_kernel(const float* __restrict__ alpha, int Tn, int M,
+__global__ __launch_bounds__(kSelThreads) void golden_trace_ordered_kernel(const float* __restrict__ alpha, int Tn, int M,
                                                                    int budget, int L, int32_t* __restrict__ kept) {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     int32_t* s_pos = reinterpret_cast<int32_t*>(smem);                 // [budget + L]
@@ -310,17 +730,20 @@ extern "C" fk_status fk_golden_trace(const float* alpha, int32_t n_kv_heads, int
     if (budget + interval > kTraceMaxCache) return FK_ERR_UNSUPPORTED;
     const int M = golden_steps(T, budget, interval);
     if (M == 0) return FK_OK;
-    const size_t lds = sizeof(int32_t) * ((size_t)budget + interval) + sizeof(uint32_t) * (size_t)budget;
-    // candidates per lane: a wavefront's stretch is the budget over the 16 wavefronts, rounded up to whole 64s
-    const int per_lane = ((budget + kSelWaves - 1) / kSelWaves + kWave - 1) / kWave;
-    auto launch = [&](auto kern, bool (&lds_ok)[kMaxDevices]) -> fk_status {
-        if (!allow_dynamic_lds((const void*)kern, sizeof(int32_t) * 2 * kTraceMaxCache, lds_ok)) return FK_ERR_LAUNCH;
-        hipLaunchKernelGGL(kern, dim3(n_kv_heads), dim3(kSelThreads), lds, (hipStream_t)stream, alpha, T, M, budget, interval,
-                           kept);
+    auto launch = [&](auto kern, bool (&lds_ok)[kMaxDevices], size_t lds, size_t most) -> fk_status {
+        if (!allow_dynamic_lds((const void*)kern, most, lds_ok)) return FK_ERR_LAUNCH;
+        hipLaunchKernelGGL(kern, dim3(n_kv_heads), dim3(kTrThreads), lds, (hipStream_t)stream, alpha, T, M, budget, interval, kept);
         return launch_status();
     };
-    static bool ok2[kMaxDevices] = {}, ok4[kMaxDevices] = {}, ok12[kMaxDevices] = {};
-    if (per_lane <= 2) return launch(golden_trace_kernel<2>, ok2);
-    if (per_lane <= 4) return launch(golden_trace_kernel<4>, ok4);
-    return launch(golden_trace_kernel<12>, ok12);   // budget + interval <= kTraceMaxCache: at most 12
+    static bool ok1[kMaxDevices] = {}, ok2[kMaxDevices] = {}, ok4[kMaxDevices] = {}, ok8[kMaxDevices] = {}, ok_ordered[kMaxDevices] = {};
+    if (budget > kTraceSlots || interval > kTrWrite * kTrFresh) {
+        const size_t lds = sizeof(int32_t) * ((size_t)budget + interval) + sizeof(uint32_t) * (size_t)budget;
+        return launch(golden_trace_ordered_kernel<12>, ok_ordered, lds, sizeof(int32_t) * 2 * kTraceMaxCache);   // 12 * 1024 = kTraceMaxCache
+    }
+    const size_t lds = (size_t)trace_lds(budget, interval).bytes;
+    const int per = (budget + kTrHold - 1) / kTrHold;   // slots of a thread
+    if (per <= 1) return launch(golden_trace_kernel<1>, ok1, lds, kTraceMaxLds);
+    if (per <= 2) return launch(golden_trace_kernel<2>, ok2, lds, kTraceMaxLds);
+    if (per <= 4) return launch(golden_trace_kernel<4>, ok4, lds, kTraceMaxLds);
+    return launch(golden_trace_kernel<8>, ok8, lds, kTraceMaxLds);
 }

@@ -138,6 +138,38 @@ def test_trace_on_large_budgets(gpu, Hkv, T, B, L):
     assert np.array_equal(d_kept.cpu().numpy(), golden.trace(alpha, B, L))
 
 
+# slots of a holding thread 1, 2, 4, 8 (budget / 512) and the ordered kernel beyond, newest pairs of a writing thread (L / 448) up to five, one
+# step, nothing but the newest; scores by which the trace's bins fill, stand empty, move away from the cut or cannot divide
+@pytest.mark.parametrize("scores", ["smooth", "equal", "crowds", "zeros", "special", "jumps"])
+@pytest.mark.parametrize("T,B,L", [(40, 3, 1), (60, 10, 10), (1500, 100, 8), (3000, 512, 449), (2400, 513, 64), (3000, 1024, 448), (4000, 1025, 100), (4200, 2048, 128),
+                                   (4400, 2048, 1900), (8000, 4096, 300), (14000, 4096, 2240), (14000, 4096, 2241), (9000, 4097, 500)])
+def test_trace_score_distributions(gpu, T, B, L, scores):
+    import paper_2602_03203_amd as fk
+    from oracle import golden
+    M = golden.n_steps(T, B, L)
+    rng = np.random.default_rng(T + B + L)
+    x = np.abs(1 + 0.2 * rng.standard_normal((2, M, T))) * np.where(rng.random((2, 1, T)) < 0.02, 20.0, 1.0) / T   # as attention gives them
+    if scores != "special":
+        x = np.maximum.accumulate(x[:, ::-1], axis=1)[:, ::-1]
+    if scores == "equal":
+        x[:] = 0.25
+    elif scores == "crowds":      # a few values, hundreds of pairs each
+        x = np.round(x * T * 8) / (8 * T)
+    elif scores == "zeros":       # most pairs are never looked at again
+        x *= rng.random((2, 1, T)) < 0.1
+    elif scores == "special":     # both signs and zeros, infinities, NaN, a huge outlier, the smallest numbers
+        x *= rng.choice([-1.0, 1.0], size=x.shape)
+        for v in (0.0, -0.0, np.inf, -np.inf, np.nan, 3e38, 1e-45, -1e-45):
+            x[rng.random(x.shape) < 0.01] = v
+    elif scores == "jumps":       # every step at another scale
+        x *= 2.0 ** rng.integers(-60, 60, size=(2, M, 1))
+    alpha = x.astype(np.float32)
+    print(f"trace T={T} B={B} L={L} M={M} {scores}", flush=True)
+    d_kept = torch.full((2, M, B), -1, dtype=torch.int32, device="cuda")
+    fk.fk_golden_trace(torch.from_numpy(alpha).cuda(), T, B, L, d_kept)
+    assert np.array_equal(d_kept.cpu().numpy(), golden.trace(alpha, B, L))
+
+
 def test_layer_slice_at_paper_budget(gpu):
     """Budget 256, L 64 on a 2048-token trace, 8 query heads in 2 groups, bf16: 27 steps, tiles on and
     off the diagonal, every output compared."""
