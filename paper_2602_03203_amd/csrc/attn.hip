@@ -403,12 +403,21 @@ __global__ __launch_bounds__((AttnCfg<T, D, G>::THREADS)) void attn_kernel(const
 
     if constexpr (C::PVM) {
         constexpr int PS = C::PS, KRS = C::KRS;
-        const int n16 = lane & 15, quad = lane >> 4;
+        const int n16 = lane & 15, quad = lane >> 4, key0 = attn_qk_key<D>(0, n16);   // the lane's logits: keys key0 and key0 + KEY1 of a tile
+        constexpr int KEY1 = attn_qk_key<D>(1, 0);
         constexpr int KS = D / 32;          // k-steps of q.K^T
         constexpr int ET = D / 16;          // channel tiles of P.V
         constexpr int HR = G < 4 ? G : 4;   // of a lane's four result rows, those that can belong to a head
         uint16_t* my_pb = reinterpret_cast<uint16_t*>(s_p) + (size_t)wave * C::PROWS * PS;   // [PROWS][PS] bf16
         unsigned char* my_k = s_kt + (size_t)wave * KT * KRS;   // D = 128
+        auto put_pair = [&](uint16_t* p, uint32_t w) {   // probabilities of the lane's two keys
+            if constexpr (KEY1 == 1) {
+                *reinterpret_cast<uint32_t*>(p + key0) = w;
+            } else {
+                p[key0] = (uint16_t)w;
+                p[key0 + KEY1] = (uint16_t)(w >> 16);
+            }
+        };
         B128 qa[KS];
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks) {
@@ -446,7 +455,7 @@ __global__ __launch_bounds__((AttnCfg<T, D, G>::THREADS)) void attn_kernel(const
         auto fetch64 = [&](int base, B128 (&kd)[2][2], uint2 (&v)[8]) {   // D = 64
 #pragma unroll
             for (int nt = 0; nt < 2; ++nt) {
-                const int kc = min(base + nt * 16 + n16, end - 1);
+                const int kc = min(base + attn_qk_key<D>(nt, n16), end - 1);
 #pragma unroll
                 for (int ks = 0; ks < 2; ++ks) kd[nt][ks].u = ld_stream<NT>((kc == new_slot ? knew_row : Krow + (size_t)kc * CH) + ks * 4 + quad);
             }
@@ -497,10 +506,10 @@ __global__ __launch_bounds__((AttnCfg<T, D, G>::THREADS)) void attn_kernel(const
                     vr[u] = ld_stream<NT>((kc == new_slot ? vnew_row : Vrow + (size_t)kc * CH) + n16);
                 }
 #pragma unroll
-                for (int u = 0; u < 8; ++u) *reinterpret_cast<uint4*>(my_k + (quad * 8 + u) * KRS + n16 * 16) = kr[u];
+                for (int u = 0; u < 8; ++u) *reinterpret_cast<uint4*>(my_k + (quad * 4 + attn_qk_row<D>(u)) * KRS + n16 * 16) = kr[u];
             }
             __builtin_amdgcn_wave_barrier();
-            // B operand of q.K^T: lane = key n16 of tile nt, channels ks*32 + quad*8 .. +8
+            // B operand of q.K^T: lane = key attn_qk_key(nt, n16), channels ks*32 + quad*8 .. +8
             f32x4_t c[2];
 #pragma unroll
             for (int nt = 0; nt < 2; ++nt) {
@@ -515,44 +524,38 @@ __global__ __launch_bounds__((AttnCfg<T, D, G>::THREADS)) void attn_kernel(const
             }
             bool changed = false;
             float corr[4];
-            uint32_t pb[2][4], p3[2][4];
+            uint32_t pw[4], p3[4];   // bf16 pairs: keys key0 and key0 + KEY1
             if constexpr (FEAT) {  // keep the step's logits: the second pass turns them into attention weights
                 if (quad * 4 < GP) {
-                    if (base + n16 < end)
-                        *reinterpret_cast<float4*>(lg_row + (size_t)(base + n16) * GP + quad * 4) =
+                    if (base + key0 < end)
+                        *reinterpret_cast<float4*>(lg_row + (size_t)(base + key0) * GP + quad * 4) =
                             make_float4(c[0][0] * P.scale_log2e, c[0][1] * P.scale_log2e, c[0][2] * P.scale_log2e, c[0][3] * P.scale_log2e);
-                    if (base + 16 + n16 < end)
-                        *reinterpret_cast<float4*>(lg_row + (size_t)(base + 16 + n16) * GP + quad * 4) =
+                    if (base + key0 + KEY1 < end)
+                        *reinterpret_cast<float4*>(lg_row + (size_t)(base + key0 + KEY1) * GP + quad * 4) =
                             make_float4(c[1][0] * P.scale_log2e, c[1][1] * P.scale_log2e, c[1][2] * P.scale_log2e, c[1][3] * P.scale_log2e);
                 }
             }
 #pragma unroll
             for (int i = 0; i < HR; ++i) {
-                const float s0 = (base + n16 < end) ? c[0][i] * P.scale_log2e : kNegBig;
-                const float s1 = (base + 16 + n16 < end) ? c[1][i] * P.scale_log2e : kNegBig;
+                const float s0 = (base + key0 < end) ? c[0][i] * P.scale_log2e : kNegBig;
+                const float s1 = (base + key0 + KEY1 < end) ? c[1][i] * P.scale_log2e : kNegBig;
                 const float mn = fmaxf(m_run[i], row16_max(fmaxf(s0, s1)));
                 changed |= mn > m_run[i];
                 corr[i] = exp2f(m_run[i] - mn);
                 // probabilities rounded to bf16; the SAME rounded values go into l, so the weights stay normalised
                 const float e0 = exp2f(s0 - mn), e1 = exp2f(s1 - mn);
-                const uint32_t u0 = __float_as_uint(e0) + 0x8000u, u1 = __float_as_uint(e1) + 0x8000u;
-                pb[0][i] = u0 >> 16;
-                pb[1][i] = u1 >> 16;
+                const uint32_t w = pack_bf16(e0, e1);
+                pw[i] = w;
                 if constexpr (C::SPLIT_P) {   // each term of what the ones before leave; GP = 4: row quad q holds term q, GP = 8: q / 2
-                    const float r0 = e0 - __uint_as_float(u0 & 0xffff0000u), r1 = e1 - __uint_as_float(u1 & 0xffff0000u);
-                    const uint32_t v0 = __float_as_uint(r0) + 0x8000u, v1 = __float_as_uint(r1) + 0x8000u;
-                    p3[0][i] = __float_as_uint(r0 - __uint_as_float(v0 & 0xffff0000u)) >> 16;
-                    p3[1][i] = __float_as_uint(r1 - __uint_as_float(v1 & 0xffff0000u)) >> 16;
+                    const float r0 = e0 - bf16_lo(w), r1 = e1 - bf16_hi(w);
+                    const uint32_t w2 = pack_bf16(r0, r1);
+                    p3[i] = pack_bf16(r0 - bf16_lo(w2), r1 - bf16_hi(w2));
                     const int term = quad * 4 / GP;
-                    pb[0][i] = term == 0 ? pb[0][i] : v0 >> 16;
-                    pb[1][i] = term == 0 ? pb[1][i] : v1 >> 16;
-                    if constexpr (!THIRD) {
-                        pb[0][i] = term < 2 ? pb[0][i] : p3[0][i];
-                        pb[1][i] = term < 2 ? pb[1][i] : p3[1][i];
-                    }
+                    pw[i] = term == 0 ? w : w2;
+                    if constexpr (!THIRD) pw[i] = term < 2 ? pw[i] : p3[i];
                     l_run[i] = l_run[i] * corr[i] + e0 + e1;
                 } else {
-                    l_run[i] = l_run[i] * corr[i] + __uint_as_float(u0 & 0xffff0000u) + __uint_as_float(u1 & 0xffff0000u);
+                    l_run[i] = l_run[i] * corr[i] + bf16_lo(w) + bf16_hi(w);
                     if constexpr (FEAT) lx_run[i] = lx_run[i] * corr[i] + e0 + e1;
                 }
                 m_run[i] = mn;
@@ -560,13 +563,9 @@ __global__ __launch_bounds__((AttnCfg<T, D, G>::THREADS)) void attn_kernel(const
             if (quad * 4 < C::PROWS) {
 #pragma unroll
                 for (int i = 0; i < HR; ++i) {
-                    my_pb[(quad * 4 + i) * PS + n16] = (uint16_t)pb[0][i];
-                    my_pb[(quad * 4 + i) * PS + 16 + n16] = (uint16_t)pb[1][i];
+                    put_pair(my_pb + (quad * 4 + i) * PS, pw[i]);
                     if constexpr (THIRD) {
-                        if (quad < 2) {
-                            my_pb[(16 + quad * 4 + i) * PS + n16] = (uint16_t)p3[0][i];
-                            my_pb[(16 + quad * 4 + i) * PS + 16 + n16] = (uint16_t)p3[1][i];
-                        }
+                        if (quad < 2) put_pair(my_pb + (16 + quad * 4 + i) * PS, p3[i]);
                     }
                 }
             }

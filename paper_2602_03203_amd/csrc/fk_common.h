@@ -14,11 +14,11 @@ static constexpr int kWave = 64;
 __device__ __forceinline__ float bf16_lo(uint32_t w) { return __uint_as_float(w << 16); }
 __device__ __forceinline__ float bf16_hi(uint32_t w) { return __uint_as_float(w & 0xffff0000u); }
 
-// round-to-nearest-even fp32 -> bf16 bits (NaN stays NaN)
-__device__ __forceinline__ uint32_t f32_to_bf16(float f) {
-    uint32_t u = __float_as_uint(f);
-    if ((u & 0x7fffffffu) > 0x7f800000u) return (u >> 16) | 0x40u;
-    return (u + 0x7fffu + ((u >> 16) & 1u)) >> 16;
+// two floats rounded to bf16 (nearest even), the first in the lower half
+__device__ __forceinline__ uint32_t pack_bf16(float a, float b) {
+    typedef __attribute__((ext_vector_type(2))) float f32x2_t;
+    typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2_t;
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2_t{a, b}), bf16x2_t));
 }
 
 // 16 bytes of a row as fp32 lanes: 4 floats (fp32) or 8 floats (bf16)
@@ -39,7 +39,7 @@ template <> struct Vec16<bf16_t> {
 };
 
 __device__ __forceinline__ void store_out(float* p, float v) { *p = v; }
-__device__ __forceinline__ void store_out(bf16_t* p, float v) { *p = (bf16_t)f32_to_bf16(v); }
+__device__ __forceinline__ void store_out(bf16_t* p, float v) { *p = (bf16_t)pack_bf16(v, v); }
 
 // ---- cross-lane ------------------------------------------------------------------------
 // DPP controls (GCN/CDNA encoding)

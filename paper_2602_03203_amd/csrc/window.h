@@ -81,6 +81,14 @@ __host__ __device__ inline int attn_rotation(int row, int split, int ntiles) {
     return (int)(((unsigned)row * 37u + (unsigned)split * 11u) % (unsigned)ntiles);
 }
 
+// Which key of a tile of 32 is row (column) n of K in half nt of q.K^T.  Slot u of lane group `quad` of P.V, one 16x16x32 product, is key
+// quad * 8 + u: with the logits transposed, as in the windows, a lane then holds the logits of exactly these keys, and its
+// probabilities are an operand as they are.  head_dim 128: a lane's two logits are neighbours and go to LDS in one store.  head_dim 64, where
+// the operand comes straight from the cache, whose rows should not be every second one (128 rows of 2112 pairs 14.8 us, so 15.3): key, key + 4.
+template <int D> __host__ __device__ constexpr int attn_qk_key(int nt, int n) { return D == 128 ? 2 * n + nt : n / 4 * 8 + nt * 4 + n % 4; }
+// ... and where the keys of a tile lie in LDS, so that the rows of a half follow each other
+template <int D> __host__ __device__ constexpr int attn_qk_row(int key) { return D == 128 ? key % 2 * 16 + key / 2 : key / 4 % 2 * 16 + key / 8 * 4 + key % 4; }
+
 // bf16 pairs with an infinity or a NaN among them
 __device__ __forceinline__ bool pair_not_finite(uint32_t w) { return (w & 0x7f80u) == 0x7f80u || (w & 0x7f800000u) == 0x7f800000u; }
 

@@ -10,15 +10,20 @@
 //
 // Operands change places against attn_kernel (logits K.Q^T, outputs V^T.P^T: the same products, transposed), so that every
 // result of a lane belongs to ONE query: a row maximum takes two cross-lane steps instead of four for each of four queries, and a
-// correction is one exponential instead of four.  Lane (quad, n16): query n16, keys quad * 4 + i of either half of the tile.
+// correction is one exponential instead of four.  Lane (quad, n16): query n16, keys quad * 8 .. + 7 of the tile (attn_qk_key), which are the keys
+// of its share of P.V: the probabilities become an operand in the registers they are in.
 //
 // A step that splits a row merges the splits' records eight at a time, weighed by the largest maximum of the eight.  A workgroup here
 // meets the splits one after the other, so it walks the keys once before, for the maxima alone (SPLIT).
 //
-// Bound by the vector work of the softmax (a product of 16 queries with 32 keys takes 16 matrix and some 120 vector instructions).
-// 128 rows of 2048 pairs, 128 steps: 205 us (0.35 PFLOP/s) against 2.9 ms step by step; with features 200 us (271 with attn_kernel's
-// operand order) and 106 us for the planes.  Two groups: with one the K and V tiles are read twice as often, with three the
-// registers spill.
+// Bound by instruction issue: two groups of 16 queries with 32 keys take 32 matrix and some 260 vector instructions (64 of them where a
+// maximum moved, which it does in most of the eight tiles of a wavefront), 4100 cycles for the two wavefronts of a SIMD; of a workgroup's
+// 46 000 cycles 2700 are its start and 5000 its merge.  128 rows of 2048 pairs, 128 steps: 165 us (0.43 PFLOP/s) against 2.9 ms step by
+// step; with features 165 us and 106 us for the planes.  It was 206 us with the probabilities through LDS, a merge of every group by itself with scalar
+// reads (6600 cycles), a branch per group in every loop, a walk whose counter was not known to be the same for a wavefront (masks
+// in every tile), and V waited for together with the next tile's K.  Measured and not kept: K as operand straight from the L2 (16 rows of
+// 64 bytes a load: 218 us against 182); all of a tile's operands read ahead, higher wavefront priority around the products: no
+// difference.  Two groups: with one the K and V tiles are read twice as often, with three the registers spill.
 //
 // The feature planes are sums over the steps IN ORDER, one fp32 addition per step: a second launch recomputes the logits (the
 // same products again: the same bits) with a pair per lane, its wavefronts walking the steps in order, so every plane is
@@ -41,25 +46,24 @@ union X128 {
 static constexpr float kXNegBig = -1.0e30f;
 static constexpr int kXWaves = 8, kXThreads = kXWaves * kWave;
 static constexpr int kXKT = 32;                     // keys of a tile
-static constexpr int kXPS = kXKT + 8;               // bf16 row stride of a P tile
 static constexpr int kSplitBatch = 64;              // splits whose maxima are held at once (a multiple of the merge's eight)
 
 // GROUPS: groups of SPG steps per workgroup, at most
-template <int D, int GROUPS> struct WindowCfg {
+template <int D, int GROUPS, bool SPLIT = false> struct WindowCfg {
     static constexpr int CH = D / 8, ET = D / 16, KS = D / 32;   // 16-byte chunks of a row, channel tiles, k-steps
-    static constexpr int KRS = D * 2 + 16;                       // padded byte stride of a K (D = 128) or query row in LDS
+    static constexpr int KRS = D * 2 + 16;                       // padded byte stride of a K or query row in LDS
     static constexpr int TERMS = D == 64 ? 3 : 1;                // bf16 terms of a probability
     static constexpr int PART = D + 4;                           // float stride of a wavefront's partial accumulator [16][D]
-    // dynamic LDS: per wavefront K tile [32][KRS] bytes (D = 128) and P tiles [GROUPS][TERMS][16][40] bf16, later in their place its
-    // partial accumulators [TERMS][16][PART] | queries [GROUPS][16][KRS] | m, l, exact l, weights [8][16] floats each | with splits:
-    // maxima [kSplitBatch][GROUPS * 16], merged splits [GROUPS * 16][D], their maxima and normalisers [GROUPS * 16], correction and
+    // dynamic LDS: per wavefront K tile [32][KRS] bytes, later in its place the partial accumulators [JOINT][TERMS][16][PART] (JOINT: groups
+    // merged at once) | queries [GROUPS][16][KRS] | m, l, exact l, weights [8][16] floats each | with splits:
+    // maxima [kSplitBatch][GROUPS * 16], merged splits [GROUPS * 16][D], their maxima [GROUPS * 16] and normalisers [2][GROUPS * 16], correction and
     // weight of the split being merged [16]
-    static constexpr size_t K_BYTES = D == 128 ? (size_t)kXKT * KRS : 0;
-    static constexpr size_t P_BYTES = (size_t)GROUPS * TERMS * 16 * kXPS * 2, PART_BYTES = (size_t)TERMS * 16 * PART * 4;
-    static constexpr size_t WAVE_BYTES = K_BYTES + P_BYTES > PART_BYTES ? K_BYTES + P_BYTES : PART_BYTES;
+    static constexpr int JOINT = !SPLIT && TERMS == 1 ? GROUPS : 1;
+    static constexpr size_t K_BYTES = (size_t)kXKT * KRS, PART_BYTES = (size_t)TERMS * 16 * PART * 4;
+    static constexpr size_t WAVE_BYTES = K_BYTES > JOINT * PART_BYTES ? K_BYTES : JOINT * PART_BYTES;
     static constexpr size_t Q_BYTES = (size_t)GROUPS * 16 * KRS;
-    static constexpr size_t LDS_BYTES = kXWaves * WAVE_BYTES + Q_BYTES + 4 * sizeof(float) * kXWaves * 16;
-    static constexpr size_t MERGE_BYTES = sizeof(float) * (GROUPS * 16 * (kSplitBatch + D + 2) + 32);
+    static constexpr size_t LDS_BYTES = kXWaves * WAVE_BYTES + Q_BYTES + 4 * sizeof(float) * JOINT * kXWaves * 16;
+    static constexpr size_t MERGE_BYTES = sizeof(float) * (GROUPS * 16 * (kSplitBatch + D + 3) + 32);
 };
 
 // maximum / sum over the four lanes that share a query (lane % 16)
@@ -84,10 +88,10 @@ __device__ __forceinline__ uint32_t float_order(float f) {
 __device__ __forceinline__ float order_float(uint32_t o) { return __uint_as_float((o & 0x80000000u) ? o ^ 0x80000000u : ~o); }
 
 template <int D, bool FEAT, bool SPLIT, int GROUPS>
-__global__ __launch_bounds__(kXThreads, 2) void window_attn_kernel(const WindowParams P, int spg, int gpb, int blocks) {
-    using C = WindowCfg<D, GROUPS>;
-    constexpr int CH = C::CH, ET = C::ET, KS = C::KS, KRS = C::KRS, TERMS = C::TERMS, PART = C::PART;
-    constexpr int KL = D == 128 ? 8 : 4;   // 16-byte K loads per lane and tile
+__global__ __launch_bounds__(kXThreads, 2) void window_attn_kernel(const WindowParams P, int spg, int blocks) {
+    using C = WindowCfg<D, GROUPS, SPLIT>;
+    constexpr int CH = C::CH, ET = C::ET, KS = C::KS, KRS = C::KRS, TERMS = C::TERMS, PART = C::PART, JOINT = C::JOINT, STAT = JOINT * kXWaves * 16;
+    constexpr int KL = CH / 2;   // 16-byte K loads per lane and tile
     // The workgroups of one row sit on one XCD (blocks are dealt to the eight XCDs round robin) and share its L2; fewer than eight
     // rows are spread over the XCDs.
     const bool few = P.rows < 8;
@@ -100,13 +104,12 @@ __global__ __launch_bounds__(kXThreads, 2) void window_attn_kernel(const WindowP
 
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     unsigned char* my_k = smem + (size_t)wave * C::WAVE_BYTES;
-    uint16_t* my_pb = reinterpret_cast<uint16_t*>(my_k + C::K_BYTES);
     unsigned char* s_q = smem + kXWaves * C::WAVE_BYTES;
-    float* s_m = reinterpret_cast<float*>(s_q + C::Q_BYTES);   // [8][16]
-    float *s_l = s_m + kXWaves * 16, *s_lx = s_l + kXWaves * 16, *s_w = s_lx + kXWaves * 16;
-    uint32_t* s_top = reinterpret_cast<uint32_t*>(s_w + kXWaves * 16);   // [kSplitBatch][GROUPS * 16] maxima of the splits
+    float* s_m = reinterpret_cast<float*>(s_q + C::Q_BYTES);   // [JOINT][8][16]
+    float *s_l = s_m + STAT, *s_lx = s_l + STAT, *s_w = s_lx + STAT;
+    uint32_t* s_top = reinterpret_cast<uint32_t*>(s_w + STAT);   // [kSplitBatch][GROUPS * 16] maxima of the splits
     float* s_out = reinterpret_cast<float*>(s_top + kSplitBatch * GROUPS * 16);   // [GROUPS * 16][D]
-    float *s_out_m = s_out + GROUPS * 16 * D, *s_out_l = s_out_m + GROUPS * 16, *s_c = s_out_l + GROUPS * 16, *s_cw = s_c + 16;
+    float *s_out_m = s_out + GROUPS * 16 * D, *s_out_l = s_out_m + GROUPS * 16, *s_c = s_out_l + 2 * GROUPS * 16, *s_cw = s_c + 16;
     __shared__ int s_bad;   // a new value that not every step of a run sees is infinite or NaN
     __shared__ int s_split_len[GROUPS * 16], s_nsplit[GROUPS * 16], s_tiles[GROUPS * 16];
 
@@ -128,11 +131,11 @@ __global__ __launch_bounds__(kXThreads, 2) void window_attn_kernel(const WindowP
     }
 
     // matrix column r of group k: step t_first + k * spg + r / G, head r % G
-    const int t_first = blk * gpb * spg, t_end = min(t_first + gpb * spg, P.T);
+    const int t_first = blk * GROUPS * spg, t_end = min(t_first + GROUPS * spg, P.T);
     auto step_of = [&](int k, int r) { return t_first + k * spg + r / G; };
     auto q_row = [&](int k, int r) { return (((size_t)min(step_of(k, r), P.T - 1) * P.batch + b) * P.n_kv + hkv) * G + r % G; };
 
-    for (int i = tid; i < gpb * 16 * CH; i += kXThreads) {   // the queries, for all wavefronts
+    for (int i = tid; i < GROUPS * 16 * CH; i += kXThreads) {   // the queries, for all wavefronts
         const int k = i / (16 * CH), r = i / CH % 16, ch = i % CH;
         const bool live = r < spg * G && step_of(k, r) < P.T;
         const xu32x4_t q = reinterpret_cast<const xu32x4_t*>(P.q_seq)[q_row(k, r) * CH + ch];
@@ -149,6 +152,9 @@ __global__ __launch_bounds__(kXThreads, 2) void window_attn_kernel(const WindowP
         }
     }
     __syncthreads();
+    // Counted here, where all wavefronts have the row's length, and looked at when the results are out (at the end, the answer took 1 us to come).
+    uint32_t arrived = 0;
+    if (!FEAT && blocks > 1 && tid == 0) arrived = __hip_atomic_fetch_add(&P.row_cnt[row], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 
     // A run of steps of one plan is taken together (nearly always all of the workgroup's).  A step that does not see a pair gives it
     // weight 0, which must not meet an infinity or a NaN of a new value: where there are any, the run starts over one step at a time.
@@ -176,11 +182,11 @@ __global__ __launch_bounds__(kXThreads, 2) void window_attn_kernel(const WindowP
             const int kc = min(key, n_max - 1);
             return kc < n0 ? cache + (size_t)kc * CH : fresh + (size_t)(kc - n0) * new_stride;
         };
-        // K of a tile in the layout of the matrix operand: lane (quad, n16) holds key nt * 16 + n16, 16-byte chunk ks * 4 + quad
+        // K of a tile in the layout of the matrix operand: lane (quad, n16) holds key attn_qk_key(nt, n16), 16-byte chunk ks * 4 + quad
         auto fetch_operand = [&](int base, X128 (&x)[2 * KS]) {
 #pragma unroll
             for (int nt = 0; nt < 2; ++nt) {
-                const xu32x4_t* p = pair_of(Kr, kn, base + nt * 16 + n16);
+                const xu32x4_t* p = pair_of(Kr, kn, base + attn_qk_key<D>(nt, n16));
 #pragma unroll
                 for (int ks = 0; ks < KS; ++ks) x[nt * KS + ks].u = p[ks * 4 + quad];
             }
@@ -210,7 +216,6 @@ __global__ __launch_bounds__(kXThreads, 2) void window_attn_kernel(const WindowP
                     const int base = start + t * kXKT, mine = min(base / split_len, nsplit - 1);
 #pragma unroll
                     for (int k = 0; k < GROUPS; ++k) {
-                        if (k >= gpb) continue;
                         xf32x4_t c[2];
                         c[0] = c[1] = (xf32x4_t){0.f, 0.f, 0.f, 0.f};
 #pragma unroll
@@ -222,7 +227,7 @@ __global__ __launch_bounds__(kXThreads, 2) void window_attn_kernel(const WindowP
 #pragma unroll
                         for (int nt = 0; nt < 2; ++nt)
 #pragma unroll
-                            for (int i = 0; i < 4; ++i) mx[k] = fmaxf(mx[k], base + nt * 16 + quad * 4 + i < lim[k] ? c[nt][i] * P.scale_log2e : kXNegBig);
+                            for (int i = 0; i < 4; ++i) mx[k] = fmaxf(mx[k], base + attn_qk_key<D>(nt, quad * 4 + i) < lim[k] ? c[nt][i] * P.scale_log2e : kXNegBig);
                     }
                     if (t + 1 == w1 || min((base + kXKT) / split_len, nsplit - 1) != mine) {
 #pragma unroll
@@ -239,7 +244,8 @@ __global__ __launch_bounds__(kXThreads, 2) void window_attn_kernel(const WindowP
 
             int tile_tid = threadIdx.x;   // (opaque as well: what this split needs does not take registers in the walk above)
             asm volatile("" : "+v"(tile_tid));
-            const int lane = tile_tid & (kWave - 1), wave = tile_tid / kWave, n16 = lane & 15, quad = lane >> 4;
+            const int lane = tile_tid & (kWave - 1), n16 = lane & 15, quad = lane >> 4;
+            const int wave = __builtin_amdgcn_readfirstlane(tile_tid / kWave);   // (the walk and its addresses are the wavefront's: scalars, branches)
             const int ntiles = (stop - start + kXKT - 1) / kXKT;
             const int rot = rotate ? attn_rotation(row, sp, ntiles) : 0;
             float m_run[GROUPS], l_run[GROUPS][4], lx_run[GROUPS][4];   // l: one sum per key of a quarter of the tile, as in a single step
@@ -257,33 +263,24 @@ __global__ __launch_bounds__(kXThreads, 2) void window_attn_kernel(const WindowP
                 }
             }
             auto base_of = [&](int t) { return start + (t + rot < ntiles ? t + rot : t + rot - ntiles) * kXKT; };
-            // The next tile's K is fetched a tile ahead, V while the tile's logits and weights are formed.
-            X128 kr[KL], vr[8];   // D = 128: lane (quad, n16) holds key base + quad * 8 + u, 16-byte chunk n16; D = 64: K as operand, V 8 bytes
+            // The next tile's K is fetched a tile ahead, V before the tile's logits and weights are formed.
+            X128 kr[KL], vr[8];   // K: lane holds the keys lane / CH * KL + u, 16-byte chunk lane % CH; V: key quad * 8 + u, a 16th of the row
+            const int kkey = lane / CH * KL, kch = lane % CH, krow = attn_qk_row<D>(kkey);   // (kkey: a multiple of KL, 4 or 8)
             auto fetch_k = [&](int base) {
-                if constexpr (D == 128) {
-                    if (base + kXKT <= n0) {   // a whole tile of cached pairs: one address, constant offsets
-                        const xu32x4_t* p = Kr + (size_t)(base + quad * 8) * CH + n16;
+                if (base + kXKT <= n0) {   // a whole tile of cached pairs: one address, constant offsets
+                    const xu32x4_t* p = Kr + (size_t)(base + kkey) * CH + kch;
 #pragma unroll
-                        for (int u = 0; u < 8; ++u) kr[u].u = p[u * CH];
-                        return;
-                    }
-#pragma unroll
-                    for (int u = 0; u < 8; ++u) kr[u].u = pair_of(Kr, kn, base + quad * 8 + u)[n16];
-                } else {
-                    fetch_operand(base, kr);
+                    for (int u = 0; u < KL; ++u) kr[u].u = p[u * CH];
+                    return;
                 }
+#pragma unroll
+                for (int u = 0; u < KL; ++u) kr[u].u = pair_of(Kr, kn, base + kkey + u)[kch];
             };
             if (wave < ntiles) fetch_k(base_of(wave));
             for (int t = wave; t < ntiles; t += kXWaves) {
                 const int base = base_of(t);
-                X128 kd[D == 128 ? 1 : KL];
-                if constexpr (D == 128) {
 #pragma unroll
-                    for (int u = 0; u < 8; ++u) *reinterpret_cast<xu32x4_t*>(my_k + (quad * 8 + u) * KRS + n16 * 16) = kr[u].u;
-                } else {
-#pragma unroll
-                    for (int u = 0; u < KL; ++u) kd[u] = kr[u];
-                }
+                for (int u = 0; u < KL; ++u) *reinterpret_cast<xu32x4_t*>(my_k + (krow + attn_qk_row<D>(u)) * KRS + kch * 16) = kr[u].u;
                 auto load_v = [&](const xu32x4_t* p, X128& x) {
                     if constexpr (D == 128) {
                         x.u = p[n16];
@@ -293,6 +290,8 @@ __global__ __launch_bounds__(kXThreads, 2) void window_attn_kernel(const WindowP
                         x.w[1] = y.y;
                     }
                 };
+                // The next tile's K before this one's V: what waits for V (the last loads) then finds K there too.
+                if (t + kXWaves < ntiles) fetch_k(base_of(t + kXWaves));
                 if (base + kXKT <= n0) {
                     const xu32x4_t* p = Vr + (size_t)(base + quad * 8) * CH;
 #pragma unroll
@@ -301,104 +300,116 @@ __global__ __launch_bounds__(kXThreads, 2) void window_attn_kernel(const WindowP
 #pragma unroll
                     for (int u = 0; u < 8; ++u) load_v(pair_of(Vr, vn, base + quad * 8 + u), vr[u]);
                 }
-                if (t + kXWaves < ntiles) fetch_k(base_of(t + kXWaves));
                 __builtin_amdgcn_wave_barrier();
                 const bool partial = base + kXKT > n_first;   // some step does not see the whole tile
+                xf32x4_t c[GROUPS][2];
 #pragma unroll
-                for (int k = 0; k < GROUPS; ++k) {
-                    if (k >= gpb) continue;
-                    xf32x4_t c[2];
-                    c[0] = c[1] = (xf32x4_t){0.f, 0.f, 0.f, 0.f};
+                for (int k = 0; k < GROUPS; ++k) c[k][0] = c[k][1] = (xf32x4_t){0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-                    for (int ks = 0; ks < KS; ++ks) {
+                for (int ks = 0; ks < KS; ++ks) {
+                    X128 kb[2];
+#pragma unroll
+                    for (int nt = 0; nt < 2; ++nt) {
+                        kb[nt].u = *reinterpret_cast<const xu32x4_t*>(my_k + (nt * 16 + n16) * KRS + (ks * 4 + quad) * 16);
+                    }
+#pragma unroll
+                    for (int k = 0; k < GROUPS; ++k) {
                         const X128 q = query(k, ks);
 #pragma unroll
-                        for (int nt = 0; nt < 2; ++nt) {
-                            X128 kb;
-                            if constexpr (D == 128) kb.u = *reinterpret_cast<const xu32x4_t*>(my_k + (nt * 16 + n16) * KRS + (ks * 4 + quad) * 16);
-                            else kb = kd[nt * KS + ks];
-                            c[nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kb.v, q.v, c[nt], 0, 0, 0);
-                        }
+                        for (int nt = 0; nt < 2; ++nt) c[k][nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kb[nt].v, q.v, c[k][nt], 0, 0, 0);
                     }
+                }
+                float x[GROUPS][9];   // arguments of the exponentials: eight keys and the correction
+                auto key_of = [&](int j) { return attn_qk_key<D>(j / 4, quad * 4 + j % 4); };
+                float lo = 0.f;
+                bool changed[GROUPS];
+#pragma unroll
+                for (int k = 0; k < GROUPS; ++k) {
                     const int left = lim[k] - base;   // this lane's query sees the tile's keys [0, left)
-                    float x[9];                       // arguments of the exponentials: eight keys and the correction
                     float mn = kXNegBig;
 #pragma unroll
                     for (int j = 0; j < 8; ++j) {
-                        x[j] = c[j / 4][j % 4] * P.scale_log2e;
-                        if (partial && j / 4 * 16 + quad * 4 + j % 4 >= left) x[j] = kXNegBig;
-                        mn = fmaxf(mn, x[j]);
+                        x[k][j] = c[k][j / 4][j % 4] * P.scale_log2e;
+                        mn = fmaxf(mn, x[k][j]);
+                    }
+                    if (partial) {
+                        mn = kXNegBig;
+#pragma unroll
+                        for (int j = 0; j < 8; ++j) {
+                            if (key_of(j) >= left) x[k][j] = kXNegBig;
+                            mn = fmaxf(mn, x[k][j]);
+                        }
                     }
                     mn = fmaxf(m_run[k], quads_max(mn));
-                    const bool changed = mn > m_run[k];
-                    float lo = 0.f;
-                    x[8] = m_run[k];
+                    changed[k] = mn > m_run[k];
+                    x[k][8] = m_run[k];
 #pragma unroll
                     for (int j = 0; j < 9; ++j) {
-                        x[j] -= mn;
-                        lo = fminf(lo, x[j]);
+                        x[k][j] -= mn;
+                        lo = fminf(lo, x[k][j]);
                     }
                     m_run[k] = mn;
-                    if (__any(lo < -126.f)) {   // exp2f's way round denormal results, only where there can be one
+                }
+                if (__any(lo < -126.f)) {   // exp2f's way round denormal results, only where there can be one
 #pragma unroll
-                        for (int j = 0; j < 9; ++j) x[j] = exp2f(x[j]);
-                    } else {
+                    for (int k = 0; k < GROUPS; ++k)
 #pragma unroll
-                        for (int j = 0; j < 9; ++j) x[j] = __builtin_amdgcn_exp2f(x[j]);
-                    }
-                    if (partial) {   // 0 also where a step sees none of the tile
+                        for (int j = 0; j < 9; ++j) x[k][j] = exp2f(x[k][j]);
+                } else {
+#pragma unroll
+                    for (int k = 0; k < GROUPS; ++k)
+#pragma unroll
+                        for (int j = 0; j < 9; ++j) x[k][j] = __builtin_amdgcn_exp2f(x[k][j]);
+                }
+                if (partial) {   // 0 also where a step sees none of the tile
+#pragma unroll
+                    for (int k = 0; k < GROUPS; ++k)
 #pragma unroll
                         for (int j = 0; j < 8; ++j)
-                            if (j / 4 * 16 + quad * 4 + j % 4 >= left) x[j] = 0.f;
-                    }
-                    uint16_t* pb = my_pb + k * TERMS * 16 * kXPS;
-                    uint32_t u[8];   // probabilities rounded to bf16 in the upper half
+                            if (key_of(j) >= lim[k] - base) x[k][j] = 0.f;
+                }
+                X128 pa[GROUPS][TERMS];   // probabilities of query n16 in bf16, term by term: the keys of this lane's logits, quad * 8 + u
+                auto at = [](int u) { return D == 128 ? u % 2 * 4 + u / 2 : u; };   // the u-th of these keys is logit at(u)
 #pragma unroll
-                    for (int j = 0; j < 8; ++j) u[j] = __float_as_uint(x[j]) + 0x8000u;
+                for (int k = 0; k < GROUPS; ++k) {
+                    float y[8];   // rounded
+#pragma unroll
+                    for (int w = 0; w < 4; ++w) {
+                        pa[k][0].w[w] = pack_bf16(x[k][at(2 * w)], x[k][at(2 * w + 1)]);
+                        y[at(2 * w)] = bf16_lo(pa[k][0].w[w]);
+                        y[at(2 * w + 1)] = bf16_hi(pa[k][0].w[w]);
+                    }
 #pragma unroll
                     for (int i = 0; i < 4; ++i) {
-                        if constexpr (TERMS == 1) l_run[k][i] = fmaf(l_run[k][i], x[8], __uint_as_float(u[i] & 0xffff0000u)) + __uint_as_float(u[4 + i] & 0xffff0000u);
-                        else l_run[k][i] = fmaf(l_run[k][i], x[8], x[i]) + x[4 + i];
-                        if constexpr (FEAT) lx_run[k][i] = fmaf(lx_run[k][i], x[8], x[i]) + x[4 + i];
+                        if constexpr (TERMS == 1) l_run[k][i] = fmaf(l_run[k][i], x[k][8], y[i]) + y[4 + i];
+                        else l_run[k][i] = fmaf(l_run[k][i], x[k][8], x[k][i]) + x[k][4 + i];
+                        if constexpr (FEAT) lx_run[k][i] = fmaf(lx_run[k][i], x[k][8], x[k][i]) + x[k][4 + i];
                     }
-                    auto put = [&](uint16_t* p) {   // the upper halves: keys quad * 4 .. + 3 of either half of the tile
+                    if constexpr (TERMS > 1) {   // each term of what the ones before leave (the third has no bits beyond bf16)
 #pragma unroll
-                        for (int nt = 0; nt < 2; ++nt) {
-                            const xu32x2_t w = {__builtin_amdgcn_perm(u[nt * 4 + 1], u[nt * 4], 0x07060302u), __builtin_amdgcn_perm(u[nt * 4 + 3], u[nt * 4 + 2], 0x07060302u)};
-                            *reinterpret_cast<xu32x2_t*>(p + n16 * kXPS + nt * 16 + quad * 4) = w;
-                        }
-                    };
-                    put(pb);
-                    if constexpr (TERMS > 1) {   // each term of what the ones before leave
-#pragma unroll
-                        for (int s = 1; s < TERMS; ++s) {
-#pragma unroll
-                            for (int j = 0; j < 8; ++j) {
-                                x[j] -= __uint_as_float(u[j] & 0xffff0000u);
-                                u[j] = __float_as_uint(x[j]) + (s == 1 ? 0x8000u : 0u);   // (the third has no bits beyond bf16)
-                            }
-                            put(pb + s * 16 * kXPS);
+                        for (int w = 0; w < 4; ++w) {
+                            const float r0 = x[k][at(2 * w)] - y[at(2 * w)], r1 = x[k][at(2 * w + 1)] - y[at(2 * w + 1)];
+                            pa[k][1].w[w] = pack_bf16(r0, r1);
+                            pa[k][2].w[w] = pack_bf16(r0 - bf16_lo(pa[k][1].w[w]), r1 - bf16_hi(pa[k][1].w[w]));
                         }
                     }
-                    if (__any(changed)) {
+                }
+                if (t != wave) {   // (at the first tile there is nothing yet)
+#pragma unroll
+                    for (int k = 0; k < GROUPS; ++k) {
+                        if (!__any(changed[k])) continue;
 #pragma unroll
                         for (int e = 0; e < ET; ++e)
 #pragma unroll
                             for (int i = 0; i < 4; ++i) {
-                                o[k][e][i] *= x[8];
+                                o[k][e][i] *= x[k][8];
                                 if constexpr (TERMS > 1) {
-                                    o2[k][e][i] *= x[8];
-                                    o3[k][e][i] *= x[8];
+                                    o2[k][e][i] *= x[k][8];
+                                    o3[k][e][i] *= x[k][8];
                                 }
                             }
                     }
                 }
-                __builtin_amdgcn_wave_barrier();
-                X128 pa[GROUPS][TERMS];   // query n16, keys base + quad * 8 ..
-#pragma unroll
-                for (int k = 0; k < GROUPS; ++k)
-#pragma unroll
-                    for (int s = 0; s < TERMS; ++s) pa[k][s].u = *reinterpret_cast<const xu32x4_t*>(my_pb + ((k * TERMS + s) * 16 + n16) * kXPS + quad * 8);
                 // V^T: tile e = channel n16 * ET + e over this lane's 8 keys (8 x ET transpose in registers)
                 auto transposed = [&](int e) {
                     const uint32_t sel = (e & 1) ? 0x07060302u : 0x05040100u;
@@ -425,7 +436,6 @@ __global__ __launch_bounds__(kXThreads, 2) void window_attn_kernel(const WindowP
                     const X128 vb = transposed(e);
 #pragma unroll
                     for (int k = 0; k < GROUPS; ++k) {
-                        if (k >= gpb) continue;
                         o[k][e] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vb.v, pa[k][0].v, o[k][e], 0, 0, 0);
                         if constexpr (TERMS > 1) {
                             o2[k][e] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vb.v, pa[k][1].v, o2[k][e], 0, 0, 0);
@@ -436,31 +446,35 @@ __global__ __launch_bounds__(kXThreads, 2) void window_attn_kernel(const WindowP
                 __builtin_amdgcn_wave_barrier();
             }
 
-            // ---- merge the wavefronts' partials, one group after the other ------------------------------------
+            // ---- merge the wavefronts' partials, JOINT groups at once ------------------------------------
             int tid = threadIdx.x;   // (opaque: or everything that the merge derives from it is kept in registers over the tile loop)
             asm volatile("" : "+v"(tid));
 #pragma unroll
-            for (int k = 0; k < GROUPS; ++k) {
-                if (k >= gpb) continue;
-                auto live = [&](int r) { return r < spg * G && step_of(k, r) >= ta && step_of(k, r) < tb; };
-                float* dst = reinterpret_cast<float*>(my_k) + n16 * PART + quad * 4 * ET;   // the loop is over
+            for (int k0 = 0; k0 < GROUPS; k0 += JOINT) {
+                auto live = [&](int k, int r) { return r < spg * G && step_of(k, r) >= ta && step_of(k, r) < tb; };
                 auto publish = [&](float* to, const xf32x4_t* x) {
 #pragma unroll
                     for (int i = 0; i < 4; ++i)
 #pragma unroll
                         for (int e = 0; e < ET; e += 4) *reinterpret_cast<float4*>(to + i * ET + e) = make_float4(x[e][i], x[e + 1][i], x[e + 2][i], x[e + 3][i]);
                 };
-                publish(dst, o[k]);
-                if constexpr (TERMS > 1) {
-                    publish(dst + 16 * PART, o2[k]);
-                    publish(dst + 32 * PART, o3[k]);
-                }
-                const float ls = quads_sum((l_run[k][0] + l_run[k][1]) + (l_run[k][2] + l_run[k][3]));
-                const float lxs = FEAT ? quads_sum((lx_run[k][0] + lx_run[k][1]) + (lx_run[k][2] + lx_run[k][3])) : 0.f;
-                if (quad == 0) {
-                    s_m[wave * 16 + n16] = m_run[k];
-                    s_l[wave * 16 + n16] = ls;
-                    if (FEAT) s_lx[wave * 16 + n16] = lxs;
+#pragma unroll
+                for (int g = 0; g < JOINT; ++g) {
+                    const int k = k0 + g;
+                    float* dst = reinterpret_cast<float*>(my_k + g * C::PART_BYTES) + n16 * PART + quad * 4 * ET;   // the loop is over
+                    publish(dst, o[k]);
+                    if constexpr (TERMS > 1) {
+                        publish(dst + 16 * PART, o2[k]);
+                        publish(dst + 32 * PART, o3[k]);
+                    }
+                    const float ls = quads_sum((l_run[k][0] + l_run[k][1]) + (l_run[k][2] + l_run[k][3]));
+                    const float lxs = FEAT ? quads_sum((lx_run[k][0] + lx_run[k][1]) + (lx_run[k][2] + lx_run[k][3])) : 0.f;
+                    if (quad == 0) {
+                        const int i = (g * kXWaves + wave) * 16 + n16;
+                        s_m[i] = m_run[k];
+                        s_l[i] = ls;
+                        if (FEAT) s_lx[i] = lxs;
+                    }
                 }
                 __syncthreads();
                 if (s_bad && tb - ta > 1) {   // (the same for every thread: all tiles of the split are done)
@@ -469,20 +483,20 @@ __global__ __launch_bounds__(kXThreads, 2) void window_attn_kernel(const WindowP
                     break;
                 }
                 const bool merging = SPLIT && nused > 1;
-                if (tid < kXWaves * 16) {   // weight of every partial; row maximum and exact normaliser for the second launch
-                    const int r = tid % 16;
+                if (tid < JOINT * kXWaves * 16) {   // weight of every partial; row maximum and exact normaliser for the second launch
+                    const int r = tid % 16, g = tid / (kXWaves * 16), at = g * kXWaves * 16 + r;
                     float mn = kXNegBig;
 #pragma unroll
-                    for (int g2 = 0; g2 < kXWaves; ++g2) mn = fmaxf(mn, s_m[g2 * 16 + r]);
+                    for (int g2 = 0; g2 < kXWaves; ++g2) mn = fmaxf(mn, s_m[at + g2 * 16]);
                     s_w[tid] = exp2f(s_m[tid] - mn);
-                    if (FEAT && tid < 16 && live(r)) {
+                    if (FEAT && tid % (kXWaves * 16) < 16 && live(k0 + g, r)) {
                         float lx = 0.f;
 #pragma unroll
-                        for (int g2 = 0; g2 < kXWaves; ++g2) lx = fmaf(s_lx[g2 * 16 + r], exp2f(s_m[g2 * 16 + r] - mn), lx);
-                        P.stat[((size_t)row * P.T + step_of(k, r)) * G + r % G] = make_float2(mn, 1.0f / lx);
+                        for (int g2 = 0; g2 < kXWaves; ++g2) lx = fmaf(s_lx[at + g2 * 16], exp2f(s_m[at + g2 * 16] - mn), lx);
+                        P.stat[((size_t)row * P.T + step_of(k0 + g, r)) * G + r % G] = make_float2(mn, 1.0f / lx);
                     }
-                } else if (merging && tid < (kXWaves + 1) * 16) {   // the split's record joins the others as in a single step: c0, weight
-                    const int r = tid % 16, q = k * 16 + r;
+                } else if (merging && tid < (kXWaves + 1) * 16) {   // (JOINT = 1) the split's record joins the others as in a single step: c0, weight
+                    const int r = tid % 16, q = k0 * 16 + r;
                     const uint32_t* tops = s_top + (sp % kSplitBatch) * (GROUPS * 16) + q;
                     float cm = sp == 0 ? kXNegBig : s_out_m[q], c0 = 1.f;
                     if (sp % 8 == 0) {
@@ -496,45 +510,56 @@ __global__ __launch_bounds__(kXThreads, 2) void window_attn_kernel(const WindowP
                 }
                 __syncthreads();
 #pragma unroll
-                for (int j = 0; j < 16 * D / kXThreads; ++j) {
-                    const int r = (tid + j * kXThreads) / D, d = tid % D;
-                    float a = 0.f, l = 0.f;
-                    float a2 = 0.f, a3 = 0.f;
+                for (int g = 0; g < JOINT; ++g) {
+                    const int k = k0 + g;
+                    if (tid < 16 * D / 4) {   // four channels of a query
+                        const int r = tid / (D / 4), d = tid % (D / 4) * 4;
+                        float a[4] = {0.f, 0.f, 0.f, 0.f}, a2[4] = {0.f, 0.f, 0.f, 0.f}, a3[4] = {0.f, 0.f, 0.f, 0.f}, l = 0.f;
+                        auto add = [](const float* p, float w, float (&to)[4]) {
+                            const float4 v = *reinterpret_cast<const float4*>(p);
+                            to[0] = fmaf(v.x, w, to[0]);
+                            to[1] = fmaf(v.y, w, to[1]);
+                            to[2] = fmaf(v.z, w, to[2]);
+                            to[3] = fmaf(v.w, w, to[3]);
+                        };
 #pragma unroll
-                    for (int g2 = 0; g2 < kXWaves; ++g2) {
-                        const float *p = reinterpret_cast<const float*>(smem + (size_t)g2 * C::WAVE_BYTES) + r * PART + d, w = s_w[g2 * 16 + r];
-                        a = fmaf(p[0], w, a);
+                        for (int g2 = 0; g2 < kXWaves; ++g2) {
+                            const float *p = reinterpret_cast<const float*>(smem + (size_t)g2 * C::WAVE_BYTES + g * C::PART_BYTES) + r * PART + d, w = s_w[(g * kXWaves + g2) * 16 + r];
+                            add(p, w, a);
+                            if constexpr (TERMS > 1) {
+                                add(p + 16 * PART, w, a2);
+                                add(p + 32 * PART, w, a3);
+                            }
+                            l = fmaf(s_l[(g * kXWaves + g2) * 16 + r], w, l);
+                        }
                         if constexpr (TERMS > 1) {
-                            a2 = fmaf(p[16 * PART], w, a2);
-                            a3 = fmaf(p[32 * PART], w, a3);
-                        }
-                    }
-                    if constexpr (TERMS > 1) a = add_terms(a, a2, a3);
 #pragma unroll
-                    for (int g2 = 0; g2 < kXWaves; ++g2) l = fmaf(s_l[g2 * 16 + r], s_w[g2 * 16 + r], l);
-                    if (merging) {
-                        float *sum = s_out + (k * 16 + r) * D + d, before = sp == 0 ? 0.f : *sum * s_c[r];
-                        *sum = a = fmaf(a, s_cw[r], before);
-                        if (d < 1 || sp == nused - 1) {   // (every thread that divides by it works it out)
-                            before = sp == 0 ? 0.f : s_out_l[k * 16 + r] * s_c[r];
-                            l = fmaf(l, s_cw[r], before);
+                            for (int i = 0; i < 4; ++i) a[i] = add_terms(a[i], a2[i], a3[i]);
+                        }
+                        if (merging) {
+                            float* sum = s_out + (k * 16 + r) * D + d;
+                            const float c0 = s_c[r], cw = s_cw[r];
+#pragma unroll
+                            for (int i = 0; i < 4; ++i) {
+                                const float before = sp == 0 ? 0.f : sum[i] * c0;
+                                sum[i] = a[i] = fmaf(a[i], cw, before);
+                            }
+                            l = fmaf(l, cw, sp == 0 ? 0.f : s_out_l[(sp & 1) * 16 * GROUPS + k * 16 + r] * c0);
+                            if (d == 0) s_out_l[((sp & 1) ^ 1) * 16 * GROUPS + k * 16 + r] = l;   // (read by the others of the row before the next barrier)
+                        }
+                        if (sp == nused - 1 && live(k, r)) {
+                            const xu32x2_t v = {pack_bf16(a[0] / l, a[1] / l), pack_bf16(a[2] / l, a[3] / l)};
+                            *reinterpret_cast<xu32x2_t*>(reinterpret_cast<bf16_t*>(P.out_seq) + q_row(k, r) * D + d) = v;
                         }
                     }
-                    if (sp == nused - 1 && live(r)) store_out(reinterpret_cast<bf16_t*>(P.out_seq) + q_row(k, r) * D + d, a / l);
-                    if (merging && d == 0 && sp < nused - 1) s_out_l[k * 16 + r] = l;
                 }
                 __syncthreads();
             }
         }
     }
-    if constexpr (!FEAT) {   // the last workgroup of the row sets its length: all of them have read it by then
-        if (tid == 0) {
-            const bool last = blocks == 1 || __hip_atomic_fetch_add(&P.row_cnt[row], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == (uint32_t)blocks - 1;
-            if (last) {
-                if (blocks > 1) __hip_atomic_store(&P.row_cnt[row], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                P.len[row] = n1;
-            }
-        }
+    if (!FEAT && tid == 0 && arrived == (uint32_t)blocks - 1) {   // the last workgroup of the row sets its length: all of them have read it by then
+        if (blocks > 1) __hip_atomic_store(&P.row_cnt[row], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        P.len[row] = n1;
     }
 }
 
@@ -686,26 +711,31 @@ __global__ __launch_bounds__(kXThreads) void window_feat_planes_kernel(const Win
 
 template <int D, bool FEAT, bool SPLIT, int GROUPS>
 static fk_status window_launch(const WindowParams& P, hipStream_t st) {
-    using C = WindowCfg<D, GROUPS>;
-    const int spg = 16 / P.g;
-    // two groups share every tile that is loaded; one where that leaves CUs without a workgroup
-    const int gpb = GROUPS > 1 && (long long)P.rows * ((P.T + 2 * spg - 1) / (2 * spg)) >= 256 ? 2 : 1;
-    const int blocks = (P.T + spg * gpb - 1) / (spg * gpb);
+    using C = WindowCfg<D, GROUPS, SPLIT>;
+    const int spg = 16 / P.g, blocks = (P.T + spg * GROUPS - 1) / (spg * GROUPS);
     auto kern = window_attn_kernel<D, FEAT, SPLIT, GROUPS>;
     const size_t lds = C::LDS_BYTES + (SPLIT ? C::MERGE_BYTES : 0);
     static bool lds_ok[kMaxDevices] = {};
     if (!allow_dynamic_lds((const void*)kern, lds, lds_ok)) return FK_ERR_LAUNCH;
-    hipLaunchKernelGGL(kern, dim3((P.rows < 8 ? P.rows : (P.rows + 7) / 8 * 8) * blocks), dim3(kXThreads), lds, st, P, spg, gpb, blocks);
+    hipLaunchKernelGGL(kern, dim3((P.rows < 8 ? P.rows : (P.rows + 7) / 8 * 8) * blocks), dim3(kXThreads), lds, st, P, spg, blocks);
     return launch_status();
 }
 
+template <int D, bool FEAT, bool SPLIT>
+static fk_status window_groups(const WindowParams& P, hipStream_t st) {
+    // two groups share every tile that is loaded; one where that leaves CUs without a workgroup
+    const int spg = 16 / P.g;
+    if ((long long)P.rows * ((P.T + 2 * spg - 1) / (2 * spg)) >= 256) return window_launch<D, FEAT, SPLIT, 2>(P, st);
+    return window_launch<D, FEAT, SPLIT, 1>(P, st);
+}
+
 fk_status window_attn(const WindowParams& P, bool split, hipStream_t st) {
-    if (P.shape.head_dim == 64) return split ? window_launch<64, false, true, 2>(P, st) : window_launch<64, false, false, 2>(P, st);
-    return split ? window_launch<128, false, true, 2>(P, st) : window_launch<128, false, false, 2>(P, st);
+    if (P.shape.head_dim == 64) return split ? window_groups<64, false, true>(P, st) : window_groups<64, false, false>(P, st);
+    return split ? window_groups<128, false, true>(P, st) : window_groups<128, false, false>(P, st);
 }
 
 fk_status window_feat(const WindowParams& P, int max_len, hipStream_t st) {
-    const fk_status s = window_launch<128, true, false, 2>(P, st);
+    const fk_status s = window_groups<128, true, false>(P, st);
     if (s != FK_OK) return s;
     const dim3 grid((max_len + kXWaves * 32 - 1) / (kXWaves * 32), P.rows);
     if (P.g <= 4) hipLaunchKernelGGL(window_feat_planes_kernel<4>, grid, dim3(kXThreads), 0, st, P);
