@@ -260,7 +260,6 @@ __global__ __launch_bounds__((AttnCfg<T, D, G>::THREADS)) void attn_kernel(const
         if (P.by_length) row = row_by_length<C::THREADS>(P.len, gridDim.y, P.cap, row, reinterpret_cast<int*>(smem));
     }
     const int split = blockIdx.x;
-    const int b = row / P.n_kv, hkv = row % P.n_kv;
     const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
 
     // PVM: head | P tiles | K tiles, the partial accumulators live in the K tiles; fp32: acc | head
@@ -277,9 +276,9 @@ __global__ __launch_bounds__((AttnCfg<T, D, G>::THREADS)) void attn_kernel(const
     const int n_old = min(max(P.len[row], 0), P.cap);
     const bool do_append = appending && n_old < P.cap;
     const int n = n_old + (do_append ? 1 : 0);
-    // splits in use; if the caller's max_len was too small the last split runs on to the row's end (slower, still right)
-    const int used = min((n + P.split_len - 1) / P.split_len, P.nsplit);
-    T* out = reinterpret_cast<T*>(P.out) + ((size_t)b * P.n_kv + hkv) * G * D;
+    // if the caller's max_len was too small the last split runs on to the row's end (slower, still right)
+    const bool one_split = n <= P.split_len || P.nsplit == 1;   // (no division before the loads: they wait for what is worked out here)
+    T* out = reinterpret_cast<T*>(P.out) + (size_t)row * G * D;
 
     // Every workgroup of the row calls finish() once, as its last action.  With one workgroup per
     // row it just publishes the new length.  With several, all of them (also those whose split lies
@@ -308,7 +307,8 @@ __global__ __launch_bounds__((AttnCfg<T, D, G>::THREADS)) void attn_kernel(const
             if (do_append && tid == 0) P.len[row] = n;
             return;
         }
-        if (!appending && used <= 1) return;  // same decision in every workgroup of the row
+        if (!appending && one_split) return;  // same decision in every workgroup of the row
+        const int used = min((n + P.split_len - 1) / P.split_len, P.nsplit);   // splits in use
         if (wrote_record) wait_stores_done();
         __syncthreads();
         if (tid == 0) {
@@ -364,12 +364,12 @@ __global__ __launch_bounds__((AttnCfg<T, D, G>::THREADS)) void attn_kernel(const
         finish(false);
         return;
     }
-    if (split >= used) {
+    const int start = split * P.split_len;
+    if (start >= n) {
         finish(false);
         return;
     }
-    const int start = split * P.split_len;
-    const int end = split == used - 1 ? n : start + P.split_len;
+    const int end = split == P.nsplit - 1 ? n : min(n, start + P.split_len);
 
     T* Kr = reinterpret_cast<T*>(P.K) + (size_t)row * P.cap * D;
     T* Vr = reinterpret_cast<T*>(P.V) + (size_t)row * P.cap * D;
@@ -384,14 +384,14 @@ __global__ __launch_bounds__((AttnCfg<T, D, G>::THREADS)) void attn_kernel(const
         } else if (tid < 2 * CH) {
             reinterpret_cast<uint4*>(Vr + (size_t)n_old * D)[tid - CH] = vnew_row[tid - CH];
         } else if (tid == 2 * CH) {
-            P.pos[(size_t)row * P.cap + n_old] = P.pos_new[b];
+            P.pos[(size_t)row * P.cap + n_old] = P.pos_new[row / P.n_kv];
         }
         if constexpr (!C::PVM) __syncthreads();  // the fp32 path reads the row back from the cache
     }
     const int new_slot = owns_new ? n_old : -1;
     const uint4* Krow = reinterpret_cast<const uint4*>(Kr);
     const uint4* Vrow = reinterpret_cast<const uint4*>(Vr);
-    const T* qrow = reinterpret_cast<const T*>(P.q) + ((size_t)b * P.n_kv + hkv) * G * D;
+    const T* qrow = reinterpret_cast<const T*>(P.q) + (size_t)row * G * D;
 
     const int dl = lane % CH;   // 16-byte chunk of the row (P.V layout)
     const int kgv = lane / CH;  // key group (P.V layout)
@@ -768,11 +768,11 @@ __global__ __launch_bounds__((AttnCfg<T, D, G>::THREADS)) void attn_kernel(const
 #pragma unroll 8
             for (int g2 = 0; g2 < NG; ++g2) a = fmaf(s_acc[(size_t)g2 * C::ACC_STRIDE + (size_t)h * D + d], s_w[g2 * G + h], a);
         }
-        if (d == 0 || used == 1) {
+        if (d == 0 || one_split) {
 #pragma unroll 8
             for (int g2 = 0; g2 < NG; ++g2) ls = fmaf(s_l[g2 * G + h], s_w[g2 * G + h], ls);
         }
-        if (used == 1) {
+        if (one_split) {
             store_out(out + idx, a / ls);
         } else {
             st_agent(rec + (size_t)h * (D + 2) + d, a);
@@ -847,7 +847,7 @@ __global__ __launch_bounds__((AttnCfg<T, D, G>::THREADS)) void attn_kernel(const
             }
         }
     }
-    finish(used > 1);
+    finish(!one_split);
 }
 
 template <typename T, int D, int G>
