@@ -30,7 +30,14 @@ static constexpr int kSelLdsHead = kRangeWords + 4 * 256 + 32 + kRangePart;  // 
 // a workspace between them): kSelChunk workgroups, one per chunk of a row, each keep the k best candidates of
 // their chunk (any pair among the row's k best is among its chunk's k best, under the same total order); kSelMerge
 // workgroups, one per row, then select among the chunks' survivors, whose keys fit LDS.  Same result, bit for bit.
+//   A chunk need not select at all where a bound is known that at least k of the row's pairs reach: it passes on what reaches the bound.  The bound
+// is a guess, the same for all chunks of a row: of a sample of the row, one key from each of 2048 stretches, the r-th best, r so far
+// above the k * 2048 / n expected among the k best (six standard deviations and eight) that fewer than k pairs over it do not happen by chance.
+// The merge counts, and selects from the whole row, slowly, if it does; a chunk with more than k pairs over the bound (ties) selects.
+// 32 rows of 131072 pairs, the best 1920: chunks that select 20.5 us and the merge of 15360 survivors 25.7; so 14.2 and, of 4500, 11.4 (20.8 and 13.5 with
+// the chunks of a row on all XCDs, each of which then fetches the sample).
 enum { kSelWhole = 0, kSelChunk = 1, kSelMerge = 2 };
+static constexpr int kSelSample = 2048;
 struct SelSplit {
     int nchunk;      // chunks per row
     int chunk_len;   // candidates per chunk (the last chunk runs on to the row's end)
@@ -43,8 +50,13 @@ __global__ __launch_bounds__(THREADS) FK_TWO_PER_CU void select_keep_kernel(cons
                                                               const int32_t* __restrict__ len,
                                                               int cap, int budget, int recent, int lds_keys,
                                                               int32_t* __restrict__ keep, SelSplit sp) {
-    const int row = MODE == kSelChunk ? blockIdx.x / sp.nchunk : blockIdx.x;
-    const int chunk = MODE == kSelChunk ? blockIdx.x % sp.nchunk : 0;
+    int row = blockIdx.x, chunk = 0;
+    if constexpr (MODE == kSelChunk) {   // blocks are dealt to the eight XCDs in turn: a row's chunks, which all read its sample, on one
+        const int rows = gridDim.x / sp.nchunk, per = (int)blockIdx.x / 8;
+        const bool deal = rows % 8 == 0;
+        row = deal ? per / sp.nchunk * 8 + (int)blockIdx.x % 8 : (int)blockIdx.x / sp.nchunk;
+        chunk = deal ? per % sp.nchunk : (int)blockIdx.x % sp.nchunk;
+    }
     const int n = min(len[row], cap);
     const int kmax = budget - recent;
     int32_t* out = MODE == kSelChunk ? sp.cand + ((size_t)row * sp.nchunk + chunk) * kmax : keep + (size_t)row * budget;
@@ -71,13 +83,81 @@ __global__ __launch_bounds__(THREADS) FK_TWO_PER_CU void select_keep_kernel(cons
         ncand = chunk == sp.nchunk - 1 ? ncand - first : min(ncand - first, sp.chunk_len);
         if (ncand < 0) ncand = 0;
         k = min(kmax, ncand);
-        if (threadIdx.x == 0) sp.count[(size_t)row * sp.nchunk + chunk] = k;
-        if (k == ncand) {  // the whole chunk survives (also: an empty chunk, nothing to keep)
+    }
+    // kSelChunk: a key that at least k pairs of the row reach in all likelihood (0: none was looked for).  Every survivor of a row with a bound
+    // reaches it, so k survivors prove that the k best do.
+    uint32_t bound = 0;
+    constexpr int HELD = 16;   // of a chunk of up to HELD * THREADS pairs every thread holds its share of a wavefront's stretch
+    float held[HELD];
+    const bool holds = MODE == kSelChunk && ncand <= HELD * THREADS;
+    if constexpr (MODE == kSelChunk) {
+        if (holds && ncand > 0) {   // (on their way while the bound is found)
+#pragma unroll
+            for (int u = 0; u < HELD; ++u) held[u] = sc[first + min((wave * HELD + u) * kWave + lane, ncand - 1)];
+        }
+        const int all = n - recent;   // the row's candidates
+        const float mean = (float)kSelSample * (float)kmax / (float)all;
+        const int r = (int)(mean + 6.f * sqrtf(mean)) + 8;
+        if (all >= 8 * kSelSample && 4 * r <= kSelSample && lds_keys >= kSelSample) {
+            for (int i = threadIdx.x; i < kRangeWords + 4 * 256; i += THREADS) s_range[i] = 0;
+            KeyRange kr;
+            static_assert(kSelSample == 2 * THREADS, "two stretches a thread");
+            const float len = (float)all / kSelSample;
+            float v[2];
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {   // a pair of every stretch, its place in it by a hash: no period of the scores fits it
+                const int i = threadIdx.x + u * THREADS;
+                const float frac = (float)((uint32_t)i * 2654435761u >> 8) * (1.f / 16777216.f);
+                v[u] = sc[min((int)(((float)i + frac) * len), all - 1)];
+            }
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+                const uint32_t key = score_key(v[u]);
+                s_key[threadIdx.x + u * THREADS] = key;
+                kr.add(key);
+            }
+            const RangePlan rp = kr.plan(s_wmm);
+            uint32_t left = 0;
+            range_select<THREADS, 2>([&](int i, bool& valid) { valid = true; return s_key[i]; }, kSelSample, (uint32_t)r, s_range, s_hist, s_wtot, rp,
+                                     threadIdx.x, &bound, &left);
+            __syncthreads();   // the sample gives way to the chunk's keys
+        }
+        sc += first;
+        if (ncand == 0 || (k == ncand && bound <= 1)) {  // the whole chunk survives
+            if (threadIdx.x == 0) sp.count[(size_t)row * sp.nchunk + chunk] = k;
             for (int j = threadIdx.x; j < ncand; j += THREADS) out[j] = first + j;
             return;
         }
-        sc += first;
+        if (bound > 1 && holds) {   // what reaches the bound, in order
+            uint32_t over = 0;
+#pragma unroll
+            for (int u = 0; u < HELD; ++u)
+                over += (uint32_t)__popcll(__ballot((wave * HELD + u) * kWave + lane < ncand && score_key(held[u]) >= bound));
+            if (lane == 0) s_wtot[wave] = over;
+            __syncthreads();
+            uint32_t before = 0, total = 0;
+#pragma unroll
+            for (int w = 0; w < WAVES; ++w) {
+                before += w < wave ? s_wtot[w] : 0u;
+                total += s_wtot[w];
+            }
+            if (total <= (uint32_t)kmax) {
+                if (threadIdx.x == 0) sp.count[(size_t)row * sp.nchunk + chunk] = (int)total;
+#pragma unroll
+                for (int u = 0; u < HELD; ++u) {
+                    const int i = (wave * HELD + u) * kWave + lane;
+                    const bool in = i < ncand && score_key(held[u]) >= bound;
+                    const unsigned long long m = __ballot(in);
+                    if (in) out[before + __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0))] = first + i;
+                    before += (uint32_t)__popcll(m);
+                }
+                return;
+            }
+            bound = 0;   // too many: its k best, which all reach it
+            __syncthreads();   // s_wtot has been read
+        }
     }
+    bool whole = MODE != kSelMerge;   // candidates are the row's (the chunk's) slots, not a list of them
     constexpr int kMaxChunks = 16;
     int base_of[kMaxChunks + 1];  // kSelMerge: where every chunk's survivors start in the merged list (registers)
     if constexpr (MODE == kSelMerge) {
@@ -88,38 +168,44 @@ __global__ __launch_bounds__(THREADS) FK_TWO_PER_CU void select_keep_kernel(cons
             if (c < sp.nchunk) tot += sp.count[(size_t)row * sp.nchunk + c];
         }
         base_of[kMaxChunks] = tot;
-        ncand = tot;  // >= k: every chunk keeps min(k, its size)
+        if (tot >= k) ncand = tot;
+        else whole = true;   // the chunks' bound was too high
     }
 
     // The row's keys are read from global memory once and kept in LDS (rows beyond the LDS share of the launch are
     // re-read from global memory in every pass).  Eight loads in flight per thread.
-    const bool in_lds = ncand <= lds_keys;  // kSelMerge: the host sized the launch so that it is
+    const bool in_lds = ncand <= lds_keys && (MODE != kSelMerge || !whole);  // kSelMerge: the host sized the launch so that the survivors are
     KeyRange kr;                            // gathered while the keys are written to LDS
     for (int i = threadIdx.x; i < kRangeWords + 4 * 256; i += THREADS) s_range[i] = 0;
-    if constexpr (MODE == kSelMerge) {
-        // Slot, then score: two dependent reads, eight of either in flight per thread (chunk by chunk, one survivor at a time, this
-        // gather took 15 of 37 us at 32 rows of 15360 survivors).
-        const int32_t* lists = sp.cand + (size_t)row * sp.nchunk * kmax;
-        for (int i0 = threadIdx.x; i0 < ncand; i0 += 8 * THREADS) {
-            int slot[8];
-            float v[8];
+    if (MODE == kSelMerge && !whole) {
+        // Slot, then score: two dependent reads, eight of either in flight per thread (one survivor at a time, this gather took 15 of 37 us at 32
+        // rows of 15360 survivors); a wavefront stays with one chunk.
+        const int group = WAVES / sp.nchunk, step = group * kWave;   // wavefronts of a chunk (2 <= nchunk <= 16)
+        const int c = wave / group, at = (wave - c * group) * kWave + lane;
+        if (c < sp.nchunk) {
+            int base = 0, cnt = 0;
 #pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                const int i = min(i0 + u * THREADS, ncand - 1);
-                int off = i;   // survivor i is number i - base_of[c] of its chunk c
+            for (int x = 0; x < kMaxChunks; ++x)
+                if (x == c) {
+                    base = base_of[x];
+                    cnt = base_of[x + 1] - base;
+                }
+            const int32_t* list = sp.cand + ((size_t)row * sp.nchunk + c) * kmax;
+            for (int i0 = at; i0 < cnt; i0 += 8 * step) {
+                int slot[8];
+                float v[8];
 #pragma unroll
-                for (int c = 1; c < kMaxChunks; ++c) off = i >= base_of[c] ? c * kmax + i - base_of[c] : off;
-                slot[u] = lists[off];
-            }
+                for (int u = 0; u < 8; ++u) slot[u] = list[min(i0 + u * step, cnt - 1)];
 #pragma unroll
-            for (int u = 0; u < 8; ++u) v[u] = sc[slot[u]];
+                for (int u = 0; u < 8; ++u) v[u] = sc[slot[u]];
 #pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                if (i0 + u * THREADS < ncand) {
-                    const uint32_t key = score_key(v[u]);
-                    s_slot[i0 + u * THREADS] = (uint32_t)slot[u];
-                    s_key[i0 + u * THREADS] = key;
-                    kr.add(key);
+                for (int u = 0; u < 8; ++u) {
+                    if (i0 + u * step < cnt) {
+                        const uint32_t key = score_key(v[u]);
+                        s_slot[base + i0 + u * step] = (uint32_t)slot[u];
+                        s_key[base + i0 + u * step] = key;
+                        kr.add(key);
+                    }
                 }
             }
         }
@@ -138,15 +224,43 @@ __global__ __launch_bounds__(THREADS) FK_TWO_PER_CU void select_keep_kernel(cons
             }
         }
     }
-    RangePlan rp = {};
-    if (in_lds) rp = kr.plan(s_wmm);
-    else __syncthreads();
     auto key_at = [&](int i) { return in_lds ? s_key[i] : score_key(sc[i]); };
 
-    // (rows read from global memory: 16 loads in flight per thread)
+    const int stretch = (((ncand + WAVES - 1) / WAVES) + kWave - 1) / kWave * kWave;   // of a wavefront in the ordered pass
+    const int w0 = min(wave * stretch, ncand), w1 = min(w0 + stretch, ncand);
     uint32_t prefix = 0;
     uint32_t want = (uint32_t)k;   // how many still to take among keys equal to the threshold
-    if (k > 0) {
+    bool select = k > 0;
+    if constexpr (MODE == kSelChunk) {
+        if (bound > 1) {
+            __syncthreads();
+            uint32_t over = 0;
+            for (int i0 = w0; i0 < w1; i0 += 4 * kWave) {
+                uint32_t kv[4];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) kv[u] = key_at(min(i0 + u * kWave + lane, ncand - 1));
+#pragma unroll
+                for (int u = 0; u < 4; ++u) over += (uint32_t)__popcll(__ballot(i0 + u * kWave + lane < w1 && kv[u] >= bound));
+            }
+            if (lane == 0) s_wtot[2 * wave] = over;
+            __syncthreads();
+            over = 0;
+            for (int w = 0; w < WAVES; ++w) over += s_wtot[2 * w];
+            __syncthreads();   // s_wtot has been read
+            if (over <= (uint32_t)kmax) {   // pass on all that reach the bound (otherwise: its k best, which all do)
+                k = (int)over;
+                prefix = bound - 1;
+                want = 0;
+                select = false;
+            }
+        }
+        if (threadIdx.x == 0) sp.count[(size_t)row * sp.nchunk + chunk] = k;
+    }
+    RangePlan rp = {};
+    if (select && in_lds) rp = kr.plan(s_wmm);
+    else __syncthreads();
+    // (rows read from global memory: 16 loads in flight per thread)
+    if (select) {
         auto key_of = [&](int i, bool& valid) { valid = true; return key_at(i); };
         if (in_lds) range_select<THREADS, 2>(key_of, ncand, (uint32_t)k, s_range, s_hist, s_wtot, rp, threadIdx.x, &prefix, &want);
         else msd_select<THREADS, 16>(key_of, ncand, (uint32_t)k, s_hist, 0u, ~0u, &prefix, &want);
@@ -155,8 +269,6 @@ __global__ __launch_bounds__(THREADS) FK_TWO_PER_CU void select_keep_kernel(cons
     // wavefront owns one contiguous stretch of the row and walks it 64 slots at a time (coalesced, no barrier inside):
     // first to count its kept slots, then, with the counts of the stretches before it, to write them in order.
     const uint32_t T = prefix;
-    const int stretch = (((ncand + WAVES - 1) / WAVES) + kWave - 1) / kWave * kWave;
-    const int w0 = min(wave * stretch, ncand), w1 = min(w0 + stretch, ncand);
     auto walk = [&](auto u_, auto write_, uint32_t& gt_run, uint32_t& eq_run) {
         constexpr int U = decltype(u_)::value;
         constexpr bool WRITE = decltype(write_)::value;
@@ -173,7 +285,7 @@ __global__ __launch_bounds__(THREADS) FK_TWO_PER_CU void select_keep_kernel(cons
                     const uint32_t g_below = __builtin_amdgcn_mbcnt_hi((uint32_t)(mg >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mg, 0));
                     const uint32_t e_below = __builtin_amdgcn_mbcnt_hi((uint32_t)(me >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)me, 0));
                     const uint32_t gb = gt_run + g_below, eb = eq_run + e_below;   // kept counts before slot i
-                    const int slot = MODE == kSelMerge ? (live ? (int)s_slot[i] : 0) : first + i;
+                    const int slot = MODE == kSelMerge && !whole ? (live ? (int)s_slot[i] : 0) : first + i;
                     if (live && kv[u] > T) out[gb + min(eb, want)] = slot;
                     else if (live && kv[u] == T && eb < want) out[gb + eb] = slot;
                 }

@@ -107,3 +107,35 @@ def test_split_selection_over_value_ranges(gpu, ora, kind):
     fk.fk_select_keep_ws(desc, gpu.to_dev(sc), None, torch.full((1, 2), n, dtype=torch.int32, device="cuda"), n, budget, recent, keep,
                          torch.empty(need, dtype=torch.uint8, device="cuda"))
     gpu.assert_keep_equal(keep.cpu().numpy(), ora.select_keep(sc, c.pos, c.len, budget, recent, "sort"), c.len, budget, kind)
+
+
+def sampled_slots(n_cand):
+    """The slots whose scores a split selection looks at for its bound: one of each of 2048 stretches, placed by a hash (fp32, as on the device)."""
+    i = np.arange(2048, dtype=np.uint32)
+    frac = ((i * np.uint32(2654435761)) >> np.uint32(8)).astype(np.float32) * np.float32(1 / 16777216)
+    return np.minimum(((i.astype(np.float32) + frac) * (np.float32(n_cand) / np.float32(2048))).astype(np.int64), n_cand - 1)
+
+
+# the bound of a split selection: right, too high for every pair but the sampled ones (the merge starts over), with all of the best in one chunk,
+# among ties, and useless; rows too short for a sample; a length hint below the length (the last chunk is longer than the others)
+@pytest.mark.parametrize("kind", ["normal", "sampled", "one chunk", "ramp", "two", "equal", "nan", "infinite"])
+@pytest.mark.parametrize("n,lens,hint,budget,recent", [(70001, [70001, 20000, 16500, 900], 70001, 700, 16), (131072, [131072, 131071, 60000, 16384 + 128], 131072, 2048, 128),
+                                                       (40000, [40000, 39000, 30000, 20000], 20000, 300, 0)])
+def test_split_selection_by_a_sampled_bound(gpu, ora, kind, n, lens, hint, budget, recent):
+    import paper_2602_03203_amd as fk
+    sc = np.stack([values(kind, n, 80 + b) for b in range(4)])[:, None]
+    for b in range(4):
+        if kind == "sampled" and lens[b] > budget:
+            sc[b, 0, sampled_slots(lens[b] - recent)] += 100.0
+        elif kind == "one chunk":
+            sc[b, 0, lens[b] // 3: lens[b] // 3 + budget] += 100.0
+        elif kind == "ramp":
+            sc[b, 0] += np.arange(n, dtype=np.float32) / 1000
+    pos, ln = np.broadcast_to(np.arange(n, dtype=np.int32), (4, 1, n)), np.array(lens, np.int32)
+    desc = fk.CacheDesc(4, 1, 1, 64, n, "bf16")
+    need = fk.fk_select_keep_workspace(desc, hint, budget, recent)
+    assert need > 0
+    print(f"sampled bound {kind} {lens} hint {hint} budget {budget}", flush=True)
+    keep = torch.full((4, 1, budget), -1, dtype=torch.int32, device="cuda")
+    fk.fk_select_keep_ws(desc, gpu.to_dev(sc), None, torch.from_numpy(ln[:, None].copy()).cuda(), hint, budget, recent, keep, torch.empty(need, dtype=torch.uint8, device="cuda"))
+    gpu.assert_keep_equal(keep.cpu().numpy(), ora.select_keep(sc, np.ascontiguousarray(pos), ln, budget, recent, "sort"), ln, budget, kind)
