@@ -19,7 +19,7 @@
 // Bound by instruction issue: two groups of 16 queries with 32 keys take 32 matrix and some 260 vector instructions (64 of them where a
 // maximum moved, which it does in most of the eight tiles of a wavefront), 4100 cycles for the two wavefronts of a SIMD; of a workgroup's
 // 46 000 cycles 2700 are its start and 5000 its merge.  128 rows of 2048 pairs, 128 steps: 165 us (0.43 PFLOP/s) against 2.9 ms step by
-// step; with features 165 us and 106 us for the planes.  It was 206 us with the probabilities through LDS, a merge of every group by itself with scalar
+// step; with features 165 us and 91 us for the planes.  It was 206 us with the probabilities through LDS, a merge of every group by itself with scalar
 // reads (6600 cycles), a branch per group in every loop, a walk whose counter was not known to be the same for a wavefront (masks
 // in every tile), and V waited for together with the next tile's K.  Measured and not kept: K as operand straight from the L2 (16 rows of
 // 64 bytes a load: 218 us against 182); all of a tile's operands read ahead, higher wavefront priority around the products: no
@@ -564,19 +564,24 @@ __global__ __launch_bounds__(kXThreads, 2) void window_attn_kernel(const WindowP
 }
 
 // ---------------------------------------------------------------------------------------------------------
-// The planes.  A wavefront owns 32 keys (two tiles of a 16x16x32 product, K as the B operand in registers for the whole walk) and
+// The planes.  A wavefront owns 16 keys (a tile of a 16x16x32 product, K as the B operand in registers for the whole walk) and
 // takes 16 padded queries at a time, GP heads of SPT = 16 / GP steps, from LDS.  Matrix row r is head r / SPT, step r % SPT:
 // the four results of a lane belong to one key and to HPL = 4 / SPT heads, their steps in order.
+// Bound by instruction issue and by how evenly the wavefronts fill the chip: 128 rows of 2176 keys, 128 steps 106 us with 32 keys a wavefront, four
+// wavefronts a SIMD (2.1 rounds of workgroups) and branches on the keys by lane; 91 with 16 keys and six wavefronts.  Two and four tiles of
+// queries at a time: 0 to 30 % slower, the registers leave five wavefronts or spill.
 // ---------------------------------------------------------------------------------------------------------
 static constexpr int kFeatQ = 64;   // padded queries per staged block
+static constexpr int kFeatKeys = kXWaves * 16;   // keys of a workgroup
 
 template <int GP>
-__global__ __launch_bounds__(kXThreads) void window_feat_planes_kernel(const WindowParams P) {
+__global__ __launch_bounds__(kXThreads, 6) void window_feat_planes_kernel(const WindowParams P) {
 #pragma clang fp contract(off)   // a step's weight is rounded before it is added, as in the single steps
     constexpr int SPT = 16 / GP, HPL = 4 / SPT, QRS = WindowCfg<128, 2>::KRS, kXCH = WindowCfg<128, 2>::CH;
     constexpr int LD = kFeatQ * kXCH / kXThreads;
     const int row = blockIdx.y, b = row / P.n_kv, hkv = row % P.n_kv, G = P.g, T = P.T;
-    const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave, n16 = lane & 15, quad = lane >> 4;
+    const int tid = threadIdx.x, lane = tid & (kWave - 1), n16 = lane & 15, quad = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);   // (scalar: so are the branches on its keys)
     const int n0 = min(max(P.len[row], 0), P.cap), n1 = min(n0 + T, P.cap);
     // steps from which the windows of the last 8, 16 and 32 queries of the chunk are open
     const int on8 = P.chunk_len - 8 - P.chunk_pos, on16 = on8 - 8, on32 = on8 - 24;
@@ -588,27 +593,22 @@ __global__ __launch_bounds__(kXThreads) void window_feat_planes_kernel(const Win
     float* feat = P.feat + (size_t)row * kFeatPlanes * P.cap * GP;
     const size_t plane = (size_t)P.cap * GP;
 
-    for (int k0 = blockIdx.x * (kXWaves * 32); k0 < n1; k0 += gridDim.x * (kXWaves * 32)) {
-        const int kb = k0 + wave * 32;
-        X128 kreg[2][4];
+    for (int k0 = blockIdx.x * kFeatKeys; k0 < n1; k0 += gridDim.x * kFeatKeys) {
+        const int kb = k0 + wave * 16, key = kb + n16;   // the wavefront's first key, the lane's
+        X128 kreg[4];
 #pragma unroll
-        for (int nt = 0; nt < 2; ++nt)
+        for (int ks = 0; ks < 4; ++ks) kreg[ks].u = Kr[(size_t)min(key, n1 - 1) * kXCH + ks * 4 + quad];
+        // this lane's sums, head quad * HPL + h; a new pair's start from zero
+        float wl[HPL], w32[HPL], w16[HPL], w8[HPL];
 #pragma unroll
-            for (int ks = 0; ks < 4; ++ks) kreg[nt][ks].u = Kr[(size_t)min(kb + nt * 16 + n16, n1 - 1) * kXCH + ks * 4 + quad];
-        // this lane's sums: key kb + nt * 16 + n16, head quad * HPL + h; a new pair's start from zero
-        float wl[2][HPL], w32[2][HPL], w16[2][HPL], w8[2][HPL];
-#pragma unroll
-        for (int nt = 0; nt < 2; ++nt)
-#pragma unroll
-            for (int h = 0; h < HPL; ++h) {
-                const int key = kb + nt * 16 + n16;
-                const float* f = feat + (size_t)min(key, n1 - 1) * GP + quad * HPL + h;
-                const bool old = key < n0;
-                wl[nt][h] = old ? f[3 * plane] : 0.f;
-                w32[nt][h] = old && T > on32 ? f[2 * plane] : 0.f;
-                w16[nt][h] = old && T > on16 ? f[plane] : 0.f;
-                w8[nt][h] = old && T > on8 ? f[0] : 0.f;
-            }
+        for (int h = 0; h < HPL; ++h) {
+            const float* f = feat + (size_t)min(key, n1 - 1) * GP + quad * HPL + h;
+            const bool old = key < n0;
+            wl[h] = old ? f[3 * plane] : 0.f;
+            w32[h] = old && T > on32 ? f[2 * plane] : 0.f;
+            w16[h] = old && T > on16 ? f[plane] : 0.f;
+            w8[h] = old && T > on8 ? f[0] : 0.f;
+        }
         xu32x4_t qr[LD];
         float2 st;
         // padded query x of a block: 16-row tile x / 16, matrix row x % 16
@@ -644,42 +644,43 @@ __global__ __launch_bounds__(kXThreads) void window_feat_planes_kernel(const Win
 #pragma unroll
             for (int qt = 0; qt < kFeatQ / 16; ++qt) {
                 const int t0 = tb + qt * SPT;     // first step of the tile
-                X128 a[4];
+                xf32x4_t c = (xf32x4_t){0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-                for (int ks = 0; ks < 4; ++ks) a[ks].u = *reinterpret_cast<const xu32x4_t*>(s_q[buf] + (qt * 16 + n16) * QRS + (ks * 4 + quad) * 16);
+                for (int ks = 0; ks < 4; ++ks) {
+                    X128 q;
+                    q.u = *reinterpret_cast<const xu32x4_t*>(s_q[buf] + (qt * 16 + n16) * QRS + (ks * 4 + quad) * 16);
+                    c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(q.v, kreg[ks].v, c, 0, 0, 0);
+                }
                 const float4 mx = *reinterpret_cast<const float4*>(&s_max[buf][qt * 16 + quad * 4]);
                 const float4 iv = *reinterpret_cast<const float4*>(&s_inv[buf][qt * 16 + quad * 4]);
                 const float m4[4] = {mx.x, mx.y, mx.z, mx.w}, i4[4] = {iv.x, iv.y, iv.z, iv.w};
-                const bool plain = kb + 32 <= n0 + t0 + 1 && t0 + SPT <= min(on32, T);   // nothing hidden, no window open
+                float x[4], lo = 0.f;
 #pragma unroll
-                for (int nt = 0; nt < 2; ++nt) {
-                    xf32x4_t c = (xf32x4_t){0.f, 0.f, 0.f, 0.f};
+                for (int i = 0; i < 4; ++i) {
+                    x[i] = c[i] * P.scale_log2e - m4[i];
+                    lo = fminf(lo, x[i]);
+                }
+                if (__any(lo < -126.f)) {   // exp2f's way round denormal results, only where there can be one
 #pragma unroll
-                    for (int ks = 0; ks < 4; ++ks) c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[ks].v, kreg[nt][ks].v, c, 0, 0, 0);
-                    float x[4], lo = 0.f;
+                    for (int i = 0; i < 4; ++i) x[i] = exp2f(x[i]);
+                } else {
 #pragma unroll
-                    for (int i = 0; i < 4; ++i) {
-                        x[i] = c[i] * P.scale_log2e - m4[i];
-                        lo = fminf(lo, x[i]);
-                    }
-                    if (__any(lo < -126.f)) {   // exp2f's way round denormal results, only where there can be one
+                    for (int i = 0; i < 4; ++i) x[i] = __builtin_amdgcn_exp2f(x[i]);
+                }
 #pragma unroll
-                        for (int i = 0; i < 4; ++i) x[i] = exp2f(x[i]);
-                    } else {
+                for (int i = 0; i < 4; ++i) x[i] *= i4[i];
+                if (kb + 16 <= n0 + t0 + 1 && t0 + SPT <= min(on32, T)) {   // nothing hidden, no window open
 #pragma unroll
-                        for (int i = 0; i < 4; ++i) x[i] = __builtin_amdgcn_exp2f(x[i]);
-                    }
+                    for (int i = 0; i < 4; ++i) wl[i / SPT] += x[i];
+                } else {
 #pragma unroll
                     for (int i = 0; i < 4; ++i) {
                         const int h = i / SPT, t = t0 + i % SPT;   // element i: matrix row quad * 4 + i
-                        const float p = x[i] * i4[i];
-                        if (plain) {
-                            wl[nt][h] += p;
-                        } else if (kb + nt * 16 + n16 <= n0 + t && t < T) {
-                            wl[nt][h] += p;
-                            if (t >= on32) w32[nt][h] += p;
-                            if (t >= on16) w16[nt][h] += p;
-                            if (t >= on8) w8[nt][h] += p;
+                        if (key <= n0 + t && t < T) {
+                            wl[h] += x[i];
+                            if (t >= on32) w32[h] += x[i];
+                            if (t >= on16) w16[h] += x[i];
+                            if (t >= on8) w8[h] += x[i];
                         }
                     }
                 }
@@ -688,18 +689,15 @@ __global__ __launch_bounds__(kXThreads) void window_feat_planes_kernel(const Win
             __syncthreads();
         }
 #pragma unroll
-        for (int nt = 0; nt < 2; ++nt)
-#pragma unroll
-            for (int h = 0; h < HPL; ++h) {
-                const int key = kb + nt * 16 + n16;
-                if (key >= n1) continue;
-                float* f = feat + (size_t)key * GP + quad * HPL + h;
-                f[3 * plane] = wl[nt][h];
-                if (key >= n0 || T > on32) f[2 * plane] = w32[nt][h];
-                if (key >= n0 || T > on16) f[plane] = w16[nt][h];
-                if (key >= n0 || T > on8) f[0] = w8[nt][h];
-                if (key >= n0) f[4 * plane] = f[5 * plane] = 0.f;
-            }
+        for (int h = 0; h < HPL; ++h) {
+            if (key >= n1) continue;
+            float* f = feat + (size_t)key * GP + quad * HPL + h;
+            f[3 * plane] = wl[h];
+            if (key >= n0 || T > on32) f[2 * plane] = w32[h];
+            if (key >= n0 || T > on16) f[plane] = w16[h];
+            if (key >= n0 || T > on8) f[0] = w8[h];
+            if (key >= n0) f[4 * plane] = f[5 * plane] = 0.f;
+        }
     }
     // the last workgroup of the row sets its length: all of them have read it by then
     __syncthreads();
@@ -737,7 +735,7 @@ fk_status window_attn(const WindowParams& P, bool split, hipStream_t st) {
 fk_status window_feat(const WindowParams& P, int max_len, hipStream_t st) {
     const fk_status s = window_groups<128, true, false>(P, st);
     if (s != FK_OK) return s;
-    const dim3 grid((max_len + kXWaves * 32 - 1) / (kXWaves * 32), P.rows);
+    const dim3 grid((max_len + kFeatKeys - 1) / kFeatKeys, P.rows);
     if (P.g <= 4) hipLaunchKernelGGL(window_feat_planes_kernel<4>, grid, dim3(kXThreads), 0, st, P);
     else hipLaunchKernelGGL(window_feat_planes_kernel<8>, grid, dim3(kXThreads), 0, st, P);
     return launch_status();
