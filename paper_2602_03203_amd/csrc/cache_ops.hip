@@ -27,6 +27,61 @@ __global__ __launch_bounds__(64) void append_kernel(uint4* __restrict__ K, uint4
     }
 }
 
+static constexpr int kCompactThreads = 1024;
+
+// ---------------------------------------------------------------------------------------
+// close a chunk of the attention features (Appendix B.1) and compact them with the cache
+//
+// feat [rows][6][cap][GP]: planes w8, w16, w32, wL (sums of this chunk's attention weights over
+// the last 8 / 16 / 32 queries and over the whole chunk), cum, dec (sums carried over earlier
+// chunks, plain and decayed by 0.9 per chunk).  At the end of a chunk cum += wL, dec = 0.9 dec
+// + wL and the four chunk planes restart from zero; rows over budget move slot keep[j] to slot
+// j in the same pass (ascending tiles, all sources of a tile read before it is written: the
+// argument of compact_kernel).  One workgroup per row; a thread owns 4 heads of a slot.  The workgroups of compact_kernel's launch that run
+// it come first in its grid: 128 rows of 2176 pairs, four heads, 8.6 us in a launch of its own before the compaction's 42; in one launch 46.4. (Two workgroups a CU, with four
+// registers spilled, take 53: more rows in flight make the compaction slower, 42 -> 48.)
+// ---------------------------------------------------------------------------------------
+
+template <int Q4 /* float4 units per slot */>
+__device__ __forceinline__ void feat_roll(float4* __restrict__ feat, int row, int n /* length before the compaction */,
+                                          const int32_t* __restrict__ keep, int cap, int budget) {
+    if (n <= 0) return;
+    const size_t pl4 = (size_t)cap * Q4;
+    float4* f = feat + (size_t)row * 6 * pl4;
+    float4 *wl = f + 3 * pl4, *cum = f + 4 * pl4, *dec = f + 5 * pl4;
+    const bool gather = n > budget;
+    const int32_t* kp = keep + (size_t)row * budget;
+    const int n_out = gather ? budget : n;
+    constexpr int tile = kCompactThreads / Q4;  // slots per pass
+    const int sl = threadIdx.x / Q4, q = threadIdx.x % Q4;
+    for (int base = 0; base < n_out; base += tile) {
+        const int j = base + sl;
+        int src = -1;
+        if (j < n_out) src = gather ? kp[j] : j;
+        const bool ok = src >= 0 && src < n;
+        float4 c = make_float4(0.f, 0.f, 0.f, 0.f), d = c, w = c;
+        if (ok) {
+            c = cum[(size_t)src * Q4 + q];
+            d = dec[(size_t)src * Q4 + q];
+            w = wl[(size_t)src * Q4 + q];
+        }
+        __syncthreads();
+        if (ok) {
+            cum[(size_t)j * Q4 + q] = make_float4(c.x + w.x, c.y + w.y, c.z + w.z, c.w + w.w);
+            dec[(size_t)j * Q4 + q] = make_float4(fmaf(kFeatDecay, d.x, w.x), fmaf(kFeatDecay, d.y, w.y),
+                                                  fmaf(kFeatDecay, d.z, w.z), fmaf(kFeatDecay, d.w, w.w));
+        }
+    }
+    __syncthreads();  // every wL source has been read
+    const float4 zero = make_float4(0.f, 0.f, 0.f, 0.f);
+    for (int t = threadIdx.x; t < n * Q4; t += kCompactThreads) {
+        f[t] = zero;
+        f[pl4 + t] = zero;
+        f[2 * pl4 + t] = zero;
+        f[3 * pl4 + t] = zero;
+    }
+}
+
 // ---------------------------------------------------------------------------------------
 // compact (stable in-place gather)
 //
@@ -38,27 +93,36 @@ __global__ __launch_bounds__(64) void append_kernel(uint4* __restrict__ K, uint4
 // [tT, (t+1)T); a source of any later tile is >= (t+1)T, and every source of tile t or of an
 // earlier tile has already been read, so no live source is overwritten.  Entries with
 // keep[j] == j (the untouched prefix) cost no traffic.
-// grid.x = row, grid.y = tensor * slices + slice (K slices, then V slices), last y = pos
+// grid.x = row, grid.y = tensor * slices + slice (K slices, then V slices), last y = pos; Q4 > 0: the attention features before them
 // ---------------------------------------------------------------------------------------
-static constexpr int kCompactThreads = 1024;
 static constexpr int kCompactU = 4;     // 16-byte loads in flight per thread
 static constexpr int kSliceChunks = 8;  // 16-byte chunks per column slice
 typedef unsigned int u32x4_t __attribute__((ext_vector_type(4)));
 
-// The workgroup that moves the positions also sets len[row] = min(len[row], budget) (no second launch).  No other
-// workgroup may then read len[row]: what moves is decided by keep alone (rows at or under budget carry the
+// The workgroup that moves the positions (Q4 > 0: the features, which go by the length) also sets len[row] = min(len[row], budget) (no
+// second launch).  No other workgroup may then read len[row]: what moves is decided by keep alone (rows at or under budget carry the
 // identity, entries with keep[j] == j or outside [0, cap) move nothing).
+template <int Q4 /* float4 units of a feature plane per slot; 0: no features */>
 __global__ __launch_bounds__(kCompactThreads) void compact_kernel(uint4* __restrict__ K, uint4* __restrict__ V,
-                                                                  int32_t* __restrict__ pos,
+                                                                  int32_t* __restrict__ pos, float4* __restrict__ feat,
                                                                   int32_t* __restrict__ len,
                                                                   const int32_t* __restrict__ keep,
                                                                   int cap, int budget, int chunks) {
-    const int row = blockIdx.x;
+    const int row = blockIdx.x, part = (int)blockIdx.y - (Q4 > 0);
+    if constexpr (Q4 > 0) {
+        if (part < 0) {
+            const int old = len[row];
+            __syncthreads();   // every wavefront has it
+            if (threadIdx.x == 0 && old > budget) len[row] = budget;
+            feat_roll<Q4>(feat, row, min(old, cap), keep, cap, budget);
+            return;
+        }
+    }
     const int n = cap;
     const int32_t* kp = keep + (size_t)row * budget;
     const int slices = chunks / kSliceChunks;
-    if ((int)blockIdx.y == 2 * slices) {
-        if (threadIdx.x == 0 && len[row] > budget) len[row] = budget;
+    if (part == 2 * slices) {
+        if (Q4 == 0 && threadIdx.x == 0 && len[row] > budget) len[row] = budget;
         int32_t* p = pos + (size_t)row * cap;
         for (int base = 0; base < budget; base += kCompactThreads * kCompactU) {
             int32_t val[kCompactU];
@@ -78,7 +142,7 @@ __global__ __launch_bounds__(kCompactThreads) void compact_kernel(uint4* __restr
         }
         return;
     }
-    const int tensor = blockIdx.y / slices, slice = blockIdx.y % slices;
+    const int tensor = part / slices, slice = part % slices;
     uint4* X = (tensor == 0 ? K : V) + (size_t)row * cap * chunks + slice * kSliceChunks;
     constexpr int spi = kCompactThreads / kSliceChunks;  // slots per load instruction of the workgroup
     constexpr int tile = spi * kCompactU;
@@ -119,61 +183,6 @@ __global__ __launch_bounds__(kCompactThreads) void compact_kernel(uint4* __restr
     }
 }
 
-// ---------------------------------------------------------------------------------------
-// close a chunk of the attention features (Appendix B.1) and compact them with the cache
-//
-// feat [rows][6][cap][GP]: planes w8, w16, w32, wL (sums of this chunk's attention weights over
-// the last 8 / 16 / 32 queries and over the whole chunk), cum, dec (sums carried over earlier
-// chunks, plain and decayed by 0.9 per chunk).  At the end of a chunk cum += wL, dec = 0.9 dec
-// + wL and the four chunk planes restart from zero; rows over budget move slot keep[j] to slot
-// j in the same pass (ascending tiles, all sources of a tile read before it is written: the
-// argument of compact_kernel).  One workgroup per row; a thread owns 4 heads of a slot.
-// ---------------------------------------------------------------------------------------
-
-template <int Q4 /* float4 units per slot */>
-__global__ __launch_bounds__(kCompactThreads) void feat_roll_kernel(float4* __restrict__ feat,
-                                                                    const int32_t* __restrict__ len,
-                                                                    const int32_t* __restrict__ keep, int cap,
-                                                                    int budget) {
-    const int row = blockIdx.x;
-    const int n = min(len[row], cap);
-    if (n <= 0) return;
-    const size_t pl4 = (size_t)cap * Q4;
-    float4* f = feat + (size_t)row * 6 * pl4;
-    float4 *wl = f + 3 * pl4, *cum = f + 4 * pl4, *dec = f + 5 * pl4;
-    const bool gather = n > budget;
-    const int32_t* kp = keep + (size_t)row * budget;
-    const int n_out = gather ? budget : n;
-    constexpr int tile = kCompactThreads / Q4;  // slots per pass
-    const int sl = threadIdx.x / Q4, q = threadIdx.x % Q4;
-    for (int base = 0; base < n_out; base += tile) {
-        const int j = base + sl;
-        int src = -1;
-        if (j < n_out) src = gather ? kp[j] : j;
-        const bool ok = src >= 0 && src < n;
-        float4 c = make_float4(0.f, 0.f, 0.f, 0.f), d = c, w = c;
-        if (ok) {
-            c = cum[(size_t)src * Q4 + q];
-            d = dec[(size_t)src * Q4 + q];
-            w = wl[(size_t)src * Q4 + q];
-        }
-        __syncthreads();
-        if (ok) {
-            cum[(size_t)j * Q4 + q] = make_float4(c.x + w.x, c.y + w.y, c.z + w.z, c.w + w.w);
-            dec[(size_t)j * Q4 + q] = make_float4(fmaf(kFeatDecay, d.x, w.x), fmaf(kFeatDecay, d.y, w.y),
-                                                  fmaf(kFeatDecay, d.z, w.z), fmaf(kFeatDecay, d.w, w.w));
-        }
-    }
-    __syncthreads();  // every wL source has been read
-    const float4 zero = make_float4(0.f, 0.f, 0.f, 0.f);
-    for (int t = threadIdx.x; t < n * Q4; t += kCompactThreads) {
-        f[t] = zero;
-        f[pl4 + t] = zero;
-        f[2 * pl4 + t] = zero;
-        f[3 * pl4 + t] = zero;
-    }
-}
-
 }  // namespace fk
 
 using namespace fk;
@@ -201,8 +210,8 @@ extern "C" fk_status fk_compact(const fk_cache_desc* desc, void* K, void* V, int
     const int chunks = desc->head_dim * (desc->dtype == FK_F32 ? 4 : 2) / 16;
     const int rows = desc->batch * desc->n_kv_heads;
     hipStream_t st = (hipStream_t)stream;
-    hipLaunchKernelGGL(compact_kernel, dim3(rows, 2 * (chunks / kSliceChunks) + 1), dim3(kCompactThreads), 0, st, (uint4*)K, (uint4*)V,
-                       pos, len, keep_idx, desc->capacity, budget, chunks);
+    hipLaunchKernelGGL(compact_kernel<0>, dim3(rows, 2 * (chunks / kSliceChunks) + 1), dim3(kCompactThreads), 0, st, (uint4*)K, (uint4*)V,
+                       pos, nullptr, len, keep_idx, desc->capacity, budget, chunks);
     return launch_status();
 }
 
@@ -217,14 +226,8 @@ extern "C" fk_status fk_compact_feat(const fk_cache_desc* desc, void* K, void* V
     const int rows = desc->batch * desc->n_kv_heads;
     const int g = desc->n_q_heads / desc->n_kv_heads;
     hipStream_t st = (hipStream_t)stream;
-    // the features first: their kernel needs the lengths as they were; the cache's compaction then clamps them
-    if (g <= 4)
-        hipLaunchKernelGGL(feat_roll_kernel<1>, dim3(rows), dim3(kCompactThreads), 0, st, (float4*)feat, len, keep_idx,
-                           desc->capacity, budget);
-    else
-        hipLaunchKernelGGL(feat_roll_kernel<2>, dim3(rows), dim3(kCompactThreads), 0, st, (float4*)feat, len, keep_idx,
-                           desc->capacity, budget);
-    hipLaunchKernelGGL(compact_kernel, dim3(rows, 2 * (chunks / kSliceChunks) + 1), dim3(kCompactThreads), 0, st, (uint4*)K, (uint4*)V,
-                       pos, len, keep_idx, desc->capacity, budget, chunks);
+    const auto kern = g <= 4 ? compact_kernel<1> : compact_kernel<2>;
+    hipLaunchKernelGGL(kern, dim3(rows, 2 * (chunks / kSliceChunks) + 2), dim3(kCompactThreads), 0, st, (uint4*)K, (uint4*)V, pos,
+                       (float4*)feat, len, keep_idx, desc->capacity, budget, chunks);
     return launch_status();
 }
