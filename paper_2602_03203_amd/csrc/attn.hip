@@ -1032,19 +1032,18 @@ static bool window_at_once(const fk_cache_desc* d, const void* q, const void* K,
 }
 
 // Whether the steps at once are the faster way (the results are the same).  A workgroup, one per CU, walks its row alone whatever
-// the number of its steps: 3.1 us for 256 pairs (head_dim 64: 2.2) and 4.8 us for every split of a split row; a single step spreads the
+// the number of its steps: 2.6 us for 256 pairs (head_dim 64: 1.8) and 4.2 us for every split of a split row; a single step spreads the
 // row over the chip: its bytes at 10 TB/s, 0.8 us for 256 pairs of a split, and the merge.  us, at once and one by one:
-//   D = 128, g = 4:  128 rows of 2048  T = 2: 28 and 48;  64 rows of 4096  T = 2: 72 and 51, T = 4: 73 and 97;  1 row of 8192
-//     T = 16: 181 and 160, T = 64: 182 and 618
-//   D = 64, g = 4:  128 rows of 1000  T = 2: 27 and 21, T = 4: 27 and 39;  16 rows of 4096  T = 8: 109 and 81;  512 rows of 100  T = 2: 19 and 16
-// Fitted to 1620 such pairs (g 1, 4, 8; 1 to 512 rows; 100 to 8192 pairs; T 2 to 64): the slower way, by more than a tenth, at 15.
+//   D = 128:  g = 8, 16 rows of 1896  T = 8: 47 and 73;  4 rows of 2393  T = 8: 56 and 77;  8 rows of 444  T = 2: 11 and 18
+//   D = 64:  g = 8, 4 rows of 567  T = 4: 20 and 31;  64 rows of 1711  T = 4: 33 and 42;  g = 1, 1 row of 1682  T = 8: 37 and 46
+// Of 220 such pairs (g 1 to 8; 1 to 256 rows; 100 to 8192 pairs; T 2 to 32) the slower way, by more than a tenth, at 2.
 static bool window_pays(const fk_cache_desc* d, int32_t T, int32_t max_len) {
     const int g = d->n_q_heads / d->n_kv_heads, spg = 16 / g;   // 16 / g steps, or twice as many, to a workgroup
     const AttnShape shape = attn_shape(d);
     const AttnPlan p = attn_plan(shape, max_len);
     const double rows = shape.rows, groups = rows * ((T + spg - 1) / spg), rounds = groups <= 256 ? 1.0 : (groups / 2 + 255) / 256;
     const bool split = p.nsplit > 1;
-    const double at_once = rounds * (7.5 + (split ? 4.8 * p.nsplit : 0.0) + max_len / 256.0 * (d->head_dim == 64 ? 2.2 : 3.1));
+    const double at_once = rounds * (6.5 + (split ? 4.2 * p.nsplit : 0.0) + max_len / 256.0 * (d->head_dim == 64 ? 1.8 : 2.6));
     const double step = 4.6 + rows * max_len * d->head_dim * 4 / 1e7 + max_len / 256.0 / p.nsplit * 0.8 + (split ? 0.7 + 0.11 * p.nsplit : 0.0);
     return T * step >= at_once;
 }
