@@ -10,34 +10,32 @@
 // ascending: every candidate above T, the first `take` candidates equal to T in slot order
 // (slot order is position order, so ties go to the lower position), and the protected tail.
 #include "select_common.h"
-#include <type_traits>
 
 namespace fk {
 
 // LDS (u32): histogram and list of range_select | histograms [4][256] of msd_select | wavefront totals [16][2] | key range
-// [kRangePart] | keys [lds_keys]
+// [kRangePart] | keys [lds_keys] | kSelMerge: their slots [lds_keys]
 static constexpr int kSelMaxLdsKeys = 36 * 1024;  // 144 KB of keys beside the histograms
 static constexpr int kSelLdsHead = kRangeWords + 4 * 256 + 32 + kRangePart;  // words before the keys
-// Two workgroups of sixteen wavefronts share a CU if a wavefront takes no more than 80 scalar registers (800 of them a SIMD, and
-// sixteen more for every wavefront): 512 rows of 2176 keys 12.8 -> 10.2 us with 78 instead of 93, sampled 22.3 -> 16.9 with 78 instead of 90 (20.1 before
-// its range selection, with 58); 40 to 50 of them spilled to vector lanes do not show at 128 rows.
+struct SelLds {
+    uint32_t *range, *hist, *wtot, *wmm, *key;
+    __device__ __forceinline__ explicit SelLds(uint32_t* mem)
+        : range(mem), hist(range + kRangeWords), wtot(hist + 4 * 256), wmm(wtot + 32), key(wmm + kRangePart) {}
+};
+// Two workgroups of sixteen wavefronts share a CU if a wavefront takes no more than 64 vector registers and 80 scalar ones (800 of
+// them a SIMD, and sixteen more for every wavefront): 512 rows of 2176 keys 12.8 -> 10.2 us with 78 instead of 93, sampled
+// 22.3 -> 16.9 with 78 instead of 90 (20.1 before its range selection, with 58).  About fifty of them spilled to vector lanes do
+// not show at 128 rows.
 #define FK_TWO_PER_CU __attribute__((amdgpu_num_sgpr(80)))
 // (Four wavefronts per row instead of sixteen were measured and dropped: 11.3 against 8.1 us; a pass is a chain
 // key -> atomic -> barrier -> scan of LDS round trips, which more wavefronts shorten.)
 //
 // Long rows of a small batch (one-shot compression of a long prompt: 32 rows of 131072 pairs) would leave most of the
 // chip idle with one workgroup per row, and their keys do not fit LDS.  fk_select_keep_ws splits such rows (two launches,
-// a workspace between them): kSelChunk workgroups, one per chunk of a row, each keep the k best candidates of
+// a workspace between them): workgroups of select_chunk_kernel, one per chunk of a row, each keep the k best candidates of
 // their chunk (any pair among the row's k best is among its chunk's k best, under the same total order); kSelMerge
 // workgroups, one per row, then select among the chunks' survivors, whose keys fit LDS.  Same result, bit for bit.
-//   A chunk need not select at all where a bound is known that at least k of the row's pairs reach: it passes on what reaches the bound.  The bound
-// is a guess, the same for all chunks of a row: of a sample of the row, one key from each of 2048 stretches, the r-th best, r so far
-// above the k * 2048 / n expected among the k best (six standard deviations and eight) that fewer than k pairs over it do not happen by chance.
-// The merge counts, and selects from the whole row, slowly, if it does; a chunk with more than k pairs over the bound (ties) selects.
-// 32 rows of 131072 pairs, the best 1920: chunks that select 20.5 us and the merge of 15360 survivors 25.7; so 14.2 and, of 4500, 11.4 (20.8 and 13.5 with
-// the chunks of a row on all XCDs, each of which then fetches the sample).
-enum { kSelWhole = 0, kSelChunk = 1, kSelMerge = 2 };
-static constexpr int kSelSample = 2048;
+enum { kSelWhole = 0, kSelMerge = 1 };
 struct SelSplit {
     int nchunk;      // chunks per row
     int chunk_len;   // candidates per chunk (the last chunk runs on to the row's end)
@@ -45,119 +43,102 @@ struct SelSplit {
     int32_t* cand;   // [rows][nchunk][budget - recent] their slots, ascending
 };
 
+// Keys of the scores sc[0 .. ncand - 1] to LDS, eight loads in flight per thread; their range.
+template <int THREADS>
+__device__ __forceinline__ void keys_to_lds(const float* __restrict__ sc, int ncand, uint32_t* s_key, KeyRange& kr) {
+    for (int i0 = threadIdx.x; i0 < ncand; i0 += 8 * THREADS) {
+        float v[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) v[u] = sc[min(i0 + u * THREADS, ncand - 1)];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            if (i0 + u * THREADS < ncand) {
+                const uint32_t key = score_key(v[u]);
+                s_key[i0 + u * THREADS] = key;
+                kr.add(key);
+            }
+        }
+    }
+}
+
+// The ordered pass: of the candidates [0, ncand) those above T and the first `want` equal to T, their slots ascending.  Every
+// wavefront owns one contiguous stretch and walks it 64 candidates at a time (coalesced, no barrier inside): first to count
+// its kept ones (kept_count), then, with the counts of the stretches before it, to write them in order (kept_write).
+// U: candidates in flight per thread.  Between the two every wavefront's counts are in wtot [16][2] (above, equal).
+template <int THREADS, int U, bool WRITE, typename KeyFn, typename SlotFn>
+__device__ __forceinline__ void kept_walk(KeyFn key_at, SlotFn slot_at, int ncand, uint32_t T, uint32_t want, int32_t* out, uint32_t& gt_run,
+                                          uint32_t& eq_run) {
+    constexpr int WAVES = THREADS / kWave;
+    const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
+    const int stretch = (((ncand + WAVES - 1) / WAVES) + kWave - 1) / kWave * kWave;
+    const int w0 = min(wave * stretch, ncand), w1 = min(w0 + stretch, ncand);
+    for (int i0 = w0; i0 < w1; i0 += U * kWave) {
+        uint32_t kv[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) kv[u] = key_at(min(i0 + u * kWave + lane, ncand - 1));
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int i = i0 + u * kWave + lane;
+            const bool live = i < w1;
+            const unsigned long long mg = __ballot(live && kv[u] > T), me = __ballot(live && kv[u] == T);
+            if constexpr (WRITE) {
+                const uint32_t g_below = __builtin_amdgcn_mbcnt_hi((uint32_t)(mg >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mg, 0));
+                const uint32_t e_below = __builtin_amdgcn_mbcnt_hi((uint32_t)(me >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)me, 0));
+                const uint32_t gb = gt_run + g_below, eb = eq_run + e_below;   // kept counts before slot i
+                const int slot = slot_at(i, live);
+                if (live && kv[u] > T) out[gb + min(eb, want)] = slot;
+                else if (live && kv[u] == T && eb < want) out[gb + eb] = slot;
+            }
+            gt_run += (uint32_t)__popcll(mg);
+            eq_run += (uint32_t)__popcll(me);
+        }
+    }
+}
+template <int THREADS, typename KeyFn>
+__device__ __forceinline__ void kept_count(KeyFn key_at, bool in_lds, int ncand, uint32_t T, uint32_t* wtot) {
+    uint32_t gt = 0, eq = 0;
+    auto none = [](int, bool) { return 0; };
+    if (in_lds) kept_walk<THREADS, 2, false>(key_at, none, ncand, T, 0u, nullptr, gt, eq);
+    else kept_walk<THREADS, 16, false>(key_at, none, ncand, T, 0u, nullptr, gt, eq);
+    if ((threadIdx.x & (kWave - 1)) == 0) {
+        wtot[2 * (threadIdx.x / kWave)] = gt;
+        wtot[2 * (threadIdx.x / kWave) + 1] = eq;
+    }
+    __syncthreads();
+}
+template <int THREADS, typename KeyFn, typename SlotFn>
+__device__ __forceinline__ void kept_write(KeyFn key_at, SlotFn slot_at, bool in_lds, int ncand, uint32_t T, uint32_t want, const uint32_t* wtot, int32_t* out) {
+    uint32_t gt_before = 0, eq_before = 0;
+    for (int w = 0; w < (int)threadIdx.x / kWave; ++w) {
+        gt_before += wtot[2 * w];
+        eq_before += wtot[2 * w + 1];
+    }
+    if (in_lds) kept_walk<THREADS, 2, true>(key_at, slot_at, ncand, T, want, out, gt_before, eq_before);
+    else kept_walk<THREADS, 16, true>(key_at, slot_at, ncand, T, want, out, gt_before, eq_before);
+}
+
 template <int THREADS, int MODE>
 __global__ __launch_bounds__(THREADS) FK_TWO_PER_CU void select_keep_kernel(const float* __restrict__ scores,
                                                               const int32_t* __restrict__ len,
                                                               int cap, int budget, int recent, int lds_keys,
                                                               int32_t* __restrict__ keep, SelSplit sp) {
-    int row = blockIdx.x, chunk = 0;
-    if constexpr (MODE == kSelChunk) {   // blocks are dealt to the eight XCDs in turn: a row's chunks, which all read its sample, on one
-        const int rows = gridDim.x / sp.nchunk, per = (int)blockIdx.x / 8;
-        const bool deal = rows % 8 == 0;
-        row = deal ? per / sp.nchunk * 8 + (int)blockIdx.x % 8 : (int)blockIdx.x / sp.nchunk;
-        chunk = deal ? per % sp.nchunk : (int)blockIdx.x % sp.nchunk;
-    }
+    const int row = blockIdx.x;
     const int n = min(len[row], cap);
-    const int kmax = budget - recent;
-    int32_t* out = MODE == kSelChunk ? sp.cand + ((size_t)row * sp.nchunk + chunk) * kmax : keep + (size_t)row * budget;
+    int32_t* out = keep + (size_t)row * budget;
     if (n <= budget) {  // nothing to prune: the identity over the whole row, which makes the compaction a no-op
-        if (MODE != kSelChunk)
-            for (int j = threadIdx.x; j < budget; j += THREADS) out[j] = j;
+        for (int j = threadIdx.x; j < budget; j += THREADS) out[j] = j;
         return;
     }
     const float* sc = scores + (size_t)row * cap;
-    const int first = MODE == kSelChunk ? chunk * sp.chunk_len : 0;  // first slot of this workgroup's candidates
-    int ncand = n - recent;  // candidates: slots [first, first + ncand)
-    int k = kmax;            // how many of them stay (0 <= k < ncand; a chunk: k <= ncand)
+    const int k = budget - recent;   // how many of the candidates stay (0 <= k < ncand; kSelMerge: 1 <= k <= ncand)
+    int ncand = n - recent;          // candidates: slots [0, ncand), kSelMerge: a list of slots
 
     extern __shared__ __attribute__((aligned(16))) uint32_t s_sel_mem[];
-    uint32_t* s_range = s_sel_mem;                // [kRangeWords]
-    uint32_t* s_hist = s_range + kRangeWords;     // [4][256]
-    uint32_t* s_wtot = s_hist + 4 * 256;          // [16][2]: kept counts of every wavefront (greater, equal)
-    uint32_t* s_wmm = s_wtot + 32;                // [kRangePart]
-    uint32_t* s_key = s_wmm + kRangePart;         // [lds_keys]
-    uint32_t* s_slot = s_key + lds_keys;          // kSelMerge: [lds_keys] the candidates' slots
+    const SelLds s(s_sel_mem);
+    uint32_t* s_slot = s.key + lds_keys;   // kSelMerge
     constexpr int WAVES = THREADS / kWave;
     const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
-    if constexpr (MODE == kSelChunk) {
-        ncand = chunk == sp.nchunk - 1 ? ncand - first : min(ncand - first, sp.chunk_len);
-        if (ncand < 0) ncand = 0;
-        k = min(kmax, ncand);
-    }
-    // kSelChunk: a key that at least k pairs of the row reach in all likelihood (0: none was looked for).  Every survivor of a row with a bound
-    // reaches it, so k survivors prove that the k best do.
-    uint32_t bound = 0;
-    constexpr int HELD = 16;   // of a chunk of up to HELD * THREADS pairs every thread holds its share of a wavefront's stretch
-    float held[HELD];
-    const bool holds = MODE == kSelChunk && ncand <= HELD * THREADS;
-    if constexpr (MODE == kSelChunk) {
-        if (holds && ncand > 0) {   // (on their way while the bound is found)
-#pragma unroll
-            for (int u = 0; u < HELD; ++u) held[u] = sc[first + min((wave * HELD + u) * kWave + lane, ncand - 1)];
-        }
-        const int all = n - recent;   // the row's candidates
-        const float mean = (float)kSelSample * (float)kmax / (float)all;
-        const int r = (int)(mean + 6.f * sqrtf(mean)) + 8;
-        if (all >= 8 * kSelSample && 4 * r <= kSelSample && lds_keys >= kSelSample) {
-            for (int i = threadIdx.x; i < kRangeWords + 4 * 256; i += THREADS) s_range[i] = 0;
-            KeyRange kr;
-            static_assert(kSelSample == 2 * THREADS, "two stretches a thread");
-            const float len = (float)all / kSelSample;
-            float v[2];
-#pragma unroll
-            for (int u = 0; u < 2; ++u) {   // a pair of every stretch, its place in it by a hash: no period of the scores fits it
-                const int i = threadIdx.x + u * THREADS;
-                const float frac = (float)((uint32_t)i * 2654435761u >> 8) * (1.f / 16777216.f);
-                v[u] = sc[min((int)(((float)i + frac) * len), all - 1)];
-            }
-#pragma unroll
-            for (int u = 0; u < 2; ++u) {
-                const uint32_t key = score_key(v[u]);
-                s_key[threadIdx.x + u * THREADS] = key;
-                kr.add(key);
-            }
-            const RangePlan rp = kr.plan(s_wmm);
-            uint32_t left = 0;
-            range_select<THREADS, 2>([&](int i, bool& valid) { valid = true; return s_key[i]; }, kSelSample, (uint32_t)r, s_range, s_hist, s_wtot, rp,
-                                     threadIdx.x, &bound, &left);
-            __syncthreads();   // the sample gives way to the chunk's keys
-        }
-        sc += first;
-        if (ncand == 0 || (k == ncand && bound <= 1)) {  // the whole chunk survives
-            if (threadIdx.x == 0) sp.count[(size_t)row * sp.nchunk + chunk] = k;
-            for (int j = threadIdx.x; j < ncand; j += THREADS) out[j] = first + j;
-            return;
-        }
-        if (bound > 1 && holds) {   // what reaches the bound, in order
-            uint32_t over = 0;
-#pragma unroll
-            for (int u = 0; u < HELD; ++u)
-                over += (uint32_t)__popcll(__ballot((wave * HELD + u) * kWave + lane < ncand && score_key(held[u]) >= bound));
-            if (lane == 0) s_wtot[wave] = over;
-            __syncthreads();
-            uint32_t before = 0, total = 0;
-#pragma unroll
-            for (int w = 0; w < WAVES; ++w) {
-                before += w < wave ? s_wtot[w] : 0u;
-                total += s_wtot[w];
-            }
-            if (total <= (uint32_t)kmax) {
-                if (threadIdx.x == 0) sp.count[(size_t)row * sp.nchunk + chunk] = (int)total;
-#pragma unroll
-                for (int u = 0; u < HELD; ++u) {
-                    const int i = (wave * HELD + u) * kWave + lane;
-                    const bool in = i < ncand && score_key(held[u]) >= bound;
-                    const unsigned long long m = __ballot(in);
-                    if (in) out[before + __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0))] = first + i;
-                    before += (uint32_t)__popcll(m);
-                }
-                return;
-            }
-            bound = 0;   // too many: its k best, which all reach it
-            __syncthreads();   // s_wtot has been read
-        }
-    }
-    bool whole = MODE != kSelMerge;   // candidates are the row's (the chunk's) slots, not a list of them
+    bool listed = MODE == kSelMerge;
     constexpr int kMaxChunks = 16;
     int base_of[kMaxChunks + 1];  // kSelMerge: where every chunk's survivors start in the merged list (registers)
     if constexpr (MODE == kSelMerge) {
@@ -169,15 +150,15 @@ __global__ __launch_bounds__(THREADS) FK_TWO_PER_CU void select_keep_kernel(cons
         }
         base_of[kMaxChunks] = tot;
         if (tot >= k) ncand = tot;
-        else whole = true;   // the chunks' bound was too high
+        else listed = false;   // the chunks' bound was too high: from the whole row
     }
 
     // The row's keys are read from global memory once and kept in LDS (rows beyond the LDS share of the launch are
-    // re-read from global memory in every pass).  Eight loads in flight per thread.
-    const bool in_lds = ncand <= lds_keys && (MODE != kSelMerge || !whole);  // kSelMerge: the host sized the launch so that the survivors are
-    KeyRange kr;                            // gathered while the keys are written to LDS
-    for (int i = threadIdx.x; i < kRangeWords + 4 * 256; i += THREADS) s_range[i] = 0;
-    if (MODE == kSelMerge && !whole) {
+    // re-read from global memory in every pass).
+    const bool in_lds = MODE == kSelMerge ? listed : ncand <= lds_keys;  // kSelMerge: the host sized the launch so that the survivors are
+    KeyRange kr;                                                         // gathered while the keys are written to LDS
+    for (int i = threadIdx.x; i < kRangeWords + 4 * 256; i += THREADS) s.range[i] = 0;
+    if (MODE == kSelMerge && listed) {
         // Slot, then score: two dependent reads, eight of either in flight per thread (one survivor at a time, this gather took 15 of 37 us at 32
         // rows of 15360 survivors); a wavefront stays with one chunk.
         const int group = WAVES / sp.nchunk, step = group * kWave;   // wavefronts of a chunk (2 <= nchunk <= 16)
@@ -190,7 +171,7 @@ __global__ __launch_bounds__(THREADS) FK_TWO_PER_CU void select_keep_kernel(cons
                     base = base_of[x];
                     cnt = base_of[x + 1] - base;
                 }
-            const int32_t* list = sp.cand + ((size_t)row * sp.nchunk + c) * kmax;
+            const int32_t* list = sp.cand + ((size_t)row * sp.nchunk + c) * k;
             for (int i0 = at; i0 < cnt; i0 += 8 * step) {
                 int slot[8];
                 float v[8];
@@ -203,120 +184,158 @@ __global__ __launch_bounds__(THREADS) FK_TWO_PER_CU void select_keep_kernel(cons
                     if (i0 + u * step < cnt) {
                         const uint32_t key = score_key(v[u]);
                         s_slot[base + i0 + u * step] = (uint32_t)slot[u];
-                        s_key[base + i0 + u * step] = key;
+                        s.key[base + i0 + u * step] = key;
                         kr.add(key);
                     }
                 }
             }
         }
-    } else if (in_lds) {
-        for (int i0 = threadIdx.x; i0 < ncand; i0 += 8 * THREADS) {
-            float v[8];
-#pragma unroll
-            for (int u = 0; u < 8; ++u) v[u] = sc[min(i0 + u * THREADS, ncand - 1)];
-#pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                if (i0 + u * THREADS < ncand) {
-                    const uint32_t key = score_key(v[u]);
-                    s_key[i0 + u * THREADS] = key;
-                    kr.add(key);
-                }
-            }
-        }
-    }
-    auto key_at = [&](int i) { return in_lds ? s_key[i] : score_key(sc[i]); };
-
-    const int stretch = (((ncand + WAVES - 1) / WAVES) + kWave - 1) / kWave * kWave;   // of a wavefront in the ordered pass
-    const int w0 = min(wave * stretch, ncand), w1 = min(w0 + stretch, ncand);
-    uint32_t prefix = 0;
-    uint32_t want = (uint32_t)k;   // how many still to take among keys equal to the threshold
-    bool select = k > 0;
-    if constexpr (MODE == kSelChunk) {
-        if (bound > 1) {
-            __syncthreads();
-            uint32_t over = 0;
-            for (int i0 = w0; i0 < w1; i0 += 4 * kWave) {
-                uint32_t kv[4];
-#pragma unroll
-                for (int u = 0; u < 4; ++u) kv[u] = key_at(min(i0 + u * kWave + lane, ncand - 1));
-#pragma unroll
-                for (int u = 0; u < 4; ++u) over += (uint32_t)__popcll(__ballot(i0 + u * kWave + lane < w1 && kv[u] >= bound));
-            }
-            if (lane == 0) s_wtot[2 * wave] = over;
-            __syncthreads();
-            over = 0;
-            for (int w = 0; w < WAVES; ++w) over += s_wtot[2 * w];
-            __syncthreads();   // s_wtot has been read
-            if (over <= (uint32_t)kmax) {   // pass on all that reach the bound (otherwise: its k best, which all do)
-                k = (int)over;
-                prefix = bound - 1;
-                want = 0;
-                select = false;
-            }
-        }
-        if (threadIdx.x == 0) sp.count[(size_t)row * sp.nchunk + chunk] = k;
+    } else if (MODE == kSelWhole && in_lds) {
+        keys_to_lds<THREADS>(sc, ncand, s.key, kr);
     }
     RangePlan rp = {};
-    if (select && in_lds) rp = kr.plan(s_wmm);
+    if (in_lds) rp = kr.plan(s.wmm);
     else __syncthreads();
-    // (rows read from global memory: 16 loads in flight per thread)
-    if (select) {
+    auto key_at = [&](int i) { return in_lds ? s.key[i] : score_key(sc[i]); };
+    uint32_t T = 0, want = 0;   // kept: keys above T and the first `want` equal to it (k == 0: no candidate)
+    if (k > 0) {   // (rows read from global memory: 16 loads in flight per thread)
         auto key_of = [&](int i, bool& valid) { valid = true; return key_at(i); };
-        if (in_lds) range_select<THREADS, 2>(key_of, ncand, (uint32_t)k, s_range, s_hist, s_wtot, rp, threadIdx.x, &prefix, &want);
-        else msd_select<THREADS, 16>(key_of, ncand, (uint32_t)k, s_hist, 0u, ~0u, &prefix, &want);
+        if (in_lds) range_select<THREADS, 2>(key_of, ncand, (uint32_t)k, s.range, s.hist, s.wtot, rp, threadIdx.x, &T, &want);
+        else msd_select<THREADS, 16>(key_of, ncand, (uint32_t)k, s.hist, 0u, ~0u, &T, &want);
+        auto slot_at = [&](int i, bool live) { return MODE == kSelMerge && listed ? (live ? (int)s_slot[i] : 0) : i; };
+        kept_count<THREADS>(key_at, in_lds, ncand, T, s.wtot);
+        kept_write<THREADS>(key_at, slot_at, in_lds, ncand, T, want, s.wtot, out);
     }
-    // now: keep key > prefix, and the first `want` keys == prefix (k == 0: keep no candidate).  Ordered pass: every
-    // wavefront owns one contiguous stretch of the row and walks it 64 slots at a time (coalesced, no barrier inside):
-    // first to count its kept slots, then, with the counts of the stretches before it, to write them in order.
-    const uint32_t T = prefix;
-    auto walk = [&](auto u_, auto write_, uint32_t& gt_run, uint32_t& eq_run) {
-        constexpr int U = decltype(u_)::value;
-        constexpr bool WRITE = decltype(write_)::value;
-        for (int i0 = w0; i0 < w1; i0 += U * kWave) {
-            uint32_t kv[U];
+    for (int j = threadIdx.x; j < recent; j += THREADS) out[k + j] = n - recent + j;
+}
+
+// One chunk of a row.  It need not select at all where a bound is known that at least k of the row's pairs reach: it passes on what
+// reaches the bound.  The bound is a guess, the same for all chunks of a row: of a sample of the row, one key from each of 2048
+// stretches, the r-th best, r so far above the k * 2048 / n expected among the k best (six standard deviations and eight) that fewer
+// than k pairs reach it only where the sample's places themselves decide.  The merge counts, and selects from the whole row if it does.
+// A chunk with more than k pairs over the bound selects.
+// 32 rows of 131072 pairs, the best 1920: chunks that select 20.5 us and the merge of 15360 survivors 25.7; so 14.2 and, of 4500,
+// 11.4 (20.8 and 13.5 with the chunks of a row on all XCDs, each of which then fetches the sample).
+static constexpr int kSelSample = 2048;
+
+template <int THREADS>
+__global__ __launch_bounds__(THREADS) void select_chunk_kernel(const float* __restrict__ scores, const int32_t* __restrict__ len, int cap,
+                                                               int budget, int recent, int lds_keys, SelSplit sp) {
+    // blocks are dealt to the eight XCDs in turn: a row's chunks, which all read its sample, on one
+    const int rows = gridDim.x / sp.nchunk, per = (int)blockIdx.x / 8;
+    const bool deal = rows % 8 == 0;
+    const int row = deal ? per / sp.nchunk * 8 + (int)blockIdx.x % 8 : (int)blockIdx.x / sp.nchunk;
+    const int chunk = deal ? per % sp.nchunk : (int)blockIdx.x % sp.nchunk;
+    const int n = min(len[row], cap);
+    if (n <= budget) return;   // nothing to prune
+    const int kmax = budget - recent, all = n - recent;   // all: the row's candidates
+    const int first = chunk * sp.chunk_len;               // first slot of this chunk's
+    const int ncand = max(chunk == sp.nchunk - 1 ? all - first : min(all - first, sp.chunk_len), 0);
+    const float* sc = scores + (size_t)row * cap;
+    int32_t* out = sp.cand + ((size_t)row * sp.nchunk + chunk) * kmax;
+    int32_t* count = sp.count + (size_t)row * sp.nchunk + chunk;
+
+    extern __shared__ __attribute__((aligned(16))) uint32_t s_sel_mem[];
+    const SelLds s(s_sel_mem);
+    constexpr int WAVES = THREADS / kWave;
+    const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
+    constexpr int HELD = 16;   // of a chunk of up to HELD * THREADS pairs every thread holds its share of a wavefront's stretch
+    float held[HELD];
+    const bool holds = ncand <= HELD * THREADS;
+    if (holds && ncand > 0) {   // (on their way while the bound is found)
 #pragma unroll
-            for (int u = 0; u < U; ++u) kv[u] = key_at(min(i0 + u * kWave + lane, ncand - 1));
+        for (int u = 0; u < HELD; ++u) held[u] = sc[first + min((wave * HELD + u) * kWave + lane, ncand - 1)];
+    }
+    // A key that at least k pairs of the row reach in all likelihood (0: none was looked for).  Every survivor of a row with a
+    // bound reaches it, so k survivors prove that the k best do.
+    uint32_t bound = 0;
+    const float mean = (float)kSelSample * (float)kmax / (float)all;
+    const int r = (int)(mean + 6.f * sqrtf(mean)) + 8;
+    if (all >= 8 * kSelSample && 4 * r <= kSelSample && lds_keys >= kSelSample) {
+        for (int i = threadIdx.x; i < kRangeWords + 4 * 256; i += THREADS) s.range[i] = 0;
+        KeyRange kr;
+        static_assert(kSelSample == 2 * THREADS, "two stretches a thread");
+        const float len = (float)all / kSelSample;
+        float v[2];
 #pragma unroll
-            for (int u = 0; u < U; ++u) {
-                const int i = i0 + u * kWave + lane;
-                const bool live = i < w1;
-                const unsigned long long mg = __ballot(live && kv[u] > T), me = __ballot(live && kv[u] == T);
-                if constexpr (WRITE) {
-                    const uint32_t g_below = __builtin_amdgcn_mbcnt_hi((uint32_t)(mg >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mg, 0));
-                    const uint32_t e_below = __builtin_amdgcn_mbcnt_hi((uint32_t)(me >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)me, 0));
-                    const uint32_t gb = gt_run + g_below, eb = eq_run + e_below;   // kept counts before slot i
-                    const int slot = MODE == kSelMerge && !whole ? (live ? (int)s_slot[i] : 0) : first + i;
-                    if (live && kv[u] > T) out[gb + min(eb, want)] = slot;
-                    else if (live && kv[u] == T && eb < want) out[gb + eb] = slot;
-                }
-                gt_run += (uint32_t)__popcll(mg);
-                eq_run += (uint32_t)__popcll(me);
-            }
+        for (int u = 0; u < 2; ++u) {   // a pair of every stretch, its place in it by a hash: no period of the scores fits it
+            const int i = threadIdx.x + u * THREADS;
+            const float frac = (float)((uint32_t)i * 2654435761u >> 8) * (1.f / 16777216.f);
+            v[u] = sc[min((int)(((float)i + frac) * len), all - 1)];
         }
-    };
-    constexpr std::integral_constant<int, 2> few{};
-    constexpr std::integral_constant<int, 16> many{};
-    uint32_t gt = 0, eq = 0;
-    if (k > 0) {
-        if (in_lds) walk(few, std::false_type{}, gt, eq);
-        else walk(many, std::false_type{}, gt, eq);
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            const uint32_t key = score_key(v[u]);
+            s.key[threadIdx.x + u * THREADS] = key;
+            kr.add(key);
+        }
+        const RangePlan rp = kr.plan(s.wmm);
+        uint32_t left = 0;
+        range_select<THREADS, 2>([&](int i, bool& valid) { valid = true; return s.key[i]; }, kSelSample, (uint32_t)r, s.range, s.hist, s.wtot, rp,
+                                 threadIdx.x, &bound, &left);
+        __syncthreads();   // the sample gives way to the chunk's keys
     }
-    if (lane == 0) {
-        s_wtot[2 * wave] = gt;
-        s_wtot[2 * wave + 1] = eq;
+    if (ncand == 0 || (ncand <= kmax && bound <= 1)) {  // the whole chunk survives
+        if (threadIdx.x == 0) *count = ncand;
+        for (int j = threadIdx.x; j < ncand; j += THREADS) out[j] = first + j;
+        return;
     }
-    __syncthreads();
-    uint32_t gt_before = 0, eq_before = 0;
-    for (int w = 0; w < wave; ++w) {
-        gt_before += s_wtot[2 * w];
-        eq_before += s_wtot[2 * w + 1];
+    if (bound > 1 && holds) {   // what reaches the bound, in order
+        uint32_t over = 0;
+#pragma unroll
+        for (int u = 0; u < HELD; ++u)
+            over += (uint32_t)__popcll(__ballot((wave * HELD + u) * kWave + lane < ncand && score_key(held[u]) >= bound));
+        if (lane == 0) s.wtot[wave] = over;
+        __syncthreads();
+        uint32_t before = 0, total = 0;
+#pragma unroll
+        for (int w = 0; w < WAVES; ++w) {
+            before += w < wave ? s.wtot[w] : 0u;
+            total += s.wtot[w];
+        }
+        if (total <= (uint32_t)kmax) {
+            if (threadIdx.x == 0) *count = (int)total;
+#pragma unroll
+            for (int u = 0; u < HELD; ++u) {
+                const int i = (wave * HELD + u) * kWave + lane;
+                const bool in = i < ncand && score_key(held[u]) >= bound;
+                const unsigned long long m = __ballot(in);
+                if (in) out[before + __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0))] = first + i;
+                before += (uint32_t)__popcll(m);
+            }
+            return;
+        }
+        bound = 0;   // too many: its k best, which all reach it
+        __syncthreads();   // wtot has been read
     }
-    if (k > 0) {
-        if (in_lds) walk(few, std::true_type{}, gt_before, eq_before);
-        else walk(many, std::true_type{}, gt_before, eq_before);
+    sc += first;
+    const bool in_lds = ncand <= lds_keys;
+    KeyRange kr;
+    for (int i = threadIdx.x; i < kRangeWords + 4 * 256; i += THREADS) s.range[i] = 0;
+    if (in_lds) keys_to_lds<THREADS>(sc, ncand, s.key, kr);
+    auto key_at = [&](int i) { return in_lds ? s.key[i] : score_key(sc[i]); };
+    auto slot_at = [&](int i, bool) { return first + i; };
+    uint32_t T = 0, want = 0;
+    const RangePlan rp = kr.plan(s.wmm);
+    bool over_bound = false;
+    int k = min(kmax, ncand);
+    if (bound > 1) {   // pass on all that reach the bound, if they are not too many (otherwise: its k best, which all do)
+        kept_count<THREADS>(key_at, in_lds, ncand, bound - 1, s.wtot);
+        uint32_t over = 0;
+        for (int w = 0; w < WAVES; ++w) over += s.wtot[2 * w];
+        over_bound = over <= (uint32_t)kmax;
+        T = bound - 1;
+        if (over_bound) k = (int)over;
+        else __syncthreads();   // wtot has been read
     }
-    if (MODE != kSelChunk)
-        for (int j = threadIdx.x; j < recent; j += THREADS) out[k + j] = n - recent + j;
+    if (threadIdx.x == 0) *count = k;
+    if (!over_bound) {
+        auto key_of = [&](int i, bool& valid) { valid = true; return key_at(i); };
+        if (in_lds) range_select<THREADS, 2>(key_of, ncand, (uint32_t)k, s.range, s.hist, s.wtot, rp, threadIdx.x, &T, &want);
+        else msd_select<THREADS, 16>(key_of, ncand, (uint32_t)k, s.hist, 0u, ~0u, &T, &want);
+        kept_count<THREADS>(key_at, in_lds, ncand, T, s.wtot);
+    }
+    kept_write<THREADS>(key_at, slot_at, in_lds, ncand, T, want, s.wtot, out);
 }
 
 // ---------------------------------------------------------------------------------------
@@ -644,13 +663,13 @@ extern "C" fk_status fk_select_keep_ws(const fk_cache_desc* desc, const float* s
     SelSplit sp = {p.nchunk, p.chunk_len, reinterpret_cast<int32_t*>(workspace),
                    reinterpret_cast<int32_t*>(static_cast<char*>(workspace) + p.count_bytes)};
     {
-        auto kern = select_keep_kernel<kSelThreads, kSelChunk>;
+        auto kern = select_chunk_kernel<kSelThreads>;
         const int lds_keys = ((p.chunk_len < kSelMaxLdsKeys ? p.chunk_len : kSelMaxLdsKeys) + 3) & ~3;
         const size_t lds = sizeof(uint32_t) * (kSelLdsHead + (size_t)lds_keys);
         static bool lds_ok[kMaxDevices] = {};
         if (!allow_dynamic_lds((const void*)kern, 160 * 1024, lds_ok)) return FK_ERR_LAUNCH;
         hipLaunchKernelGGL(kern, dim3(rows * p.nchunk), dim3(kSelThreads), lds, st, scores, len, desc->capacity, budget,
-                           protect_recent, lds_keys, keep_idx, sp);
+                           protect_recent, lds_keys, sp);
         if (launch_status() != FK_OK) return FK_ERR_LAUNCH;
     }
     {
