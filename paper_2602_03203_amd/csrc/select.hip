@@ -43,10 +43,10 @@ struct SelSplit {
     int32_t* cand;   // [rows][nchunk][budget - recent] their slots, ascending
 };
 
-// Keys of the scores sc[0 .. ncand - 1] to LDS, eight loads in flight per thread; their range.
+// Keys of the scores sc[from .. ncand - 1] to LDS, eight loads in flight per thread; their range.
 template <int THREADS>
-__device__ __forceinline__ void keys_to_lds(const float* __restrict__ sc, int ncand, uint32_t* s_key, KeyRange& kr) {
-    for (int i0 = threadIdx.x; i0 < ncand; i0 += 8 * THREADS) {
+__device__ __forceinline__ void keys_to_lds(const float* __restrict__ sc, int from, int ncand, uint32_t* s_key, KeyRange& kr) {
+    for (int i0 = from + threadIdx.x; i0 < ncand; i0 += 8 * THREADS) {
         float v[8];
 #pragma unroll
         for (int u = 0; u < 8; ++u) v[u] = sc[min(i0 + u * THREADS, ncand - 1)];
@@ -191,7 +191,7 @@ __global__ __launch_bounds__(THREADS) FK_TWO_PER_CU void select_keep_kernel(cons
             }
         }
     } else if (MODE == kSelWhole && in_lds) {
-        keys_to_lds<THREADS>(sc, ncand, s.key, kr);
+        keys_to_lds<THREADS>(sc, 0, ncand, s.key, kr);
     }
     RangePlan rp = {};
     if (in_lds) rp = kr.plan(s.wmm);
@@ -212,10 +212,14 @@ __global__ __launch_bounds__(THREADS) FK_TWO_PER_CU void select_keep_kernel(cons
 // One chunk of a row.  It need not select at all where a bound is known that at least k of the row's pairs reach: it passes on what
 // reaches the bound.  The bound is a guess, the same for all chunks of a row: of a sample of the row, one key from each of 2048
 // stretches, the r-th best, r so far above the k * 2048 / n expected among the k best (six standard deviations and eight) that fewer
-// than k pairs reach it only where the sample's places themselves decide.  The merge counts, and selects from the whole row if it does.
-// A chunk with more than k pairs over the bound selects.
-// 32 rows of 131072 pairs, the best 1920: chunks that select 20.5 us and the merge of 15360 survivors 25.7; so 14.2 and, of 4500,
-// 11.4 (20.8 and 13.5 with the chunks of a row on all XCDs, each of which then fetches the sample).
+// than k pairs reach it only where scores go by the sample's own places.  The merge counts, and selects from the whole row, by one
+// workgroup and out of global memory, if it does: 32 rows of 131072 pairs then take 167 us (55 without a bound).
+// A chunk with more than k pairs that reach the bound, but not more above it (equal scores), passes on the latter and the first of
+// the others; one with more above it (most of the best in one chunk) selects.
+// 32 rows of 131072 pairs, the best 1920, both launches, us, without a bound and with it: normal scores 45.0 and 23.2, all equal 30.5
+// and 24.8, two values 42.0 and 27.5, the best in one chunk 47.3 and 39.5, rising scores 48.7 and 34.2.  64 rows, chunks of 32736: 49.5
+// and 37.1, 30.5 and 30.2, 52.0 and 32.8, 51.3 and 52.5, 50.9 and 47.5.  What it loses is the sample's time where every chunk still walks all its
+// pairs: 32 rows of 32768, all equal, 17.2 and 17.7.  (With a row's chunks on all XCDs, each of which then fetches the sample, the first launch takes 21 us, not 14.)
 static constexpr int kSelSample = 2048;
 
 template <int THREADS>
@@ -239,16 +243,21 @@ __global__ __launch_bounds__(THREADS) void select_chunk_kernel(const float* __re
     const SelLds s(s_sel_mem);
     constexpr int WAVES = THREADS / kWave;
     const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
-    constexpr int HELD = 16;   // of a chunk of up to HELD * THREADS pairs every thread holds its share of a wavefront's stretch
+    // On its way while the bound is found: the chunk's first HELD * THREADS pairs.  Those of a chunk that has no more stay in registers, a share of
+    // a wavefront's stretch in every thread.
+    constexpr int HELD = 16;
     float held[HELD];
-    const bool holds = ncand <= HELD * THREADS;
-    if (holds && ncand > 0) {   // (on their way while the bound is found)
+    const bool holds = ncand <= HELD * THREADS, in_lds = ncand <= lds_keys;
+    if (holds && ncand > 0) {
 #pragma unroll
         for (int u = 0; u < HELD; ++u) held[u] = sc[first + min((wave * HELD + u) * kWave + lane, ncand - 1)];
+    } else if (in_lds && ncand > 0) {
+#pragma unroll
+        for (int u = 0; u < HELD; ++u) held[u] = sc[first + u * THREADS + threadIdx.x];
     }
     // A key that at least k pairs of the row reach in all likelihood (0: none was looked for).  Every survivor of a row with a
     // bound reaches it, so k survivors prove that the k best do.
-    uint32_t bound = 0;
+    uint32_t bound = 0, left = 0;   // left: the bound's number among the sampled pairs equal to it, 1 where scores differ
     const float mean = (float)kSelSample * (float)kmax / (float)all;
     const int r = (int)(mean + 6.f * sqrtf(mean)) + 8;
     if (all >= 8 * kSelSample && 4 * r <= kSelSample && lds_keys >= kSelSample) {
@@ -270,7 +279,6 @@ __global__ __launch_bounds__(THREADS) void select_chunk_kernel(const float* __re
             kr.add(key);
         }
         const RangePlan rp = kr.plan(s.wmm);
-        uint32_t left = 0;
         range_select<THREADS, 2>([&](int i, bool& valid) { valid = true; return s.key[i]; }, kSelSample, (uint32_t)r, s.range, s.hist, s.wtot, rp,
                                  threadIdx.x, &bound, &left);
         __syncthreads();   // the sample gives way to the chunk's keys
@@ -281,55 +289,97 @@ __global__ __launch_bounds__(THREADS) void select_chunk_kernel(const float* __re
         return;
     }
     if (bound > 1 && holds) {   // what reaches the bound, in order
+        auto slot_of = [&](int u) { return (wave * HELD + u) * kWave + lane; };
+        auto key_of = [&](int u) { return slot_of(u) < ncand ? score_key(held[u]) : 0u; };
         uint32_t over = 0;
 #pragma unroll
-        for (int u = 0; u < HELD; ++u)
-            over += (uint32_t)__popcll(__ballot((wave * HELD + u) * kWave + lane < ncand && score_key(held[u]) >= bound));
+        for (int u = 0; u < HELD; ++u) over += (uint32_t)__popcll(__ballot(key_of(u) >= bound));
         if (lane == 0) s.wtot[wave] = over;
         __syncthreads();
-        uint32_t before = 0, total = 0;
+        uint32_t before = 0, total = 0;   // pairs that reach the bound
 #pragma unroll
         for (int w = 0; w < WAVES; ++w) {
             before += w < wave ? s.wtot[w] : 0u;
             total += s.wtot[w];
         }
+        auto below = [](unsigned long long m) { return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0)); };
         if (total <= (uint32_t)kmax) {
             if (threadIdx.x == 0) *count = (int)total;
 #pragma unroll
             for (int u = 0; u < HELD; ++u) {
-                const int i = (wave * HELD + u) * kWave + lane;
-                const bool in = i < ncand && score_key(held[u]) >= bound;
+                const bool in = key_of(u) >= bound;
                 const unsigned long long m = __ballot(in);
-                if (in) out[before + __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0))] = first + i;
+                if (in) out[before + below(m)] = first + slot_of(u);
                 before += (uint32_t)__popcll(m);
             }
             return;
         }
-        bound = 0;   // too many: its k best, which all reach it
+        if (left > 1) {
+            over = 0;
+#pragma unroll
+            for (int u = 0; u < HELD; ++u) over += (uint32_t)__popcll(__ballot(key_of(u) > bound));
+            if (lane == 0) s.wtot[WAVES + wave] = over;
+            __syncthreads();
+            uint32_t gt = 0, above = 0;   // pairs above the bound: before this wavefront's, all
+#pragma unroll
+            for (int w = 0; w < WAVES; ++w) {
+                gt += w < wave ? s.wtot[WAVES + w] : 0u;
+                above += s.wtot[WAVES + w];
+            }
+            if (above <= (uint32_t)kmax) {
+                const uint32_t want = (uint32_t)kmax - above;
+                uint32_t eq = before - gt;
+                if (threadIdx.x == 0) *count = kmax;
+#pragma unroll
+                for (int u = 0; u < HELD; ++u) {
+                    const uint32_t key = key_of(u);
+                    const unsigned long long mg = __ballot(key > bound), me = __ballot(key == bound);
+                    const uint32_t eb = eq + below(me);
+                    if (key > bound || (key == bound && eb < want)) out[gt + below(mg) + min(eb, want)] = first + slot_of(u);
+                    gt += (uint32_t)__popcll(mg);
+                    eq += (uint32_t)__popcll(me);
+                }
+                return;
+            }
+        }
         __syncthreads();   // wtot has been read
     }
     sc += first;
-    const bool in_lds = ncand <= lds_keys;
     KeyRange kr;
     for (int i = threadIdx.x; i < kRangeWords + 4 * 256; i += THREADS) s.range[i] = 0;
-    if (in_lds) keys_to_lds<THREADS>(sc, ncand, s.key, kr);
+    if (in_lds && !holds) {
+#pragma unroll
+        for (int u = 0; u < HELD; ++u) {
+            const uint32_t key = score_key(held[u]);
+            s.key[u * THREADS + threadIdx.x] = key;
+            kr.add(key);
+        }
+    }
+    if (in_lds) keys_to_lds<THREADS>(sc, holds ? 0 : HELD * THREADS, ncand, s.key, kr);
     auto key_at = [&](int i) { return in_lds ? s.key[i] : score_key(sc[i]); };
     auto slot_at = [&](int i, bool) { return first + i; };
     uint32_t T = 0, want = 0;
     const RangePlan rp = kr.plan(s.wmm);
-    bool over_bound = false;
+    bool passed = false;
     int k = min(kmax, ncand);
-    if (bound > 1) {   // pass on all that reach the bound, if they are not too many (otherwise: its k best, which all do)
-        kept_count<THREADS>(key_at, in_lds, ncand, bound - 1, s.wtot);
-        uint32_t over = 0;
-        for (int w = 0; w < WAVES; ++w) over += s.wtot[2 * w];
-        over_bound = over <= (uint32_t)kmax;
-        T = bound - 1;
-        if (over_bound) k = (int)over;
-        else __syncthreads();   // wtot has been read
+    if (bound > 1 && !holds) {   // the same of longer chunks
+        T = bound;
+        kept_count<THREADS>(key_at, in_lds, ncand, T, s.wtot);
+        uint32_t above = 0, equal = 0;
+        for (int w = 0; w < WAVES; ++w) {
+            above += s.wtot[2 * w];
+            equal += s.wtot[2 * w + 1];
+        }
+        passed = above <= (uint32_t)kmax;
+        if (passed) {
+            want = min(equal, (uint32_t)kmax - above);
+            k = (int)(above + want);
+        } else {
+            __syncthreads();   // wtot has been read
+        }
     }
     if (threadIdx.x == 0) *count = k;
-    if (!over_bound) {
+    if (!passed) {   // (with a bound: more than k pairs reach it, so the k best do)
         auto key_of = [&](int i, bool& valid) { valid = true; return key_at(i); };
         if (in_lds) range_select<THREADS, 2>(key_of, ncand, (uint32_t)k, s.range, s.hist, s.wtot, rp, threadIdx.x, &T, &want);
         else msd_select<THREADS, 16>(key_of, ncand, (uint32_t)k, s.hist, 0u, ~0u, &T, &want);

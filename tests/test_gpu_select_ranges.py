@@ -116,8 +116,21 @@ def sampled_slots(n_cand):
     return np.minimum(((i.astype(np.float32) + frac) * (np.float32(n_cand) / np.float32(2048))).astype(np.int64), n_cand - 1)
 
 
+def split_plan(rows, hint, budget, recent):
+    """(chunks of a row, pairs of a chunk but the last) as the library cuts rows for fk_select_keep_ws."""
+    nchunk = min(256 // rows, 18 * 1024 // (budget - recent), 16)
+    return nchunk, ((hint - recent + nchunk - 1) // nchunk + 3) // 4 * 4
+
+
+def looks_for_bound(n, chunk_len, budget, recent):
+    """Whether the chunks of a row of n pairs look for a bound, and how many of the 2048 sampled scores reach it."""
+    mean = 2048 * (budget - recent) / (n - recent)
+    reach = int(mean + 6 * np.sqrt(mean)) + 8
+    return n - recent >= 8 * 2048 and 4 * reach <= 2048 and chunk_len >= 2048, reach
+
+
 # the bound of a split selection: right, too high for every pair but the sampled ones (the merge starts over), with all of the best in one chunk,
-# among ties, and useless; rows too short for a sample; a length hint below the length (the last chunk is longer than the others)
+# among ties, and useless; rows too short for a sample; the last shape has chunks too short for one
 @pytest.mark.parametrize("kind", ["normal", "sampled", "one chunk", "ramp", "two", "equal", "nan", "infinite"])
 @pytest.mark.parametrize("n,lens,hint,budget,recent", [(70001, [70001, 20000, 16500, 900], 70001, 700, 16), (131072, [131072, 131071, 60000, 16384 + 128], 131072, 2048, 128),
                                                        (40000, [40000, 39000, 30000, 20000], 20000, 300, 0)])
@@ -138,4 +151,52 @@ def test_split_selection_by_a_sampled_bound(gpu, ora, kind, n, lens, hint, budge
     print(f"sampled bound {kind} {lens} hint {hint} budget {budget}", flush=True)
     keep = torch.full((4, 1, budget), -1, dtype=torch.int32, device="cuda")
     fk.fk_select_keep_ws(desc, gpu.to_dev(sc), None, torch.from_numpy(ln[:, None].copy()).cuda(), hint, budget, recent, keep, torch.empty(need, dtype=torch.uint8, device="cuda"))
+    gpu.assert_keep_equal(keep.cpu().numpy(), ora.select_keep(sc, np.ascontiguousarray(pos), ln, budget, recent, "sort"), ln, budget, kind)
+
+
+# The bound in chunks that a workgroup cannot hold in registers (more than 16384 pairs), in LDS and in global memory, because there are
+# few chunks or because the last one runs on to the end of a row longer than the hint; rows in multiples of eight, whose chunks are dealt
+# to the XCDs in another order; "over" says of the first row's last chunk whether normal scores leave it with more pairs over the bound than
+# it may pass on.  "coarse": the cut goes through equal scores, of which a chunk has more than it may pass on, but not above them.
+@pytest.mark.parametrize("kind", ["normal", "sampled", "one chunk", "ramp", "two", "equal", "coarse", "infinite"])
+@pytest.mark.parametrize("batch,hkv,n,lens,hint,budget,recent,last,over", [
+    (8, 8, 131072, None, 131072, 1930, 10, "lds", False),               # 4 chunks of 32768
+    (8, 1, 131072, None, 131072, 4432, 32, "lds", False),               # 4 chunks of 32768, kept lists that fill the merge
+    (1, 2, 131072, [131072], 131072, 9100, 100, "global", False),       # 2 chunks of 65536
+    (2, 1, 90000, [90000, 61000], 60000, 3000, 100, "global", False),   # a last chunk of 40000
+    (2, 1, 90000, [90000, 60000], 40000, 3000, 100, "global", True),    # ... of 56000
+    (1, 4, 90000, [90000], 40000, 300, 0, "global", True),              # 15 chunks of 2500 and one of 52500
+    (24, 1, 40000, None, 40000, 333, 33, "registers", False),           # 24 rows, 10 chunks
+    (2, 4, 33000, [33000, 25001], 33000, 900, 7, "registers", False),   # 8 rows, 16 chunks
+])
+def test_split_selection_bound_in_long_chunks(gpu, ora, kind, batch, hkv, n, lens, hint, budget, recent, last, over):
+    import paper_2602_03203_amd as fk
+    rows = batch * hkv
+    lens = lens or [n - 1000 * b for b in range(batch)]
+    nchunk, chunk_len = split_plan(rows, hint, budget, recent)
+    tail = lens[0] - recent - (nchunk - 1) * chunk_len
+    found, reach = looks_for_bound(lens[0], chunk_len, budget, recent)
+    assert found and last == ("registers" if tail <= 16384 else "lds" if tail <= min(chunk_len, 36 * 1024) else "global")
+    expected = reach / 2048 * tail   # pairs of the tail that reach the bound
+    assert expected > 1.1 * (budget - recent) if over else expected < 0.9 * (budget - recent)
+    base = np.stack([values("two" if kind == "two" else "equal" if kind == "equal" else "infinite" if kind == "infinite" else "normal", n, 300 + r) for r in range(min(rows, 8))])
+    sc = np.stack([np.roll(base[r % 8], 977 * r) for r in range(rows)]).reshape(batch, hkv, n)   # every row its own
+    for b in range(batch):
+        if kind == "sampled":
+            sc[b][:, sampled_slots(lens[b] - recent)] += 100.0
+        elif kind == "one chunk":
+            sc[b][:, lens[b] // 3: lens[b] // 3 + budget] += 100.0
+        elif kind == "ramp":
+            sc[b] += np.arange(n, dtype=np.float32) / 1000
+        elif kind == "coarse":
+            sc[b] = np.round(sc[b])
+    desc = fk.CacheDesc(batch, hkv, hkv, 64, n, "bf16")
+    need = fk.fk_select_keep_workspace(desc, hint, budget, recent)
+    assert need >= rows * nchunk * (budget - recent + 1) * 4
+    print(f"bound in long chunks {kind} {batch}x{hkv} {lens} hint {hint} budget {budget}", flush=True)
+    pos, ln = np.broadcast_to(np.arange(n, dtype=np.int32), (batch, hkv, n)), np.array(lens, np.int32)
+    keep = torch.full((batch, hkv, budget), -1, dtype=torch.int32, device="cuda")
+    work = torch.full((need,), 0xA5, dtype=torch.uint8, device="cuda")
+    d_len = torch.from_numpy(np.repeat(ln[:, None], hkv, axis=1)).cuda()
+    fk.fk_select_keep_ws(desc, gpu.to_dev(sc), None, d_len, hint, budget, recent, keep, work)
     gpu.assert_keep_equal(keep.cpu().numpy(), ora.select_keep(sc, np.ascontiguousarray(pos), ln, budget, recent, "sort"), ln, budget, kind)
