@@ -549,14 +549,17 @@ __global__ __launch_bounds__(kTrThreads) void golden_trace_kernel(const float* _
     }
 }
 
-// Budgets beyond kTraceSlots, whose slots do not fit the registers (4 groups of 8000, L = 256: 12.3 us a step, with sixteen slots a thread, 180 registers of them spilled, 10 to 30).  One workgroup per KV group.  LDS holds the cache's positions (ascending; B + L of them: the B of this step and the
-// L that are generated before the next one) and the keys of its first B entries under this step's future scores.
+// Budgets beyond kTraceSlots, whose slots do not fit the registers (4 groups of 8000, L = 256: 12.3 us a step; with sixteen slots a
+// thread, 180 registers of them spilled, 10 to 30), and intervals beyond what the writing threads hold (kTrFresh each).  One workgroup per
+// KV group.  LDS holds the cache's positions (ascending; B + L of them: the B of this step and the L that are generated before the next
+// one) and the keys of its first B entries under this step's future scores.
 // A step: (1) the loads of the NEXT step's future scores at every position that can still be a candidate then are
 // issued (they land while the step selects); (2) range_select finds the key of the (B - L)-th best candidate;
 // (3) every wavefront walks its own contiguous stretch of the candidates, first to count its survivors, then, with
 // the counts of the stretches before it, to move them (position and next key) to the front in order.  Sources are
 // in registers before the barrier that precedes the moves, so the compaction is safe in place.
-// PER_LANE: candidates one lane holds (stretch of a wavefront / 64) and newest pairs one thread holds (L / 1024), at most.
+// PER_LANE: candidates one lane holds (stretch of a wavefront / 64) and newest pairs one thread holds (L / 1024), at most.  Four where that
+// is enough: 8 groups of 4096, L = 2304: 8.1 us a step, 10.9 with twelve; 4 of 2500, L = 2400: 6.0 and 8.8.
 template <int PER_LANE>
 __global__ __launch_bounds__(kSelThreads) void golden_trace_ordered_kernel(const float* __restrict__ alpha, int Tn, int M,
                                                                    int budget, int L, int32_t* __restrict__ kept) {
@@ -735,10 +738,11 @@ extern "C" fk_status fk_golden_trace(const float* alpha, int32_t n_kv_heads, int
         hipLaunchKernelGGL(kern, dim3(n_kv_heads), dim3(kTrThreads), lds, (hipStream_t)stream, alpha, T, M, budget, interval, kept);
         return launch_status();
     };
-    static bool ok1[kMaxDevices] = {}, ok2[kMaxDevices] = {}, ok4[kMaxDevices] = {}, ok8[kMaxDevices] = {}, ok_ordered[kMaxDevices] = {};
+    static bool ok1[kMaxDevices] = {}, ok2[kMaxDevices] = {}, ok4[kMaxDevices] = {}, ok8[kMaxDevices] = {}, ok_ordered4[kMaxDevices] = {}, ok_ordered12[kMaxDevices] = {};
     if (budget > kTraceSlots || interval > kTrWrite * kTrFresh) {
         const size_t lds = sizeof(int32_t) * ((size_t)budget + interval) + sizeof(uint32_t) * (size_t)budget;
-        return launch(golden_trace_ordered_kernel<12>, ok_ordered, lds, sizeof(int32_t) * 2 * kTraceMaxCache);   // 12 * 1024 = kTraceMaxCache
+        if (budget <= 4 * kSelThreads) return launch(golden_trace_ordered_kernel<4>, ok_ordered4, lds, sizeof(int32_t) * 2 * kTraceMaxCache);
+        return launch(golden_trace_ordered_kernel<12>, ok_ordered12, lds, sizeof(int32_t) * 2 * kTraceMaxCache);   // 12 * 1024 = kTraceMaxCache
     }
     const size_t lds = (size_t)trace_lds(budget, interval).bytes;
     const int per = (budget + kTrHold - 1) / kTrHold;   // slots of a thread
