@@ -142,16 +142,21 @@ static constexpr uint32_t kStays = 0x80000000u, kTrDown = 0xfffffffeu;   // a po
 //   The threshold: the cut moves little from step to step, so the keys around the last one are counted in 512 bins of the bit pattern,
 // its bin the 320th, and a bin has places for the first eight pairs themselves.  Keys above the bins are not counted, keys below
 // them by vote.  One wavefront finds the bin in which the count from the bottom reaches E and ranks its pairs; bins get finer or
-// coarser as they fill.  Where the bin has more pairs (ties) or the cut has left the bins, and at the first step, the pairs
-// that are left (or all) are counted again over their own range, of the keys or, if those are equal, of the positions.
+// coarser as they fill.  A bin with more pairs, up to 64, is gathered and ranked by one wavefront.  One with more still (ties), and all
+// pairs at the first step and where the cut has left the bins, are counted again over their own range, of the keys or, if those are
+// equal, of the positions.  After a cut among equal keys the next one is taken to be among the same keys, until their number says otherwise.
 //   The other wavefronts write the results two steps later: they keep the candidates in position order, each with the slot that holds it,
 // look up which slots were given away, close the gaps and append the newest.
 //   Step t, first part: cut found | slots given away at t - 1 filled | step t - 2 written.  Second part: who goes, the others counted for
 // t + 1 | the newest counted, the gaps of t - 1 looked up.
-//   us a step, and with all candidates moved in order at every step, four barriers beside those of a range_select: 8 groups of 2048 pairs,
-// L = 128: 2.4 (4.9); 4 of 512, L = 32: 1.4 (3.4); 8 of 4096, L = 128: 3.6 (6.7); the cut always among hundreds of equal keys: 4.8 (4.7),
-// 2.8 (3.7) and 7.6 (6.9).  What is left is the issue of some 4000 instructions on one CU.  Measured and not kept: the writing wavefronts load
-// the next scores in position order for all (3.1: their instructions cost more than the scattered loads); 256 bins (the cut leaves them).
+//   us a step, and with all candidates moved in order at every step (golden_trace_ordered_kernel, four barriers beside those of a range_select):
+//     8 groups of 2048 pairs, L = 128: 2.3 and 4.9; 4 of 512, L = 32: 1.4 and 3.4; 8 of 1024, L = 64: 1.6 and 4.3; 8 of 4096, L = 128: 3.6 and 6.8
+//     the cut always among hundreds of equal keys: 4.1 and 4.7, 2.6 and 3.7, 3.1 and 4.0, 6.1 and 6.9
+//     every step's scores at another scale, the cut never near the last one: 5.1 and 4.9, 3.3 and 3.4, 3.8 and 4.1, 7.3 and 6.7
+// What is left is the issue of some 4000 instructions on one CU.  Measured and not kept: the writing wavefronts load the next scores in
+// position order for all (3.1: their instructions cost more than the scattered loads); 256 bins (the cut leaves them).  Counting again
+// with returned places also over all keys (the whole range rarely has a bin of eight), with a vote per slot for equal bins, and a second
+// histogram instead of the gathered 64: 4.8, 2.8 and 7.5 among equal keys, 6.0, 3.2 and 9.3 at another scale every step.
 // PER: slots of a holding thread.
 struct TraceLds {   // byte offsets in the dynamic LDS
     int sorted, fresh, fresh_slot, gone, bytes;
@@ -169,7 +174,7 @@ __host__ __device__ inline TraceLds trace_lds(int budget, int L) {
 // Where the count over the bins from the bottom reaches E; one wavefront.  bin < 0: it does not.
 struct TraceCut {
     int bin;
-    uint32_t want, inbin, near;   // number of the cut in its bin, pairs of the bin, pairs of the eight bins around it
+    uint32_t want, inbin, near, all;   // number of the cut in its bin, pairs of the bin, pairs of the eight bins around it, of all bins
 };
 __device__ __forceinline__ TraceCut trace_cut(const uint32_t* hist, uint32_t E, int lane) {
     const uint4 a = *reinterpret_cast<const uint4*>(hist + 8 * lane), b = *reinterpret_cast<const uint4*>(hist + 8 * lane + 4);
@@ -178,7 +183,8 @@ __device__ __forceinline__ TraceCut trace_cut(const uint32_t* hist, uint32_t E, 
     const uint32_t incl = wave_scan_incl(tot);
     uint32_t left = E - (incl - tot);   // number of the cut from this lane's first pair on
     const unsigned long long who = __ballot(left - 1u < tot);   // 1 <= left <= tot: one lane, or none
-    if (who == 0) return {-1, 0, 0, 0};
+    const uint32_t all = __builtin_amdgcn_readlane(incl, kWave - 1);
+    if (who == 0) return {-1, 0, 0, 0, all};
     uint32_t sub = 0, in = c[0];
 #pragma unroll
     for (int j = 1; j < 8; ++j) {   // past the bins below it
@@ -189,7 +195,7 @@ __device__ __forceinline__ TraceCut trace_cut(const uint32_t* hist, uint32_t E, 
     }
     const int src = __ffsll((long long)who) - 1;
     return {8 * src + (int)__builtin_amdgcn_readlane(sub, src), (uint32_t)__builtin_amdgcn_readlane(left, src),
-            (uint32_t)__builtin_amdgcn_readlane(in, src), (uint32_t)__builtin_amdgcn_readlane(tot, src)};
+            (uint32_t)__builtin_amdgcn_readlane(in, src), (uint32_t)__builtin_amdgcn_readlane(tot, src), all};
 }
 // the want-th lowest of a bin's pairs (inbin <= kTrCap of them): key and position
 __device__ __forceinline__ uint2 trace_rank(const uint2* bin, uint32_t inbin, uint32_t want, int lane) {
@@ -219,8 +225,8 @@ __global__ __launch_bounds__(kTrThreads) void golden_trace_kernel(const float* _
     uint16_t* s_fresh_slot = reinterpret_cast<uint16_t*>(smem + off.fresh_slot);
     uint8_t* s_gone = smem + off.gone;
     __shared__ __attribute__((aligned(16))) uint32_t s_hist[3][kTrBins];   // this step's, the next one's; of a recount, zero in between
-    // [0] key and [1] position of the highest pair that goes | [2] found: 2 by position | [3] shift of the bins, [4] first key of the bins | not found: the
-    // cut is number [5] of the pairs with keys [6] .. [7]
+    // [0] key and [1] position of the highest pair that goes | [2] found: 2 among equal keys | [3] shift of the bins, [4] first key of the bins | not found: the
+    // cut is number [5] of the [0] pairs (all ones: it is not known how many) with the [7] keys after [6]; [1]: these are the only keys in its bin, perhaps
     __shared__ __attribute__((aligned(16))) uint32_t s_cut[8];
     __shared__ uint32_t s_taken[2], s_lo, s_hi, s_count[kTrWriteWaves];
     const int hp = blockIdx.x, k = budget - L, wave = threadIdx.x / kWave;
@@ -250,6 +256,8 @@ __global__ __launch_bounds__(kTrThreads) void golden_trace_kernel(const float* _
         if (tid == 0) {
             s_lo = 0xffffffffu;
             s_hi = 0;
+            s_cut[0] = ~0u;
+            s_cut[1] = 0;
             s_cut[2] = 0;   // the first step has no bins
             s_cut[3] = 0;
             s_cut[5] = (uint32_t)L;
@@ -330,12 +338,12 @@ __global__ __launch_bounds__(kTrThreads) void golden_trace_kernel(const float* _
                         s_cut[4] = __builtin_elementwise_sub_sat(T.x, (uint32_t)kTrCut << shift);
                     }
                 } else if (lane == 0) {
-                    const bool in = c.bin > 0;
-                    const uint32_t lo = s_cut[4] + ((uint32_t)max(c.bin, 0) << shift);
-                    s_cut[2] = 0;
+                    const bool in = c.bin > 0, guess = c.bin == kTrCut && s_cut[2] == 2 && c.inbin > (uint32_t)kWave && (s_cut[0] - s_cut[4]) >> shift == (uint32_t)kTrCut;
+                    const uint32_t lo = guess ? s_cut[0] : in ? s_cut[4] + ((uint32_t)c.bin << shift) : 0u;
+                    *reinterpret_cast<uint4*>(s_cut) = make_uint4(in ? c.inbin : ~0u, guess, 0u, (uint32_t)shift);
                     s_cut[5] = in ? c.want : (uint32_t)L;
-                    s_cut[6] = in ? lo : 0u;
-                    s_cut[7] = in ? lo + min((1u << shift) - 1u, kTrDown - lo) : kTrDown;
+                    s_cut[6] = lo;
+                    s_cut[7] = guess ? 0u : in ? min((1u << shift) - 1u, kTrDown - lo) : kTrDown;
                 }
                 __builtin_amdgcn_s_setprio(0);
             }
@@ -378,64 +386,124 @@ __global__ __launch_bounds__(kTrThreads) void golden_trace_kernel(const float* _
         }
         __syncthreads();
         if (__builtin_expect(t <= M && s_cut[2] == 0, 0)) {
-            // count the pairs that are left over their own range, until the cut's bin can be ranked
-            uint32_t want = s_cut[5], klo = s_cut[6], khi = s_cut[7];
-            uint32_t plo = kTrDown - (uint32_t)(budget + (t - 1) * L - 1), phi = kTrDown;
+            // count the pairs that are left over their own range, of the keys or, if those are equal, of the positions, until they can be ranked
+            uint32_t want = s_cut[5], in = s_cut[0], klo = s_cut[6], kspan = s_cut[7];
+            uint32_t plo = kTrDown - (uint32_t)(budget + (t - 1) * L - 1), pspan = kTrDown - plo;
             uint32_t* hist = s_hist[2];
             int shift = (int)s_cut[3];
-            bool whole = klo == 0 && khi == kTrDown;
+            bool whole = in == ~0u, first = true, guess = s_cut[1] != 0;
+            constexpr int STEP = PER < 4 ? PER : 4;   // atomics in flight
+            auto member = [&](int u) { return (key[u] - klo <= kspan) & (np[u] - plo <= pspan); };
             for (;;) {
-                auto member = [&](int u) { return (key[u] >= klo) & (key[u] <= khi) & (np[u] >= plo) & (np[u] <= phi); };
-                if (klo != khi) {
+                if (in <= (uint32_t)kWave) {   // few enough for one wavefront
+                    if (holds) {
+#pragma unroll
+                        for (int u0 = 0; u0 < PER; u0 += STEP) {
+                            uint32_t place[STEP];
+#pragma unroll
+                            for (int v = 0; v < STEP; ++v) {
+                                place[v] = (uint32_t)kWave;
+                                if (member(u0 + v)) place[v] = atomicAdd(&hist[0], 1u);
+                            }
+#pragma unroll
+                            for (int v = 0; v < STEP; ++v)
+                                if (place[v] < (uint32_t)kWave) s_bin[place[v]] = make_uint2(np[u0 + v], key[u0 + v]);
+                        }
+                    }
+                    __syncthreads();
+                    if (cuts) {
+                        const uint2 e = s_bin[lane];
+                        in = hist[0];
+                        const unsigned long long me = (unsigned long long)e.y << 32 | e.x;
+                        uint32_t rank = 0;
+#pragma unroll 4
+                        for (uint32_t q = 0; q < in; q += 2) {
+                            const uint4 o = *reinterpret_cast<const uint4*>(s_bin + q);
+                            rank += ((unsigned long long)o.y << 32 | o.x) < me;
+                            rank += ((unsigned long long)o.w << 32 | o.z) < me && q + 1 < in;
+                        }
+                        const int at = __ffsll((long long)__ballot((uint32_t)lane < in && rank == want - 1)) - 1;   // one lane: all differ
+                        const uint32_t T = __builtin_amdgcn_readlane(e.y, at), p = __builtin_amdgcn_readlane(e.x, at);
+                        const bool equal = __ballot((uint32_t)lane < in && e.y != T) == 0;
+                        if (first && !equal) shift = max(shift - (30 - __clz((int)in)), 0);   // (it was this step's bin)
+                        if (lane == 0) {
+                            *reinterpret_cast<uint4*>(s_cut) = make_uint4(T, p, equal ? 2u : 1u, (uint32_t)shift);
+                            s_cut[4] = __builtin_elementwise_sub_sat(T, (uint32_t)kTrCut << shift);
+                            hist[0] = 0;
+                        }
+                    }
+                    __syncthreads();
+                    break;
+                }
+                if (kspan != 0) {
                     uint32_t lo = 0xffffffffu, hi = 0;
                     if (holds) {
 #pragma unroll
                         for (int u = 0; u < PER; ++u) {
-                            lo = member(u) ? min(lo, key[u]) : lo;
-                            hi = member(u) ? max(hi, key[u]) : hi;
+                            const uint32_t d = key[u] - klo;
+                            lo = min(lo, d);   // (others are beyond the span)
+                            hi = max(hi, d <= kspan ? d : 0u);
                         }
                         wave_min_max(lo, hi);
-                        if (lane == 0 && lo <= hi) {
+                        if (lane == 0) {
                             atomicMin(&s_lo, lo);
                             atomicMax(&s_hi, hi);
                         }
                     }
                     __syncthreads();
-                    klo = s_lo;
-                    khi = s_hi;
+                    klo += s_lo;
+                    kspan = s_hi - s_lo;
                 }
-                const bool by_key = klo != khi;
-                const uint32_t first = by_key ? klo : plo, span = by_key ? khi - klo : phi - plo;
-                const int sh = span == 0 ? 0 : max(23 - __clz((int)span), 0);   // span >> sh < 512
+                const bool by_key = kspan != 0;
+                const uint32_t from = by_key ? klo : plo, span = by_key ? kspan : pspan;
+                const int sh = max(23 - __clz((int)span | 1), 0);   // span >> sh < 512
                 if (holds) {
+                    if (whole && by_key) {   // (hardly ever few to a bin)
 #pragma unroll
-                    for (int u = 0; u < PER; ++u) {
-                        const bool in = member(u);
-                        const uint32_t bin = ((by_key ? key[u] : np[u]) - first) >> sh;
-                        const unsigned long long act = __ballot(in);
-                        if (act == 0) continue;
-                        const uint32_t lead = __builtin_amdgcn_readlane(bin, __ffsll((long long)act) - 1);
-                        if (__popcll(act) > kTrCap && __ballot(in && bin == lead) == act) {   // one bin, and more than it has places for
-                            if (lane == 0) atomicAdd(&hist[lead], (uint32_t)__popcll(act));
-                        } else if (in) {
-                            const uint32_t place = atomicAdd(&hist[bin], 1u);
-                            if (place < (uint32_t)kTrCap) s_bin[bin * kTrCap + place] = make_uint2(np[u], key[u]);
+                        for (int u = 0; u < PER; ++u)
+                            if (key[u] - klo <= kspan) atomicAdd(&hist[(key[u] - klo) >> sh], 1u);
+                    } else {
+#pragma unroll
+                        for (int u0 = 0; u0 < PER; u0 += STEP) {
+                            uint32_t bin[STEP], place[STEP];
+#pragma unroll
+                            for (int v = 0; v < STEP; ++v) {
+                                bin[v] = ((by_key ? key[u0 + v] : np[u0 + v]) - from) >> sh;
+                                place[v] = (uint32_t)kTrCap;
+                                if (member(u0 + v)) place[v] = atomicAdd(&hist[bin[v]], 1u);
+                            }
+#pragma unroll
+                            for (int v = 0; v < STEP; ++v)
+                                if (place[v] < (uint32_t)kTrCap) s_bin[bin[v] * kTrCap + place[v]] = make_uint2(np[u0 + v], key[u0 + v]);
                         }
                     }
                 }
                 __syncthreads();
                 if (cuts) {
-                    const TraceCut c = trace_cut(hist, want, lane);   // it is there
-                    const bool found = c.inbin <= (uint32_t)kTrCap;
-                    uint2 T = make_uint2(0u, 0u);
-                    if (found) T = trace_rank(s_bin + c.bin * kTrCap, c.inbin, c.want, lane);
-                    // the next step's bins: two or three pairs to one
-                    if (by_key && !found) shift = min(max(sh - (30 - __clz((int)c.inbin)), 0), 22);
-                    else if (by_key && whole) shift = min(sh, 22);
+                    const TraceCut c = trace_cut(hist, want, lane);
+                    if (guess && c.all != in) {   // other keys beside it
+                        if (lane == 0) {
+                            const uint32_t lo = s_cut[4] + ((uint32_t)kTrCut << shift);
+                            s_cut[6] = lo;
+                            s_cut[7] = min((1u << shift) - 1u, kTrDown - lo);
+                        }
+                    } else {   // it is there
+                        const bool found = c.inbin <= (uint32_t)kTrCap && !(whole && by_key);
+                        uint2 T = make_uint2(c.inbin, 0u);
+                        if (found) T = trace_rank(s_bin + c.bin * kTrCap, c.inbin, c.want, lane);
+                        // the next step's bins: two or three pairs to one
+                        if (by_key && c.inbin > (uint32_t)kTrCap) shift = min(max(sh - (30 - __clz((int)c.inbin)), 0), 22);
+                        else if (by_key && whole) shift = min(sh, 22);
+                        if (lane == 0) {
+                            const uint32_t lo = (uint32_t)c.bin << sh;
+                            *reinterpret_cast<uint4*>(s_cut) = make_uint4(T.x, T.y, found ? by_key ? 1 : 2 : 0, (uint32_t)shift);
+                            s_cut[5] = c.want;
+                            s_cut[6] = from + lo;
+                            s_cut[7] = min((1u << sh) - 1u, span - lo);
+                            if (found) s_cut[4] = __builtin_elementwise_sub_sat(T.x, (uint32_t)kTrCut << shift);
+                        }
+                    }
                     if (lane == 0) {
-                        const uint32_t lo = first + ((uint32_t)c.bin << sh);
-                        *reinterpret_cast<uint4*>(s_cut) = make_uint4(T.x, T.y, found ? by_key ? 1 : 2 : 0, (uint32_t)shift);
-                        *reinterpret_cast<uint4*>(s_cut + 4) = make_uint4(__builtin_elementwise_sub_sat(T.x, (uint32_t)kTrCut << shift), c.want, lo, lo + min((1u << sh) - 1u, first + span - lo));
                         s_lo = 0xffffffffu;
                         s_hi = 0;
                     }
@@ -443,17 +511,18 @@ __global__ __launch_bounds__(kTrThreads) void golden_trace_kernel(const float* _
                     for (int i = 0; i < kTrBins; i += 4 * kWave) *reinterpret_cast<uint4*>(hist + i + 4 * lane) = make_uint4(0, 0, 0, 0);
                 }
                 __syncthreads();
-                if (s_cut[2] != 0) break;
-                whole = false;
-                want = s_cut[5];
-                if (by_key) {
-                    klo = s_cut[6];
-                    khi = s_cut[7];
+                const uint4 c0 = *reinterpret_cast<const uint4*>(s_cut), c1 = *reinterpret_cast<const uint4*>(s_cut + 4);   // (written again after another barrier)
+                if (c0.z != 0) break;
+                in = c0.x;
+                want = c1.y;
+                if (by_key || (guess && c0.y != 0)) {
+                    klo = c1.z;
+                    kspan = c1.w;
                 } else {
-                    plo = s_cut[6];
-                    phi = s_cut[7];
+                    plo = c1.z;
+                    pspan = c1.w;
                 }
-                __syncthreads();   // s_cut has been read
+                whole = first = guess = false;
             }
         }
         if (cuts) {

@@ -170,6 +170,35 @@ def test_trace_score_distributions(gpu, T, B, L, scores):
     assert np.array_equal(d_kept.cpu().numpy(), golden.trace(alpha, B, L))
 
 
+# A cut's bin with more pairs than places: a few dozen to gather, hundreds of equal keys again and again, hundreds of which some are only
+# nearly equal, equal stretches of positions, and crowds at the lowest numbers, below which there is no room for the bins
+@pytest.mark.parametrize("scores", ["dozens", "crowds", "near", "stretches", "lowest"])
+@pytest.mark.parametrize("T,B,L", [(1500, 100, 8), (2400, 513, 64), (4000, 1025, 100), (4200, 2048, 128), (8000, 4096, 300)])
+def test_trace_cut_in_a_full_bin(gpu, T, B, L, scores):
+    import paper_2602_03203_amd as fk
+    from oracle import golden
+    M = golden.n_steps(T, B, L)
+    rng = np.random.default_rng(T + B)
+    x = np.abs(1 + 0.2 * rng.standard_normal((2, M, T))) / T
+    x = np.maximum.accumulate(x[:, ::-1], axis=1)[:, ::-1]
+    if scores == "dozens":
+        x = np.round(x * T * 256) / (256 * T)
+    elif scores == "stretches":
+        x = np.repeat(x[:, :, ::40], 40, axis=2)[:, :, :T]
+    elif scores == "lowest":
+        r = rng.random(x.shape)
+        x = np.where(r < 0.5, -3.4e38, np.where(r < 0.6, np.nan, -3.3e38 * (0.9 + 0.1 * r)))
+    else:
+        x = np.round(x * T * 8) / (8 * T)
+        if scores == "near":   # a few units in the last place
+            x = np.where(rng.random(x.shape) < 0.2, x * (1 + 1e-6 * rng.random(x.shape)), x)
+    alpha = x.astype(np.float32)
+    print(f"trace full bin T={T} B={B} L={L} M={M} {scores}", flush=True)
+    d_kept = torch.full((2, M, B), -1, dtype=torch.int32, device="cuda")
+    fk.fk_golden_trace(torch.from_numpy(alpha).cuda(), T, B, L, d_kept)
+    assert np.array_equal(d_kept.cpu().numpy(), golden.trace(alpha, B, L))
+
+
 def test_layer_slice_at_paper_budget(gpu):
     """Budget 256, L 64 on a 2048-token trace, 8 query heads in 2 groups, bf16: 27 steps, tiles on and
     off the diagonal, every output compared."""
