@@ -452,22 +452,29 @@ __global__ __launch_bounds__((AttnCfg<T, D, G>::THREADS)) void attn_kernel(const
         const int ntiles = (end - start + KT - 1) / KT;
         const int rot = P.rotate ? attn_rotation(row, split, ntiles) : 0;
         auto base_of = [&](int t) { return start + (t + rot < ntiles ? t + rot : t + rot - ntiles) * KT; };
-        auto fetch64 = [&](int base, B128 (&kd)[2][2], uint2 (&v)[8]) {   // D = 64
+        // Feature steps run one workgroup a row: with one head, whose softmax is short, the next tile's loads are issued a tile ahead (32
+        // rows of 8192 pairs 62 -> 55 us; with more heads the registers cost more than that: four heads +10 %, eight +30 % at 512 rows).
+        constexpr bool AHEAD = FEAT && D == 64 && G == 1;
+        // The order of a tile's loads, head_dim 64: K's first halves, its second halves, V (one head, 128 rows of 2112 pairs 14.1 us; the halves of
+        // a row together 14.8).  Feature steps: the halves of a row together (four heads, 32 rows of 4000 pairs 36.3 us, otherwise 37.7), and a
+        // tile ahead V before K (32 rows of 4000 pairs 31.2 us, otherwise 32.5).
+        auto fetch64 = [&](int base, B128 (&kd)[2][2], uint2 (&v)[8]) {
+            auto load_k = [&]() {
 #pragma unroll
-            for (int nt = 0; nt < 2; ++nt) {
-                const int kc = min(base + attn_qk_key<D>(nt, n16), end - 1);
-#pragma unroll
-                for (int ks = 0; ks < 2; ++ks) kd[nt][ks].u = ld_stream<NT>((kc == new_slot ? knew_row : Krow + (size_t)kc * CH) + ks * 4 + quad);
-            }
+                for (int i = 0; i < 4; ++i) {
+                    const int nt = FEAT ? i / 2 : i % 2, ks = FEAT ? i % 2 : i / 2;
+                    const int kc = min(base + attn_qk_key<D>(nt, n16), end - 1);
+                    kd[nt][ks].u = ld_stream<NT>((kc == new_slot ? knew_row : Krow + (size_t)kc * CH) + ks * 4 + quad);
+                }
+            };
+            if constexpr (!AHEAD) load_k();
 #pragma unroll
             for (int u = 0; u < 8; ++u) {  // lane (quad, n16): key base + quad*8 + u, channels n16*4 .. +4
                 const int kc = min(base + quad * 8 + u, end - 1);
                 v[u] = ld_stream<NT>(reinterpret_cast<const uint2*>(kc == new_slot ? vnew_row : Vrow + (size_t)kc * CH) + n16);
             }
+            if constexpr (AHEAD) load_k();
         };
-        // Feature steps run one workgroup a row: with one head, whose softmax is short, the next tile's loads are issued a tile ahead (32
-        // rows of 8192 pairs 62 -> 55 us; with more heads the registers cost more than that: four heads +10 %, eight +30 % at 512 rows).
-        constexpr bool AHEAD = FEAT && D == 64 && G == 1;
         B128 kd_next[2][2];
         uint2 v_next[8];
         if constexpr (AHEAD) {
