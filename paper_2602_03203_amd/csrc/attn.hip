@@ -249,8 +249,12 @@ __device__ __forceinline__ int row_by_length(const int32_t* len, int rows, int c
     return row;
 }
 
+// Two heads of head_dim 128 are told to leave room for two workgroups on a CU, which they do by themselves but for two registers (130 of
+// them, 128 told: 512 rows of 300 pairs 15.6 and 13.9 us; the same streamed 14.4 and 12.4).  One and three heads have 128; four 125; told, they spill.
+template <typename T, int D, int G, bool FEAT> constexpr bool attn_two() { return sizeof(T) == 2 && D == 128 && G == 2 && !FEAT; }
+
 template <typename T, int D, int G, bool FEAT, bool NT>
-__global__ __launch_bounds__((AttnCfg<T, D, G>::THREADS)) void attn_kernel(const AttnParams P) {
+__global__ __launch_bounds__((AttnCfg<T, D, G>::THREADS), (attn_two<T, D, G, FEAT>() ? 4 : AttnCfg<T, D, G>::WAVES / 4)) void attn_kernel(const AttnParams P) {
     using C = AttnCfg<T, D, G>;
     constexpr int CH = C::CH, KG = C::KG, WAVES = C::WAVES, KT = C::KT, VU = C::VU, EPL = C::EPL, GP = C::GP, NG = C::NG;
     extern __shared__ __attribute__((aligned(16))) float smem[];
@@ -403,14 +407,14 @@ __global__ __launch_bounds__((AttnCfg<T, D, G>::THREADS)) void attn_kernel(const
 
     if constexpr (C::PVM) {
         constexpr int PS = C::PS, KRS = C::KRS;
-        const int n16 = lane & 15, quad = lane >> 4, key0 = attn_qk_key<D>(0, n16);   // the lane's logits: keys key0 and key0 + KEY1 of a tile
+        const int n16 = lane & 15, quad = lane >> 4;
         constexpr int KEY1 = attn_qk_key<D>(1, 0);
         constexpr int KS = D / 32;          // k-steps of q.K^T
         constexpr int ET = D / 16;          // channel tiles of P.V
         constexpr int HR = G < 4 ? G : 4;   // of a lane's four result rows, those that can belong to a head
         uint16_t* my_pb = reinterpret_cast<uint16_t*>(s_p) + (size_t)wave * C::PROWS * PS;   // [PROWS][PS] bf16
         unsigned char* my_k = s_kt + (size_t)wave * KT * KRS;   // D = 128
-        auto put_pair = [&](uint16_t* p, uint32_t w) {   // probabilities of the lane's two keys
+        auto put_pair = [&](uint16_t* p, int key0, uint32_t w) {   // probabilities of the lane's two keys
             if constexpr (KEY1 == 1) {
                 *reinterpret_cast<uint32_t*>(p + key0) = w;
             } else {
@@ -529,6 +533,9 @@ __global__ __launch_bounds__((AttnCfg<T, D, G>::THREADS)) void attn_kernel(const
                     c[nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(qa[ks].v, kb.v, c[nt], 0, 0, 0);
                 }
             }
+            int any_lane = threadIdx.x;
+            if constexpr (attn_two<T, D, G, FEAT>()) asm volatile("" : "+v"(any_lane));   // (opaque: the key would stay in a register)
+            const int key0 = attn_qk_key<D>(0, any_lane & 15);   // the lane's logits: keys key0 and key0 + KEY1 of the tile
             bool changed = false;
             float corr[4];
             uint32_t pw[4], p3[4];   // bf16 pairs: keys key0 and key0 + KEY1
@@ -570,9 +577,9 @@ __global__ __launch_bounds__((AttnCfg<T, D, G>::THREADS)) void attn_kernel(const
             if (quad * 4 < C::PROWS) {
 #pragma unroll
                 for (int i = 0; i < HR; ++i) {
-                    put_pair(my_pb + (quad * 4 + i) * PS, pw[i]);
+                    put_pair(my_pb + (quad * 4 + i) * PS, key0, pw[i]);
                     if constexpr (THIRD) {
-                        if (quad < 2) put_pair(my_pb + (16 + quad * 4 + i) * PS, p3[i]);
+                        if (quad < 2) put_pair(my_pb + (16 + quad * 4 + i) * PS, key0, p3[i]);
                     }
                 }
             }
