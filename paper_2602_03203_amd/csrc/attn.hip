@@ -250,7 +250,8 @@ __device__ __forceinline__ int row_by_length(const int32_t* len, int rows, int c
 }
 
 // Two heads of head_dim 128 are told to leave room for two workgroups on a CU, which they do by themselves but for two registers (130 of
-// them, 128 told: 512 rows of 300 pairs 15.6 and 13.9 us; the same streamed 14.4 and 12.4).  One and three heads have 128; four 125; told, they spill.
+// them, 128 told: 512 rows of 300 pairs 15.6 and 13.9 us; the same streamed 14.4 and 12.4).  One and three heads have 128; four 125; told,
+// they spill.
 template <typename T, int D, int G, bool FEAT> constexpr bool attn_two() { return sizeof(T) == 2 && D == 128 && G == 2 && !FEAT; }
 
 template <typename T, int D, int G, bool FEAT, bool NT>

@@ -38,8 +38,8 @@ static constexpr int kCompactThreads = 1024;
 // + wL and the four chunk planes restart from zero; rows over budget move slot keep[j] to slot
 // j in the same pass (ascending tiles, all sources of a tile read before it is written: the
 // argument of compact_kernel).  One workgroup per row; a thread owns 4 heads of a slot.  The workgroups of compact_kernel's launch that run
-// it come first in its grid: 128 rows of 2176 pairs, four heads, 8.6 us in a launch of its own before the compaction's 42; in one launch 46.4. (Two workgroups a CU, with four
-// registers spilled, take 53: more rows in flight make the compaction slower, 42 -> 48.)
+// it come first in its grid: 128 rows of 2176 pairs, four heads, 8.6 us in a launch of its own before the compaction's 42; in one launch
+// 46.4. (Two workgroups a CU, with four registers spilled, take 53: more rows in flight make the compaction slower, 42 -> 48.)
 // ---------------------------------------------------------------------------------------
 
 template <int Q4 /* float4 units per slot */>
@@ -149,8 +149,8 @@ __global__ __launch_bounds__(kCompactThreads) void compact_kernel(uint4* __restr
     const int sl = threadIdx.x / kSliceChunks;           // slot within that group
     const int c = threadIdx.x % kSliceChunks;            // 16-byte chunk inside the slice
     // One tile's rows and another tile's indices are in flight while a tile is stored (128 rows of 2048 kept pairs, 265 MB read and
-    // written: 49 us with a round trip to memory per tile, 41.5 us, 6.4 TB/s, so; 32 rows: 25 and 14.7 us).  The rows of tile t + 1 may be read before
-    // tile t is stored: they lie at or behind their own destinations, past the slots of tile t.
+    // written: 49 us with a round trip to memory per tile, 41.5 us, 6.4 TB/s, so; 32 rows: 25 and 14.7 us).  The rows of tile t + 1 may be
+    // read before tile t is stored: they lie at or behind their own destinations, past the slots of tile t.
     auto load_idx = [&](int base, int (&src)[kCompactU]) {   // -1: nothing to move
 #pragma unroll
         for (int u = 0; u < kCompactU; ++u) {

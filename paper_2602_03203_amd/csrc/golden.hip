@@ -65,8 +65,8 @@ __global__ __launch_bounds__(kPoolThreads) void golden_pool_kernel(const T* __re
             // A head has less than the loads in flight take, so they go on into the next ones.  (Head by head, 32 heads of 4096 tokens, L = 16:
             // 226 us, so 131; 32 heads of 2000 tokens in 4 groups, L = 8: 107 and 55.  From 64 queries on, head by head is 1 to 3 % the
             // faster; a kernel of its own, because the other one's registers cost these short workgroups their number on a CU, 8 heads of 4096 tokens
-            // without pooling, L = 32: 52 us in one kernel, 42 so.)  This row group takes pairs (head, query) rg, rg + RG, ...: dh heads and dq queries on, one head
-            // more where that leaves the block.
+            // without pooling, L = 32: 52 us in one kernel, 42 so.)  This row group takes pairs (head, query) rg, rg + RG, ...: dh heads
+            // and dq queries on, one head more where that leaves the block.
             constexpr int U = kPoolU / 2;
             const int total = rows * g, dh = RG / rows, dq = RG % rows;
             const size_t step = ((size_t)dh * Tn + dq) * ld, wrap = (size_t)(Tn - rows) * ld;
@@ -225,8 +225,9 @@ __global__ __launch_bounds__(kTrThreads) void golden_trace_kernel(const float* _
     uint16_t* s_fresh_slot = reinterpret_cast<uint16_t*>(smem + off.fresh_slot);
     uint8_t* s_gone = smem + off.gone;
     __shared__ __attribute__((aligned(16))) uint32_t s_hist[3][kTrBins];   // this step's, the next one's; of a recount, zero in between
-    // [0] key and [1] position of the highest pair that goes | [2] found: 2 among equal keys | [3] shift of the bins, [4] first key of the bins | not found: the
-    // cut is number [5] of the [0] pairs (all ones: it is not known how many) with the [7] keys after [6]; [1]: these are the only keys in its bin, perhaps
+    // [0] key and [1] position of the highest pair that goes | [2] found: 2 among equal keys | [3] shift of the bins, [4] first key of the
+    // bins | not found: the cut is number [5] of the [0] pairs (all ones: it is not known how many) with the [7] keys after [6]; [1]: these
+    // are the only keys in its bin, perhaps
     __shared__ __attribute__((aligned(16))) uint32_t s_cut[8];
     __shared__ uint32_t s_taken[2], s_lo, s_hi, s_count[kTrWriteWaves];
     const int hp = blockIdx.x, k = budget - L, wave = threadIdx.x / kWave;

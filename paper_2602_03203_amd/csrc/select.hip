@@ -24,7 +24,7 @@ struct SelLds {
 };
 // Two workgroups of sixteen wavefronts share a CU if a wavefront takes no more than 64 vector registers and 80 scalar ones (800 of
 // them a SIMD, and sixteen more for every wavefront): 512 rows of 2176 keys 12.8 -> 10.2 us with 78 instead of 93, sampled
-// 22.3 -> 16.9 with 78 instead of 90 (20.1 before its range selection, with 58).  About fifty of them spilled to vector lanes do
+// 22.3 -> 16.9 with 78 instead of 90 (20.1 before its range selection, with 58).  The 40 to 45 of them that are spilled to vector lanes do
 // not show at 128 rows.
 #define FK_TWO_PER_CU __attribute__((amdgpu_num_sgpr(80)))
 // (Four wavefronts per row instead of sixteen were measured and dropped: 11.3 against 8.1 us; a pass is a chain
@@ -219,7 +219,8 @@ __global__ __launch_bounds__(THREADS) FK_TWO_PER_CU void select_keep_kernel(cons
 // 32 rows of 131072 pairs, the best 1920, both launches, us, without a bound and with it: normal scores 45.0 and 23.2, all equal 30.5
 // and 24.8, two values 42.0 and 27.5, the best in one chunk 47.3 and 39.5, rising scores 48.7 and 34.2.  64 rows, chunks of 32736: 49.5
 // and 37.1, 30.5 and 30.2, 52.0 and 32.8, 51.3 and 52.5, 50.9 and 47.5.  What it loses is the sample's time where every chunk still walks all its
-// pairs: 32 rows of 32768, all equal, 17.2 and 17.7.  (With a row's chunks on all XCDs, each of which then fetches the sample, the first launch takes 21 us, not 14.)
+// pairs: 32 rows of 32768, all equal, 17.2 and 17.7.  (With a row's chunks on all XCDs, each of which then fetches the sample, the first
+// launch takes 21 us, not 14.)
 static constexpr int kSelSample = 2048;
 
 template <int THREADS>
