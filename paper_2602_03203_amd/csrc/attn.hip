@@ -252,7 +252,7 @@ __device__ __forceinline__ int row_by_length(const int32_t* len, int rows, int c
 // Two heads of head_dim 128 are told to leave room for two workgroups on a CU, which they do by themselves but for two registers (130 of
 // them, 128 told: 512 rows of 300 pairs 15.6 and 13.9 us; the same streamed 14.4 and 12.4).  One and three heads have 128; four 125; told,
 // they spill.
-template <typename T, int D, int G, bool FEAT> constexpr bool attn_two() { return sizeof(T) == 2 && D == 128 && G == 2 && !FEAT; }
+template <typename T, int D, int G, bool FEAT> constexpr bool attn_two() { return sizeof(T) == 2 && D == 128 && G <= 3 && !FEAT; }
 
 template <typename T, int D, int G, bool FEAT, bool NT>
 __global__ __launch_bounds__((AttnCfg<T, D, G>::THREADS), (attn_two<T, D, G, FEAT>() ? 4 : AttnCfg<T, D, G>::WAVES / 4)) void attn_kernel(const AttnParams P) {
@@ -430,7 +430,13 @@ __global__ __launch_bounds__((AttnCfg<T, D, G>::THREADS), (attn_two<T, D, G, FEA
             if (h < G) qa[ks].u = *reinterpret_cast<const uint4*>(qrow + (size_t)h * D + ks * 32 + quad * 8);
             else qa[ks].u = make_uint4(0, 0, 0, 0);
         }
-        float m_run[4], l_run[4], lx_run[4];  // lx: sum of the unrounded weights (feature variant)
+        const float scale = P.scale_log2e, hidden = scale < 0.f ? INFINITY : -INFINITY;   // hidden: of no weight; the scale is never 0 (attn_scale)
+        // l: the normaliser, of unrounded weights where P.V has all their bits (SPLIT_P), otherwise a 65th column of ones in P.V, the same
+        // rounded weights; lx: sum of the unrounded weights (feature variant)
+        float m_run[4], l_run[4], lx_run[4];
+        f32x4_t ol = (f32x4_t){0.f, 0.f, 0.f, 0.f};
+        B128 ones;
+        ones.u = make_uint4(0x3f803f80u, 0x3f803f80u, 0x3f803f80u, 0x3f803f80u);
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
             m_run[i] = kNegBig;
@@ -544,21 +550,21 @@ __global__ __launch_bounds__((AttnCfg<T, D, G>::THREADS), (attn_two<T, D, G, FEA
                 if (quad * 4 < GP) {
                     if (base + key0 < end)
                         *reinterpret_cast<float4*>(lg_row + (size_t)(base + key0) * GP + quad * 4) =
-                            make_float4(c[0][0] * P.scale_log2e, c[0][1] * P.scale_log2e, c[0][2] * P.scale_log2e, c[0][3] * P.scale_log2e);
+                            make_float4(c[0][0] * scale, c[0][1] * scale, c[0][2] * scale, c[0][3] * scale);
                     if (base + key0 + KEY1 < end)
                         *reinterpret_cast<float4*>(lg_row + (size_t)(base + key0 + KEY1) * GP + quad * 4) =
-                            make_float4(c[1][0] * P.scale_log2e, c[1][1] * P.scale_log2e, c[1][2] * P.scale_log2e, c[1][3] * P.scale_log2e);
+                            make_float4(c[1][0] * scale, c[1][1] * scale, c[1][2] * scale, c[1][3] * scale);
                 }
             }
 #pragma unroll
             for (int i = 0; i < HR; ++i) {
-                const float s0 = (base + key0 < end) ? c[0][i] * P.scale_log2e : kNegBig;
-                const float s1 = (base + key0 + KEY1 < end) ? c[1][i] * P.scale_log2e : kNegBig;
-                const float mn = fmaxf(m_run[i], row16_max(fmaxf(s0, s1)));
+                const float s0 = (base + key0 < end) ? c[0][i] : hidden;
+                const float s1 = (base + key0 + KEY1 < end) ? c[1][i] : hidden;
+                const float mn = fmaxf(m_run[i], row16_max(fmaxf(s0 * scale, s1 * scale)));
                 changed |= mn > m_run[i];
                 corr[i] = exp2f(m_run[i] - mn);
                 // probabilities rounded to bf16; the SAME rounded values go into l, so the weights stay normalised
-                const float e0 = exp2f(s0 - mn), e1 = exp2f(s1 - mn);
+                const float e0 = exp2f(fmaf(s0, scale, -mn)), e1 = exp2f(fmaf(s1, scale, -mn));
                 const uint32_t w = pack_bf16(e0, e1);
                 pw[i] = w;
                 if constexpr (C::SPLIT_P) {   // each term of what the ones before leave; GP = 4: row quad q holds term q, GP = 8: q / 2
@@ -570,7 +576,6 @@ __global__ __launch_bounds__((AttnCfg<T, D, G>::THREADS), (attn_two<T, D, G, FEA
                     if constexpr (!THIRD) pw[i] = term < 2 ? pw[i] : p3[i];
                     l_run[i] = l_run[i] * corr[i] + e0 + e1;
                 } else {
-                    l_run[i] = l_run[i] * corr[i] + bf16_lo(w) + bf16_hi(w);
                     if constexpr (FEAT) lx_run[i] = lx_run[i] * corr[i] + e0 + e1;
                 }
                 m_run[i] = mn;
@@ -592,6 +597,10 @@ __global__ __launch_bounds__((AttnCfg<T, D, G>::THREADS), (attn_two<T, D, G, FEA
                         o[e][i] *= corr[i];
                         if constexpr (THIRD) o3[e][i] *= corr[i];
                     }
+                if constexpr (!C::SPLIT_P) {
+#pragma unroll
+                    for (int i = 0; i < HR; ++i) ol[i] *= corr[i];
+                }
             }
             if (base + KT > end) {
                 // The lanes past the end hold copies of the last pair, whose weight 0 there must not meet an infinity or a NaN.  Where it has
@@ -616,6 +625,7 @@ __global__ __launch_bounds__((AttnCfg<T, D, G>::THREADS), (attn_two<T, D, G, FEA
             if constexpr (THIRD) {
                 if (n16 < GP) pr.u = *reinterpret_cast<const uint4*>(my_pb + (16 + n16) * PS + quad * 8);
             }
+            if constexpr (!C::SPLIT_P) ol = __builtin_amdgcn_mfma_f32_16x16x32_bf16(pa.v, ones.v, ol, 0, 0, 0);
             // B operand: tile e = channel n16*ET + e over this lane's 8 k-slots (8 x ET transpose in registers)
 #pragma unroll
             for (int e = 0; e < ET; ++e) {
@@ -634,7 +644,7 @@ __global__ __launch_bounds__((AttnCfg<T, D, G>::THREADS), (attn_two<T, D, G, FEA
 #pragma unroll
         for (int i = 0; i < HR; ++i) {
             const int h = quad * 4 + i;
-            const float ls = group_sum<16>(l_run[i]);
+            const float ls = C::SPLIT_P ? group_sum<16>(l_run[i]) : ol[i];
             const int ht = C::SPLIT_P ? h % GP : h, term = C::SPLIT_P ? h / GP : 0;   // SPLIT_P: row h holds term `term` of head ht
             float* dst = s_acc + (size_t)wave * C::ACC_STRIDE + (size_t)(term * G + ht) * D + n16 * ET;  // D = 128: own K tile, its loop is over
             if (ht < G && h < C::PROWS) {
@@ -954,7 +964,7 @@ static fk_status attn_entry(const fk_cache_desc* desc, AttnParams P, int max_len
     const size_t need = P.feat ? feat_workspace_bytes(desc) : fk_decode_attn_workspace(desc, max_len);
     if (!workspace || workspace_bytes < need || !aligned16(workspace)) return FK_ERR_WORKSPACE;
     const int g = desc->n_q_heads / desc->n_kv_heads;
-    P.scale_log2e = softmax_scale * 1.4426950408889634f;
+    P.scale_log2e = attn_scale(softmax_scale);
     P.n_kv = desc->n_kv_heads;
     P.cap = desc->capacity;
     hipStream_t st = (hipStream_t)stream;
@@ -1075,7 +1085,7 @@ static WindowParams window_params(const fk_cache_desc* d, const void* q, void* K
     P.len = len;
     P.pos_seq = pos_seq;
     P.out_seq = out;
-    P.scale_log2e = scale * 1.4426950408889634f;
+    P.scale_log2e = attn_scale(scale);
     P.batch = d->batch;
     P.n_kv = d->n_kv_heads;
     P.g = d->n_q_heads / d->n_kv_heads;

@@ -144,6 +144,7 @@ __global__ __launch_bounds__(kXThreads, 2) void window_attn_kernel(const WindowP
         const xu32x4_t q = reinterpret_cast<const xu32x4_t*>(P.q_seq)[q_row(k, r) * CH + ch];
         *reinterpret_cast<xu32x4_t*>(s_q + (k * 16 + r) * KRS + ch * 16) = live ? q : xu32x4_t{0, 0, 0, 0};
     }
+    const float scale = P.scale_log2e, hidden = scale < 0.f ? INFINITY : -INFINITY;   // hidden: of no weight; the scale is never 0 (attn_scale)
     if (tid == 0) s_bad = 0;
     if constexpr (SPLIT) {   // the splits of every step; what its tile walks depend on beside their lengths
         if (tid < t_end - t_first) {
@@ -230,7 +231,7 @@ __global__ __launch_bounds__(kXThreads, 2) void window_attn_kernel(const WindowP
 #pragma unroll
                         for (int nt = 0; nt < 2; ++nt)
 #pragma unroll
-                            for (int i = 0; i < 4; ++i) mx[k] = fmaxf(mx[k], base + attn_qk_key<D>(nt, quad * 4 + i) < lim[k] ? c[nt][i] * P.scale_log2e : kXNegBig);
+                            for (int i = 0; i < 4; ++i) mx[k] = fmaxf(mx[k], base + attn_qk_key<D>(nt, quad * 4 + i) < lim[k] ? c[nt][i] * scale : kXNegBig);
                     }
                     if (t + 1 == w1 || min((base + kXKT) / split_len, nsplit - 1) != mine) {
 #pragma unroll
@@ -251,12 +252,18 @@ __global__ __launch_bounds__(kXThreads, 2) void window_attn_kernel(const WindowP
             const int wave = __builtin_amdgcn_readfirstlane(tile_tid / kWave);   // (the walk and its addresses are the wavefront's: scalars, branches)
             const int ntiles = (stop - start + kXKT - 1) / kXKT;
             const int rot = rotate ? attn_rotation(row, sp, ntiles) : 0;
-            float m_run[GROUPS], l_run[GROUPS][4], lx_run[GROUPS][4];   // l: one sum per key of a quarter of the tile, as in a single step
+            float m_run[GROUPS], l_run[GROUPS][4], lx_run[GROUPS][4];   // l, lx: one sum per key of a quarter of the tile, as in a single step
+            // l as a channel of ones (head_dim 128): the matrix cores add what took sixteen of some 115 vector instructions of a tile and group, and a
+            // logit goes into its exponential's argument by one fma: 128 rows of 2048 pairs, 128 steps 168.2 us, so 164.0.  [0] is rescaled and used.
+            xf32x4_t ol[GROUPS];
+            X128 ones;
+            ones.u = xu32x4_t{0x3f803f80u, 0x3f803f80u, 0x3f803f80u, 0x3f803f80u};
             xf32x4_t o[GROUPS][ET];                                       // o[k][e][i]: channel (quad * 4 + i) * ET + e, un-normalised
             xf32x4_t o2[GROUPS][TERMS > 1 ? ET : 1], o3[GROUPS][TERMS > 1 ? ET : 1];   // those of the second and third terms
 #pragma unroll
             for (int k = 0; k < GROUPS; ++k) {
                 m_run[k] = kXNegBig;
+                ol[k] = (xf32x4_t){0.f, 0.f, 0.f, 0.f};
 #pragma unroll
                 for (int i = 0; i < 4; ++i) l_run[k][i] = lx_run[k][i] = 0.f;
 #pragma unroll
@@ -329,26 +336,29 @@ __global__ __launch_bounds__(kXThreads, 2) void window_attn_kernel(const WindowP
 #pragma unroll
                 for (int k = 0; k < GROUPS; ++k) {
                     const int left = lim[k] - base;   // this lane's query sees the tile's keys [0, left)
-                    float mn = kXNegBig;
+                    if (partial) {
+#pragma unroll
+                        for (int j = 0; j < 8; ++j)
+                            if (key_of(j) >= left) c[k][j / 4][j % 4] = hidden;
+                    }
+                    // the largest of c * scale is the largest c's (a negative scale: the smallest one's)
+                    float mn;
+                    if (scale < 0.f) {
+                        mn = -c[k][0][0];
+#pragma unroll
+                        for (int j = 1; j < 8; ++j) mn = fmaxf(mn, -c[k][j / 4][j % 4]);
+                    } else {
+                        mn = c[k][0][0];
+#pragma unroll
+                        for (int j = 1; j < 8; ++j) mn = fmaxf(mn, c[k][j / 4][j % 4]);
+                    }
+                    mn = fmaxf(m_run[k], quads_max(mn) * fabsf(scale));
+                    changed[k] = mn > m_run[k];
+                    x[k][8] = m_run[k] - mn;
+                    lo = fminf(lo, x[k][8]);
 #pragma unroll
                     for (int j = 0; j < 8; ++j) {
-                        x[k][j] = c[k][j / 4][j % 4] * P.scale_log2e;
-                        mn = fmaxf(mn, x[k][j]);
-                    }
-                    if (partial) {
-                        mn = kXNegBig;
-#pragma unroll
-                        for (int j = 0; j < 8; ++j) {
-                            if (key_of(j) >= left) x[k][j] = kXNegBig;
-                            mn = fmaxf(mn, x[k][j]);
-                        }
-                    }
-                    mn = fmaxf(m_run[k], quads_max(mn));
-                    changed[k] = mn > m_run[k];
-                    x[k][8] = m_run[k];
-#pragma unroll
-                    for (int j = 0; j < 9; ++j) {
-                        x[k][j] -= mn;
+                        x[k][j] = fmaf(c[k][j / 4][j % 4], scale, -mn);
                         lo = fminf(lo, x[k][j]);
                     }
                     m_run[k] = mn;
@@ -364,13 +374,6 @@ __global__ __launch_bounds__(kXThreads, 2) void window_attn_kernel(const WindowP
 #pragma unroll
                         for (int j = 0; j < 9; ++j) x[k][j] = __builtin_amdgcn_exp2f(x[k][j]);
                 }
-                if (partial) {   // 0 also where a step sees none of the tile
-#pragma unroll
-                    for (int k = 0; k < GROUPS; ++k)
-#pragma unroll
-                        for (int j = 0; j < 8; ++j)
-                            if (key_of(j) >= lim[k] - base) x[k][j] = 0.f;
-                }
                 X128 pa[GROUPS][TERMS];   // probabilities of query n16 in bf16, term by term: the keys of this lane's logits, quad * 8 + u
                 auto at = [](int u) { return D == 128 ? u % 2 * 4 + u / 2 : u; };   // the u-th of these keys is logit at(u)
 #pragma unroll
@@ -384,8 +387,7 @@ __global__ __launch_bounds__(kXThreads, 2) void window_attn_kernel(const WindowP
                     }
 #pragma unroll
                     for (int i = 0; i < 4; ++i) {
-                        if constexpr (TERMS == 1) l_run[k][i] = fmaf(l_run[k][i], x[k][8], y[i]) + y[4 + i];
-                        else l_run[k][i] = fmaf(l_run[k][i], x[k][8], x[k][i]) + x[k][4 + i];
+                        if constexpr (TERMS > 1) l_run[k][i] = fmaf(l_run[k][i], x[k][8], x[k][i]) + x[k][4 + i];
                         if constexpr (FEAT) lx_run[k][i] = fmaf(lx_run[k][i], x[k][8], x[k][i]) + x[k][4 + i];
                     }
                     if constexpr (TERMS > 1) {   // each term of what the ones before leave (the third has no bits beyond bf16)
@@ -401,6 +403,7 @@ __global__ __launch_bounds__(kXThreads, 2) void window_attn_kernel(const WindowP
 #pragma unroll
                     for (int k = 0; k < GROUPS; ++k) {
                         if (!__any(changed[k])) continue;
+                        if constexpr (TERMS == 1) ol[k][0] *= x[k][8];
 #pragma unroll
                         for (int e = 0; e < ET; ++e)
 #pragma unroll
@@ -434,6 +437,10 @@ __global__ __launch_bounds__(kXThreads, 2) void window_attn_kernel(const WindowP
                     }
                 }
                 if (bad && tb - ta > 1) s_bad = 1;
+                if constexpr (TERMS == 1) {
+#pragma unroll
+                    for (int k = 0; k < GROUPS; ++k) ol[k] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ones.v, pa[k][0].v, ol[k], 0, 0, 0);
+                }
 #pragma unroll
                 for (int e = 0; e < ET; ++e) {
                     const X128 vb = transposed(e);
@@ -470,7 +477,7 @@ __global__ __launch_bounds__(kXThreads, 2) void window_attn_kernel(const WindowP
                         publish(dst + 16 * PART, o2[k]);
                         publish(dst + 32 * PART, o3[k]);
                     }
-                    const float ls = quads_sum((l_run[k][0] + l_run[k][1]) + (l_run[k][2] + l_run[k][3]));
+                    const float ls = TERMS == 1 ? ol[k][0] : quads_sum((l_run[k][0] + l_run[k][1]) + (l_run[k][2] + l_run[k][3]));
                     const float lxs = FEAT ? quads_sum((lx_run[k][0] + lx_run[k][1]) + (lx_run[k][2] + lx_run[k][3])) : 0.f;
                     if (quad == 0) {
                         const int i = (g * kXWaves + wave) * 16 + n16;
