@@ -97,20 +97,44 @@ __device__ __forceinline__ float row16_max(float v) {
     return v;
 }
 
+// over the KG key groups of a wavefront (fp32): lanes that differ in bit 5, and with four groups in bit 4
+__device__ __forceinline__ float add_halves(float a, float b) {   // lower lanes: a of both halves; upper ones: b
+    auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+    return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+__device__ __forceinline__ float add_rows(float a, float b) {   // even rows of 16 lanes: a of two neighbouring rows; odd ones: b
+    auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+    return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+template <int KG> __device__ __forceinline__ float lanes_sum(float v) {
+    v = add_halves(v, v);
+    return KG == 4 ? add_rows(v, v) : v;
+}
+template <int KG> __device__ __forceinline__ float lanes_max(float v) {
+    auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    v = fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+    if (KG == 4) {
+        auto x = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+        v = fmaxf(__uint_as_float(x[0]), __uint_as_float(x[1]));
+    }
+    return v;
+}
+
 // ---- geometry ------------------------------------------------------------------------------
-template <typename T, int D, int G> struct AttnCfg {
+// HEADS: fp32, a workgroup for every query head (attn_by_head)
+template <typename T, int D, int G, bool HEADS = false> struct AttnCfg {
     static constexpr bool MFMA = sizeof(T) == 2;
     static constexpr bool PVM = MFMA;                       // P.V on MFMA as well
     static constexpr bool SPLIT_P = PVM && D == 64;         // probabilities as three bf16 terms, together all 24 bits of them
     static constexpr int CH = D * (int)sizeof(T) / 16;      // 16-byte chunks per row = lanes per key (P.V layout)
     static constexpr int KG = kWave / CH;                   // key groups per wave in the P.V layout
-    static constexpr int WAVES = PVM ? 8 : 4;
+    static constexpr int WAVES = PVM ? 8 : HEADS ? 16 : 4;
     static constexpr int THREADS = WAVES * kWave;
     static constexpr int KT = MFMA ? 32 : KG * 4;           // keys per wave iteration
     static constexpr int VU = KT / KG;                      // V (and fp32 K) loads per lane per iteration
     static constexpr int EPL = Vec16<T>::N;                 // channels per lane
     static constexpr int GP = G <= 4 ? 4 : 8;               // heads padded to the MFMA result rows in use
-    static constexpr int NG = PVM ? WAVES : WAVES * KG;     // partial accumulators per workgroup
+    static constexpr int NG = PVM || HEADS ? WAVES : WAVES * KG;     // partial accumulators per workgroup
     static constexpr int PS = KT + 8;                       // PVM: bf16 row stride of the P tile in LDS
     static constexpr int KRS = 272;                         // D = 128: padded byte stride of a K row in LDS
     // dynamic LDS (floats unless noted):
@@ -254,17 +278,17 @@ __device__ __forceinline__ int row_by_length(const int32_t* len, int rows, int c
 // they spill.
 template <typename T, int D, int G, bool FEAT> constexpr bool attn_two() { return sizeof(T) == 2 && D == 128 && G <= 3 && !FEAT; }
 
-template <typename T, int D, int G, bool FEAT, bool NT>
-__global__ __launch_bounds__((AttnCfg<T, D, G>::THREADS), (attn_two<T, D, G, FEAT>() ? 4 : AttnCfg<T, D, G>::WAVES / 4)) void attn_kernel(const AttnParams P) {
-    using C = AttnCfg<T, D, G>;
+template <typename T, int D, int G, bool FEAT, bool NT, bool HEADS = false>
+__global__ __launch_bounds__((AttnCfg<T, D, G, HEADS>::THREADS), (attn_two<T, D, G, FEAT>() ? 4 : AttnCfg<T, D, G, HEADS>::WAVES / 4)) void attn_kernel(const AttnParams P) {
+    using C = AttnCfg<T, D, G, HEADS>;
     constexpr int CH = C::CH, KG = C::KG, WAVES = C::WAVES, KT = C::KT, VU = C::VU, EPL = C::EPL, GP = C::GP, NG = C::NG;
     extern __shared__ __attribute__((aligned(16))) float smem[];
     constexpr bool CAN_ORDER = C::PVM && NT && !FEAT;
-    int row = blockIdx.y;
+    int row = HEADS ? blockIdx.x : blockIdx.y;   // (HEADS: so that the workgroups of a row sit on one XCD where the rows are a multiple of eight)
     if constexpr (CAN_ORDER) {
         if (P.by_length) row = row_by_length<C::THREADS>(P.len, gridDim.y, P.cap, row, reinterpret_cast<int*>(smem));
     }
-    const int split = blockIdx.x;
+    const int split = HEADS ? 0 : blockIdx.x, head = HEADS ? blockIdx.y : 0, heads = HEADS ? gridDim.y : G;
     const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
 
     // PVM: head | P tiles | K tiles, the partial accumulators live in the K tiles; fp32: acc | head
@@ -283,7 +307,8 @@ __global__ __launch_bounds__((AttnCfg<T, D, G>::THREADS), (attn_two<T, D, G, FEA
     const int n = n_old + (do_append ? 1 : 0);
     // if the caller's max_len was too small the last split runs on to the row's end (slower, still right)
     const bool one_split = n <= P.split_len || P.nsplit == 1;   // (no division before the loads: they wait for what is worked out here)
-    T* out = reinterpret_cast<T*>(P.out) + (size_t)row * G * D;
+    T* out = reinterpret_cast<T*>(P.out) + ((size_t)row * heads + head) * D;
+    uint32_t arrived = 0;   // HEADS, thread 0
 
     // Every workgroup of the row calls finish() once, as its last action.  With one workgroup per
     // row it just publishes the new length.  With several, all of them (also those whose split lies
@@ -307,6 +332,13 @@ __global__ __launch_bounds__((AttnCfg<T, D, G>::THREADS), (attn_two<T, D, G, FEA
                     }
                 return;
             }
+        }
+        if constexpr (HEADS) {   // the last workgroup of the row: the others have read its length
+            if (do_append && tid == 0 && arrived == gridDim.y - 1) {
+                if (gridDim.y > 1) __hip_atomic_store(&P.row_cnt[row], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                P.len[row] = n;
+            }
+            return;
         }
         if (gridDim.x == 1) {
             if (do_append && tid == 0) P.len[row] = n;
@@ -383,7 +415,7 @@ __global__ __launch_bounds__((AttnCfg<T, D, G>::THREADS), (attn_two<T, D, G, FEA
     const bool owns_new = do_append && n_old >= start && n_old < end;
     const uint4* knew_row = reinterpret_cast<const uint4*>(reinterpret_cast<const T*>(P.k_new) + (size_t)row * D);
     const uint4* vnew_row = reinterpret_cast<const uint4*>(reinterpret_cast<const T*>(P.v_new) + (size_t)row * D);
-    if (owns_new) {
+    if (owns_new && head == 0) {
         if (tid < CH) {
             reinterpret_cast<uint4*>(Kr + (size_t)n_old * D)[tid] = knew_row[tid];
         } else if (tid < 2 * CH) {
@@ -391,12 +423,12 @@ __global__ __launch_bounds__((AttnCfg<T, D, G>::THREADS), (attn_two<T, D, G, FEA
         } else if (tid == 2 * CH) {
             P.pos[(size_t)row * P.cap + n_old] = P.pos_new[row / P.n_kv];
         }
-        if constexpr (!C::PVM) __syncthreads();  // the fp32 path reads the row back from the cache
+        if constexpr (!C::PVM && !HEADS) __syncthreads();  // this fp32 path reads the row back from the cache
     }
     const int new_slot = owns_new ? n_old : -1;
     const uint4* Krow = reinterpret_cast<const uint4*>(Kr);
     const uint4* Vrow = reinterpret_cast<const uint4*>(Vr);
-    const T* qrow = reinterpret_cast<const T*>(P.q) + (size_t)row * G * D;
+    const T* qrow = reinterpret_cast<const T*>(P.q) + ((size_t)row * heads + head) * D;
 
     const int dl = lane % CH;   // 16-byte chunk of the row (P.V layout)
     const int kgv = lane / CH;  // key group (P.V layout)
@@ -684,10 +716,14 @@ __global__ __launch_bounds__((AttnCfg<T, D, G>::THREADS), (attn_two<T, D, G, FEA
 #pragma unroll
             for (int u = 0; u < VU; ++u) {
                 key[u] = base + u * KG + kgv;
-                kr[u] = Krow[(size_t)min(key[u], end - 1) * CH + dl];
+                const int kc = min(key[u], end - 1);
+                kr[u] = (HEADS && kc == new_slot ? knew_row : Krow + (size_t)kc * CH)[dl];
             }
 #pragma unroll
-            for (int u = 0; u < VU; ++u) vr[u] = Vrow[(size_t)min(key[u], end - 1) * CH + dl];
+            for (int u = 0; u < VU; ++u) {
+                const int kc = min(key[u], end - 1);
+                vr[u] = (HEADS && kc == new_slot ? vnew_row : Vrow + (size_t)kc * CH)[dl];
+            }
             float s[VU][G];
 #pragma unroll
             for (int u = 0; u < VU; ++u) {
@@ -745,26 +781,50 @@ __global__ __launch_bounds__((AttnCfg<T, D, G>::THREADS), (attn_two<T, D, G, FEA
                     for (int e = 0; e < EPL; ++e) acc[h][e] = fmaf(p[u][h], vf[e], acc[h][e]);
             }
         }
-        if (dl == 0) {
+        if constexpr (HEADS) {
+            // The wavefront's key groups become one partial: two halves of the wavefront, with D = 64 two rows of 16 lanes in each.  A swap puts
+            // one value's parts beside the other's, so the sums of a pair take one addition: a lane ends with G * EPL / KG of them.
 #pragma unroll
             for (int h = 0; h < G; ++h) {
-                s_m[(wave * KG + kgv) * G + h] = m[h];
-                s_l[(wave * KG + kgv) * G + h] = l[h];
+                const float mn = lanes_max<KG>(m[h]), w = exp2f(m[h] - mn);
+                l[h] = lanes_sum<KG>(l[h] * w);
+#pragma unroll
+                for (int e = 0; e < EPL; ++e) acc[h][e] *= w;
+                if (lane == 0) {
+                    s_m[wave * G + h] = mn;
+                    s_l[wave * G + h] = l[h];
+                }
+                float* dst = s_acc + (size_t)wave * C::ACC_STRIDE + (size_t)h * D + dl * EPL;
+                const float a = add_halves(acc[h][0], acc[h][1]), b = add_halves(acc[h][2], acc[h][3]);   // upper lanes: of channels 1 and 3
+                if constexpr (KG == 2) {
+                    dst[lane / 32] = a;
+                    dst[2 + lane / 32] = b;
+                } else {
+                    dst[lane / 16 % 2 * 2 + lane / 32] = add_rows(a, b);
+                }
             }
+        } else {
+            if (dl == 0) {
+#pragma unroll
+                for (int h = 0; h < G; ++h) {
+                    s_m[(wave * KG + kgv) * G + h] = m[h];
+                    s_l[(wave * KG + kgv) * G + h] = l[h];
+                }
+            }
+            float* dst = s_acc + (size_t)(wave * KG + kgv) * C::ACC_STRIDE + dl * EPL;
+#pragma unroll
+            for (int h = 0; h < G; ++h)
+#pragma unroll
+                for (int e4 = 0; e4 < EPL; e4 += 4)
+                    *reinterpret_cast<float4*>(dst + (size_t)h * D + e4) =
+                        make_float4(acc[h][e4], acc[h][e4 + 1], acc[h][e4 + 2], acc[h][e4 + 3]);
         }
     }
 
     // ---- merge the partials of the workgroup -----------------------------------------------------
-    if constexpr (!C::PVM) {
-        float* dst = s_acc + (size_t)(wave * KG + kgv) * C::ACC_STRIDE + dl * EPL;
-#pragma unroll
-        for (int h = 0; h < G; ++h)
-#pragma unroll
-            for (int e4 = 0; e4 < EPL; e4 += 4)
-                *reinterpret_cast<float4*>(dst + (size_t)h * D + e4) =
-                    make_float4(acc[h][e4], acc[h][e4 + 1], acc[h][e4 + 2], acc[h][e4 + 3]);
-    }
     __syncthreads();
+    // (all wavefronts have the row's length; looked at when the result is out)
+    if (HEADS && do_append && gridDim.y > 1 && tid == 0) arrived = __hip_atomic_fetch_add(&P.row_cnt[row], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     for (int t = tid; t < NG * G; t += C::THREADS) {  // weight of every partial: 2^(m_g - M)
         const int h = t % G;
         float mn = kNegBig;
@@ -875,6 +935,18 @@ __global__ __launch_bounds__((AttnCfg<T, D, G>::THREADS), (attn_two<T, D, G, FEA
     finish(!one_split);
 }
 
+// fp32, short rows that all fit the chip: a workgroup of sixteen wavefronts for every query head, rows not split.  The vector instructions of
+// the group's heads are what such a step waits for (one head on four wavefronts takes 4.3 us at two rows of 144 pairs of head_dim 64, eight
+// take 7.6, and of that 1.6 for merging splits); K and V are read once per head, from the L2.  us a step, so and with splits:
+//   2 rows of 144, D = 64  g = 1: 3.4 and 4.3, 4: 3.5 and 5.2, 8: 3.6 and 7.6;  8 rows, g = 4  800 pairs 6.3 and 6.5, 1200 7.8 and 7.3
+//   8 rows, D = 128  g = 1  144: 4.0 and 4.3, 260: 5.0 and 4.7;  g = 2  260: 5.1 and 5.3, 400: 6.3 and 5.5;  g = 4  570: 7.7 and 8.6, 800: 9.5 and 9.8
+// The heads of a row share an XCD's L2 where the rows are a multiple of eight; otherwise the copies have to fit all of them together (21 rows
+// of 570, g = 4, D = 128: 10.5 and 9.3).
+static bool attn_by_head(int rows, int g, int max_len, int head_dim) {
+    if ((long long)rows * g > 256 || max_len > (head_dim == 64 ? 250 + 140 * g : 200 * g - 100)) return false;
+    return rows % 8 == 0 || (long long)rows * g * max_len * head_dim <= (1 << 22);
+}
+
 template <typename T, int D, int G>
 static fk_status attn_launch(const fk_cache_desc* d, const AttnParams& base, int max_len, void* ws, hipStream_t st) {
     using C = AttnCfg<T, D, G>;
@@ -928,6 +1000,16 @@ static fk_status attn_launch(const fk_cache_desc* d, const AttnParams& base, int
             static bool lds_ok[kMaxDevices] = {};
             if (!allow_dynamic_lds((const void*)kern, kAlone > C::LDS_BYTES ? kAlone : C::LDS_BYTES, lds_ok)) return FK_ERR_LAUNCH;
             hipLaunchKernelGGL(kern, dim3(p.nsplit, rows), dim3(C::THREADS), lds, st, P);
+            return launch_status();
+        }
+    }
+    if constexpr (!C::PVM) {
+        if (attn_by_head(rows, G, max_len, D)) {
+            using H = AttnCfg<T, D, 1, true>;
+            P.split_len = (d->capacity + 31) / 32 * 32;   // the whole row, whatever max_len says
+            P.nsplit = 1;
+            static_assert(H::LDS_BYTES <= 64 * 1024, "within the limit that kernels have from the start");
+            hipLaunchKernelGGL((attn_kernel<T, D, 1, false, false, true>), dim3(rows, G), dim3(H::THREADS), H::LDS_BYTES, st, P);
             return launch_status();
         }
     }

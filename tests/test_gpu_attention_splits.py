@@ -116,3 +116,40 @@ def test_head_dim_64_weights_keep_their_24_bits(gpu, g, features):
         fk.fk_decode_step(desc, qg, K, V, pos, ln, k, vn, pn, 4, scale, out, fk.new_attn_workspace(desc))
     off = (out.double() * (3.0 + w[:, :, None]) - rest[:, :, None]).abs() / M
     assert off.max() < 2.0 ** -21, f"weights off by 2^{torch.log2(off.max()).item():.1f}"
+
+
+# rows, group, head_dim, capacity (the length hint): a workgroup per query head up to 250 + 140 g and 200 g - 100 pairs, 256 workgroups, and,
+# where the rows are no multiple of eight, copies of K and V that fit the L2s
+BY_HEAD = [(2, 4, 64, 300), (2, 1, 64, 390), (2, 1, 64, 391), (8, 2, 128, 300), (8, 2, 128, 301), (3, 8, 64, 520), (32, 8, 128, 140), (33, 8, 128, 140),
+           (5, 3, 128, 500), (21, 4, 128, 390), (21, 4, 128, 391), (16, 5, 64, 257), (1, 7, 128, 9), (256, 1, 64, 70)]
+
+
+@pytest.mark.parametrize("rows,g,D,cap", BY_HEAD)
+def test_fp32_steps_by_query_head(gpu, rows, g, D, cap):
+    """Three steps of rows at the edges of the wavefronts' rounds (16 wavefronts of 16 or 8 pairs), empty and full ones among them, with the
+    tolerance of the other fp32 steps; lengths, new pairs and counters as they must be."""
+    import paper_2602_03203_amd as fk
+    print(f"fp32 by head rows={rows} g={g} D={D} cap={cap}", flush=True)
+    gen = torch.Generator(device="cuda").manual_seed(rows + g + cap)
+    mk = lambda *s: torch.randn(s, generator=gen, device="cuda")   # noqa: E731
+    desc = fk.CacheDesc(rows, g, 1, D, cap, "f32")
+    K, V, q, k, v = mk(rows, 1, cap, D), mk(rows, 1, cap, D), mk(3, rows, g, D), mk(3, rows, 1, D), mk(3, rows, 1, D)
+    edges = [0, cap, cap - 1, cap - 2, 1, 15, 16, 127, 128, 255, 256]
+    ln = torch.tensor([min(edges[r % len(edges)], cap) for r in range(rows)], dtype=torch.int32, device="cuda").reshape(rows, 1)
+    pos, pn = torch.zeros((rows, 1, cap), dtype=torch.int32, device="cuda"), torch.arange(3 * rows, dtype=torch.int32, device="cuda").reshape(3, rows) + 7
+    ws, out, K0, V0, n0 = fk.new_attn_workspace(desc), torch.zeros_like(q), K.clone(), V.clone(), ln[:, 0].tolist()
+    K[:, :, cap // 2 + 1:][torch.arange(cap // 2 + 1, cap, device="cuda")[None, None, :] >= ln[:, :, None]] = float("nan")   # what is not live is not used
+    V.masked_fill_(torch.isnan(K), float("nan"))
+    for t in range(3):
+        fk.fk_decode_step(desc, q[t], K, V, pos, ln, k[t], v[t], pn[t], cap, 0.3, out[t], ws)
+    assert int(ws[:4 * rows].view(torch.int32).abs().max()) == 0
+    for r in range(rows):
+        n = n0[r]
+        for t in range(3):
+            if n < cap:
+                K0[r, 0, n], V0[r, 0, n] = k[t, r, 0], v[t, r, 0]
+                assert int(pos[r, 0, n]) == int(pn[t, r])
+                n += 1
+            p = torch.softmax(0.3 * (q[t, r].double() @ K0[r, 0, :n].double().T), 1)
+            gpu.assert_attn_close(out[t, r].double().cpu().numpy(), (p @ V0[r, 0, :n].double()).cpu().numpy(), "f32", f"row {r} of {n} pairs, step {t}")
+        assert int(ln[r, 0]) == n and torch.equal(K[r, 0, :n], K0[r, 0, :n]) and torch.equal(V[r, 0, :n], V0[r, 0, :n])
