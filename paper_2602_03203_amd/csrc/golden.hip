@@ -7,101 +7,140 @@
 //          the largest alpha[.][t] (ties: lower position), evicted pairs never return  (Eq. 5, second half)
 //
 // pool is the only kernel that touches the O(T^2) input and is HBM bound: a workgroup owns one
-// (key tile, block, group) and streams g * L row segments of 256 bytes (16 lanes x 16 bytes, 16 rows per workgroup
-// instruction, eight loads in flight per thread); chunks wholly above the diagonal are never read (A is causal), so
-// the traffic is the lower triangle below query B + L.  future is a
-// running maximum down the block axis; trace is sequential by nature: one workgroup per group walks the M steps.
+// (key tile, block, group) and streams g * L row segments of 256 to 1024 bytes (16 bytes a lane, eight loads in flight
+// per thread); chunks wholly above the diagonal are never read (A is causal), so the traffic is the lower triangle below
+// query B + L.  future is a running maximum down the block axis; trace is sequential by nature: one workgroup per group walks the M steps.
 #include "select_common.h"
 
 namespace fk {
 
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
-static constexpr int kPoolThreads = 256;
+static constexpr int kPoolThreads = 512;
 static constexpr int kPoolU = 8;   // loads in flight per thread
 
-// 32 heads of 8192 tokens, bf16: 2.0 GB of causal entries in 341 us, 5.9 TB/s (354 us with a division per load to find the load's
-// head and query, four loads in flight).  Wider segments are no faster, 512 bytes 343 us, 1 KB 370 us: the fewer and longer
-// workgroups leave CUs idle at the end.
-// FEW: blocks of fewer than 64 queries.
-template <typename T, bool FEW>
+template <int W>   // value i (lower lanes) and i + W (upper lanes) of both halves added up, i < W
+__device__ __forceinline__ void add_halves(float* v) {
+#pragma unroll
+    for (int i = 0; i < W; ++i) {
+        auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v[i]), __float_as_uint(v[i + W]), false, false);
+        v[i] = __uint_as_float(r[0]) + __uint_as_float(r[1]);
+    }
+}
+template <int W>   // the same for the odd and even rows of 16 lanes
+__device__ __forceinline__ void add_rows(float* v) {
+#pragma unroll
+    for (int i = 0; i < W; ++i) {
+        auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v[i]), __float_as_uint(v[i + W]), false, false);
+        v[i] = __uint_as_float(r[0]) + __uint_as_float(r[1]);
+    }
+}
+// Bound by HBM.  32 heads of 8192 tokens, bf16: 2.0 GB of causal entries in 315 us, 6.4 TB/s (5.9 while tiles and XCDs went in step: see below).
+// The loads of a pass are under no condition where the whole pass is there: behind a condition the compiler waited for the first seven
+// before it issued the eighth.  Partial sums of a wavefront are added in registers (through LDS, sixteen to a key, no slower).
+template <typename T, int LPR>   // LPR: lanes of a row segment, 16, 32 or 64
 __global__ __launch_bounds__(kPoolThreads) void golden_pool_kernel(const T* __restrict__ A, int g, int Tn, size_t ld,
                                                                    int budget, int L, int M,
                                                                    float* __restrict__ a_tilde) {
     constexpr int EPC = Vec16<T>::N;   // elements per 16-byte chunk
-    constexpr int LPR = 16;            // lanes of a row segment
     constexpr int KT = LPR * EPC;      // keys per tile
-    constexpr int RG = kPoolThreads / LPR;   // row groups of the workgroup
-    const int i0 = blockIdx.x * KT, t = blockIdx.y + 1, hp = blockIdx.z;
+    constexpr int RG = kPoolThreads / LPR, U = kPoolU;   // row groups of the workgroup, loads in flight
+    // Block t has `live(t)` tiles with keys that its queries see, more the later it is; the first and the last block, the second and the last but
+    // one, ... share the workgroups of a row of the grid, so that hardly any finds nothing to do.  From row to row the tiles move on by one
+    // workgroup: tile i always on XCD i % 8 would read through two of the sixteen channels of that XCD's L2 only.
+    const int tiles = (Tn + KT - 1) / KT, hp = blockIdx.z;
+    auto live = [&](int t) { return (min(budget + (t + 1) * L, Tn) + KT - 1) / KT; };
+    int t = blockIdx.y + 1, tile = (int)((blockIdx.x + blockIdx.y) % gridDim.x);
+    if (tile >= live(t)) {
+        tile -= live(t);
+        if (M - (int)blockIdx.y == t) return;
+        t = M - blockIdx.y;
+        if (tile >= live(t)) return;
+    }
+    const int i0 = tile * KT;
     const int q0 = budget + t * L, q1 = min(q0 + L, Tn);
     const int c = threadIdx.x % LPR, rg = threadIdx.x / LPR;
-    const int i_mine = i0 + c * EPC;   // this lane's first key; queries before it see none of its keys and are not read
+    const int i_mine = i0 + c * EPC;   // this lane's first key; queries before it see none of its keys
     float acc[EPC];
 #pragma unroll
     for (int e = 0; e < EPC; ++e) acc[e] = 0.f;
-    const int qs = max(q0, i0), rows = q1 - qs;   // rows <= 0: above the diagonal for the whole block
+    const int qs = max(q0, i0), rows = q1 - qs;
+    float* to = a_tilde + ((size_t)hp * M + (t - 1)) * Tn + i0;
+    for (int z = tile + live(t); z < tiles; z += live(t))   // tiles above the diagonal
+        for (int k = threadIdx.x; k < KT && z * KT + k < Tn; k += kPoolThreads) to[(z - tile) * KT + k] = 0.f;
     if (i_mine < q1 && (size_t)i_mine < ld) {
-        // read once, never again: non-temporal, so the lines do not push anything out of the caches
-        auto load = [](const T* p) { return __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(p)); };
-        if constexpr (!FEW) {   // head by head
-            for (int h = 0; h < g; ++h) {
-                const T* head = A + (size_t)(hp * g + h) * Tn * ld + i_mine;
-                for (int q = qs + rg; q < q1; q += RG * kPoolU) {
-                    u32x4 v[kPoolU];
-#pragma unroll
-                    for (int u = 0; u < kPoolU; ++u) {
-                        const int qu = q + u * RG;
-                        v[u] = (u32x4){0, 0, 0, 0};
-                        if (qu < q1 && qu >= i_mine) v[u] = load(head + (size_t)qu * ld);
-                    }
-                    float x[kPoolU][EPC];
-#pragma unroll
-                    for (int u = 0; u < kPoolU; ++u) Vec16<T>::unpack(make_uint4(v[u].x, v[u].y, v[u].z, v[u].w), x[u]);
-#pragma unroll
-                    for (int e = 0; e < EPC; ++e)
-                        acc[e] += ((x[0][e] + x[1][e]) + (x[2][e] + x[3][e])) + ((x[4][e] + x[5][e]) + (x[6][e] + x[7][e]));
+        // This row group takes the pairs (head, query) rg, rg + RG, ...: dh heads and dq queries on, one head more where that leaves the block.
+        const int total = rows * g, dh = RG / rows, dq = RG % rows;
+        const size_t step = ((size_t)dh * Tn + dq) * ld, wrap = (size_t)(Tn - rows) * ld;
+        int q = rg % rows;
+        const T* p = A + ((size_t)(hp * g + rg / rows) * Tn + qs + q) * ld + i_mine;
+        const bool below = qs >= i0 + KT - 1;   // every query sees every key of the tile
+        for (int r0 = 0; r0 < total; r0 += RG * U) {
+            u32x4 v[U];
+            // (read once, never again: non-temporal, so the lines do not push anything out of the caches)
+            auto load = [](const T* p) { return __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(p)); };
+            auto advance = [&]() {
+                p += step;
+                q += dq;
+                if (q >= rows) {
+                    q -= rows;
+                    p += wrap;
                 }
-            }
-        } else {
-            // A head has less than the loads in flight take, so they go on into the next ones.  (Head by head, 32 heads of 4096 tokens, L = 16:
-            // 226 us, so 131; 32 heads of 2000 tokens in 4 groups, L = 8: 107 and 55.  From 64 queries on, head by head is 1 to 3 % the
-            // faster; a kernel of its own, because the other one's registers cost these short workgroups their number on a CU, 8 heads of 4096 tokens
-            // without pooling, L = 32: 52 us in one kernel, 42 so.)  This row group takes pairs (head, query) rg, rg + RG, ...: dh heads
-            // and dq queries on, one head more where that leaves the block.
-            constexpr int U = kPoolU / 2;
-            const int total = rows * g, dh = RG / rows, dq = RG % rows;
-            const size_t step = ((size_t)dh * Tn + dq) * ld, wrap = (size_t)(Tn - rows) * ld;
-            int q = rg % rows;
-            const T* p = A + ((size_t)(hp * g + rg / rows) * Tn + qs + q) * ld + i_mine;
-            for (int r = rg; r < total; r += RG * U) {
-                u32x4 v[U];
+            };
+            if (below && r0 + RG * U <= total) {   // (no load under a condition)
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    v[u] = load(p);
+                    advance();
+                }
+            } else {
 #pragma unroll
                 for (int u = 0; u < U; ++u) {
                     v[u] = (u32x4){0, 0, 0, 0};
-                    if (r + u * RG < total && qs + q >= i_mine) v[u] = load(p);
-                    p += step;
-                    q += dq;
-                    if (q >= rows) {
-                        q -= rows;
-                        p += wrap;
-                    }
+                    if (r0 + rg + u * RG < total && qs + q >= i_mine) v[u] = load(p);
+                    advance();
                 }
-                float x[U][EPC];
-#pragma unroll
-                for (int u = 0; u < U; ++u) Vec16<T>::unpack(make_uint4(v[u].x, v[u].y, v[u].z, v[u].w), x[u]);
-#pragma unroll
-                for (int e = 0; e < EPC; ++e) acc[e] += (x[0][e] + x[1][e]) + (x[2][e] + x[3][e]);
             }
+            float x[EPC], y[EPC];
+            auto sum = [&](int u, float (&to)[EPC]) {   // of four
+                float a[EPC], b[EPC];
+                auto pair = [&](int w, float (&z)[EPC]) {
+                    float z1[EPC];
+                    Vec16<T>::unpack(make_uint4(v[w].x, v[w].y, v[w].z, v[w].w), z);
+                    Vec16<T>::unpack(make_uint4(v[w + 1].x, v[w + 1].y, v[w + 1].z, v[w + 1].w), z1);
+#pragma unroll
+                    for (int e = 0; e < EPC; ++e) z[e] += z1[e];
+                };
+                pair(u, a);
+                pair(u + 2, b);
+#pragma unroll
+                for (int e = 0; e < EPC; ++e) to[e] = a[e] + b[e];
+            };
+            sum(0, x);
+            sum(4, y);
+#pragma unroll
+            for (int e = 0; e < EPC; ++e) acc[e] += x[e] + y[e];
         }
     }
-    __shared__ float s_acc[RG][KT + 4];
+    // the row groups of a wavefront in registers (a lane ends with its share of its chunk's keys), the wavefronts through LDS
+    constexpr int WAVES = kPoolThreads / kWave, E = EPC * LPR / kWave;
+    __shared__ float s_acc[WAVES][KT];
+    int first = c * EPC;   // this lane's first key of the tile
+    if constexpr (LPR <= 32) {
+        add_halves<EPC / 2>(acc);
+        first += (int)threadIdx.x / 32 % 2 * (EPC / 2);
+    }
+    if constexpr (LPR == 16) {
+        add_rows<E>(acc);
+        first += (int)threadIdx.x / 16 % 2 * E;
+    }
 #pragma unroll
-    for (int e = 0; e < EPC; ++e) s_acc[rg][c * EPC + e] = acc[e];
+    for (int e = 0; e < E; ++e) s_acc[threadIdx.x / kWave][first + e] = acc[e];
     __syncthreads();
     for (int k = threadIdx.x; k < KT && i0 + k < Tn; k += kPoolThreads) {
         float s = 0.f;
 #pragma unroll
-        for (int r = 0; r < RG; ++r) s += s_acc[r][k];
-        a_tilde[((size_t)hp * M + (t - 1)) * Tn + i0 + k] = s / ((float)g * (float)L);
+        for (int r = 0; r < WAVES; ++r) s += s_acc[r][k];
+        to[k] = s / ((float)g * (float)L);
     }
 }
 
@@ -783,14 +822,27 @@ extern "C" fk_status fk_golden_scores(const void* A, int32_t dtype, int32_t n_q_
     if (M > 65535 || n_kv_heads > 65535) return FK_ERR_UNSUPPORTED;
     const int g = n_q_heads / n_kv_heads;
     hipStream_t st = (hipStream_t)stream;
+    auto pool = [&](auto kern, auto* a, int lanes) {
+        const int tile = lanes * 16 / (int)sizeof(*a);
+        const int most = 2 * ((T + tile - 1) / tile), pair = (int)((2ll * budget + (M + 3ll) * interval) / tile) + 2;   // live tiles of two blocks
+        hipLaunchKernelGGL(kern, dim3(pair < most ? pair : most, (M + 1) / 2, n_kv_heads), dim3(kPoolThreads), 0, st, a, g, T, (size_t)ld, budget, interval, M, block_scores);
+    };
+    // How wide a workgroup's tile is, 1 KB, 512 or 256 bytes of a row.  Wide ones waste the least where rows do not start on a line of 128 bytes
+    // (32 heads of 5001 tokens, L = 32: 176 us, 512 bytes 185, 256 bytes 205) and leave a short block's workgroups the most to do (8 heads of 4096,
+    // L = 32: 47, 62 and 92); 512 bytes fill the chip better at the end (32 heads of 8192: 324 us, so 343 and 338); 256 where there would be
+    // fewer workgroups than CUs (one group of 2500 tokens, L = 1000: 28, 512 bytes 37, 1 KB 58).
+    const size_t row_bytes = (size_t)T * (dtype == FK_F32 ? 4 : 2), pitch = (size_t)ld * (dtype == FK_F32 ? 4 : 2);
+    const bool few = (long long)((row_bytes + 1023) / 1024) * M * n_kv_heads < 256, half = pitch % 128 == 0 && (long long)g * interval >= 128;
     if (dtype == FK_F32) {
-        const int KT = 64;
-        hipLaunchKernelGGL((interval < 64 ? golden_pool_kernel<float, true> : golden_pool_kernel<float, false>), dim3((T + KT - 1) / KT, M, n_kv_heads), dim3(kPoolThreads), 0, st,
-                           (const float*)A, g, T, (size_t)ld, budget, interval, M, block_scores);
+        const float* a = static_cast<const float*>(A);
+        if (few) pool(golden_pool_kernel<float, 16>, a, 16);
+        else if (half) pool(golden_pool_kernel<float, 32>, a, 32);
+        else pool(golden_pool_kernel<float, 64>, a, 64);
     } else {
-        const int KT = 128;
-        hipLaunchKernelGGL((interval < 64 ? golden_pool_kernel<bf16_t, true> : golden_pool_kernel<bf16_t, false>), dim3((T + KT - 1) / KT, M, n_kv_heads), dim3(kPoolThreads), 0, st,
-                           (const bf16_t*)A, g, T, (size_t)ld, budget, interval, M, block_scores);
+        const bf16_t* a = static_cast<const bf16_t*>(A);
+        if (few) pool(golden_pool_kernel<bf16_t, 16>, a, 16);
+        else if (half) pool(golden_pool_kernel<bf16_t, 32>, a, 32);
+        else pool(golden_pool_kernel<bf16_t, 64>, a, 64);
     }
     hipLaunchKernelGGL(golden_future_kernel, dim3((T + 255) / 256, n_kv_heads), dim3(256), 0, st, block_scores, T, M, alpha);
     return launch_status();

@@ -81,13 +81,24 @@ def test_small_traces(gpu, dtype, Hq, g, T, B, L):
     assert run_case(gpu, dtype, Hq, g, T, B, L) > 0
 
 
-# pooling blocks around the number of queries from which they are taken head by head (64), fewer than a workgroup's row groups (16) and one;
+# pooling blocks of 63 to 65 queries, of fewer than a workgroup's row groups and of one;
 # the causal edge runs through the tiles
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 @pytest.mark.parametrize("Hq,g,T,B,L", [(3, 3, 700, 130, 63), (4, 2, 700, 130, 64), (4, 4, 700, 130, 65), (5, 5, 400, 100, 15), (4, 2, 400, 100, 17),
                                         (8, 8, 300, 60, 5), (3, 1, 200, 60, 1)])
 def test_pooling_of_short_blocks(gpu, dtype, Hq, g, T, B, L):
     assert run_case(gpu, dtype, Hq, g, T, B, L) > 0
+
+
+# the three widths of a workgroup's tile (256 bytes of a row where 1 KB gave fewer than 256 workgroups, 512 where rows start on a line and a block
+# has 128 (head, query) pairs, 1 KB), blocks of an odd and an even number that share the workgroups of a row of the grid, and the passes of
+# 64, 128 and 256 pairs full, one short of it and one beyond; every entry above the diagonal is written
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("Hq,g,T,B,L,ld", [(4, 1, 2049, 70, 32, 2056), (4, 1, 2048, 70, 32, 2048), (8, 4, 1100, 40, 32, 1152), (8, 4, 1100, 40, 33, 1152),
+                                           (6, 2, 1025, 100, 64, 1088), (8, 1, 1536, 20, 16, 1536), (6, 3, 1030, 5, 5, 1032), (2, 2, 900, 300, 128, 904),
+                                           (2, 2, 900, 300, 256, 960)])
+def test_pooling_tile_widths(gpu, dtype, Hq, g, T, B, L, ld):
+    assert run_case(gpu, dtype, Hq, g, T, B, L, ld=ld) > 0
 
 
 @pytest.mark.parametrize("T", [48, 49])
