@@ -127,6 +127,28 @@ fk_status fk_decode_step(const fk_cache_desc *desc, const void *q, void *K, void
                          size_t workspace_bytes, void *stream);
 
 /*
+ * The arguments of one fk_decode_step, or with feat of one fk_decode_step_feat, in one place: for callers whose
+ * foreign-function interface takes its time per argument and that make the same call again and again.
+ * fk_decode_step_packed(a) is that call, with its checks, results and status.
+ */
+typedef struct {
+    fk_cache_desc desc;
+    int32_t max_len;
+    const void *q;
+    void *K, *V;
+    int32_t *pos, *len;
+    const void *k_new, *v_new;
+    const int32_t *pos_new;
+    void *out, *workspace;
+    size_t workspace_bytes;
+    void *stream;
+    float softmax_scale;
+    int32_t chunk_pos, chunk_len;   /* with feat */
+    float *feat;                    /* null: fk_decode_step */
+} fk_step_args;
+fk_status fk_decode_step_packed(const fk_step_args *args);
+
+/*
  * fk_decode_step for callers that cannot allocate device memory (code under HIP graph capture, tight serving
  * loops, harnesses that forbid hipMalloc): same arguments and results as fk_decode_step without the workspace,
  * which is a fixed FK_STATIC_SCRATCH_BYTES array inside the library's device image (each GPU the library runs on

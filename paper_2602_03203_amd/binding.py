@@ -19,8 +19,8 @@ LIB_PATH = os.path.join(_HERE, "libfk.so")
 FK_OK, FK_ERR_INVALID_ARG, FK_ERR_UNSUPPORTED, FK_ERR_WORKSPACE, FK_ERR_LAUNCH = range(5)
 FK_F32, FK_BF16 = 0, 1
 
-SYMBOLS = ["fk_status_string", "fk_version", "fk_append", "fk_decode_attn_workspace", "fk_decode_attn", "fk_decode_step", "fk_decode_window", "fk_decode_step_static",
-           "fk_score_kv", "fk_select_keep", "fk_select_keep_workspace", "fk_select_keep_ws", "fk_select_keep_sampled", "fk_compact", "fk_decode_step_feat_workspace",
+SYMBOLS = ["fk_status_string", "fk_version", "fk_append", "fk_decode_attn_workspace", "fk_decode_attn", "fk_decode_step", "fk_decode_step_packed", "fk_decode_window",
+           "fk_decode_step_static", "fk_score_kv", "fk_select_keep", "fk_select_keep_workspace", "fk_select_keep_ws", "fk_select_keep_sampled", "fk_compact", "fk_decode_step_feat_workspace",
            "fk_decode_step_feat", "fk_decode_window_feat", "fk_score_kv_feat", "fk_compact_feat", "fk_golden_steps", "fk_golden_scores",
            "fk_golden_trace", "fk_stream_read"]
 
@@ -33,6 +33,13 @@ class fk_cache_desc(ctypes.Structure):
 class fk_scorer(ctypes.Structure):
     _fields_ = [("w1", ctypes.c_void_p), ("b1", ctypes.c_void_p), ("w2", ctypes.c_void_p), ("b2", ctypes.c_void_p),
                 ("hidden", ctypes.c_int32), ("per_head", ctypes.c_int32), ("skip_len", ctypes.c_int32)]
+
+
+class fk_step_args(ctypes.Structure):
+    _fields_ = ([("desc", fk_cache_desc), ("max_len", ctypes.c_int32)] +
+                [(n, ctypes.c_void_p) for n in ("q", "K", "V", "pos", "len", "k_new", "v_new", "pos_new", "out", "workspace")] +
+                [("workspace_bytes", ctypes.c_size_t), ("stream", ctypes.c_void_p), ("softmax_scale", ctypes.c_float),
+                 ("chunk_pos", ctypes.c_int32), ("chunk_len", ctypes.c_int32), ("feat", ctypes.c_void_p)])
 
 
 class FkError(RuntimeError):
@@ -67,6 +74,7 @@ def lib() -> ctypes.CDLL:
         L.fk_select_keep_ws.restype, L.fk_select_keep_ws.argtypes = ctypes.c_int, [dp, vp, vp, vp, i32, i32, i32, vp, vp, sz, vp]
         L.fk_select_keep_sampled.restype, L.fk_select_keep_sampled.argtypes = ctypes.c_int, [dp, vp, vp, vp, vp, i32, i32, i32, i32, vp, vp]
         L.fk_compact.restype, L.fk_compact.argtypes = ctypes.c_int, [dp, vp, vp, vp, vp, vp, i32, vp]
+        L.fk_decode_step_packed.restype, L.fk_decode_step_packed.argtypes = ctypes.c_int, None   # (called with one pointer made beforehand)
         L.fk_decode_step_feat_workspace.restype, L.fk_decode_step_feat_workspace.argtypes = sz, [dp]
         L.fk_decode_step_feat.restype, L.fk_decode_step_feat.argtypes = ctypes.c_int, [dp, vp, vp, vp, vp, vp, vp, vp, vp, i32, f32, vp, i32, i32, vp, vp, sz, vp]
         L.fk_decode_window_feat.restype, L.fk_decode_window_feat.argtypes = ctypes.c_int, [dp, vp, vp, vp, vp, vp, vp, vp, vp, i32, i32, f32, vp, i32, i32, vp, vp, sz, vp]
@@ -104,6 +112,18 @@ def _call(name: str, *cargs) -> None:
     _check(f(*cargs), name)
 
 
+def _pack_step(name: str, cargs):
+    """The arguments of a recorded fk_decode_step / fk_decode_step_feat call as the library's struct; None where that cannot hold them (a feature step
+    without its state, which the library refuses)."""
+    feature = name == "fk_decode_step_feat"
+    desc, buffers, (max_len, scale), tail = cargs[0]._obj, cargs[1:9], cargs[9:11], cargs[11:]
+    feat, chunk_pos, chunk_len = tail[:3] if feature else (0, 0, 0)
+    if feature and not feat:
+        return None
+    out, ws, nbytes, stream = tail[-4:]
+    return fk_step_args(desc, max_len, *buffers, out, ws, nbytes, stream, scale, chunk_pos, chunk_len, feat)
+
+
 def prepare(fn, *args, **kwargs):
     """Marshal once, call many times.  Runs the wrapper `fn(*args, **kwargs)` WITHOUT calling the library and returns a
     zero-argument callable that makes the same library call(s) with the arguments as converted now (device pointers,
@@ -118,11 +138,18 @@ def prepare(fn, *args, **kwargs):
         _recording = None
     if len(calls) == 1:
         f, cargs, name = calls[0]
+        packed = None
+        if name in ("fk_decode_step", "fk_decode_step_feat"):
+            # made once per generated token: one pointer to the arguments instead of the conversion of fifteen (0.5 us of a call)
+            packed = _pack_step(name, cargs)
+            if packed is not None:
+                f, cargs = lib().fk_decode_step_packed, (ctypes.c_void_p(ctypes.addressof(packed)),)
 
         def run_one():
             code = f(*cargs)
             if code:
                 _check(code, name)
+        run_one.packed = packed   # lives as long as the callable
         return run_one
 
     def run_all():

@@ -1333,3 +1333,12 @@ extern "C" fk_status fk_decode_window_feat(const fk_cache_desc* desc, const void
     }
     return FK_OK;
 }
+
+extern "C" fk_status fk_decode_step_packed(const fk_step_args* a) {
+    if (!a) return FK_ERR_INVALID_ARG;
+    if (a->feat)
+        return fk_decode_step_feat(&a->desc, a->q, a->K, a->V, a->pos, a->len, a->k_new, a->v_new, a->pos_new, a->max_len, a->softmax_scale,
+                                   a->feat, a->chunk_pos, a->chunk_len, a->out, a->workspace, a->workspace_bytes, a->stream);
+    return fk_decode_step(&a->desc, a->q, a->K, a->V, a->pos, a->len, a->k_new, a->v_new, a->pos_new, a->max_len, a->softmax_scale, a->out,
+                          a->workspace, a->workspace_bytes, a->stream);
+}

@@ -130,3 +130,31 @@ def test_argument_validation_of_the_next_row_calls(fklib):
     assert L.fk_golden_trace(0, 2, 512, 64, 16, p, 0) == fklib.FK_ERR_INVALID_ARG
     assert L.fk_golden_trace(p, 2, 100000, 20000, 16, p, 0) == fklib.FK_ERR_UNSUPPORTED
     assert L.fk_golden_trace(p, 2, 64, 64, 16, p, 0) == fklib.FK_OK
+
+
+def test_packed_step_is_the_step(fklib):
+    """fk_decode_step_packed on the struct that prepare() fills: the same status as the call it stands for, argument by argument."""
+    L, D, p = fklib.lib(), fklib.fk_cache_desc, 4096
+    good = D(2, 8, 2, 128, 512, fklib.FK_BF16)
+    need, feat_need = L.fk_decode_attn_workspace(ctypes.byref(good), 512), L.fk_decode_step_feat_workspace(ctypes.byref(good))
+    step = [p] * 8 + [512, 1.0, p, p, need - 1, 0]                 # one byte of workspace short: refused last
+    feat = [p] * 8 + [512, 1.0, p, 0, 128, p, p, feat_need - 1, 0]
+
+    def both(name, desc, args):
+        cargs = (ctypes.byref(desc), *args)
+        packed = fklib._pack_step(name, cargs)
+        direct = getattr(L, name)(*cargs)
+        return (direct, direct) if packed is None else (direct, L.fk_decode_step_packed(ctypes.c_void_p(ctypes.addressof(packed))))
+    for name, args in (("fk_decode_step", step), ("fk_decode_step_feat", feat)):
+        assert both(name, good, args) == (fklib.FK_ERR_WORKSPACE,) * 2
+        assert both(name, D(2, 8, 2, 96, 512, 1), args) == (fklib.FK_ERR_UNSUPPORTED,) * 2
+        for i in [j for j, v in enumerate(args) if v == p]:          # every pointer missing, and the 16-byte aligned ones off
+            a, b = both(name, good, args[:i] + [0] + args[i + 1:])
+            assert a == b and a in (fklib.FK_ERR_INVALID_ARG, fklib.FK_ERR_WORKSPACE), i
+            a, b = both(name, good, args[:i] + [p + 4] + args[i + 1:])
+            assert a == b and a in (fklib.FK_ERR_INVALID_ARG, fklib.FK_ERR_WORKSPACE), i
+        for bad in (0, 513):
+            assert both(name, good, args[:8] + [bad] + args[9:]) == (fklib.FK_ERR_INVALID_ARG,) * 2
+    for chunk in ((128, 128), (-1, 128), (0, 0)):
+        assert both("fk_decode_step_feat", good, feat[:11] + list(chunk) + feat[13:]) == (fklib.FK_ERR_INVALID_ARG,) * 2
+    assert L.fk_decode_step_packed(None) == fklib.FK_ERR_INVALID_ARG

@@ -340,6 +340,32 @@ def test_prepared_call_replays_the_direct_call(gpu, ora):
         fk.prepare(fk.fk_select_keep, desc, d_sc, None, d_ln, cap, cap + 1, recent, keep)()
 
 
+
+
+@pytest.mark.parametrize("features", [False, True])
+def test_prepared_step_is_the_direct_step(gpu, features):
+    """A decode step marshalled by fk.prepare passes its arguments in one struct: outputs and state are those of the direct call, bit for bit."""
+    import paper_2602_03203_amd as fk
+    gen = torch.Generator(device="cuda").manual_seed(4)
+    mk = lambda *s: torch.randn(s, generator=gen, device="cuda").to(torch.bfloat16)   # noqa: E731
+    desc = fk.CacheDesc(3, 8, 2, 128, 200, "bf16")
+    K0, V0, q, k, v = mk(3, 2, 200, 128), mk(3, 2, 200, 128), mk(3, 8, 128), mk(3, 2, 128), mk(3, 2, 128)
+    pn, res = torch.tensor([9, 8, 7], dtype=torch.int32, device="cuda"), []
+    for prepared in (True, False):
+        K, V, out = K0.clone(), V0.clone(), torch.zeros_like(q)
+        ln, pos = torch.tensor([[150, 3]] * 3, dtype=torch.int32, device="cuda"), torch.zeros((3, 2, 200), dtype=torch.int32, device="cuda")
+        feat = fk.new_feat(desc)
+        more = (151, 0.2, feat, 5, 16, out, fk.new_feat_workspace(desc)) if features else (151, 0.2, out, fk.new_attn_workspace(desc))
+        fn = fk.fk_decode_step_feat if features else fk.fk_decode_step
+        for _ in range(2):
+            if prepared:
+                fk.prepare(fn, desc, q, K, V, pos, ln, k, v, pn, *more)()
+            else:
+                fn(desc, q, K, V, pos, ln, k, v, pn, *more)
+        res.append((out, K, V, pos, ln, feat))
+    for a, b in zip(*res):
+        assert torch.equal(a.view(torch.uint8), b.view(torch.uint8))
+    assert int(res[0][4][0, 0]) == 152
 def test_select_keep_special_values(gpu, ora):
     import paper_2602_03203_amd as fk
     cap, budget, recent = 1200, 700, 100
