@@ -144,19 +144,20 @@ __global__ __launch_bounds__(kPoolThreads) void golden_pool_kernel(const T* __re
     }
 }
 
-// alpha[t] = max(a~[t], alpha[t + 1]), walking the blocks from the last to the first; one thread per key,
-// eight blocks' loads in flight
+// alpha[t] = max(a~[t], alpha[t + 1]), walking the blocks from the last to the first; one thread per key, kFutureU blocks' loads in
+// flight (a wavefront or two a SIMD: a walk of 47 blocks waits for memory six times with eight, twice with 32)
+static constexpr int kFutureU = 32;
 __global__ void golden_future_kernel(const float* __restrict__ a_tilde, int Tn, int M, float* __restrict__ alpha) {
     const int i = blockIdx.x * blockDim.x + threadIdx.x, hp = blockIdx.y;
     if (i >= Tn) return;
     const size_t o0 = (size_t)hp * M * Tn + i;
-    float run = 0.f;
-    for (int t = M; t >= 1; t -= 8) {
-        float a[8];
+    float run = -INFINITY;
+    for (int t = M; t >= 1; t -= kFutureU) {
+        float a[kFutureU];
 #pragma unroll
-        for (int u = 0; u < 8; ++u) a[u] = t - u >= 1 ? a_tilde[o0 + (size_t)(t - u - 1) * Tn] : 0.f;
+        for (int u = 0; u < kFutureU; ++u) a[u] = a_tilde[o0 + (size_t)max(t - u - 1, 0) * Tn];   // (past the first block that one again)
 #pragma unroll
-        for (int u = 0; u < 8; ++u) {
+        for (int u = 0; u < kFutureU; ++u) {
             if (t - u >= 1) {
                 run = t - u == M ? a[u] : fmaxf(run, a[u]);
                 alpha[o0 + (size_t)(t - u - 1) * Tn] = run;
