@@ -88,21 +88,20 @@ __device__ __forceinline__ void feat_roll(float4* __restrict__ feat, int row, in
 // keep[] is ascending with keep[j] >= j.  A workgroup owns one 128-byte column slice of one
 // tensor of one row (bytes of different slices never alias, so slices are independent; 128
 // bytes = two whole 64-byte memory requests per slot, narrower slices fetch and write partial
-// lines and cost 1.5x the time) and walks the destination slots in ascending tiles of 512
+// lines and cost 1.5x the time) and walks the destination slots in ascending tiles of 512 (256)
 // slots: all sources of a tile are loaded into registers, a barrier, then the tile is stored.  A store of tile t lands in slots
 // [tT, (t+1)T); a source of any later tile is >= (t+1)T, and every source of tile t or of an
 // earlier tile has already been read, so no live source is overwritten.  Entries with
 // keep[j] == j (the untouched prefix) cost no traffic.
 // grid.x = row, grid.y = tensor * slices + slice (K slices, then V slices), last y = pos; Q4 > 0: the attention features before them
 // ---------------------------------------------------------------------------------------
-static constexpr int kCompactU = 4;     // 16-byte loads in flight per thread
 static constexpr int kSliceChunks = 8;  // 16-byte chunks per column slice
 typedef unsigned int u32x4_t __attribute__((ext_vector_type(4)));
 
 // The workgroup that moves the positions (Q4 > 0: the features, which go by the length) also sets len[row] = min(len[row], budget) (no
 // second launch).  No other workgroup may then read len[row]: what moves is decided by keep alone (rows at or under budget carry the
 // identity, entries with keep[j] == j or outside [0, cap) move nothing).
-template <int Q4 /* float4 units of a feature plane per slot; 0: no features */>
+template <int Q4 /* float4 units of a feature plane per slot; 0: no features */, int U /* 16-byte loads of a tile per thread */, bool FEW>
 __global__ __launch_bounds__(kCompactThreads) void compact_kernel(uint4* __restrict__ K, uint4* __restrict__ V,
                                                                   int32_t* __restrict__ pos, float4* __restrict__ feat,
                                                                   int32_t* __restrict__ len,
@@ -124,20 +123,20 @@ __global__ __launch_bounds__(kCompactThreads) void compact_kernel(uint4* __restr
     if (part == 2 * slices) {
         if (Q4 == 0 && threadIdx.x == 0 && len[row] > budget) len[row] = budget;
         int32_t* p = pos + (size_t)row * cap;
-        for (int base = 0; base < budget; base += kCompactThreads * kCompactU) {
-            int32_t val[kCompactU];
-            int src[kCompactU];
+        for (int base = 0; base < budget; base += kCompactThreads * U) {
+            int32_t val[U];
+            int src[U];
 #pragma unroll
-            for (int u = 0; u < kCompactU; ++u) {
-                const int j = base + u * kCompactThreads + threadIdx.x;
-                src[u] = j < budget ? kp[j] : -1;
-                if (src[u] >= 0 && src[u] < n) val[u] = p[src[u]];
-            }
+            for (int u = 0; u < U; ++u) src[u] = kp[min(base + u * kCompactThreads + (int)threadIdx.x, budget - 1)];
+#pragma unroll
+            for (int u = 0; u < U; ++u) val[u] = p[src[u] >= 0 && src[u] < n ? src[u] : 0];
+#pragma unroll
+            for (int u = 0; u < U; ++u) asm volatile("" : "+v"(val[u]));   // here before any slot is written
             __syncthreads();
 #pragma unroll
-            for (int u = 0; u < kCompactU; ++u) {
+            for (int u = 0; u < U; ++u) {
                 const int j = base + u * kCompactThreads + threadIdx.x;
-                if (src[u] >= 0 && src[u] < n && src[u] != j) p[j] = val[u];
+                if (j < budget && src[u] >= 0 && src[u] < n && src[u] != j) p[j] = val[u];
             }
         }
         return;
@@ -145,42 +144,94 @@ __global__ __launch_bounds__(kCompactThreads) void compact_kernel(uint4* __restr
     const int tensor = part / slices, slice = part % slices;
     uint4* X = (tensor == 0 ? K : V) + (size_t)row * cap * chunks + slice * kSliceChunks;
     constexpr int spi = kCompactThreads / kSliceChunks;  // slots per load instruction of the workgroup
-    constexpr int tile = spi * kCompactU;
+    constexpr int tile = spi * U;
     const int sl = threadIdx.x / kSliceChunks;           // slot within that group
     const int c = threadIdx.x % kSliceChunks;            // 16-byte chunk inside the slice
     // One tile's rows and another tile's indices are in flight while a tile is stored (128 rows of 2048 kept pairs, 265 MB read and
-    // written: 49 us with a round trip to memory per tile, 41.5 us, 6.4 TB/s, so; 32 rows: 25 and 14.7 us).  The rows of tile t + 1 may be
+    // written: 49 us with a round trip to memory per tile, 41.5 us, 6.4 TB/s, so).  The rows of tile t + 1 may be
     // read before tile t is stored: they lie at or behind their own destinations, past the slots of tile t.
-    auto load_idx = [&](int base, int (&src)[kCompactU]) {   // -1: nothing to move
+    if constexpr (FEW) {
+        // Few workgroups: the loads are under no condition and two tiles take turns in their registers.  Behind conditions, or with a tile moved
+        // from one set of registers to the other, the compiler waits for everything in flight before every store.  32 rows of 2048 pairs out of
+        // 131072 16.6 us, so 15.4 (with the copy that resets the lengths, 1.7); 4 rows of 20000 70.6 and 62.4; 36 rows of 2349, head_dim 64, 13.2 and
+        // 12.1.  Where the workgroups fill the chip twice, cold rows lose what cached ones gain: 128 rows of 2048 with features 79.4 and 80.3 from
+        // HBM, 48.2 and 47.3 out of the Infinity Cache; 128 rows of 2048, fp32, 88.5 and 89.9.
+        auto load_idx = [&](int base, int (&src)[U]) {
 #pragma unroll
-        for (int u = 0; u < kCompactU; ++u) {
-            const int j = base + u * spi + sl;
-            const int s = j < budget ? kp[j] : -1;
-            src[u] = s >= 0 && s < n && s != j ? s : -1;
+            for (int u = 0; u < U; ++u) src[u] = kp[min(base + u * spi + sl, budget - 1)];
+        };
+        auto load_rows = [&](int base, const int (&src)[U], u32x4_t (&val)[U]) {   // a bit for every row that moves
+            uint32_t moves = 0;
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int j = base + u * spi + sl, s = src[u];
+                const bool m = j < budget && s >= 0 && s < n && s != j;
+                val[u] = *reinterpret_cast<const u32x4_t*>(X + (size_t)(m ? s : 0) * chunks + c);   // (the others: slot 0, not used)
+                moves |= (uint32_t)m << u;
+            }
+            return moves;
+        };
+        auto store_rows = [&](int base, u32x4_t (&val)[U], uint32_t moves) {
+#pragma unroll
+            for (int u = 0; u < U; ++u) asm volatile("" : "+v"(val[u]));   // every row of the tile is here before any of its slots is written
+            __syncthreads();
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+                if ((moves >> u) & 1) *reinterpret_cast<u32x4_t*>(X + (size_t)(base + u * spi + sl) * chunks + c) = val[u];
+        };
+        int src0[U], src1[U];
+        u32x4_t val0[U], val1[U];
+        load_idx(0, src0);
+        load_idx(tile, src1);
+        uint32_t moves0 = load_rows(0, src0, val0), moves1;
+        for (int base = 0; base < budget; base += 2 * tile) {
+            load_idx(base + 2 * tile, src0);
+            moves1 = load_rows(base + tile, src1, val1);
+            store_rows(base, val0, moves0);
+            if (base + tile >= budget) break;
+            load_idx(base + 3 * tile, src1);
+            moves0 = load_rows(base + 2 * tile, src0, val0);
+            store_rows(base + tile, val1, moves1);
         }
-    };
-    auto load_rows = [&](const int (&src)[kCompactU], u32x4_t (&val)[kCompactU]) {
+    } else {
+        auto load_idx = [&](int base, int (&src)[U]) {   // -1: nothing to move
 #pragma unroll
-        for (int u = 0; u < kCompactU; ++u)
-            if (src[u] >= 0) val[u] = *reinterpret_cast<const u32x4_t*>(X + (size_t)src[u] * chunks + c);
-    };
-    int now[kCompactU], next[kCompactU], after[kCompactU];
-    u32x4_t val[kCompactU], val_next[kCompactU];
-    load_idx(0, now);
-    load_idx(tile, next);
-    load_rows(now, val);
-    for (int base = 0; base < budget; base += tile) {
-        load_idx(base + 2 * tile, after);
-        load_rows(next, val_next);
-        __syncthreads();
+            for (int u = 0; u < U; ++u) {
+                const int j = base + u * spi + sl;
+                const int s = j < budget ? kp[j] : -1;
+                src[u] = s >= 0 && s < n && s != j ? s : -1;
+            }
+        };
+        auto load_rows = [&](const int (&src)[U], u32x4_t (&val)[U]) {
 #pragma unroll
-        for (int u = 0; u < kCompactU; ++u) {
-            if (now[u] >= 0) *reinterpret_cast<u32x4_t*>(X + (size_t)(base + u * spi + sl) * chunks + c) = val[u];
-            now[u] = next[u];
-            next[u] = after[u];
-            val[u] = val_next[u];
+            for (int u = 0; u < U; ++u)
+                if (src[u] >= 0) val[u] = *reinterpret_cast<const u32x4_t*>(X + (size_t)src[u] * chunks + c);
+        };
+        int now[U], next[U], after[U];
+        u32x4_t val[U], val_next[U];
+        load_idx(0, now);
+        load_idx(tile, next);
+        load_rows(now, val);
+        for (int base = 0; base < budget; base += tile) {
+            load_idx(base + 2 * tile, after);
+            load_rows(next, val_next);
+            __syncthreads();
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                if (now[u] >= 0) *reinterpret_cast<u32x4_t*>(X + (size_t)(base + u * spi + sl) * chunks + c) = val[u];
+                now[u] = next[u];
+                next[u] = after[u];
+                val[u] = val_next[u];
+            }
         }
     }
+}
+
+// Workgroups that move rows: up to one a CU, or more.  A tile of half as many slots where it holds the whole row (2 rows of 128 kept pairs
+// 5.0 us, 5.6 with tiles of 512).
+template <int Q4> static auto compact_kernel_for(long long workgroups, int budget) {
+    if (workgroups > 256) return compact_kernel<Q4, 4, false>;
+    return budget <= 256 ? compact_kernel<Q4, 2, true> : compact_kernel<Q4, 4, true>;
 }
 
 }  // namespace fk
@@ -210,7 +261,7 @@ extern "C" fk_status fk_compact(const fk_cache_desc* desc, void* K, void* V, int
     const int chunks = desc->head_dim * (desc->dtype == FK_F32 ? 4 : 2) / 16;
     const int rows = desc->batch * desc->n_kv_heads;
     hipStream_t st = (hipStream_t)stream;
-    hipLaunchKernelGGL(compact_kernel<0>, dim3(rows, 2 * (chunks / kSliceChunks) + 1), dim3(kCompactThreads), 0, st, (uint4*)K, (uint4*)V,
+    hipLaunchKernelGGL(compact_kernel_for<0>(rows * 2 * (chunks / kSliceChunks), budget), dim3(rows, 2 * (chunks / kSliceChunks) + 1), dim3(kCompactThreads), 0, st, (uint4*)K, (uint4*)V,
                        pos, nullptr, len, keep_idx, desc->capacity, budget, chunks);
     return launch_status();
 }
@@ -226,7 +277,8 @@ extern "C" fk_status fk_compact_feat(const fk_cache_desc* desc, void* K, void* V
     const int rows = desc->batch * desc->n_kv_heads;
     const int g = desc->n_q_heads / desc->n_kv_heads;
     hipStream_t st = (hipStream_t)stream;
-    const auto kern = g <= 4 ? compact_kernel<1> : compact_kernel<2>;
+    const int workgroups = rows * 2 * (chunks / kSliceChunks);
+    const auto kern = g <= 4 ? compact_kernel_for<1>(workgroups, budget) : compact_kernel_for<2>(workgroups, budget);
     hipLaunchKernelGGL(kern, dim3(rows, 2 * (chunks / kSliceChunks) + 2), dim3(kCompactThreads), 0, st, (uint4*)K, (uint4*)V, pos,
                        (float4*)feat, len, keep_idx, desc->capacity, budget, chunks);
     return launch_status();

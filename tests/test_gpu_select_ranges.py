@@ -200,3 +200,37 @@ def test_split_selection_bound_in_long_chunks(gpu, ora, kind, batch, hkv, n, len
     d_len = torch.from_numpy(np.repeat(ln[:, None], hkv, axis=1)).cuda()
     fk.fk_select_keep_ws(desc, gpu.to_dev(sc), None, d_len, hint, budget, recent, keep, work)
     gpu.assert_keep_equal(keep.cpu().numpy(), ora.select_keep(sc, np.ascontiguousarray(pos), ln, budget, recent, "sort"), ln, budget, kind)
+
+
+@pytest.mark.parametrize("budget", [1, 255, 256, 257, 511, 512, 513, 1024, 1025, 1537, 2200])
+@pytest.mark.parametrize("features", [0, 4, 8])
+def test_compact_over_the_edges_of_its_tiles(gpu, budget, features):
+    """Budgets around one, two, three and four tiles of 256 and 512 slots: rows that move by one slot, by a tile and one, at random, only behind
+    a tile, and not at all; every slot of cache and positions, the carried feature sums with them, exactly."""
+    import paper_2602_03203_amd as fk
+    print(f"compact budget {budget} features {features}", flush=True)
+    gen = torch.Generator(device="cuda").manual_seed(budget)
+    n, g = budget + 600, max(features, 1)
+    desc = fk.CacheDesc(5, g, 1, 64, n, "bf16")
+    K, V = (torch.randint(-30000, 30000, (5, 1, n, 64), generator=gen, device="cuda", dtype=torch.int16).view(torch.bfloat16) for _ in range(2))
+    pos = torch.arange(5 * n, dtype=torch.int32, device="cuda").reshape(5, 1, n)
+    j = torch.arange(budget, device="cuda")
+    rand = torch.randperm(n, generator=gen, device="cuda")[:budget].sort().values
+    keep = torch.stack([j + 1, j + min(513, 600), rand, torch.where(j >= min(513, budget - 1), j + 300, j), j]).int().reshape(5, 1, budget).contiguous()
+    ln = torch.full((5, 1), n, dtype=torch.int32, device="cuda")
+    want = [x.clone() for x in (K, V, pos)]
+    for x, y in zip(want, (K, V, pos)):
+        for r in range(5):
+            x[r, 0, :budget] = y[r, 0, keep[r, 0].long()]
+    if features:
+        feat = torch.rand((5, 1, 6, n, fk.feat_heads(desc)), generator=gen, device="cuda")
+        f0 = feat.clone()
+        fk.fk_compact_feat(desc, K, V, pos, feat, ln, keep, budget)
+        for r in range(5):
+            i = keep[r, 0].long()
+            assert torch.equal(feat[r, 0, 4, :budget], f0[r, 0, 4, i] + f0[r, 0, 3, i]) and not feat[r, 0, :4].any()
+    else:
+        fk.fk_compact(desc, K, V, pos, ln, keep, budget)
+    assert ln.eq(budget).all()
+    for x, y in zip(want, (K, V, pos)):
+        assert torch.equal(x.view(torch.uint8), y.view(torch.uint8))
