@@ -16,17 +16,18 @@
 // A step that splits a row merges the splits' records eight at a time, weighed by the largest maximum of the eight.  A workgroup here
 // meets the splits one after the other, so it walks the keys once before, for the maxima alone (SPLIT).
 //
-// Bound by instruction issue and by what two wavefronts a SIMD can hide of the L2's latency: by the counters the SIMDs issue in 67 % of
-// their cycles (vector 56 %, matrix 18 %, both 7 %), a wavefront waits 30 % of its time, and the tiles come at 23 bytes a cycle and CU. Two
-// groups of 16 queries with 32 keys take 32 matrix and some 260 vector instructions (64 of them where a maximum moved, which it does in
-// most of the eight tiles of a wavefront), 4100 cycles for the two wavefronts of a SIMD; of a workgroup's 46 000 cycles 2700 are its start
-// and 5000 its merge.  128 rows of 2048 pairs, 128 steps: 165 us with the copy that resets the lengths (0.43 PFLOP/s; 178 alone under the
-// profiler, whose clock is lower) against 2.9 ms step by step; with features 5 us more and 91 us for the planes.  It was 206 us with the probabilities through LDS, a merge of every group by
-// itself with scalar reads (6600 cycles), a branch per group in every loop, a walk whose counter was not known to be the same for a
+// Bound by what two wavefronts a SIMD can hide of the L2's and the LDS's latency.  Two groups of 16 queries with 32 keys take 34 matrix and some
+// 200 vector instructions (66 of them where a maximum moved, which it does in most of the eight tiles of a wavefront), 4000 cycles for the two
+// wavefronts of a SIMD; of a workgroup's 45 000 cycles 2700 are its start and 5000 its merge.  With 260 vector instructions (weights added up
+// by them, logits scaled before the maximum) it was 2.5 % more, the SIMDs issuing in 67 % of their cycles (vector 56 %, matrix 18 %, both 7
+// %), a wavefront waiting 30 % of its time, the tiles coming at 23 bytes a cycle and CU.  128 rows of 2048 pairs, 128 steps: 164 us with the
+// copy that resets the lengths (0.43 PFLOP/s; 175 repeated without a pause, at a lower clock) against 2.9 ms step by step; with features
+// 5 us more and 91 us for the planes.  It was 206 us with the probabilities through LDS, a merge of every group by itself with scalar reads
+// (6600 cycles), a branch per group in every loop, a walk whose counter was not known to be the same for a
 // wavefront (masks in every tile), and V waited for together with the next tile's K.  Measured and not kept: K as operand straight from the
 // L2 (16 rows of 64 bytes a load: 218 us against 182); all of a tile's operands read ahead, higher wavefront priority around the products:
 // no difference; references that follow the maximum only where it is 64 times above them, 55 of 390 vector instructions of a tile fewer: 2
-// %, and split rows 5 to 12 % slower.  Two groups: with one the K and V tiles are read twice as often, with three the registers spill.
+// %, and split rows 5 to 12 % slower; V of the next tile behind P.V: 1 to 4 % slower.  Two groups: with one the K and V tiles are read twice as often, with three the registers spill.
 //
 // The feature planes are sums over the steps IN ORDER, one fp32 addition per step: a second launch recomputes the logits (the
 // same products again: the same bits) with a pair per lane, its wavefronts walking the steps in order, so every plane is
