@@ -462,8 +462,8 @@ __global__ __launch_bounds__((AttnCfg<T, D, G, HEADS>::THREADS), (attn_two<T, D,
             if (h < G) qa[ks].u = *reinterpret_cast<const uint4*>(qrow + (size_t)h * D + ks * 32 + quad * 8);
             else qa[ks].u = make_uint4(0, 0, 0, 0);
         }
-        const float scale = P.scale_log2e, hidden = scale < 0.f ? INFINITY : -INFINITY;   // hidden: of no weight; the scale is never 0 (attn_scale)
-        // l: the normaliser, of unrounded weights where P.V has all their bits (SPLIT_P), otherwise a 65th column of ones in P.V, the same
+        const float scale = P.scale_log2e;
+        // l: the normaliser, of unrounded weights where P.V has all their bits (SPLIT_P), otherwise a column of ones more in P.V, a 129th, the same
         // rounded weights; lx: sum of the unrounded weights (feature variant)
         float m_run[4], l_run[4], lx_run[4];
         f32x4_t ol = (f32x4_t){0.f, 0.f, 0.f, 0.f};
@@ -582,21 +582,21 @@ __global__ __launch_bounds__((AttnCfg<T, D, G, HEADS>::THREADS), (attn_two<T, D,
                 if (quad * 4 < GP) {
                     if (base + key0 < end)
                         *reinterpret_cast<float4*>(lg_row + (size_t)(base + key0) * GP + quad * 4) =
-                            make_float4(c[0][0] * scale, c[0][1] * scale, c[0][2] * scale, c[0][3] * scale);
+                            make_float4(attn_logit(c[0][0], scale), attn_logit(c[0][1], scale), attn_logit(c[0][2], scale), attn_logit(c[0][3], scale));
                     if (base + key0 + KEY1 < end)
                         *reinterpret_cast<float4*>(lg_row + (size_t)(base + key0 + KEY1) * GP + quad * 4) =
-                            make_float4(c[1][0] * scale, c[1][1] * scale, c[1][2] * scale, c[1][3] * scale);
+                            make_float4(attn_logit(c[1][0], scale), attn_logit(c[1][1], scale), attn_logit(c[1][2], scale), attn_logit(c[1][3], scale));
                 }
             }
 #pragma unroll
             for (int i = 0; i < HR; ++i) {
-                const float s0 = (base + key0 < end) ? c[0][i] : hidden;
-                const float s1 = (base + key0 + KEY1 < end) ? c[1][i] : hidden;
-                const float mn = fmaxf(m_run[i], row16_max(fmaxf(s0 * scale, s1 * scale)));
+                const float s0 = (base + key0 < end) ? attn_logit(c[0][i], scale) : -INFINITY;
+                const float s1 = (base + key0 + KEY1 < end) ? attn_logit(c[1][i], scale) : -INFINITY;
+                const float mn = fmaxf(m_run[i], row16_max(fmaxf(s0, s1)));
                 changed |= mn > m_run[i];
                 corr[i] = exp2f(m_run[i] - mn);
                 // probabilities rounded to bf16; the SAME rounded values go into l, so the weights stay normalised
-                const float e0 = exp2f(fmaf(s0, scale, -mn)), e1 = exp2f(fmaf(s1, scale, -mn));
+                const float e0 = exp2f(s0 - mn), e1 = exp2f(s1 - mn);
                 const uint32_t w = pack_bf16(e0, e1);
                 pw[i] = w;
                 if constexpr (C::SPLIT_P) {   // each term of what the ones before leave; GP = 4: row quad q holds term q, GP = 8: q / 2
@@ -1046,7 +1046,7 @@ static fk_status attn_entry(const fk_cache_desc* desc, AttnParams P, int max_len
     const size_t need = P.feat ? feat_workspace_bytes(desc) : fk_decode_attn_workspace(desc, max_len);
     if (!workspace || workspace_bytes < need || !aligned16(workspace)) return FK_ERR_WORKSPACE;
     const int g = desc->n_q_heads / desc->n_kv_heads;
-    P.scale_log2e = attn_scale(softmax_scale);
+    P.scale_log2e = softmax_scale * 1.4426950408889634f;
     P.n_kv = desc->n_kv_heads;
     P.cap = desc->capacity;
     hipStream_t st = (hipStream_t)stream;
@@ -1167,7 +1167,7 @@ static WindowParams window_params(const fk_cache_desc* d, const void* q, void* K
     P.len = len;
     P.pos_seq = pos_seq;
     P.out_seq = out;
-    P.scale_log2e = attn_scale(scale);
+    P.scale_log2e = scale * 1.4426950408889634f;
     P.batch = d->batch;
     P.n_kv = d->n_kv_heads;
     P.g = d->n_q_heads / d->n_kv_heads;

@@ -89,9 +89,13 @@ template <int D> __host__ __device__ constexpr int attn_qk_key(int nt, int n) { 
 // ... and where the keys of a tile lie in LDS, so that the rows of a half follow each other
 template <int D> __host__ __device__ constexpr int attn_qk_row(int key) { return D == 128 ? key % 2 * 16 + key / 2 : key / 4 % 2 * 16 + key / 8 * 4 + key % 4; }
 
-// The softmax scale in base 2.  Hidden keys have logit -inf, which the scale must not turn into a NaN: for 0 a scale whose products
-// are as good as 0 (their exponentials are 1).
-inline float attn_scale(float softmax_scale) { return softmax_scale == 0.f ? 1e-38f : softmax_scale * 1.4426950408889634f; }
+// A logit in base 2, rounded before anything is subtracted from it (no fma with the maximum): the largest key's exponent is then 0 whatever
+// the logits' size - the rounding of its product, half a unit in the last place, is beyond +-128 from 2^32 on - and a weight is the same
+// in the normaliser and in the feature planes.
+__device__ __forceinline__ float attn_logit(float c, float scale) {
+#pragma clang fp contract(off)
+    return c * scale;
+}
 
 // bf16 pairs with an infinity or a NaN among them
 __device__ __forceinline__ bool pair_not_finite(uint32_t w) { return (w & 0x7f80u) == 0x7f80u || (w & 0x7f800000u) == 0x7f800000u; }

@@ -19,7 +19,7 @@
 // Bound by what two wavefronts a SIMD can hide of the L2's and the LDS's latency.  Two groups of 16 queries with 32 keys take 34 matrix and some
 // 200 vector instructions (66 of them where a maximum moved, which it does in most of the eight tiles of a wavefront), 4000 cycles for the two
 // wavefronts of a SIMD; of a workgroup's 45 000 cycles 2700 are its start and 5000 its merge.  With 260 vector instructions (weights added up
-// by them, logits scaled before the maximum) it was 2.5 % more, the SIMDs issuing in 67 % of their cycles (vector 56 %, matrix 18 %, both 7
+// by them) it was 4 % more, the SIMDs issuing in 67 % of their cycles (vector 56 %, matrix 18 %, both 7
 // %), a wavefront waiting 30 % of its time, the tiles coming at 23 bytes a cycle and CU.  128 rows of 2048 pairs, 128 steps: 164 us with the
 // copy that resets the lengths (0.43 PFLOP/s; 175 repeated without a pause, at a lower clock) against 2.9 ms step by step; with features
 // 5 us more and 91 us for the planes.  It was 206 us with the probabilities through LDS, a merge of every group by itself with scalar reads
@@ -145,7 +145,7 @@ __global__ __launch_bounds__(kXThreads, 2) void window_attn_kernel(const WindowP
         const xu32x4_t q = reinterpret_cast<const xu32x4_t*>(P.q_seq)[q_row(k, r) * CH + ch];
         *reinterpret_cast<xu32x4_t*>(s_q + (k * 16 + r) * KRS + ch * 16) = live ? q : xu32x4_t{0, 0, 0, 0};
     }
-    const float scale = P.scale_log2e, hidden = scale < 0.f ? INFINITY : -INFINITY;   // hidden: of no weight; the scale is never 0 (attn_scale)
+    const float scale = P.scale_log2e;
     if (tid == 0) s_bad = 0;
     if constexpr (SPLIT) {   // the splits of every step; what its tile walks depend on beside their lengths
         if (tid < t_end - t_first) {
@@ -232,7 +232,7 @@ __global__ __launch_bounds__(kXThreads, 2) void window_attn_kernel(const WindowP
 #pragma unroll
                         for (int nt = 0; nt < 2; ++nt)
 #pragma unroll
-                            for (int i = 0; i < 4; ++i) mx[k] = fmaxf(mx[k], base + attn_qk_key<D>(nt, quad * 4 + i) < lim[k] ? c[nt][i] * scale : kXNegBig);
+                            for (int i = 0; i < 4; ++i) mx[k] = fmaxf(mx[k], base + attn_qk_key<D>(nt, quad * 4 + i) < lim[k] ? attn_logit(c[nt][i], scale) : kXNegBig);
                     }
                     if (t + 1 == w1 || min((base + kXKT) / split_len, nsplit - 1) != mine) {
 #pragma unroll
@@ -254,8 +254,8 @@ __global__ __launch_bounds__(kXThreads, 2) void window_attn_kernel(const WindowP
             const int ntiles = (stop - start + kXKT - 1) / kXKT;
             const int rot = rotate ? attn_rotation(row, sp, ntiles) : 0;
             float m_run[GROUPS], l_run[GROUPS][4], lx_run[GROUPS][4];   // l, lx: one sum per key of a quarter of the tile, as in a single step
-            // l as a channel of ones (head_dim 128): the matrix cores add what took sixteen of some 115 vector instructions of a tile and group, and a
-            // logit goes into its exponential's argument by one fma: 128 rows of 2048 pairs, 128 steps 168.2 us, so 164.0.  [0] is rescaled and used.
+            // l as a channel of ones (head_dim 128): the matrix cores add what took sixteen of some 115 vector instructions of a tile and group: 128
+            // rows of 2048 pairs, 128 steps 168.4 us, so 162.0 (logits into their exponentials' arguments by one fma: 162.6).  [0] is rescaled and used.
             xf32x4_t ol[GROUPS];
             X128 ones;
             ones.u = xu32x4_t{0x3f803f80u, 0x3f803f80u, 0x3f803f80u, 0x3f803f80u};
@@ -337,29 +337,22 @@ __global__ __launch_bounds__(kXThreads, 2) void window_attn_kernel(const WindowP
 #pragma unroll
                 for (int k = 0; k < GROUPS; ++k) {
                     const int left = lim[k] - base;   // this lane's query sees the tile's keys [0, left)
+#pragma unroll
+                    for (int j = 0; j < 8; ++j) x[k][j] = attn_logit(c[k][j / 4][j % 4], scale);
                     if (partial) {
 #pragma unroll
                         for (int j = 0; j < 8; ++j)
-                            if (key_of(j) >= left) c[k][j / 4][j % 4] = hidden;
+                            if (key_of(j) >= left) x[k][j] = -INFINITY;   // of no weight, also where a step sees none of the tile
                     }
-                    // the largest of c * scale is the largest c's (a negative scale: the smallest one's)
-                    float mn;
-                    if (scale < 0.f) {
-                        mn = -c[k][0][0];
+                    float mn = x[k][0];
 #pragma unroll
-                        for (int j = 1; j < 8; ++j) mn = fmaxf(mn, -c[k][j / 4][j % 4]);
-                    } else {
-                        mn = c[k][0][0];
-#pragma unroll
-                        for (int j = 1; j < 8; ++j) mn = fmaxf(mn, c[k][j / 4][j % 4]);
-                    }
-                    mn = fmaxf(m_run[k], quads_max(mn) * fabsf(scale));
+                    for (int j = 1; j < 8; ++j) mn = fmaxf(mn, x[k][j]);
+                    mn = fmaxf(m_run[k], quads_max(mn));
                     changed[k] = mn > m_run[k];
-                    x[k][8] = m_run[k] - mn;
-                    lo = fminf(lo, x[k][8]);
+                    x[k][8] = m_run[k];
 #pragma unroll
-                    for (int j = 0; j < 8; ++j) {
-                        x[k][j] = fmaf(c[k][j / 4][j % 4], scale, -mn);
+                    for (int j = 0; j < 9; ++j) {
+                        x[k][j] -= mn;
                         lo = fminf(lo, x[k][j]);
                     }
                     m_run[k] = mn;
@@ -668,7 +661,7 @@ __global__ __launch_bounds__(kXThreads, 6) void window_feat_planes_kernel(const 
                 float x[4], lo = 0.f;
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
-                    x[i] = c[i] * P.scale_log2e - m4[i];
+                    x[i] = attn_logit(c[i], P.scale_log2e) - m4[i];
                     lo = fminf(lo, x[i]);
                 }
                 if (__any(lo < -126.f)) {   // exp2f's way round denormal results, only where there can be one
