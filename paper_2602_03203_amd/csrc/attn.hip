@@ -672,6 +672,9 @@ __global__ __launch_bounds__((AttnCfg<T, D, G, HEADS>::THREADS), (attn_two<T, D,
             }
             __builtin_amdgcn_wave_barrier();
         }
+        // A wavefront without a tile still has its queries' loads open.  Left open, the compiler (one head of head_dim 128) waits for every store
+        // of wave 0 before the records are read, the arrival counter's reset among them: 8 rows of 2000 pairs 5.9 us, so 5.7; 32 of 900 6.2 and 5.9.
+        __builtin_amdgcn_s_waitcnt(0x0F70);
         // publish one partial per wave
 #pragma unroll
         for (int i = 0; i < HR; ++i) {
