@@ -91,8 +91,8 @@ __device__ __forceinline__ void feat_roll(float4* __restrict__ feat, int row, in
 // lines and cost 1.5x the time) and walks the destination slots in ascending tiles of 512 (256)
 // slots: all sources of a tile are loaded into registers, a barrier, then the tile is stored.  A store of tile t lands in slots
 // [tT, (t+1)T); a source of any later tile is >= (t+1)T, and every source of tile t or of an
-// earlier tile has already been read, so no live source is overwritten.  Entries with
-// keep[j] == j (the untouched prefix) cost no traffic.
+// earlier tile has already been read, so no live source is overwritten.  What does not move is neither
+// read nor written, but for slot 0 in its place where there are few workgroups.
 // grid.x = row, grid.y = tensor * slices + slice (K slices, then V slices), last y = pos; Q4 > 0: the attention features before them
 // ---------------------------------------------------------------------------------------
 static constexpr int kSliceChunks = 8;  // 16-byte chunks per column slice
@@ -101,8 +101,10 @@ typedef unsigned int u32x4_t __attribute__((ext_vector_type(4)));
 // The workgroup that moves the positions (Q4 > 0: the features, which go by the length) also sets len[row] = min(len[row], budget) (no
 // second launch).  No other workgroup may then read len[row]: what moves is decided by keep alone (rows at or under budget carry the
 // identity, entries with keep[j] == j or outside [0, cap) move nothing).
-template <int Q4 /* float4 units of a feature plane per slot; 0: no features */, int U /* 16-byte loads of a tile per thread */, bool FEW>
-__global__ __launch_bounds__(kCompactThreads) void compact_kernel(uint4* __restrict__ K, uint4* __restrict__ V,
+enum CompactWalk { WALK_ONE, WALK_TURNS, WALK_MOVED };
+template <int Q4 /* float4 units of a feature plane per slot; 0: no features */, int U /* 16-byte loads of a tile per thread */, int WALK,
+          bool ALONE /* one workgroup to a CU */>
+__global__ __launch_bounds__(kCompactThreads) __attribute__((amdgpu_waves_per_eu(4, (ALONE ? 4 : 8)))) void compact_kernel(uint4* __restrict__ K, uint4* __restrict__ V,
                                                                   int32_t* __restrict__ pos, float4* __restrict__ feat,
                                                                   int32_t* __restrict__ len,
                                                                   const int32_t* __restrict__ keep,
@@ -150,12 +152,9 @@ __global__ __launch_bounds__(kCompactThreads) void compact_kernel(uint4* __restr
     // One tile's rows and another tile's indices are in flight while a tile is stored (128 rows of 2048 kept pairs, 265 MB read and
     // written: 49 us with a round trip to memory per tile, 41.5 us, 6.4 TB/s, so).  The rows of tile t + 1 may be
     // read before tile t is stored: they lie at or behind their own destinations, past the slots of tile t.
-    if constexpr (FEW) {
+    if constexpr (WALK != WALK_MOVED) {
         // Few workgroups: the loads are under no condition and two tiles take turns in their registers.  Behind conditions, or with a tile moved
-        // from one set of registers to the other, the compiler waits for everything in flight before every store.  32 rows of 2048 pairs out of
-        // 131072 16.6 us, so 15.4 (with the copy that resets the lengths, 1.7); 4 rows of 20000 70.6 and 62.4; 36 rows of 2349, head_dim 64, 13.2 and
-        // 12.1.  Where the workgroups fill the chip twice, cold rows lose what cached ones gain: 128 rows of 2048 with features 79.4 and 80.3 from
-        // HBM, 48.2 and 47.3 out of the Infinity Cache; 128 rows of 2048, fp32, 88.5 and 89.9.
+        // from one set of registers to the other, the compiler waits for everything in flight before every store.  Figures: compact_kernel_for.
         auto load_idx = [&](int base, int (&src)[U]) {
 #pragma unroll
             for (int u = 0; u < U; ++u) src[u] = kp[min(base + u * spi + sl, budget - 1)];
@@ -179,20 +178,68 @@ __global__ __launch_bounds__(kCompactThreads) void compact_kernel(uint4* __restr
             for (int u = 0; u < U; ++u)
                 if ((moves >> u) & 1) *reinterpret_cast<u32x4_t*>(X + (size_t)(base + u * spi + sl) * chunks + c) = val[u];
         };
-        int src0[U], src1[U];
-        u32x4_t val0[U], val1[U];
-        load_idx(0, src0);
-        load_idx(tile, src1);
-        uint32_t moves0 = load_rows(0, src0, val0), moves1;
-        for (int base = 0; base < budget; base += 2 * tile) {
-            load_idx(base + 2 * tile, src0);
-            moves1 = load_rows(base + tile, src1, val1);
-            store_rows(base, val0, moves0);
-            if (base + tile >= budget) break;
-            load_idx(base + 3 * tile, src1);
-            moves0 = load_rows(base + 2 * tile, src0, val0);
-            store_rows(base + tile, val1, moves1);
+        if constexpr (WALK == WALK_ONE) {   // the whole row is one tile
+            int src[U];
+            u32x4_t val[U];
+            load_idx(0, src);
+            const uint32_t moves = load_rows(0, src, val);
+            store_rows(0, val, moves);
+            return;
         }
+        // ALONE: a slot that moves nothing costs this walk a load all the same.  Where the first two tiles have none that moves, the first one that
+        // does is looked for in the indices alone, and the walk starts again there (32 rows of 8192 of which nothing moves 14.1 us, so 4.4; moved
+        // from the third quarter on 19.0 and 13.1; 2048 at random as before).  The second copy of the loop takes the registers of a second workgroup.
+        constexpr int WAVES = kCompactThreads / kWave, LOOK = 4;
+        __shared__ int s_first[2][WAVES];   // a wavefront's first slot that moves; budget: none
+        auto put_first = [&](int turn, int slot) {
+            if (threadIdx.x % kWave == 0) s_first[turn][threadIdx.x / kWave] = slot;
+        };
+        auto get_first = [&](int turn) {
+            int first = budget;
+#pragma unroll
+            for (int w = 0; w < WAVES; ++w) first = min(first, s_first[turn][w]);
+            return __builtin_amdgcn_readfirstlane(first);
+        };
+        auto walk = [&](int start, auto looking) {   // true: done; false: nothing moves in the first two tiles
+            int src0[U], src1[U];
+            u32x4_t val0[U], val1[U];
+            load_idx(start, src0);
+            load_idx(start + tile, src1);
+            uint32_t moves0 = load_rows(start, src0, val0), moves1;
+            for (int base = start; base < budget; base += 2 * tile) {
+                load_idx(base + 2 * tile, src0);
+                moves1 = load_rows(base + tile, src1, val1);
+                if constexpr (looking) {
+                    if (base == start) put_first(0, __any(moves0 | moves1) ? 0 : budget);
+                }
+                store_rows(base, val0, moves0);
+                if constexpr (looking) {
+                    if (base == start && get_first(0) == budget) return false;
+                }
+                if (base + tile >= budget) break;
+                load_idx(base + 3 * tile, src1);
+                moves0 = load_rows(base + 2 * tile, src0, val0);
+                store_rows(base + tile, val1, moves1);
+            }
+            return true;
+        };
+        if (walk(0, std::integral_constant<bool, ALONE>())) return;
+        int first = budget;
+        for (int base = 2 * tile, turn = 1; first == budget && base < budget; base += LOOK * kCompactThreads, turn ^= 1) {
+            int s[LOOK], mine = budget;
+#pragma unroll
+            for (int u = 0; u < LOOK; ++u) s[u] = kp[min(base + u * kCompactThreads + (int)threadIdx.x, budget - 1)];
+#pragma unroll
+            for (int u = LOOK - 1; u >= 0; --u) {
+                const int j = base + u * kCompactThreads + (int)threadIdx.x;
+                const unsigned long long m = __ballot(j < budget && s[u] >= 0 && s[u] < n && s[u] != j);
+                if (m) mine = j - (int)(threadIdx.x % kWave) + __ffsll((long long)m) - 1;
+            }
+            put_first(turn, mine);
+            __syncthreads();
+            first = get_first(turn);
+        }
+        if (first < budget) walk(first / tile * tile, std::false_type());
     } else {
         auto load_idx = [&](int base, int (&src)[U]) {   // -1: nothing to move
 #pragma unroll
@@ -227,11 +274,27 @@ __global__ __launch_bounds__(kCompactThreads) void compact_kernel(uint4* __restr
     }
 }
 
-// Workgroups that move rows: up to one a CU, or more.  A tile of half as many slots where it holds the whole row (2 rows of 128 kept pairs
-// 5.0 us, 5.6 with tiles of 512).
-template <int Q4> static auto compact_kernel_for(long long workgroups, int budget) {
-    if (workgroups > 256) return compact_kernel<Q4, 4, false>;
-    return budget <= 256 ? compact_kernel<Q4, 2, true> : compact_kernel<Q4, 4, true>;
+// By the workgroups that move rows (128 bytes of a slot each).  us, from the Infinity Cache / from HBM, WALK_MOVED and the form taken; rows of
+// head_dim 128 in bf16 where nothing else is said:
+//   one tile             32 rows of 512 of 640 pairs 4.7 / 6.6 and 4.2 / 6.5, 64 rows 6.6 / 11.2 and 5.5 / 10.5; tiles of 256 slots for up to 256
+//                        pairs, 64 rows 5.2 / 7.6 and 4.0 / 6.4
+//   two tiles in turns   4 rows of 20000 70.6 and 62.4; 32 rows of 2048 of 2176 11.3 / 19.0 and 10.0 / 18.2, out of 32768 13.5 / 15.5 and 12.1 /
+//                        14.6; 64 rows of 2048 of 2176 19.6 / 31.1 and 18.1 / 30.9; head_dim 64, 96 rows of 2048 16.0 / 25.0 and 14.9 / 24.2
+// Where they do not pay: kept bytes beyond the Infinity Cache (64 rows of 8192 80.7 and 84.4 from the cache, 32 of 16384 126 and 128), from 129
+// workgroups on already half of it (48 rows of 8192, nothing of which moves, 11.7 and 14.3); scattered rows of more than 160 workgroups (head_dim
+// 64, 96 rows of 2048 out of 32768 20.2 and 22.7); more than 256, which fill the chip twice (128 rows of 2048 with features 79.4 and 80.3 from
+// HBM, fp32 88.5 and 89.9).  Up to 200, those of the features among them, a workgroup has a CU for itself: with two on some and none on others 16
+// rows of 2048 take 14.4 us from HBM, so 14.0; beyond, a second round would begin (64 rows of 1024 8.7 and 9.4; with features, 48 of 2048 26.5
+// and 26.9, head_dim 64, 96 of 2048 19.1 and 20.1).
+template <int Q4> static auto compact_kernel_for(long long workgroups, int rows, int budget, int cap) {
+    const bool alone = workgroups + (Q4 > 0 ? rows : 0) <= 200;
+    if (workgroups <= 256 && budget <= 256) return alone ? compact_kernel<Q4, 2, WALK_ONE, true> : compact_kernel<Q4, 2, WALK_ONE, false>;
+    if (workgroups <= 256 && budget <= 512) return alone ? compact_kernel<Q4, 4, WALK_ONE, true> : compact_kernel<Q4, 4, WALK_ONE, false>;
+    const bool turns = workgroups <= 128 ? workgroups * budget < (1 << 21)
+                                         : workgroups <= 256 && workgroups * budget <= (1 << 20) && (workgroups <= 160 || cap <= 4ll * budget);
+    if (turns)
+        return alone ? compact_kernel<Q4, 4, WALK_TURNS, true> : compact_kernel<Q4, 4, WALK_TURNS, false>;
+    return compact_kernel<Q4, 4, WALK_MOVED, false>;
 }
 
 }  // namespace fk
@@ -261,7 +324,7 @@ extern "C" fk_status fk_compact(const fk_cache_desc* desc, void* K, void* V, int
     const int chunks = desc->head_dim * (desc->dtype == FK_F32 ? 4 : 2) / 16;
     const int rows = desc->batch * desc->n_kv_heads;
     hipStream_t st = (hipStream_t)stream;
-    hipLaunchKernelGGL(compact_kernel_for<0>(rows * 2 * (chunks / kSliceChunks), budget), dim3(rows, 2 * (chunks / kSliceChunks) + 1), dim3(kCompactThreads), 0, st, (uint4*)K, (uint4*)V,
+    hipLaunchKernelGGL(compact_kernel_for<0>(rows * 2ll * (chunks / kSliceChunks), rows, budget, desc->capacity), dim3(rows, 2 * (chunks / kSliceChunks) + 1), dim3(kCompactThreads), 0, st, (uint4*)K, (uint4*)V,
                        pos, nullptr, len, keep_idx, desc->capacity, budget, chunks);
     return launch_status();
 }
@@ -277,8 +340,8 @@ extern "C" fk_status fk_compact_feat(const fk_cache_desc* desc, void* K, void* V
     const int rows = desc->batch * desc->n_kv_heads;
     const int g = desc->n_q_heads / desc->n_kv_heads;
     hipStream_t st = (hipStream_t)stream;
-    const int workgroups = rows * 2 * (chunks / kSliceChunks);
-    const auto kern = g <= 4 ? compact_kernel_for<1>(workgroups, budget) : compact_kernel_for<2>(workgroups, budget);
+    const long long workgroups = rows * 2ll * (chunks / kSliceChunks);
+    const auto kern = g <= 4 ? compact_kernel_for<1>(workgroups, rows, budget, desc->capacity) : compact_kernel_for<2>(workgroups, rows, budget, desc->capacity);
     hipLaunchKernelGGL(kern, dim3(rows, 2 * (chunks / kSliceChunks) + 2), dim3(kCompactThreads), 0, st, (uint4*)K, (uint4*)V, pos,
                        (float4*)feat, len, keep_idx, desc->capacity, budget, chunks);
     return launch_status();

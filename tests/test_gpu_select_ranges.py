@@ -234,3 +234,37 @@ def test_compact_over_the_edges_of_its_tiles(gpu, budget, features):
     assert ln.eq(budget).all()
     for x, y in zip(want, (K, V, pos)):
         assert torch.equal(x.view(torch.uint8), y.view(torch.uint8))
+
+
+# rows of head_dim 64 (two workgroups each): up to 192 workgroups look for the first slot that moves beyond the first two tiles (1024 slots), in
+# passes of 4096 slots from there; up to 256 and beyond do not
+@pytest.mark.parametrize("rows,budget", [(12, 1025), (12, 1537), (12, 5121), (12, 9300), (80, 1700), (96, 1500), (97, 1500), (128, 1500), (129, 1500)])
+@pytest.mark.parametrize("holes", [False, True])
+def test_compact_of_rows_that_move_late(gpu, rows, budget, holes):
+    """Rows that stay up to a slot at the edges of tiles and passes, and rows that stay for good; with holes, every second slot that stays has an index
+    outside the cache instead of its own."""
+    import paper_2602_03203_amd as fk
+    print(f"compact late rows {rows} budget {budget} holes {holes}", flush=True)
+    gen = torch.Generator(device="cuda").manual_seed(budget)
+    n = budget + 40
+    desc = fk.CacheDesc(rows, 1, 1, 64, n, "bf16")
+    K, V = (torch.randint(-30000, 30000, (rows, 1, n, 64), generator=gen, device="cuda", dtype=torch.int16).view(torch.bfloat16) for _ in range(2))
+    pos = torch.arange(rows * n, dtype=torch.int32, device="cuda").reshape(rows, 1, n)
+    edges = [0, 511, 512, 1023, 1024, 1025, 1535, 1536, 5119, 5120, 9216, budget - 1, budget]
+    first = torch.tensor([min(edges[r % len(edges)], budget) for r in range(rows)], device="cuda")
+    j = torch.arange(budget, device="cuda")
+    stays = j[None, :] < first[:, None]
+    keep = torch.where(stays, j, j + 1 + torch.arange(rows, device="cuda")[:, None] % 40)
+    src = keep.clone()
+    if holes:
+        keep = torch.where(stays & (j % 2 == 1), torch.where(j % 4 == 1, -1, n + j), keep)
+    keep = keep.int().reshape(rows, 1, budget).contiguous()
+    ln = torch.full((rows, 1), n, dtype=torch.int32, device="cuda")
+    want = [x.clone() for x in (K, V, pos)]
+    for x, y in zip(want, (K, V, pos)):
+        i = src.reshape(src.shape + (1,) * (y.dim() - 3)).expand((rows, budget) + y.shape[3:])
+        x[:, 0, :budget] = y[:, 0].gather(1, i)
+    fk.fk_compact(desc, K, V, pos, ln, keep, budget)
+    assert ln.eq(budget).all()
+    for x, y in zip(want, (K, V, pos)):
+        assert torch.equal(x.view(torch.uint8), y.view(torch.uint8))
