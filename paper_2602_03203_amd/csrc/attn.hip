@@ -273,9 +273,9 @@ __device__ __forceinline__ int row_by_length(const int32_t* len, int rows, int c
     return row;
 }
 
-// Two heads of head_dim 128 are told to leave room for two workgroups on a CU, which they do by themselves but for two registers (130 of
-// them, 128 told: 512 rows of 300 pairs 15.6 and 13.9 us; the same streamed 14.4 and 12.4).  One and three heads have 128; four 125; told,
-// they spill.
+// Up to three heads of head_dim 128 are told to leave room for two workgroups on a CU: by themselves they take 130 (two heads) to 134 registers,
+// told 128 (512 rows of 300 pairs: one head 16.7 and 14.9 us, two 15.6 and 13.9, three 18.1 and 15.7; the same streamed, two 14.4 and 12.4).
+// Four take 128 untold.  None of them spills.
 template <typename T, int D, int G, bool FEAT> constexpr bool attn_two() { return sizeof(T) == 2 && D == 128 && G <= 3 && !FEAT; }
 
 template <typename T, int D, int G, bool FEAT, bool NT, bool HEADS = false>
@@ -464,7 +464,10 @@ __global__ __launch_bounds__((AttnCfg<T, D, G, HEADS>::THREADS), (attn_two<T, D,
         }
         const float scale = P.scale_log2e;
         // l: the normaliser, of unrounded weights where P.V has all their bits (SPLIT_P), otherwise a column of ones more in P.V, a 129th, the same
-        // rounded weights; lx: sum of the unrounded weights (feature variant)
+        // rounded weights; lx: sum of the unrounded weights (feature variant).  Against sums by vector instructions, us: four heads, 2 rows of
+        // 144 pairs 5.34 and 5.20, 128 of 2048 23.1 and 22.9; two heads alike; one head, which has a quarter of the additions and pays for the registers,
+        // 2 of 144 alike, 128 of 2048 22.2 and 22.4, 512 of 300 14.65 and 14.85; three heads 128 of 300 6.3 and 6.4, 128 of 2048 alike.  One form
+        // for all, because windows give the same bits: there one head gains 4 %, three 6 to 7 (128 rows of 2048, 128 steps 51.9 and 49.8, 136 and 127).
         float m_run[4], l_run[4], lx_run[4];
         f32x4_t ol = (f32x4_t){0.f, 0.f, 0.f, 0.f};
         B128 ones;
@@ -940,14 +943,23 @@ __global__ __launch_bounds__((AttnCfg<T, D, G, HEADS>::THREADS), (attn_two<T, D,
 
 // fp32, short rows that all fit the chip: a workgroup of sixteen wavefronts for every query head, rows not split.  The vector instructions of
 // the group's heads are what such a step waits for (one head on four wavefronts takes 4.3 us at two rows of 144 pairs of head_dim 64, eight
-// take 7.6, and of that 1.6 for merging splits); K and V are read once per head, from the L2.  us a step, so and with splits:
-//   2 rows of 144, D = 64  g = 1: 3.4 and 4.3, 4: 3.5 and 5.2, 8: 3.6 and 7.6;  8 rows, g = 4  800 pairs 6.3 and 6.5, 1200 7.8 and 7.3
-//   8 rows, D = 128  g = 1  144: 4.0 and 4.3, 260: 5.0 and 4.7;  g = 2  260: 5.1 and 5.3, 400: 6.3 and 5.5;  g = 4  570: 7.7 and 8.6, 800: 9.5 and 9.8
-// The heads of a row share an XCD's L2 where the rows are a multiple of eight; otherwise the copies have to fit all of them together (21 rows
-// of 570, g = 4, D = 128: 10.5 and 9.3).
+// take 7.6, and of that 1.6 for merging splits); K and V are read once per head, from the L2.  How long rows may be for it depends on how full
+// the chip is: few rows split are spread over more CUs, many are not.  us a step with splits and so, from a sweep of 1 to 256 rows and seven to
+// ten lengths a group size (the lines lie where the two are equal, or below):
+//   D = 64   g = 1   8 rows of 350 5.4 and 5.4, 32 of 500 6.4 and 6.0, 128 of 390 7.4 and 5.8, 64 of 858 7.9 and 8.0
+//            g = 2   8 rows of 265 5.6 and 5.4, of 450 5.7 and 6.0, 32 of 450 6.5 and 6.3;  g = 3  8 of 335 6.0 and 5.7, of 468 6.1 and 6.4
+//            g = 4   8 rows of 567 7.2 and 6.6, of 810 7.2 and 7.7, 64 of 810 9.2 and 8.8;  g = 8  8 of 1370 12.1 and 10.1
+//   D = 128  g = 1   8 rows of 125 5.0 and 4.7, of 200 5.1 and 5.4, 32 of 220 5.9 and 5.6, 128 of 250 8.3 and 6.8
+//            g = 2   8 rows of 150 5.5 and 5.5, of 255 5.7 and 6.3, 128 of 300 11.1 and 8.6;  g = 3  8 of 350 7.5 and 7.0, of 500 7.8 and 8.5
+//            g = 4   8 rows of 350 8.0 and 7.0, of 700 9.3 and 9.8, 64 of 700 13.8 and 12.9;  g = 8  8 of 1500 19.1 and 16.6, of 1875 19.3 and 19.6
+// The heads of a row share an XCD's L2 where the rows are a multiple of eight; otherwise the copies have to fit all of them together (D = 128, g =
+// 4, 21 rows of 350 8.5 and 7.8, of 489 9.1 and 10.5).
 static bool attn_by_head(int rows, int g, int max_len, int head_dim) {
-    if ((long long)rows * g > 256 || max_len > (head_dim == 64 ? 250 + 140 * g : 200 * g - 100)) return false;
-    return rows % 8 == 0 || (long long)rows * g * max_len * head_dim <= (1 << 22);
+    if ((long long)rows * g > 256) return false;
+    static constexpr short kLongest[2][3][4] = {{{390, 340, 340, 600}, {500, 450, 570, 690}, {800, 660, 830, 810}},    // head_dim 64: up to 15, 63, 256
+                                                {{140, 140, 380, 450}, {250, 200, 420, 600}, {350, 300, 800, 900}}};   // rows by the heads of a group
+    const int longest = g <= 4 ? kLongest[head_dim == 128][rows < 16 ? 0 : rows < 64 ? 1 : 2][g - 1] : head_dim == 64 ? 250 + 140 * g : 200 * g - 100;
+    return max_len <= longest && (rows % 8 == 0 || (long long)rows * g * max_len * head_dim <= (1 << 22));
 }
 
 template <typename T, int D, int G>

@@ -118,10 +118,11 @@ def test_head_dim_64_weights_keep_their_24_bits(gpu, g, features):
     assert off.max() < 2.0 ** -21, f"weights off by 2^{torch.log2(off.max()).item():.1f}"
 
 
-# rows, group, head_dim, capacity (the length hint): a workgroup per query head up to 250 + 140 g and 200 g - 100 pairs, 256 workgroups, and,
-# where the rows are no multiple of eight, copies of K and V that fit the L2s
+# rows, group, head_dim, capacity (the length hint): a workgroup per query head up to a length by head_dim, rows (up to 15, 63, 256) and heads, 256
+# workgroups, and, where the rows are no multiple of eight, copies of K and V that fit the L2s; both sides of these lines
 BY_HEAD = [(2, 4, 64, 300), (2, 1, 64, 390), (2, 1, 64, 391), (8, 2, 128, 300), (8, 2, 128, 301), (3, 8, 64, 520), (32, 8, 128, 140), (33, 8, 128, 140),
-           (5, 3, 128, 500), (21, 4, 128, 390), (21, 4, 128, 391), (16, 5, 64, 257), (1, 7, 128, 9), (256, 1, 64, 70)]
+           (5, 3, 128, 500), (21, 4, 128, 390), (21, 4, 128, 391), (16, 5, 64, 257), (1, 7, 128, 9), (256, 1, 64, 70),
+           (8, 2, 128, 140), (8, 2, 128, 141), (16, 1, 128, 250), (16, 1, 128, 251), (64, 4, 128, 900), (64, 4, 64, 810), (15, 3, 64, 340), (128, 2, 64, 661)]
 
 
 @pytest.mark.parametrize("rows,g,D,cap", BY_HEAD)
