@@ -98,14 +98,6 @@ __device__ __forceinline__ float row16_max(float v) {
 }
 
 // over the KG key groups of a wavefront (fp32): lanes that differ in bit 5, and with four groups in bit 4
-__device__ __forceinline__ float add_halves(float a, float b) {   // lower lanes: a of both halves; upper ones: b
-    auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
-    return __uint_as_float(r[0]) + __uint_as_float(r[1]);
-}
-__device__ __forceinline__ float add_rows(float a, float b) {   // even rows of 16 lanes: a of two neighbouring rows; odd ones: b
-    auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(b), false, false);
-    return __uint_as_float(r[0]) + __uint_as_float(r[1]);
-}
 template <int KG> __device__ __forceinline__ float lanes_sum(float v) {
     v = add_halves(v, v);
     return KG == 4 ? add_rows(v, v) : v;

@@ -99,4 +99,14 @@ inline bool allow_dynamic_lds(const void* kernel, size_t bytes, bool (&done)[kMa
 
 inline bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 
+// Sums over the two halves of a wavefront, or over neighbouring rows of 16 lanes, of two values with one addition
+__device__ __forceinline__ float add_halves(float a, float b) {   // lower lanes: a of both halves; upper ones: b
+    auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+    return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+__device__ __forceinline__ float add_rows(float a, float b) {   // even rows of 16 lanes: a of two neighbouring rows; odd ones: b
+    auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+    return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+
 }  // namespace fk

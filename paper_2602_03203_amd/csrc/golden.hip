@@ -19,20 +19,14 @@ static constexpr int kPoolThreads = 512;
 static constexpr int kPoolU = 8;   // loads in flight per thread
 
 template <int W>   // value i (lower lanes) and i + W (upper lanes) of both halves added up, i < W
-__device__ __forceinline__ void add_halves(float* v) {
+__device__ __forceinline__ void fold_halves(float* v) {
 #pragma unroll
-    for (int i = 0; i < W; ++i) {
-        auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v[i]), __float_as_uint(v[i + W]), false, false);
-        v[i] = __uint_as_float(r[0]) + __uint_as_float(r[1]);
-    }
+    for (int i = 0; i < W; ++i) v[i] = add_halves(v[i], v[i + W]);
 }
 template <int W>   // the same for the odd and even rows of 16 lanes
-__device__ __forceinline__ void add_rows(float* v) {
+__device__ __forceinline__ void fold_rows(float* v) {
 #pragma unroll
-    for (int i = 0; i < W; ++i) {
-        auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v[i]), __float_as_uint(v[i + W]), false, false);
-        v[i] = __uint_as_float(r[0]) + __uint_as_float(r[1]);
-    }
+    for (int i = 0; i < W; ++i) v[i] = add_rows(v[i], v[i + W]);
 }
 // Bound by HBM.  32 heads of 8192 tokens, bf16: 2.0 GB of causal entries in 320 us, 6.3 TB/s (343 us, 5.9, while tiles and XCDs went in step: see below).
 // The loads of a pass are under no condition where the whole pass is there: behind a condition the compiler waited for the first seven
@@ -126,11 +120,11 @@ __global__ __launch_bounds__(kPoolThreads) void golden_pool_kernel(const T* __re
     __shared__ float s_acc[WAVES][KT];
     int first = c * EPC;   // this lane's first key of the tile
     if constexpr (LPR <= 32) {
-        add_halves<EPC / 2>(acc);
+        fold_halves<EPC / 2>(acc);
         first += (int)threadIdx.x / 32 % 2 * (EPC / 2);
     }
     if constexpr (LPR == 16) {
-        add_rows<E>(acc);
+        fold_rows<E>(acc);
         first += (int)threadIdx.x / 16 % 2 * E;
     }
 #pragma unroll

@@ -340,8 +340,6 @@ def test_prepared_call_replays_the_direct_call(gpu, ora):
         fk.prepare(fk.fk_select_keep, desc, d_sc, None, d_ln, cap, cap + 1, recent, keep)()
 
 
-
-
 @pytest.mark.parametrize("features", [False, True])
 def test_prepared_step_is_the_direct_step(gpu, features):
     """A decode step marshalled by fk.prepare passes its arguments in one struct: outputs and state are those of the direct call, bit for bit."""
@@ -366,6 +364,8 @@ def test_prepared_step_is_the_direct_step(gpu, features):
     for a, b in zip(*res):
         assert torch.equal(a.view(torch.uint8), b.view(torch.uint8))
     assert int(res[0][4][0, 0]) == 152
+
+
 def test_select_keep_special_values(gpu, ora):
     import paper_2602_03203_amd as fk
     cap, budget, recent = 1200, 700, 100
