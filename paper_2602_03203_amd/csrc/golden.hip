@@ -138,20 +138,21 @@ __global__ __launch_bounds__(kPoolThreads) void golden_pool_kernel(const T* __re
     }
 }
 
-// alpha[t] = max(a~[t], alpha[t + 1]), walking the blocks from the last to the first; one thread per key, kFutureU blocks' loads in
-// flight (a wavefront or two a SIMD: a walk of 223 blocks of 4096 tokens waits for memory 28 times with eight, seven times with 32: 6 us less)
-static constexpr int kFutureU = 32;
+// alpha[t] = max(a~[t], alpha[t + 1]), walking the blocks from the last to the first; one thread per key, U blocks' loads in
+// flight (a wavefront or two a SIMD: a walk of 223 blocks of 4096 tokens waits for memory 28 times with eight, seven times with 32: 6 us less;
+// no more of them than blocks)
+template <int U>
 __global__ void golden_future_kernel(const float* __restrict__ a_tilde, int Tn, int M, float* __restrict__ alpha) {
     const int i = blockIdx.x * blockDim.x + threadIdx.x, hp = blockIdx.y;
     if (i >= Tn) return;
     const size_t o0 = (size_t)hp * M * Tn + i;
     float run = -INFINITY;
-    for (int t = M; t >= 1; t -= kFutureU) {
-        float a[kFutureU];
+    for (int t = M; t >= 1; t -= U) {
+        float a[U];
 #pragma unroll
-        for (int u = 0; u < kFutureU; ++u) a[u] = a_tilde[o0 + (size_t)max(t - u - 1, 0) * Tn];   // (past the first block that one again)
+        for (int u = 0; u < U; ++u) a[u] = a_tilde[o0 + (size_t)max(t - u - 1, 0) * Tn];   // (past the first block that one again)
 #pragma unroll
-        for (int u = 0; u < kFutureU; ++u) {
+        for (int u = 0; u < U; ++u) {
             if (t - u >= 1) {
                 run = t - u == M ? a[u] : fmaxf(run, a[u]);
                 alpha[o0 + (size_t)(t - u - 1) * Tn] = run;
@@ -822,24 +823,32 @@ extern "C" fk_status fk_golden_scores(const void* A, int32_t dtype, int32_t n_q_
         const int most = 2 * ((T + tile - 1) / tile), pair = (int)((2ll * budget + (M + 3ll) * interval) / tile) + 2;   // live tiles of two blocks
         hipLaunchKernelGGL(kern, dim3(pair < most ? pair : most, (M + 1) / 2, n_kv_heads), dim3(kPoolThreads), 0, st, a, g, T, (size_t)ld, budget, interval, M, block_scores);
     };
-    // How wide a workgroup's tile is, 1 KB, 512 or 256 bytes of a row.  Wide ones waste the least where rows do not start on a line of 128 bytes
-    // (32 heads of 5001 tokens, L = 32: 176 us, 512 bytes 185, 256 bytes 205) and leave a short block's workgroups the most to do (8 heads of 4096,
-    // L = 32: 47, 62 and 92); 512 bytes fill the chip better at the end (32 heads of 8192: 324 us, so 343 and 338); 256 where there would be
-    // fewer workgroups than CUs (one group of 2500 tokens, L = 1000: 28, 512 bytes 37, 1 KB 58).
+    // How wide a workgroup's tile is, 1 KB, 512 or 256 bytes of a row, by some 440 shapes of 1000 to 8192 tokens, 1 to 64 heads, blocks of 16 to 256.
+    // Wide ones waste the least where rows do not start on a line of 128 bytes (32 heads of 5001 tokens, L = 32: 176 us, 512 bytes 185, 256 bytes
+    // 205; 8 of 5200, L = 250: 35, 39 and 46) and leave a short block's workgroups the most to do (8 heads of 4096, L = 32: 47, 62 and 92).  256 bytes
+    // where wider ones would leave CUs idle (one group of 2500 tokens, L = 1000: 28, 512 bytes 37, 1 KB 58; 8 heads of 1532, L = 128: 8.6, 10.9 and
+    // 16.4) and for large blocks (32 heads of 5504, L = 250: 173, 187 and 185), but where all rows start on the same channels, at a multiple of
+    // 1 KB, 512 bytes are spread best (32 heads of 8192: 338, 324 and 343), as they are for blocks of few (head, query) pairs (8 heads of 1856, L =
+    // 32: 11.4, 10.7 and 13.1).
     const size_t row_bytes = (size_t)T * (dtype == FK_F32 ? 4 : 2), pitch = (size_t)ld * (dtype == FK_F32 ? 4 : 2);
-    const bool few = (long long)((row_bytes + 1023) / 1024) * M * n_kv_heads < 256, half = pitch % 128 == 0 && (long long)g * interval >= 128;
+    const long long wide = (long long)((row_bytes + 1023) / 1024) * M * n_kv_heads, pairs = (long long)g * interval;
+    const bool lines = pitch % 128 == 0;
+    const int lanes = wide < 128 || (pairs >= 96 && wide < (lines ? 256 : 192)) ? 16
+                      : pairs < 96 || !lines                                    ? 64
+                      : pitch % 1024 == 0 || pairs < 192                        ? 32
+                                                                                : 16;
     if (dtype == FK_F32) {
         const float* a = static_cast<const float*>(A);
-        if (few) pool(golden_pool_kernel<float, 16>, a, 16);
-        else if (half) pool(golden_pool_kernel<float, 32>, a, 32);
+        if (lanes == 16) pool(golden_pool_kernel<float, 16>, a, 16);
+        else if (lanes == 32) pool(golden_pool_kernel<float, 32>, a, 32);
         else pool(golden_pool_kernel<float, 64>, a, 64);
     } else {
         const bf16_t* a = static_cast<const bf16_t*>(A);
-        if (few) pool(golden_pool_kernel<bf16_t, 16>, a, 16);
-        else if (half) pool(golden_pool_kernel<bf16_t, 32>, a, 32);
+        if (lanes == 16) pool(golden_pool_kernel<bf16_t, 16>, a, 16);
+        else if (lanes == 32) pool(golden_pool_kernel<bf16_t, 32>, a, 32);
         else pool(golden_pool_kernel<bf16_t, 64>, a, 64);
     }
-    hipLaunchKernelGGL(golden_future_kernel, dim3((T + 255) / 256, n_kv_heads), dim3(256), 0, st, block_scores, T, M, alpha);
+    hipLaunchKernelGGL((M <= 8 ? golden_future_kernel<8> : M <= 16 ? golden_future_kernel<16> : golden_future_kernel<32>), dim3((T + 255) / 256, n_kv_heads), dim3(256), 0, st, block_scores, T, M, alpha);
     return launch_status();
 }
 

@@ -90,22 +90,24 @@ def test_pooling_of_short_blocks(gpu, dtype, Hq, g, T, B, L):
     assert run_case(gpu, dtype, Hq, g, T, B, L) > 0
 
 
-# the three widths of a workgroup's tile (256 bytes of a row where 1 KB gave fewer than 256 workgroups, 512 where rows start on a line and a block
-# has 128 (head, query) pairs, 1 KB), blocks of an odd and an even number that share the workgroups of a row of the grid, and the passes of
-# 64, 128 and 256 pairs full, one short of it and one beyond; every entry above the diagonal is written
+# the three widths of a workgroup's tile (256, 512 and 1024 bytes of a row, by the rule below), blocks of an odd and an even number that share the
+# workgroups of a row of the grid, and passes full, one short of it and one beyond; every entry above the diagonal is written
 POOL_WIDTHS = [(4, 1, 2049, 70, 32, 2056), (4, 1, 2048, 70, 32, 2048), (8, 4, 1100, 40, 32, 1152), (8, 4, 1100, 40, 33, 1152),
                (6, 2, 1025, 100, 64, 1088), (8, 1, 1536, 20, 16, 1536), (6, 3, 1030, 5, 5, 1032), (2, 2, 900, 300, 128, 904),
-               (2, 2, 900, 300, 256, 960), (16, 4, 1100, 40, 32, 1152), (16, 4, 1100, 40, 33, 1152), (12, 1, 1800, 130, 129, 1856),
-               (24, 3, 1100, 90, 85, 1152), (16, 4, 1100, 40, 32, 1112)]
+               (2, 2, 900, 300, 256, 960), (24, 4, 1100, 40, 32, 1536), (24, 4, 1100, 40, 33, 1536), (16, 1, 1800, 130, 129, 2048),
+               (24, 3, 1100, 90, 85, 1536), (24, 4, 1100, 40, 32, 1112), (24, 6, 1100, 40, 33, 1152)]
 
 
 def pool_width(dtype, Hq, g, T, B, L, ld):
     """Bytes of a row that a workgroup of the pooling takes, by the rule of fk_golden_scores."""
     from oracle import golden
     size = 4 if dtype == "f32" else 2
-    if (T * size + 1023) // 1024 * golden.n_steps(T, B, L) * (Hq // g) < 256:
+    wide, pairs = (T * size + 1023) // 1024 * golden.n_steps(T, B, L) * (Hq // g), g * L
+    if wide < 128 or (pairs >= 96 and wide < (192 if ld * size % 128 else 256)):
         return 256
-    return 512 if ld * size % 128 == 0 and g * L >= 128 else 1024
+    if pairs < 96 or ld * size % 128:
+        return 1024
+    return 512 if ld * size % 1024 == 0 or pairs < 192 else 256
 
 
 def test_pooling_cases_reach_every_width():
