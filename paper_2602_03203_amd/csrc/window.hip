@@ -16,13 +16,12 @@
 // A step that splits a row merges the splits' records eight at a time, weighed by the largest maximum of the eight.  A workgroup here
 // meets the splits one after the other, so it walks the keys once before, for the maxima alone (SPLIT).
 //
-// Bound by what two wavefronts a SIMD can hide of the L2's and the LDS's latency.  Two groups of 16 queries with 32 keys take 34 matrix and some
-// 200 vector instructions (66 of them where a maximum moved, which it does in most of the eight tiles of a wavefront), 4000 cycles for the two
-// wavefronts of a SIMD; of a workgroup's 45 000 cycles 2700 are its start and 5000 its merge.  With 260 vector instructions (weights added up
-// by them) it was 4 % more, the SIMDs issuing in 67 % of their cycles (vector 56 %, matrix 18 %, both 7
-// %), a wavefront waiting 30 % of its time, the tiles coming at 23 bytes a cycle and CU.  128 rows of 2048 pairs, 128 steps: 164 us with the
-// copy that resets the lengths (0.43 PFLOP/s; 175 repeated without a pause, at a lower clock) against 2.9 ms step by step; with features
-// 5 us more and 91 us for the planes.  It was 206 us with the probabilities through LDS, a merge of every group by itself with scalar reads
+// Bound by what two wavefronts a SIMD can hide of the L2's and the LDS's latency.  By the counters, its share of start and merge included, a tile
+// of 32 keys with two groups of 16 queries takes 34 matrix and 304 vector instructions (349 with the weights added up by them: 4 % more time), 4100
+// cycles for the two wavefronts of a SIMD; of a workgroup's 45 000 cycles 2700 are its start and 5000 its merge.  The SIMDs issue in 67 % of
+// their cycles (vector 53 %, matrix 20 %, both 6 %), a wavefront waits 29 % of its time, the tiles come at 24 bytes a cycle and CU.  128 rows of
+// 2048 pairs, 128 steps: 162 us with the copy that resets the lengths (0.44 PFLOP/s; 169 to 179 repeated without a pause, at a lower clock)
+// against 2.9 ms step by step; with features 7 us more and 91 us for the planes.  It was 206 us with the probabilities through LDS, a merge of every group by itself with scalar reads
 // (6600 cycles), a branch per group in every loop, a walk whose counter was not known to be the same for a
 // wavefront (masks in every tile), and V waited for together with the next tile's K.  Measured and not kept: K as operand straight from the
 // L2 (16 rows of 64 bytes a load: 218 us against 182); all of a tile's operands read ahead, higher wavefront priority around the products:
