@@ -457,9 +457,9 @@ __global__ __launch_bounds__((AttnCfg<T, D, G, HEADS>::THREADS), (attn_two<T, D,
         const float scale = P.scale_log2e;
         // l: the normaliser, of unrounded weights where P.V has all their bits (SPLIT_P), otherwise a column of ones more in P.V, a 129th, the same
         // rounded weights; lx: sum of the unrounded weights (feature variant).  Against sums by vector instructions, us: four heads, 2 rows of
-        // 144 pairs 5.34 and 5.20, 128 of 2048 23.1 and 22.9; two heads alike; one head, which has a quarter of the additions and pays for the registers,
-        // 2 of 144 alike, 128 of 2048 22.2 and 22.4, 512 of 300 14.65 and 14.85; three heads 128 of 300 6.3 and 6.4, 128 of 2048 alike.  One form
-        // for all, because windows give the same bits: there one head gains 4 %, three 6 to 7 (128 rows of 2048, 128 steps 51.9 and 49.8, 136 and 127).
+        // 144 pairs 5.34 and 5.20, 128 of 2048 23.1 and 22.9; one head, which has a quarter of the additions and pays for the registers, 8 of 144 4.21
+        // and 4.14, 128 of 2048 alike, 512 of 300 14.26 and 14.20; two alike; three 8 of 144 4.86 and 4.94, 128 of 300 6.32 and 6.26.  Windows, which give
+        // the same bits: one head 4 %, three 6 to 7 (128 rows of 2048, 128 steps 51.9 and 49.8, 136 and 127).
         float m_run[4], l_run[4], lx_run[4];
         f32x4_t ol = (f32x4_t){0.f, 0.f, 0.f, 0.f};
         B128 ones;
@@ -545,6 +545,9 @@ __global__ __launch_bounds__((AttnCfg<T, D, G, HEADS>::THREADS), (attn_two<T, D,
                     const int kc = min(base + quad * 8 + u, end - 1);
                     kr[u] = ld_stream<NT>((kc == new_slot ? knew_row : Krow + (size_t)kc * CH) + n16);
                 }
+                // (One head: with the normaliser's registers the compiler sent the last two rows of K off when the first were there.  32 cold rows of
+                // 1171 pairs 8.42 us a step, so 8.19; two heads, 8 of 1624 7.17 and 7.10.  Rows out of the caches lose 0 to 1 % by it, three heads spill.)
+                if constexpr (NT && G <= 2 && attn_two<T, D, G, FEAT>()) __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
                 for (int u = 0; u < 8; ++u) {
                     const int kc = min(base + quad * 8 + u, end - 1);
@@ -566,6 +569,17 @@ __global__ __launch_bounds__((AttnCfg<T, D, G, HEADS>::THREADS), (attn_two<T, D,
                     else kb.u = *reinterpret_cast<const uint4*>(my_k + (nt * 16 + n16) * KRS + (ks * 4 + quad) * 16);
                     c[nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(qa[ks].v, kb.v, c[nt], 0, 0, 0);
                 }
+            }
+            if constexpr (attn_two<T, D, G, FEAT>()) {
+                // K's operands two reads ahead of the products, which the compiler gives up where registers are short: three heads, 128 rows of 300
+                // pairs 6.44 us a step, so 6.25, of 2048 23.1 and 22.8; two, 128 of 2048 22.7 and 22.5; one, 128 of 300 5.61 and 5.51.
+                __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);   // LDS reads
+#pragma unroll
+                for (int i = 0; i < 2 * KS - 2; ++i) {
+                    __builtin_amdgcn_sched_group_barrier(0x8, 1, 0);   // a product
+                    __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+                }
+                __builtin_amdgcn_sched_group_barrier(0x8, 2, 0);
             }
             int any_lane = threadIdx.x;
             if constexpr (attn_two<T, D, G, FEAT>()) asm volatile("" : "+v"(any_lane));   // (opaque: the key would stay in a register)
