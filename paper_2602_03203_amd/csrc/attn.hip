@@ -545,9 +545,10 @@ __global__ __launch_bounds__((AttnCfg<T, D, G, HEADS>::THREADS), (attn_two<T, D,
                     const int kc = min(base + quad * 8 + u, end - 1);
                     kr[u] = ld_stream<NT>((kc == new_slot ? knew_row : Krow + (size_t)kc * CH) + n16);
                 }
-                // (One head: with the normaliser's registers the compiler sent the last two rows of K off when the first were there.  32 cold rows of
-                // 1171 pairs 8.42 us a step, so 8.19; two heads, 8 of 1624 7.17 and 7.10.  Rows out of the caches lose 0 to 1 % by it, three heads spill.)
-                if constexpr (NT && G <= 2 && attn_two<T, D, G, FEAT>()) __builtin_amdgcn_sched_barrier(0);
+                // (One head: with the normaliser's registers the compiler sent the last two rows of K off when the first were there.  32 streamed rows of
+                // 1171 pairs 8.42 us a step, so 8.19; out of the caches 12 of 12077 15.3 and 15.1, 8 of 2000 5.95 and 6.0.  Two heads, streamed, 8 of
+                // 1624 7.17 and 7.10; out of the caches 128 of 2048 22.55 and 22.7.  Three heads spill.)
+                if constexpr ((G == 1 || (NT && G == 2)) && attn_two<T, D, G, FEAT>()) __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
                 for (int u = 0; u < 8; ++u) {
                     const int kc = min(base + quad * 8 + u, end - 1);
